@@ -14,7 +14,8 @@
 //    (for z), the last lh values of g (du is finished lh-1 steps late, when the newest g it needs has
 //    arrived), a delay line of k and v for that lag, and VEC*lh partial sums for dh.  A tile reads lh-1
 //    halo rows of k, v before its start and lh-1 halo rows of dy, q after its end.
-//  * bwd_direct_kernel / dh_direct_kernel: any lh, any group, both dtypes.  Correctness path.
+//  * any other lh, group or width, both dtypes: dq, dk, dv by the general FIR kernel (direct_kernels.hip) in both time
+//    directions, dh by dh_direct_kernel.
 //
 // kGated = false turns both paths into the backward of the featurizer convolutions of Eq. 1 (x' = h * x, no
 // gates): u = x (the k pointer), g = dy, the only activation gradient is dx = du (the dk pointer); q, v, dq, dv are
@@ -267,106 +268,13 @@ __global__ __launch_bounds__(kBlock) void dh_reduce_kernel(const float* __restri
 }
 
 // ------------------------------------------------------------------------------------- general
-constexpr int kRows = 8;
-constexpr int kChan = 64;
-constexpr int kRowLanes = 4;
-
 struct BwdDirectArgs {
     BwdPtrs p;
     int64_t B, L, D;
-    int64_t skv, sgq, sout;  // elements between batch items in k, v / dy, q / dq, dk, dv
-    int32_t hist, fut;       // rows of k, v in front of row 0 / of dy, q behind row L - 1 that hold data
+    int64_t skv, sgq;  // elements between batch items in k, v / dy, q
+    int32_t hist;      // rows of k, v in front of row 0 that hold data
     int32_t lh, group;
 };
-
-// dq, dk, dv: one lane = one channel x kRows consecutive steps, sliding along the sources with the kRows
-// matching taps in registers (backwards in time for z, forwards for du).
-template <typename T, bool kGated>
-__global__ __launch_bounds__(kChan* kRowLanes) void bwd_direct_kernel(BwdDirectArgs a) {
-    using P = Pack<T, 1>;
-    const int64_t b = blockIdx.z;
-    const int64_t c = (int64_t)blockIdx.x * kChan + (threadIdx.x % kChan);
-    const int64_t tf = ((int64_t)blockIdx.y * kRowLanes + threadIdx.x / kChan) * kRows;
-    if (c >= a.D || tf >= a.L) return;
-    const int64_t L = a.L;
-    const int64_t tl = (tf + kRows - 1 < L - 1) ? tf + kRows - 1 : L - 1;
-    const int lh = a.lh;
-    const float* hp = a.p.h + (c / a.group) * (int64_t)lh;
-    const char* dyp = static_cast<const char*>(a.p.dy);
-    const char* qp = static_cast<const char*>(a.p.q);
-    const char* kp = static_cast<const char*>(a.p.k);
-    const char* vp = static_cast<const char*>(a.p.v);
-    const int64_t seq0 = b * a.sout + c, seq0kv = b * a.skv + c, seq0gq = b * a.sgq + c;
-    auto ld = [&](const char* base, int64_t s0, int64_t t) {
-        float f[1];
-        P::unpack(P::load(base + (s0 + t * a.D) * T::kBytes), f);
-        return f[0];
-    };
-
-    float tw[kRows], acc[kRows], zz[kRows];
-    if constexpr (kGated) {
-        // z[tf + r] = sum_s h[tf + r - s] u[s], s ascending
-        int64_t s = tf - (lh - 1);
-        if (s < -(int64_t)a.hist) s = -(int64_t)a.hist;
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-            const int64_t j = tf + r - s;
-            tw[r] = (j >= 0 && j < lh) ? hp[j] : 0.0f;
-            acc[r] = 0.0f;
-        }
-        for (; s <= tl; ++s) {
-            const float u = ld(kp, seq0kv, s) * ld(vp, seq0kv, s);
-#pragma unroll
-            for (int r = 0; r < kRows; ++r) acc[r] = __builtin_fmaf(tw[r], u, acc[r]);
-#pragma unroll
-            for (int r = kRows - 1; r > 0; --r) tw[r] = tw[r - 1];
-            const int64_t j0 = tf - (s + 1);
-            tw[0] = (j0 >= 0 && j0 < lh) ? hp[j0] : 0.0f;
-        }
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) zz[r] = acc[r];
-    }
-
-    // du[tf + r] = sum_t h[t - tf - r] g[t], t ascending from tf to tl + lh - 1
-    int64_t t = tf;
-    int64_t t_last = tl + (lh - 1);
-    if (t_last > L + a.fut - 1) t_last = L + a.fut - 1;
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-        const int64_t j = t - tf - r;
-        tw[r] = (j >= 0 && j < lh) ? hp[j] : 0.0f;
-        acc[r] = 0.0f;
-    }
-    for (; t <= t_last; ++t) {
-        const float g = kGated ? ld(dyp, seq0gq, t) * ld(qp, seq0gq, t) : ld(dyp, seq0gq, t);
-#pragma unroll
-        for (int r = 0; r < kRows; ++r) acc[r] = __builtin_fmaf(tw[r], g, acc[r]);
-        // next source: every tap index grows by one
-#pragma unroll
-        for (int r = kRows - 1; r > 0; --r) tw[r] = tw[r - 1];
-        const int64_t j0 = t + 1 - tf;
-        tw[0] = (j0 >= 0 && j0 < lh) ? hp[j0] : 0.0f;
-    }
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-        if (tf + r <= tl) {
-            const int64_t off = (seq0 + (tf + r) * a.D) * T::kBytes;
-            float o[1];
-            if constexpr (kGated) {
-                const float kf = ld(kp, seq0kv, tf + r), vf = ld(vp, seq0kv, tf + r), dyf = ld(dyp, seq0gq, tf + r);
-                o[0] = dyf * zz[r];
-                P::store(static_cast<char*>(a.p.dq) + off, P::pack(o));
-                o[0] = acc[r] * vf;
-                P::store(static_cast<char*>(a.p.dk) + off, P::pack(o));
-                o[0] = acc[r] * kf;
-                P::store(static_cast<char*>(a.p.dv) + off, P::pack(o));
-            } else {
-                o[0] = acc[r];
-                P::store(static_cast<char*>(a.p.dk) + off, P::pack(o));
-            }
-        }
-    }
-}
 
 // dh[g][j]: one workgroup per (group, tap); lanes stride over (b, t, channel of the group), then a tree sum.
 // Products of fp32 factors and their sum are carried in fp64 (correctness path: the sum has B * L * group terms).
@@ -482,21 +390,38 @@ hy_status launch_direct_t(const BwdPtrs& p, const BwdShape& s, hipStream_t st) {
     a.B = s.B; a.L = s.L; a.D = s.D; a.lh = s.lh; a.group = s.group;
     a.skv = s.stride_kv();
     a.sgq = s.stride_gq();
-    a.sout = s.stride_out();
     a.hist = s.history;
-    a.fut = s.future;
-    const int64_t gx = (s.D + kChan - 1) / kChan;
-    const int64_t gy = (s.L + kRows * kRowLanes - 1) / (kRows * kRowLanes);
     const int64_t G = s.D / s.group;
-    if (gx > 0x7fffffffLL || gy > 65535 || s.B > 65535 || G > 0x7fffffffLL || s.lh > 65535) return HY_ERR_UNSUPPORTED;
-    const dim3 grid((uint32_t)gx, (uint32_t)gy, (uint32_t)s.B), gridh((uint32_t)G, (uint32_t)s.lh);
-    if (s.gated) {
-        const hy_status rc = launch_kernel((bwd_direct_kernel<T, true>), grid, dim3(kChan * kRowLanes), st, a);
-        if (rc != HY_OK) return rc;
-        return launch_kernel((dh_direct_kernel<T, true>), gridh, dim3(kBlock), st, a);
-    }
-    const hy_status rc = launch_kernel((bwd_direct_kernel<T, false>), grid, dim3(kChan * kRowLanes), st, a);
+    if (G > 0x7fffffffLL || s.lh > 65535) return HY_ERR_UNSUPPORTED;
+    // du = h *' g towards the past, gated by v and by k; z = h * u, gated by dy
+    FirProblem f[2];
+    f[0].a = p.dy;
+    f[0].b = s.gated ? p.q : nullptr;
+    f[0].h = p.h;
+    f[0].gate = s.gated ? p.v : nullptr;
+    f[0].out = p.dk;
+    f[0].gate2 = s.gated ? p.k : nullptr;
+    f[0].out2 = s.gated ? p.dv : nullptr;
+    f[0].stride_ab = s.stride_gq();
+    f[0].stride_gate = s.stride_kv();
+    f[0].stride_out = s.stride_out();
+    f[0].lo = 0;
+    f[0].hi = s.L + s.future;
+    f[0].rev = 1;
+    f[1].a = p.k;
+    f[1].b = p.v;
+    f[1].h = p.h;
+    f[1].gate = p.dy;
+    f[1].out = p.dq;
+    f[1].stride_ab = s.stride_kv();
+    f[1].stride_gate = s.stride_gq();
+    f[1].stride_out = s.stride_out();
+    f[1].lo = -(int64_t)s.history;
+    f[1].hi = s.L;
+    const hy_status rc = launch_fir(f, s.gated ? 2 : 1, s.B, s.L, s.D, s.lh, s.group, s.dtype, st);
     if (rc != HY_OK) return rc;
+    const dim3 gridh((uint32_t)G, (uint32_t)s.lh);
+    if (s.gated) return launch_kernel((dh_direct_kernel<T, true>), gridh, dim3(kBlock), st, a);
     return launch_kernel((dh_direct_kernel<T, false>), gridh, dim3(kBlock), st, a);
 }
 

@@ -164,7 +164,23 @@ hy_status launch_stencil(const ConvPtrs* p, int nprob, const ConvShape& s, hipSt
 // Ungated (featurizer) calls may bring up to three problems that share the shape (as launch_stencil does).
 bool se_walk_preferred(const ConvShape& s, int nprob = 1);
 hy_status launch_se_walk(const ConvPtrs* p, int nprob, const ConvShape& s, hipStream_t st);
-// General fp32 direct convolution: any lh, any group, both dtypes.
+// One problem of the general FIR kernel: out[t] = gate[t] * sum_j h[j] x[t -+ j] with x = a*b (b may be null: x = a;
+// gate may be null: 1), where x holds data for lo <= t < hi and terms outside do not exist.
+struct FirProblem {
+    const void* a = nullptr;
+    const void* b = nullptr;
+    const float* h = nullptr;
+    const void* gate = nullptr;
+    void* out = nullptr;
+    const void* gate2 = nullptr;  // a second gate and output of the same convolution (out2 null: none)
+    void* out2 = nullptr;
+    int64_t stride_ab = 0, stride_gate = 0, stride_out = 0;  // elements between batch items
+    int64_t lo = 0, hi = 0;
+    int32_t rev = 0;              // 1: x[t + j], the transposed convolution
+};
+// General fp32 FIR: any lh, any group, any width, both dtypes, up to three problems of one shape per launch.
+hy_status launch_fir(const FirProblem* p, int nprob, int64_t B, int64_t L, int64_t D, int32_t lh, int32_t group,
+                     hy_dtype dtype, hipStream_t st);
 hy_status launch_direct(const ConvPtrs* p, int nprob, const ConvShape& s, hipStream_t st);
 // Block-Toeplitz contraction on bf16 MFMA.  HY_ERR_UNSUPPORTED outside its domain.
 hy_status launch_mr_mfma(const ConvPtrs& p, const ConvShape& s, hipStream_t st);

@@ -1,0 +1,83 @@
+"""The general FIR kernels (fp32, and bf16 shapes no matrix-core path takes) at the edges of their tiles: segments of 128
+taps, stages of 64, register blocks of 16, tiles of 32 and 128 rows, walks of several tiles, 64-channel blocks with idle
+lanes, rows of 16-byte pieces and of single elements; forward, gradients, featurizers; and the reach of non-finite
+samples and taps."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2503_01868_amd import binding, synth
+
+from gpu_util import TOL, check_gated, dev, draw, host, say
+
+pytestmark = pytest.mark.gpu
+
+# B, L, D, lh, group
+SHAPES = [
+    (1, 1, 1, 9, 1), (2, 31, 3, 16, 3), (1, 33, 30, 17, 1), (1, 127, 64, 63, 2), (2, 128, 65, 64, 5), (1, 129, 72, 65, 8),
+    (1, 200, 40, 127, 4), (3, 300, 24, 128, 1), (1, 300, 100, 129, 20), (1, 700, 8, 257, 8), (1, 90, 16, 400, 16),
+    (2, 4200, 200, 40, 8), (1, 9000, 136, 130, 1),  # 128-row tiles, several to a walk
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "B%dL%dD%dlh%dg%d" % s)
+def test_forward(shape, dtype):
+    B, L, D, lh, group = shape
+    check_gated("hyena_mr_fwd", 9100 + L, B, L, D, lh, group, dtype, kind="mr")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", SHAPES[:-1], ids=lambda s: "B%dL%dD%dlh%dg%d" % s)
+def test_gradients(shape, dtype):
+    B, L, D, lh, group = shape
+    say("hyena_mr_bwd %s %s" % (shape, dtype))
+    rng = np.random.Generator(np.random.PCG64(9200 + L))
+    dy, q, k, v = (synth.normal_tensor(rng, (B, L, D), dtype) for _ in range(4))
+    h = synth.decay_filter(rng, D // group, lh)
+    outs = binding.hyena_mr_bwd(dev(dy), dev(q), dev(k), dev(v), dev(h), group)
+    ref = oracle.gated_conv_bwd(dy, q, k, v, h, group=group)
+    for name, got, want in zip(("dq", "dk", "dv", "dh"), outs, ref):
+        assert oracle.rel_err(host(got), want) <= (TOL["f32"] if name == "dh" else TOL[dtype]), name
+
+
+@pytest.mark.parametrize("shape", [(1, 150, 6, 9, 1), (2, 513, 72, 140, 8), (1, 4500, 96, 33, 1)],
+                         ids=lambda s: "B%dL%dD%dlh%dg%d" % s)
+def test_ungated(shape):
+    B, L, D, lh, group = shape
+    say("hyena_featurize fwd/bwd %s" % (shape,))
+    q, k, v, h = draw(9300 + L, B, L, D, lh, group, "f32")
+    outs = binding.hyena_featurize3_fwd(dev(q), dev(k), dev(v), dev(h), dev(h), dev(h), group)
+    for x, y in zip((q, k, v), outs):
+        assert oracle.rel_err(host(y), oracle.causal_conv(x, h, group=group)) <= TOL["f32"]
+    dx, dh = binding.hyena_featurize_bwd(dev(q), dev(k), dev(h), group)
+    rx, rh = oracle.causal_conv_bwd(q, k, h, group=group)
+    assert oracle.rel_err(host(dx), rx) <= TOL["f32"] and oracle.rel_err(host(dh), rh) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("L,at", [(300, 0), (300, 140), (300, 299), (4200, 129)])
+def test_non_finite_values_reach_what_the_definition_says(L, at):
+    """An infinite sample, and an infinite tap, make exactly those outputs non-finite whose sum has the term."""
+    B, D, lh = 1, 16, 128
+    say("non-finite L=%d at=%d" % (L, at))
+    q, k, v, h = draw(9400 + at, B, L, D, lh, 1, "f32", kind="mr")
+    k[0, at, 3] = float("inf")
+    h = h.copy()
+    h[5, 40] = np.inf
+    y = host(binding.hyena_mr_fwd(dev(q), dev(k), dev(v), dev(h), 1))
+    bad = np.zeros((L, D), dtype=bool)
+    bad[at:at + lh, 3] = True
+    bad[40:, 5] = True
+    assert np.array_equal(~np.isfinite(y[0]), bad)
+    dy = torch.from_numpy(np.random.Generator(np.random.PCG64(1)).standard_normal((B, L, D), dtype=np.float32))
+    dq, dk, dv, dh = (host(x) for x in binding.hyena_mr_bwd(dev(dy), dev(q), dev(k), dev(v), dev(h), 1))
+    assert np.array_equal(~np.isfinite(dq[0]), bad)
+    bad_k = np.zeros((L, D), dtype=bool)
+    bad_k[:L - 40, 5] = True
+    assert np.array_equal(~np.isfinite(dk[0]), bad_k)
+    bad_k[at, 3] = True  # dv = du * k
+    assert np.array_equal(~np.isfinite(dv[0]), bad_k)
+    bad_h = np.zeros((D, lh), dtype=bool)
+    bad_h[3, :min(lh, L - at)] = True
+    assert np.array_equal(~np.isfinite(dh), bad_h)
