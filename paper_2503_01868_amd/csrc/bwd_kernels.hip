@@ -15,11 +15,13 @@
 //    arrived), a delay line of k and v for that lag, and VEC*lh partial sums for dh.  A tile reads lh-1
 //    halo rows of k, v before its start and lh-1 halo rows of dy, q after its end.
 //  * any other lh, group or width, both dtypes: dq, dk, dv by the general FIR kernel (direct_kernels.hip) in both time
-//    directions, dh by dh_direct_kernel.
+//    directions, dh by dh_tile_kernel (sequences too short for its partial sums: dh_direct_kernel).
 //
 // kGated = false turns both paths into the backward of the featurizer convolutions of Eq. 1 (x' = h * x, no
 // gates): u = x (the k pointer), g = dy, the only activation gradient is dx = du (the dk pointer); q, v, dq, dv are
 // neither read nor written.
+#include <type_traits>
+
 #include "hy_common.hpp"
 #include "hy_launch.hpp"
 
@@ -319,6 +321,280 @@ __global__ __launch_bounds__(kBlock) void dh_direct_kernel(BwdDirectArgs a) {
     if (threadIdx.x == 0) a.p.dh[g * a.lh + j] = (float)red[0];
 }
 
+// The same filter gradient for everything but very short sequences, in two passes (App. A.4): partial sums per tile of
+// time, then a reduction.  Products and sums are fp64 as above; the vector ALUs issue fp64 FMAs as fast as unpacked fp32
+// ones, so the bound is lh FMAs per element and the layout is again around them: a workgroup owns 64 channels (one per
+// lane) and a tile of time, u = k*v and g = dy*q are formed once into LDS in fp64 (both products are exact there), and
+// a wave holds 16 lags: 16 steps of g against 16 + 15 rows of u are 256 FMAs per 48 LDS reads.  Filters of fewer than
+// 128 taps leave waves without lags: those take a share of the steps instead (kLagWaves lag blocks of 16).
+// The partial sums of a tile lie in the memory of dk, which the FIR launch behind these two overwrites: the shapes that
+// come here are the ones whose callers bring no workspace, and a tile is long enough for its sums to fit (the channels
+// of a group are summed in the wave first, as far as its size has powers of two).
+// Pairs the definition does not have are left out, not multiplied by zeros (see the FIR kernel).
+// Measured at B = 2, L = 2048, D = 1024, 128 taps, groups of 16, fp32: 1160 us with one workgroup per (group, tap), which
+// read all samples of the group once per tap; 38 + 5 us in these two.
+struct DhArgs {
+    BwdPtrs p;
+    int64_t L, D;
+    int64_t skv, sgq, sout;  // elements between batch items in k, v / dy, q / dk
+    int32_t hist;            // rows of k, v in front of row 0 that hold data
+    int32_t lh, group;
+    int32_t fold;            // largest power of two (up to 64) that divides the group: channels summed in the wave
+    int32_t ncb, rows, tiles_per_seq;
+};
+
+constexpr int kDhThreads = 512;
+constexpr int kDhT = 64;     // steps staged at a time
+constexpr int kDhRing = 192;  // rows of u: the staged steps and 128 before them
+constexpr int kDhLags = 128;  // lags per workgroup
+
+// the partial sums of batch item b, in dk's memory
+template <typename T>
+__device__ __forceinline__ double* dh_scratch(void* dk, int64_t b, int64_t sout) {
+    const uintptr_t at = reinterpret_cast<uintptr_t>(dk) + (uintptr_t)(b * sout) * T::kBytes;
+    return reinterpret_cast<double*>((at + 7) & ~(uintptr_t)7);
+}
+
+template <typename T, int VEC, int kLagWaves, bool kGated>
+__global__ __launch_bounds__(kDhThreads, 1) void dh_tile_kernel(DhArgs a) {
+    constexpr int kC = 64;
+    constexpr int kWaves = kDhThreads / 64;
+    constexpr int kSplit = kWaves / kLagWaves < 4 ? kWaves / kLagWaves : 4;  // waves that share a lag block
+    constexpr int kSub = 4 / kSplit;          // 16-step blocks per wave and staging
+    constexpr int PPR = kC / VEC, RPP = kDhThreads / PPR, kPass = kDhT / RPP;
+    static_assert(kDhT % RPP == 0, "whole passes");
+    using P = Pack<T, VEC>;
+    __shared__ __attribute__((aligned(16))) double us[kDhRing * kC];
+    __shared__ __attribute__((aligned(16))) double gs[kDhT * kC];
+
+    const int tid = threadIdx.x, lane = tid % 64, w = __builtin_amdgcn_readfirstlane(tid / 64);
+    const uint32_t lb = blockIdx.x;
+    const uint32_t tile = lb / (uint32_t)a.ncb;
+    const int64_t c0 = (int64_t)(lb % (uint32_t)a.ncb) * kC;
+    const int64_t b = tile / (uint32_t)a.tiles_per_seq;
+    const int64_t ti = tile % (uint32_t)a.tiles_per_seq;
+    const int64_t ts = ti * a.rows, te = ts + a.rows < a.L ? ts + a.rows : a.L;
+    const int64_t D = a.D, L = a.L;
+    const int64_t l0 = (int64_t)blockIdx.y * kDhLags;   // first lag of this workgroup
+    const int lagw = w % kLagWaves, part = w / kLagWaves;
+    const int64_t j0 = l0 + 16 * lagw;                  // first lag of this wave
+    const bool busy = part < kSplit && j0 < a.lh;
+
+    const int pc = tid % PPR, pr0 = tid / PPR;
+    const int64_t col = c0 + (int64_t)pc * VEC < D ? c0 + (int64_t)pc * VEC : c0;
+    const char* const kp = static_cast<const char*>(a.p.k) + (b * a.skv + col) * T::kBytes;
+    const char* const vp = kGated ? static_cast<const char*>(a.p.v) + (b * a.skv + col) * T::kBytes : nullptr;
+    const char* const yp = static_cast<const char*>(a.p.dy) + (b * a.sgq + col) * T::kBytes;
+    const char* const qp = kGated ? static_cast<const char*>(a.p.q) + (b * a.sgq + col) * T::kBytes : nullptr;
+    const int64_t row_bytes = D * T::kBytes;
+    typename P::Raw kr[kPass], vr[kPass], yr[kPass], qr[kPass];
+    typename P::Raw kh[2][kPass], vh[2][kPass];
+    // 64 rows of k, v from step s0 on, clamped into those that hold data
+    auto load_u = [&](int64_t s0, typename P::Raw (&kk)[kPass], typename P::Raw (&vv)[kPass]) {
+#pragma unroll
+        for (int i = 0; i < kPass; ++i) {
+            int64_t s = s0 + i * RPP + pr0;
+            s = s < L ? s : L - 1;
+            s = s > -(int64_t)a.hist ? s : -(int64_t)a.hist;
+            kk[i] = P::load(kp + s * row_bytes);
+            if constexpr (kGated) vv[i] = P::load(vp + s * row_bytes);
+        }
+    };
+    auto load_g = [&](int64_t t0) {
+#pragma unroll
+        for (int i = 0; i < kPass; ++i) {
+            int64_t t = t0 + i * RPP + pr0;
+            t = t < L ? t : L - 1;
+            yr[i] = P::load(yp + t * row_bytes);
+            if constexpr (kGated) qr[i] = P::load(qp + t * row_bytes);
+        }
+    };
+    auto write_prod = [&](double* rows, const typename P::Raw (&x)[kPass], const typename P::Raw (&y)[kPass]) {
+#pragma unroll
+        for (int i = 0; i < kPass; ++i) {
+            float f[VEC], g[VEC];
+            P::unpack(x[i], f);
+            if constexpr (kGated) P::unpack(y[i], g);
+            double* dst = rows + (i * RPP + pr0) * kC + pc * VEC;
+            double d[VEC];
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) d[e] = kGated ? (double)f[e] * (double)g[e] : (double)f[e];
+            if constexpr (VEC >= 2) {
+#pragma unroll
+                for (int e = 0; e < VEC; e += 2) *reinterpret_cast<double2*>(dst + e) = make_double2(d[e], d[e + 1]);
+            } else {
+                dst[0] = d[0];
+            }
+        }
+    };
+
+    // steps ts - l0 - 128 .. ts - l0 - 1 of u to ring rows 64 .. 191; staging n then writes rows 64 (n % 3) on
+    load_u(ts - l0 - 128, kh[0], vh[0]);
+    load_u(ts - l0 - 64, kh[1], vh[1]);
+    load_u(ts - l0, kr, vr);
+    load_g(ts);
+    write_prod(us + kDhT * kC, kh[0], vh[0]);
+    write_prod(us + 2 * kDhT * kC, kh[1], vh[1]);
+
+    double acc[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.0;
+
+    int slot = 0;
+    for (int64_t t0 = ts; t0 < te; t0 += kDhT) {
+        __syncthreads();
+        write_prod(us + slot * kDhT * kC, kr, vr);
+        write_prod(gs, yr, qr);
+        __syncthreads();
+        if (t0 + kDhT < te) {
+            load_u(t0 + kDhT - l0, kr, vr);
+            load_g(t0 + kDhT);
+        }
+        if (busy) {
+            // 16-row block m of the ring; blocks of u 16 lags earlier lie one block lower
+            const int blk0 = slot * 4 + part * kSub - lagw + 12;
+            auto read_u = [&](double (&x)[16], int blk) {
+                const double* p = us + (blk % 12) * 16 * kC + lane;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) x[i] = p[i * kC];
+            };
+            double ua[16], ub[16];  // rows 16 steps before the block, rows of the block
+            read_u(ub, blk0 - 1 + 12);
+#pragma unroll
+            for (int n = 0; n < kSub; ++n) {
+                const int sb = part * kSub + n;
+                const int64_t tb = t0 + 16 * sb;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) ua[i] = ub[i];
+                read_u(ub, blk0 + n);
+                const double* gp = gs + sb * 16 * kC + lane;
+                if (tb + 16 <= te && tb - j0 - 15 >= -(int64_t)a.hist) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const double g = gp[i * kC];
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[r] = __builtin_fma(g, i >= r ? ub[i - r] : ua[16 + i - r], acc[r]);
+                    }
+                } else if (tb - j0 + 15 >= -(int64_t)a.hist) {
+                    const int nt = te - tb < 16 ? (int)(te - tb) : 16;                       // steps of the tile
+                    const int64_t back64 = tb - j0 + a.hist;                                  // u reaches this far back
+                    const int back = back64 < 16 ? (back64 > -16 ? (int)back64 : -16) : 16;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const double g = gp[i * kC];
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const double x = __builtin_fma(g, i >= r ? ub[i - r] : ua[16 + i - r], acc[r]);
+                            acc[r] = (i < nt && r - i <= back) ? x : acc[r];
+                        }
+                    }
+                }
+            }
+        }
+        slot = slot == 2 ? 0 : slot + 1;
+    }
+
+    if constexpr (kSplit > 1) {  // the waves that share a lag block, summed in their order
+        __syncthreads();
+        if (busy && part > 0) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) us[(((part - 1) * kLagWaves + lagw) * 16 + r) * kC + lane] = acc[r];
+        }
+        __syncthreads();
+        if (part > 0) return;
+        if (busy) {
+#pragma unroll
+            for (int x = 0; x < kSplit - 1; ++x)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[r] += us[((x * kLagWaves + lagw) * 16 + r) * kC + lane];
+        }
+    }
+    if (!busy) return;
+    const bool own = c0 + lane < D;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = own ? acc[r] : 0.0;
+    for (int x = 1; x < a.fold; x <<= 1) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] += __shfl_xor(acc[r], x);
+    }
+    if (own && lane % a.fold == 0) {
+        double* out = dh_scratch<T>(a.p.dk, b, a.sout) + (ti * (D / a.fold) + (c0 + lane) / a.fold) * a.lh;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (j0 + r < a.lh) out[j0 + r] = acc[r];
+    }
+}
+
+// dh[g][j] = sum over batch items, tiles and the group's partial rows, in that order; four lanes share an output
+template <typename T>
+__global__ __launch_bounds__(kBlock) void dh_tile_reduce_kernel(DhArgs a, int64_t B) {
+    constexpr int kParts = 4, kOut = kBlock / kParts;
+    __shared__ double red[kParts][kOut];
+    const int o = threadIdx.x % kOut, part = threadIdx.x / kOut;
+    const int64_t n = (a.D / a.group) * a.lh;
+    const int64_t idx = (int64_t)blockIdx.x * kOut + o;
+    const int64_t idc = idx < n ? idx : n - 1;
+    const int64_t g = idc / a.lh, j = idc % a.lh;
+    const int64_t rpg = a.group / a.fold;               // partial rows per group
+    const int64_t tile_len = (a.D / a.fold) * a.lh;
+    const int64_t per = (a.tiles_per_seq + kParts - 1) / kParts;
+    const int64_t lo = part * per, hi = lo + per < a.tiles_per_seq ? lo + per : a.tiles_per_seq;
+    double s = 0.0;
+    for (int64_t b = 0; b < B; ++b) {
+        const double* base = dh_scratch<T>(a.p.dk, b, a.sout) + g * rpg * a.lh + j;
+        for (int64_t t = lo; t < hi; ++t)
+            for (int64_t c = 0; c < rpg; ++c) s += base[t * tile_len + c * a.lh];
+    }
+    red[part][o] = s;
+    __syncthreads();
+    if (part == 0 && idx < n) a.p.dh[idx] = (float)(red[0][o] + red[1][o] + red[2][o] + red[3][o]);
+}
+
+// HY_ERR_UNSUPPORTED where dk cannot hold the partial sums of one tile
+template <typename T, int VEC>
+hy_status launch_dh_tile(const BwdPtrs& p, const BwdShape& s, hipStream_t st) {
+    DhArgs a;
+    a.p = p;
+    a.L = s.L;
+    a.D = s.D;
+    a.skv = s.stride_kv();
+    a.sgq = s.stride_gq();
+    a.sout = s.stride_out();
+    a.hist = s.history;
+    a.lh = s.lh;
+    a.group = s.group;
+    a.fold = 1;
+    while (a.fold < 64 && s.group % (2 * a.fold) == 0) a.fold *= 2;
+    const int64_t ncb = (s.D + 63) / 64, nlag = (s.lh + kDhLags - 1) / kDhLags;
+    const int64_t fit = (s.L * s.D * T::kBytes - 8) / ((s.D / a.fold) * (int64_t)s.lh * 8);
+    // one workgroup per compute unit; tiles of 256 steps or more keep the 128 rows of history they start with small
+    int64_t tiles = 256 / (s.B * ncb * nlag);
+    if (tiles > s.L / 256) tiles = s.L / 256;
+    if (tiles < 1) tiles = 1;
+    if (tiles > fit) tiles = fit;
+    if (tiles < 1) return HY_ERR_UNSUPPORTED;
+    int64_t rows = ((s.L + tiles - 1) / tiles + kDhT - 1) / kDhT * kDhT;
+    if (rows > 0x7fffffffLL || ncb > 0x7fffffffLL || nlag > 65535) return HY_ERR_UNSUPPORTED;
+    tiles = (s.L + rows - 1) / rows;
+    if (s.B > 0x7fffffffLL || s.B * tiles > 0x7fffffffLL / ncb) return HY_ERR_UNSUPPORTED;
+    a.ncb = (int32_t)ncb;
+    a.rows = (int32_t)rows;
+    a.tiles_per_seq = (int32_t)tiles;
+    const dim3 grid((uint32_t)(s.B * tiles * ncb), (uint32_t)nlag), block(kDhThreads);
+    auto go = [&](auto gated_c) {
+        constexpr bool G = decltype(gated_c)::value;
+        if (s.lh <= 16) return launch_kernel((dh_tile_kernel<T, VEC, 1, G>), grid, block, st, a);
+        if (s.lh <= 32) return launch_kernel((dh_tile_kernel<T, VEC, 2, G>), grid, block, st, a);
+        if (s.lh <= 64) return launch_kernel((dh_tile_kernel<T, VEC, 4, G>), grid, block, st, a);
+        return launch_kernel((dh_tile_kernel<T, VEC, 8, G>), grid, block, st, a);
+    };
+    const hy_status rc = s.gated ? go(std::true_type{}) : go(std::false_type{});
+    if (rc != HY_OK) return rc;
+    const int64_t nout = (s.D / s.group) * s.lh;
+    return launch_kernel((dh_tile_reduce_kernel<T>), dim3((uint32_t)((nout + kBlock / 4 - 1) / (kBlock / 4))), dim3(kBlock),
+                         st, a, s.B);
+}
+
 int stencil_rows(const BwdShape& s, int64_t nvec) {
     int rows = tuning().se_rows;
     if (rows <= 0) {
@@ -393,6 +669,15 @@ hy_status launch_direct_t(const BwdPtrs& p, const BwdShape& s, hipStream_t st) {
     a.hist = s.history;
     const int64_t G = s.D / s.group;
     if (G > 0x7fffffffLL || s.lh > 65535) return HY_ERR_UNSUPPORTED;
+    // the filter gradient first: its partial sums lie in dk's memory, which the FIR launch then overwrites
+    constexpr int V = 16 / T::kBytes;
+    hy_status rc = s.D % V == 0 ? launch_dh_tile<T, V>(p, s, st) : launch_dh_tile<T, 1>(p, s, st);
+    if (rc == HY_ERR_UNSUPPORTED) {
+        const dim3 gridh((uint32_t)G, (uint32_t)s.lh);
+        rc = s.gated ? launch_kernel((dh_direct_kernel<T, true>), gridh, dim3(kBlock), st, a)
+                     : launch_kernel((dh_direct_kernel<T, false>), gridh, dim3(kBlock), st, a);
+    }
+    if (rc != HY_OK) return rc;
     // du = h *' g towards the past, gated by v and by k; z = h * u, gated by dy
     FirProblem f[2];
     f[0].a = p.dy;
@@ -418,11 +703,7 @@ hy_status launch_direct_t(const BwdPtrs& p, const BwdShape& s, hipStream_t st) {
     f[1].stride_out = s.stride_out();
     f[1].lo = -(int64_t)s.history;
     f[1].hi = s.L;
-    const hy_status rc = launch_fir(f, s.gated ? 2 : 1, s.B, s.L, s.D, s.lh, s.group, s.dtype, st);
-    if (rc != HY_OK) return rc;
-    const dim3 gridh((uint32_t)G, (uint32_t)s.lh);
-    if (s.gated) return launch_kernel((dh_direct_kernel<T, true>), gridh, dim3(kBlock), st, a);
-    return launch_kernel((dh_direct_kernel<T, false>), gridh, dim3(kBlock), st, a);
+    return launch_fir(f, s.gated ? 2 : 1, s.B, s.L, s.D, s.lh, s.group, s.dtype, st);
 }
 
 }  // namespace
