@@ -36,10 +36,18 @@ __global__ __launch_bounds__(kStencilBlock) void stencil_kernel(StencilArgs a) {
     const ConvPtrs pr = a.p[blockIdx.y];
     const int64_t item = (int64_t)blockIdx.x * kStencilBlock + threadIdx.x;
     if (item >= a.nitems) return;
-    const int64_t cv = item % a.nvec;
-    const int64_t tile = item / a.nvec;
-    const int64_t b = tile / a.tiles_per_seq;
-    const int64_t t0 = (tile % a.tiles_per_seq) * (int64_t)a.rows;
+    int64_t cv, b, t0;
+    if (a.nitems <= 0xffffffffLL) {  // 32-bit divisions: three of 64 bits are a microsecond, half of a small launch
+        const uint32_t tile = (uint32_t)item / (uint32_t)a.nvec;
+        cv = (uint32_t)item - tile * (uint32_t)a.nvec;
+        b = tile / (uint32_t)a.tiles_per_seq;
+        t0 = (int64_t)(tile - (uint32_t)b * (uint32_t)a.tiles_per_seq) * a.rows;
+    } else {
+        const int64_t tile = item / a.nvec;
+        cv = item % a.nvec;
+        b = tile / a.tiles_per_seq;
+        t0 = (tile % a.tiles_per_seq) * (int64_t)a.rows;
+    }
     const int64_t t1 = (t0 + a.rows < a.L) ? t0 + a.rows : a.L;
     const int64_t c = cv * VEC;
     const int64_t D = a.D;
@@ -55,7 +63,8 @@ __global__ __launch_bounds__(kStencilBlock) void stencil_kernel(StencilArgs a) {
     float taps[VEC][LH];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
-        const float* hp = pr.h + ((c + e) / a.group) * (int64_t)LH;
+        const int64_t g = D <= 0xffffffffLL ? (int64_t)((uint32_t)(c + e) / (uint32_t)a.group) : (c + e) / a.group;
+        const float* hp = pr.h + g * (int64_t)LH;
 #pragma unroll
         for (int j = 0; j < LH; ++j) taps[e][j] = hp[j];
     }
@@ -167,7 +176,14 @@ hy_status launch_one(const ConvPtrs* p, int nprob, const ConvShape& s, hipStream
         // concurrently walked tiles a power of two in memory, which measured best on MI355X.
         const int64_t waves_per_row = (a.nvec * nprob + kWave - 1) / kWave;
         rows = 128;
-        while (rows > 32 && s.B * ((s.L + rows - 1) / rows) * waves_per_row < 2048) rows >>= 1;
+        auto waves = [&] { return s.B * ((s.L + rows - 1) / rows) * waves_per_row; };
+        while (rows > 32 && waves() < 2048) rows >>= 1;
+        // A launch that leaves compute units with fewer than four waves is as long as one lane's chain of batches, so
+        // there a tile goes down to one batch; its halo rows are loaded beside it (measured, rows 32 / 16 / 8: fp32
+        // 1024 x 256 7.1 / 5.5 / 4.4 us, bf16 512 x 4096 8.3 / 6.3 / 6.6, 4 x 300 x 1000 8.9 / 6.6 / 6.0; with four
+        // waves at 32 rows the halo costs as much as it gains: 1024 x 4096 9.9 / 9.4 / 11.7, fp32 2048 x 1024 10.1 /
+        // 10.4 / 14.0).
+        while (rows > R && waves() < 1024) rows >>= 1;
     }
     if (rows > s.L) rows = (int)s.L;
     if (rows < 1) rows = 1;
