@@ -29,9 +29,11 @@ namespace hy {
 namespace {
 
 // ------------------------------------------------------------------------------------- stencil
+constexpr int kMaxProb = 3;  // problems of one shape per launch (the three featurizers of a chain)
+
 struct BwdStencilArgs {
-    BwdPtrs p;
-    float* partial;  // [B * tiles_per_seq][D * LH]
+    BwdPtrs p[kMaxProb];
+    float* partial[kMaxProb];  // [B * tiles_per_seq][D * LH] each
     int64_t L, D;
     int64_t skv, sgq, sout;  // elements between batch items in k, v / dy, q / dq, dk, dv
     int32_t hist, fut;       // rows of k, v in front of row 0 / of dy, q behind row L - 1 that hold data
@@ -46,6 +48,7 @@ __global__ __launch_bounds__(kBlock) void bwd_stencil_kernel(BwdStencilArgs a) {
     using P = Pack<T, VEC>;
     using Raw = typename P::Raw;
     constexpr int W = LH - 1 + R;  // window length: LH-1 older steps plus the batch
+    const BwdPtrs pr = a.p[blockIdx.y];
     const int64_t item = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (item >= a.nitems) return;
     const int64_t cv = item % a.nvec;
@@ -56,18 +59,18 @@ __global__ __launch_bounds__(kBlock) void bwd_stencil_kernel(BwdStencilArgs a) {
     const int64_t L = a.L, D = a.D;
     const int64_t c = cv * VEC;
     const int64_t seq0 = b * a.sout + c, seq0kv = b * a.skv + c, seq0gq = b * a.sgq + c;
-    const char* dyp = static_cast<const char*>(a.p.dy);
-    const char* qp = static_cast<const char*>(a.p.q);
-    const char* kp = static_cast<const char*>(a.p.k);
-    const char* vp = static_cast<const char*>(a.p.v);
-    char* dqp = static_cast<char*>(a.p.dq);
-    char* dkp = static_cast<char*>(a.p.dk);
-    char* dvp = static_cast<char*>(a.p.dv);
+    const char* dyp = static_cast<const char*>(pr.dy);
+    const char* qp = static_cast<const char*>(pr.q);
+    const char* kp = static_cast<const char*>(pr.k);
+    const char* vp = static_cast<const char*>(pr.v);
+    char* dqp = static_cast<char*>(pr.dq);
+    char* dkp = static_cast<char*>(pr.dk);
+    char* dvp = static_cast<char*>(pr.dv);
 
     float taps[VEC][LH], dh[VEC][LH];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
-        const float* hp = a.p.h + ((c + e) / a.group) * (int64_t)LH;
+        const float* hp = pr.h + ((c + e) / a.group) * (int64_t)LH;
 #pragma unroll
         for (int j = 0; j < LH; ++j) {
             taps[e][j] = hp[j];
@@ -202,7 +205,7 @@ __global__ __launch_bounds__(kBlock) void bwd_stencil_kernel(BwdStencilArgs a) {
         }
     }
 
-    float* pp = a.partial + tile * (D * LH) + c * LH;
+    float* pp = a.partial[blockIdx.y] + tile * (D * LH) + c * LH;
 #pragma unroll
     for (int e = 0; e < VEC; ++e)
 #pragma unroll
@@ -215,9 +218,16 @@ __global__ __launch_bounds__(kBlock) void bwd_stencil_kernel(BwdStencilArgs a) {
 // part of this kernel), so the reduction adds no rounding of its own to the fp32 partials.  With few terms per
 // output (up to 8: single channels and a handful of tiles) a lane sums all of them for one of 256 outputs instead:
 // a quarter of the workgroups, all loads of a lane in flight at once, no exchange.
+struct ReduceArgs {
+    const float* partial[kMaxProb];
+    float* dh[kMaxProb];
+};
+
 template <int kRedParts>
-__global__ __launch_bounds__(kBlock) void dh_reduce_kernel(const float* __restrict__ partial, float* __restrict__ dh,
-                                                           int64_t nsets, int64_t D, int32_t lh, int32_t group) {
+__global__ __launch_bounds__(kBlock) void dh_reduce_kernel(ReduceArgs a, int64_t nsets, int64_t D, int32_t lh,
+                                                           int32_t group) {
+    const float* __restrict__ partial = a.partial[blockIdx.y];
+    float* __restrict__ dh = a.dh[blockIdx.y];
     constexpr int kRedOut = kBlock / kRedParts;
     __shared__ double red[kRedParts][kRedOut];
     const int o = threadIdx.x % kRedOut, part = threadIdx.x / kRedOut;
@@ -595,10 +605,10 @@ hy_status launch_dh_tile(const BwdPtrs& p, const BwdShape& s, hipStream_t st) {
                          st, a, s.B);
 }
 
-int stencil_rows(const BwdShape& s, int64_t nvec) {
+int stencil_rows(const BwdShape& s, int64_t nvec, int nprob) {
     int rows = tuning().se_rows;
     if (rows <= 0) {
-        const int64_t waves_per_row = (nvec + kWave - 1) / kWave;
+        const int64_t waves_per_row = (nvec * nprob + kWave - 1) / kWave;
         // Measured on MI355X (L = 8192, D = 4096): 256-step tiles run 10% faster than 128-step ones (half the
         // halo rows and half the partial filter gradients), as long as four waves per CU are left.
         // The featurizer variant holds half the loads and windows per lane and wants eight waves per CU (same
@@ -615,13 +625,27 @@ int stencil_rows(const BwdShape& s, int64_t nvec) {
 template <typename T>
 constexpr int stencil_vec() { return T::kBytes == 2 ? 2 : 1; }
 
+hy_status launch_reduce(const ReduceArgs& r, int nprob, int64_t nsets, int64_t n_rows, int32_t lh, int32_t group,
+                        hipStream_t st) {
+    const int64_t nout = (n_rows / group) * lh;
+    if (nout == 0) return HY_OK;
+    const int64_t per = nsets * group <= 8 ? kBlock : kBlock / 4;
+    const dim3 grid((uint32_t)((nout + per - 1) / per), (uint32_t)nprob);
+    if (nsets * group <= 8)
+        return launch_kernel(dh_reduce_kernel<1>, grid, dim3(kBlock), st, r, nsets, n_rows, lh, group);
+    return launch_kernel(dh_reduce_kernel<4>, grid, dim3(kBlock), st, r, nsets, n_rows, lh, group);
+}
+
 template <typename T, int LH>
-hy_status launch_stencil_lh(const BwdPtrs& p, const BwdShape& s, void* ws, hipStream_t st) {
+hy_status launch_stencil_lh(const BwdPtrs* p, int nprob, const BwdShape& s, void* ws, hipStream_t st) {
     constexpr int VEC = stencil_vec<T>();
     constexpr int R = 4;
     BwdStencilArgs a;
-    a.p = p;
-    a.partial = static_cast<float*>(ws);
+    for (int i = 0; i < kMaxProb; ++i) {
+        const int x = i < nprob ? i : 0;
+        a.p[i] = p[x];
+        a.partial[i] = reinterpret_cast<float*>(static_cast<char*>(ws) + x * bwd_stencil_workspace_bytes(s, nprob));
+    }
     a.L = s.L;
     a.D = s.D;
     a.skv = s.stride_kv();
@@ -631,30 +655,35 @@ hy_status launch_stencil_lh(const BwdPtrs& p, const BwdShape& s, void* ws, hipSt
     a.fut = s.future;
     a.group = s.group;
     a.nvec = s.D / VEC;
-    a.rows = stencil_rows(s, a.nvec);
+    a.rows = stencil_rows(s, a.nvec, nprob);
     a.tiles_per_seq = (int32_t)((s.L + a.rows - 1) / a.rows);
     a.nitems = s.B * a.tiles_per_seq * a.nvec;
     const int64_t nb = (a.nitems + kBlock - 1) / kBlock;
     if (nb > 0x7fffffffLL) return HY_ERR_UNSUPPORTED;
     const hy_status rc = s.gated
-        ? launch_kernel((bwd_stencil_kernel<T, VEC, LH, R, true>), dim3((uint32_t)nb), dim3(kBlock), st, a)
-        : launch_kernel((bwd_stencil_kernel<T, VEC, LH, R, false>), dim3((uint32_t)nb), dim3(kBlock), st, a);
+        ? launch_kernel((bwd_stencil_kernel<T, VEC, LH, R, true>), dim3((uint32_t)nb, (uint32_t)nprob), dim3(kBlock), st, a)
+        : launch_kernel((bwd_stencil_kernel<T, VEC, LH, R, false>), dim3((uint32_t)nb, (uint32_t)nprob), dim3(kBlock), st, a);
     if (rc != HY_OK) return rc;
     const int64_t nsets = s.B * a.tiles_per_seq;
-    return launch_dh_reduce(a.partial, p.dh, nsets, s.D, s.lh, s.group, st);
+    ReduceArgs r;
+    for (int i = 0; i < kMaxProb; ++i) {
+        r.partial[i] = a.partial[i];
+        r.dh[i] = a.p[i].dh;
+    }
+    return launch_reduce(r, nprob, nsets, s.D, s.lh, s.group, st);
 }
 
 template <typename T>
-hy_status launch_stencil_t(const BwdPtrs& p, const BwdShape& s, void* ws, hipStream_t st) {
+hy_status launch_stencil_t(const BwdPtrs* p, int nprob, const BwdShape& s, void* ws, hipStream_t st) {
     switch (s.lh) {
-        case 1: return launch_stencil_lh<T, 1>(p, s, ws, st);
-        case 2: return launch_stencil_lh<T, 2>(p, s, ws, st);
-        case 3: return launch_stencil_lh<T, 3>(p, s, ws, st);
-        case 4: return launch_stencil_lh<T, 4>(p, s, ws, st);
-        case 5: return launch_stencil_lh<T, 5>(p, s, ws, st);
-        case 6: return launch_stencil_lh<T, 6>(p, s, ws, st);
-        case 7: return launch_stencil_lh<T, 7>(p, s, ws, st);
-        case 8: return launch_stencil_lh<T, 8>(p, s, ws, st);
+        case 1: return launch_stencil_lh<T, 1>(p, nprob, s, ws, st);
+        case 2: return launch_stencil_lh<T, 2>(p, nprob, s, ws, st);
+        case 3: return launch_stencil_lh<T, 3>(p, nprob, s, ws, st);
+        case 4: return launch_stencil_lh<T, 4>(p, nprob, s, ws, st);
+        case 5: return launch_stencil_lh<T, 5>(p, nprob, s, ws, st);
+        case 6: return launch_stencil_lh<T, 6>(p, nprob, s, ws, st);
+        case 7: return launch_stencil_lh<T, 7>(p, nprob, s, ws, st);
+        case 8: return launch_stencil_lh<T, 8>(p, nprob, s, ws, st);
         default: return HY_ERR_UNSUPPORTED;
     }
 }
@@ -713,36 +742,27 @@ bool bwd_stencil_supported(const BwdShape& s) {
     return s.lh <= 8 && s.D % vec == 0;
 }
 
-int64_t bwd_stencil_workspace_bytes(const BwdShape& s) {
+int64_t bwd_stencil_workspace_bytes(const BwdShape& s, int nprob) {
     const int vec = s.dtype == HY_BF16 ? 2 : 1;
-    const int rows = stencil_rows(s, s.D / vec);
+    const int rows = stencil_rows(s, s.D / vec, nprob);
     const int64_t tiles = (s.L + rows - 1) / rows;
     return s.B * tiles * s.D * s.lh * (int64_t)sizeof(float);
 }
 
-hy_status launch_bwd_stencil(const BwdPtrs& p, const BwdShape& s, void* ws, hipStream_t st) {
-    if (!bwd_stencil_supported(s)) return HY_ERR_UNSUPPORTED;
-    return s.dtype == HY_BF16 ? launch_stencil_t<BF16>(p, s, ws, st) : launch_stencil_t<F32>(p, s, ws, st);
+hy_status launch_bwd_stencil(const BwdPtrs* p, int nprob, const BwdShape& s, void* ws, hipStream_t st) {
+    if (!bwd_stencil_supported(s) || nprob < 1 || nprob > kMaxProb) return HY_ERR_UNSUPPORTED;
+    return s.dtype == HY_BF16 ? launch_stencil_t<BF16>(p, nprob, s, ws, st) : launch_stencil_t<F32>(p, nprob, s, ws, st);
 }
 
 hy_status launch_dh_reduce(const float* partial, float* dh, int64_t nsets, int64_t n_rows, int32_t lh, int32_t group,
                            hipStream_t st) {
-    const int64_t nout = (n_rows / group) * lh;
-    if (nout == 0) return HY_OK;
-    if (nsets * group <= 8)
-        return launch_kernel(dh_reduce_kernel<1>, dim3((uint32_t)((nout + kBlock - 1) / kBlock)), dim3(kBlock), st, partial,
-                             dh, nsets, n_rows, lh, group);
-    return launch_kernel(dh_reduce_kernel<4>, dim3((uint32_t)((nout + kBlock / 4 - 1) / (kBlock / 4))), dim3(kBlock), st,
-                         partial, dh, nsets, n_rows, lh, group);
+    return launch_reduce(ReduceArgs{{partial, partial, partial}, {dh, dh, dh}}, 1, nsets, n_rows, lh, group, st);
 }
 
 hy_status launch_bwd_zero_dh(float* dh, int64_t D, int32_t lh, int32_t group, hipStream_t st) {
-    const int64_t nout = (D / group) * lh;
-    if (nout == 0) return HY_OK;
     // a reduction over zero partial sets writes zeros (a fill kernel, not a memset, so that callers may
     // capture the call in a HIP graph)
-    return launch_kernel(dh_reduce_kernel<1>, dim3((uint32_t)((nout + kBlock - 1) / kBlock)), dim3(kBlock), st,
-                         static_cast<const float*>(dh), dh, (int64_t)0, D, lh, group);
+    return launch_dh_reduce(dh, dh, 0, D, lh, group, st);
 }
 
 hy_status launch_bwd_direct(const BwdPtrs& p, const BwdShape& s, hipStream_t st) {

@@ -210,8 +210,9 @@ hy_status launch_li_state_fold(const float* states, int64_t n, int64_t steps, co
 hy_status launch_li_direct(const LiPtrs& p, const LiShape& s, hipStream_t st);
 // Backward, short filters: fused streaming pass + reduction of partial filter gradients held in `ws`.
 bool bwd_stencil_supported(const BwdShape& s);
-int64_t bwd_stencil_workspace_bytes(const BwdShape& s);
-hy_status launch_bwd_stencil(const BwdPtrs& p, const BwdShape& s, void* ws, hipStream_t st);
+// Up to three problems of one shape per launch; `ws` holds bwd_stencil_workspace_bytes(s, nprob) bytes for each.
+int64_t bwd_stencil_workspace_bytes(const BwdShape& s, int nprob = 1);
+hy_status launch_bwd_stencil(const BwdPtrs* p, int nprob, const BwdShape& s, void* ws, hipStream_t st);
 // Backward, short bf16 filters on long stretches of time: the same arithmetic on the tile-walking data movement
 // (256 channels per workgroup, 16-row chunks through LDS); bwd_walk_preferred() says when the dispatcher takes it.
 bool bwd_walk_preferred(const BwdShape& s);
