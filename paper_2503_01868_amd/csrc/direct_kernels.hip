@@ -1,24 +1,30 @@
 // General FIR kernel: causal convolution and its transpose with optional gates, for any filter length, any group size,
-// any width and both storage types, fp32 arithmetic on the vector ALUs.  It stands behind every entry point, forward
-// and backward, for the shapes the specialised kernels do not cover (fp32 medium filters, widths and groups that do not
-// tile the matrix cores, filters longer than the specialised limits).
+// any width and both storage types, in fp32.  It stands behind every entry point, forward and backward, for the shapes
+// the bf16 kernels do not cover (fp32 medium filters, widths and groups that do not tile the matrix cores, filters
+// longer than the specialised limits).
 //
-// Bound: vector FMA issue (2 lh flop per output; 128 taps are 16 flop/B in fp32 against 10 the ALUs have per HBM byte).
-// So the kernel is laid out around the FMAs: a lane owns one channel and kR consecutive outputs, whose sums stay in
-// registers; the operand product u = a*b is formed once per workgroup into LDS as fp32 rows of 64 channels (a lane's
-// column: conflict-free), and a block of 16 taps then costs kR + 15 reads of u and 16 of taps per 16 kR FMAs.  One
-// workgroup is 4 waves x kR rows x 64 channels.  u (255 rows) and one stage of 64 taps take 80 KiB, so two workgroups
-// share a compute unit; a workgroup walks several tiles of its sequence where there are enough of them, keeping the
-// halo in LDS and loading the next tile's rows while it computes.  Filters of more than 128 taps go through in segments
-// of 128, the sums staying where they are.  Every output adds its terms in ascending source order for the causal
-// direction and ascending tap order for the transposed one, as a plain loop over the definition does.
-// Terms the definition does not have (sources before the first or behind the last row that holds data) are left out and
-// not multiplied by zeros, so a non-finite tap or sample reaches exactly the outputs it reaches in the definition; only
-// the blocks of taps that cross such an end pay for the test.
-// Measured, 128 taps, against a kernel with 8 outputs per lane and every sample and tap loaded from global memory:
-// B = 3, L = 5003, D = 1000 bf16 245 -> 106 us; B = 2, L = 2048, D = 1024 fp32 67 -> 30 us forward and 126 -> 64 us for
-// dq, dk, dv (the FMAs alone take 51, 14 and 28 us at their peak rate).
+// Bound: 2 lh flop per output (128 taps are 16 flop/B in fp32 against 10 the vector ALUs have per HBM byte and 20 the
+// fp32 matrix products have).  So the sums run on v_mfma_f32_4x4x1_16B_f32, twice the rate of vector FMAs and the same
+// arithmetic (fp32 products and sums): a block is one channel,
+//     D[i][j] += w[m - i] * x[x0 + 4 j],   output row 16 k + 4 j + i, staged row x0 + 4 j = output row + tap (m = x0 - 16 k),
+// so one operand of taps per m (lane = channel, i) serves every output block k, and one read of u per lane and x0 serves
+// all output blocks whose taps it meets.  The kSeg + 3 tap operands stay in registers; a wave owns 16 channels x 128 rows
+// (8 output blocks), a workgroup 4 waves = 64 channels.  The operand product u = a*b is formed once per workgroup into
+// LDS as fp32 rows; 255 rows take 68 KiB, so two workgroups share a compute unit.  A workgroup walks several tiles of
+// its sequence where there are enough of them, keeping the halo in LDS (bf16: with the next tile's rows in flight while
+// it computes; in fp32 they do not fit the registers beside the operands).  Outputs go back through LDS so that gates
+// are read and outputs stored as whole row pieces.  Filters of more than 128 taps go through in segments of 128, the sums
+// staying where they are.  Every output adds its terms in ascending source order for the causal direction and ascending
+// tap order for the transposed one, as a plain loop over the definition does.
+// The products multiply structural zeros (taps outside the segment, rows that hold no data), which is only harmless for
+// finite values: a workgroup that stages anything else takes the sums of that tile term by term on the vector ALUs,
+// without the terms the definition does not have, so a non-finite tap or sample reaches exactly the outputs it reaches
+// in the definition.
+// Measured, 128 taps: B = 3, L = 5003, D = 1000 bf16 86 us, B = 2, L = 2048, D = 1024 fp32 28 us, B = 1, L = 8192,
+// D = 4096 fp32 176 us (of which 115 are its memory traffic, as a filter of 32 taps shows); the same walk with vector
+// FMAs, a lane one channel and 32 outputs: 100, 30, 198 us; 8 outputs per lane straight from global memory: 258, 67 us.
 #include <type_traits>
+#include <utility>
 
 #include "hy_common.hpp"
 #include "hy_launch.hpp"
@@ -26,43 +32,48 @@
 namespace hy {
 namespace {
 
-constexpr int kChan = 64;   // channels per workgroup, one per lane
+
+constexpr int kChan = 64;   // channels per workgroup, 16 per wave
 constexpr int kWaves = 4;
 constexpr int kThreads = kWaves * kWave;
-constexpr int kSeg = 128;   // taps per segment
-constexpr int kStage = 64;  // taps staged in LDS at a time
-constexpr int kBlk = 16;    // taps per register block
-constexpr int kTapStride = kChan + 1;  // floats per staged tap: the transposing writes hit 64 different banks
+constexpr int kStride = kChan + 4;  // floats per staged row: the operand reads and the row accesses hit all banks evenly
 
 struct FirArgs {
     FirProblem p[3];
     int64_t L, D;
     int32_t lh, group;
-    int32_t ncb;             // channel blocks of 64
-    int32_t steps;           // tiles of kWaves * kR rows a workgroup walks
+    int32_t ncb;             // channel blocks
+    int32_t steps;           // tiles a workgroup walks
     int32_t walks_per_seq;
 };
 
-// VEC: elements per staging load (16 bytes where the rows allow it, else one element)
-template <typename T, int VEC, int kR>
+__device__ __forceinline__ bool not_finite(float x) { return !(__builtin_fabsf(x) <= 3.402823466e+38f); }
+
+// f(0), f(1), ... with the index as a compile-time constant
+template <typename F, int... I>
+__device__ __forceinline__ void each_index(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+// VEC: elements per row access (16 bytes where the rows allow it, else one element); kSeg: taps per segment;
+// NT: 16-row output blocks per tile
+template <typename T, int VEC, int kSeg, int NT, bool kOne>
 __global__ __launch_bounds__(kThreads, 2) void fir_kernel(FirArgs a) {
-    constexpr int TR = kWaves * kR;                // output rows per tile
+    constexpr int TR = 16 * NT;                    // output rows per tile
     constexpr int kRows = TR + kSeg - 1;           // staged rows
     constexpr int PPR = kChan / VEC;               // pieces per staged row
     constexpr int RPP = kThreads / PPR;            // rows per pass over the workgroup's lanes
-    constexpr bool kAhead = VEC > 1;               // the next tile's rows are loaded while this one is computed
-    constexpr int kPassAll = (TR + RPP - 1) / RPP;  // passes that load one tile's rows
-    constexpr int kPass = kAhead || kPassAll < 8 ? kPassAll : 8;  // passes in flight
-    constexpr int kBatch = kPass * RPP < TR ? kPass * RPP : TR;   // rows they load
-    constexpr int kTapsPer = kStage * kChan / kThreads;
-    constexpr int kMove = (kSeg - 1) * (kChan / 4) / kThreads + 1;  // float4s of halo per lane
+    constexpr int kPassAll = (TR + RPP - 1) / RPP;  // passes that cover one tile's rows
+    constexpr bool kAhead = kOne && T::kBytes == 2 && VEC > 1;  // the next tile's rows are loaded while this one is computed
+    constexpr int kPass = kAhead || kPassAll < 4 ? kPassAll : 4;  // passes in flight
+    constexpr int kBatch = kPass * RPP < TR ? kPass * RPP : TR;  // rows they cover
+    static_assert(!kAhead || kPass == kPassAll, "a tile's rows in flight at once");
+    constexpr int kMove = ((kSeg - 1) * (kChan / 4) + kThreads - 1) / kThreads;  // float4s of halo per lane
+    constexpr int kTapStride = kSeg + 8;           // a channel's taps with three zeros on either side
+    static_assert(kChan * kTapStride <= kRows * kStride, "the taps pass through the rows' memory");
     using PV = Pack<T, VEC>;
-    using P1 = Pack<T, 1>;
-    // taps first: their offsets and those of a register block's rows then fit the LDS instructions
-    __shared__ __attribute__((aligned(256))) float lds[kStage * kTapStride + kRows * kChan];
-    float* const ts = lds;
-    float* const us = lds + kStage * kTapStride;
-    static_assert(kStage * kTapStride % kChan == 0, "rows start on a multiple of 256 bytes");
+    __shared__ __attribute__((aligned(16))) float us[kRows * kStride];
+    __shared__ int flags[2][kWaves];
 
     const FirProblem pr = a.p[blockIdx.y];
     const int tid = threadIdx.x, lane = tid % kWave, w = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -73,19 +84,20 @@ __global__ __launch_bounds__(kThreads, 2) void fir_kernel(FirArgs a) {
     const int64_t t_first = (int64_t)(walk % (uint32_t)a.walks_per_seq) * a.steps * TR;
     const int64_t D = a.D, L = a.L;
     const int lh = a.lh;
-    const bool own = c0 + lane < D;
-    const int r0 = w * kR;  // first row of this wave in a tile
-    // filter of the block's first channel, and how many filters further this lane's channel is
+    // filter of the block's first channel, and how many filters further the wave's channel `lane` % 16 is
     const int64_t g0 = c0 / a.group;
-    const uint32_t gstep = ((uint32_t)(c0 - g0 * a.group) + (uint32_t)(own ? lane : D - 1 - c0)) / (uint32_t)a.group;
+    const int cw = 16 * w + lane % 16;
+    const uint32_t gstep = ((uint32_t)(c0 - g0 * a.group) + (uint32_t)(c0 + cw < D ? cw : D - 1 - c0)) / (uint32_t)a.group;
     const float* const h0 = pr.h + g0 * (int64_t)lh;
     const int64_t row_bytes = D * T::kBytes;
 
-    // ---- staging: this lane's piece of the rows it loads (a piece past the last channel re-reads the block's first)
+    // ---- rows of 64 channels: this lane's piece of the rows it loads and stores (a piece past the last channel reads
+    // the block's first one)
     const int pc = tid % PPR, pr0 = tid / PPR;
-    const int64_t piece = (b * pr.stride_ab + (c0 + (int64_t)pc * VEC < D ? c0 + (int64_t)pc * VEC : c0)) * T::kBytes;
-    const char* const ap = static_cast<const char*>(pr.a) + piece;
-    const char* const bp = pr.b ? static_cast<const char*>(pr.b) + piece : nullptr;
+    const bool own = c0 + (int64_t)pc * VEC < D;
+    const int64_t col = own ? c0 + (int64_t)pc * VEC : c0;
+    const char* const ap = static_cast<const char*>(pr.a) + (b * pr.stride_ab + col) * T::kBytes;
+    const char* const bp = pr.b ? static_cast<const char*>(pr.b) + (b * pr.stride_ab + col) * T::kBytes : nullptr;
     typename PV::Raw ra[kPass], rb[kPass];
     auto load_rows = [&](int64_t t) {  // kBatch rows from time t on, clamped into the rows that hold data
 #pragma unroll
@@ -98,19 +110,25 @@ __global__ __launch_bounds__(kThreads, 2) void fir_kernel(FirArgs a) {
             if (bp) rb[i] = PV::load(bp + off);
         }
     };
-    auto write_rows = [&](int row, int end) {  // the loaded rows to the staged rows row .. min(row + kBatch, end) - 1
+    bool bad = false;  // this lane staged a value that is not finite
+    // the loaded rows, whose first is time t, to the staged rows row .. min(row + kBatch, end) - 1; zeros where no data is
+    auto write_rows = [&](int64_t t, int row, int end) {
 #pragma unroll
         for (int i = 0; i < kPass; ++i) {
             const int rr = row + i * RPP + pr0;
             if (rr < end && (kBatch % RPP == 0 || i * RPP + pr0 < kBatch)) {
+                const int64_t tt = t + i * RPP + pr0;
+                const bool data = tt >= pr.lo && tt < pr.hi;
                 float f[VEC], g[VEC];
                 PV::unpack(ra[i], f);
-                if (bp) {
-                    PV::unpack(rb[i], g);
+                if (bp) PV::unpack(rb[i], g);
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e) f[e] *= g[e];
+                for (int e = 0; e < VEC; ++e) {
+                    if (bp) f[e] *= g[e];
+                    f[e] = data ? f[e] : 0.0f;
+                    bad |= not_finite(f[e]);
                 }
-                float* dst = us + rr * kChan + pc * VEC;
+                float* dst = us + rr * kStride + pc * VEC;
                 if constexpr (VEC >= 4) {
 #pragma unroll
                     for (int e = 0; e < VEC; e += 4)
@@ -123,175 +141,209 @@ __global__ __launch_bounds__(kThreads, 2) void fir_kernel(FirArgs a) {
         }
     };
 
-    // ---- outputs: one channel per lane, a wave stores 64 channels of a row
-    constexpr int kPut = kR < 16 ? kR : 16;  // gate rows in flight
-    const uint32_t own_off = (uint32_t)(own ? lane : 0) * T::kBytes;
-    auto put = [&](int64_t t, const float (&acc)[kR], const void* gate, void* out) {  // rows t .. t + kR - 1
-        if (t >= L) return;
-        const char* gp = static_cast<const char*>(gate) + (b * pr.stride_gate + c0) * T::kBytes + t * row_bytes;
-        char* op = static_cast<char*>(out) + (b * pr.stride_out + c0) * T::kBytes + t * row_bytes;
-        const int n = L - t < kR ? (int)(L - t) : kR;
+    // ---- products: block (channel) ch of the wave, row / column l4 of the 4 x 4 tiles
+    const int ch = lane >> 2, l4 = lane & 3;
+    const float* const up = us + 4 * l4 * kStride + 16 * w + ch;
+    float wt[kSeg + 3];  // wt[m] = tap m - l4 of the segment in staged order, zero outside it
+    bool bad_tap = false;
+
+    // Tap j' of segment [ja, jb) is h[jb - 1 - j'] (causal) or h[ja + j'] (transposed); with it output row r meets the
+    // staged row r + j', whose time is tb + r + j'
+    auto load_taps = [&](int ja, int nt) {  // through the rows' memory
+        bad_tap = false;
+        constexpr int kX = (kTapStride + kWave - 1) / kWave, kCh = 8;  // channels in flight per wave
+        for (int i0 = 0; i0 < 16; i0 += kCh) {  // a wave loads its own channels' taps
+            float f[kCh][kX];
 #pragma unroll
-        for (int rb = 0; rb < kR; rb += kPut) {
-            typename P1::Raw gr[kPut];
-            if (gate) {
+            for (int c = 0; c < kCh; ++c) {
+                const float* hp = h0 + (int64_t)__builtin_amdgcn_readlane(gstep, i0 + c) * lh;
 #pragma unroll
-                for (int r = 0; r < kPut; ++r) {
-                    gr[r] = P1::load(gp + own_off);
-                    gp += rb + r + 1 < n ? row_bytes : 0;  // behind the last row it repeats
+                for (int x = 0; x < kX; ++x) {  // unconditional loads: outside the segment its first tap, not used
+                    const int jp = x * kWave + lane - 3;
+                    const int j = jp >= 0 && jp < nt ? jp : 0;
+                    f[c][x] = hp[pr.rev ? ja + j : ja + nt - 1 - j];
                 }
             }
 #pragma unroll
-            for (int r = 0; r < kPut; ++r) {
-                float z[1] = {acc[rb + r]}, gf[1];
-                if (gate) {
-                    P1::unpack(gr[r], gf);
-                    z[0] *= gf[0];
+            for (int c = 0; c < kCh; ++c)
+#pragma unroll
+                for (int x = 0; x < kX; ++x) {
+                    const int jp = x * kWave + lane - 3;
+                    const float v = jp >= 0 && jp < nt ? f[c][x] : 0.0f;
+                    bad_tap |= not_finite(v);
+                    if (x * kWave + lane < kTapStride) us[(16 * w + i0 + c) * kTapStride + x * kWave + lane] = v;
                 }
-                if (own && rb + r < n) P1::store(op + own_off, P1::pack(z));
-                op += row_bytes;
-            }
         }
+        __syncthreads();
+        const float* tp = us + (16 * w + ch) * kTapStride + 3 - l4;
+#pragma unroll
+        for (int m = 0; m < kSeg + 3; ++m) wt[m] = tp[m];
+        __syncthreads();
     };
 
-    // tap j' of segment [ja, jb) is h[jb - 1 - j'] (causal) or h[ja + j'] (transposed); with it output row r meets the
-    // staged row r + j', whose time is tb + r + j'
-    const int nseg = (lh + kSeg - 1) / kSeg;
+    const int nseg = kOne ? 1 : (lh + kSeg - 1) / kSeg;
+    if constexpr (kOne) load_taps(0, lh);
     const int64_t t_stop = t_first + (int64_t)a.steps * TR < L ? t_first + (int64_t)a.steps * TR : L;
-    bool staged = false;
+    bool prev_bad = false;
+    int par = 0;
     for (int64_t t0 = t_first; t0 < t_stop; t0 += TR) {
-        float acc[kR];
-#pragma unroll
-        for (int r = 0; r < kR; ++r) acc[r] = 0.0f;
-
+        f32x4_t acc[NT];
         for (int sg = 0; sg < nseg; ++sg) {
             const int si = pr.rev ? sg : nseg - 1 - sg;
             const int ja = si * kSeg, jb = ja + kSeg < lh ? ja + kSeg : lh;
             const int nt = jb - ja;
             const int64_t tb = pr.rev ? t0 + ja : t0 - (jb - 1);
             const int nrow = TR + nt - 1;
-
-            auto load_taps = [&](int first, float (&f)[kTapsPer]) {
-                const int jt = first + lane;  // a wave reads 64 consecutive taps of one filter per step
-#pragma unroll
-                for (int i = 0; i < kTapsPer; ++i) {
-                    const uint32_t gs = __builtin_amdgcn_readlane(gstep, w + kWaves * i);
-                    f[i] = 0.0f;
-                    if (jt < nt) f[i] = h0[(int64_t)gs * lh + (pr.rev ? ja + jt : jb - 1 - jt)];
-                }
-            };
-            auto write_taps = [&](const float (&f)[kTapsPer]) {
-#pragma unroll
-                for (int i = 0; i < kTapsPer; ++i) ts[lane * kTapStride + w + kWaves * i] = f[i];
-            };
-
-            float tp[kTapsPer];
-            load_taps(0, tp);
-            if (staged) {
-                // one segment: the halo is the end of the rows staged for the previous tile, the new rows were loaded
-                // while that tile was computed
+            if constexpr (!kOne) {
+                if (sg > 0) __syncthreads();  // every wave is done with the previous segment's rows
+                load_taps(ja, nt);
+            }
+            bad = bad_tap;
+            if (kOne && t0 > t_first) {
+                // one segment: the halo is the end of the rows staged for the previous tile
                 f32x4_t mv[kMove];
                 const int nmv = (nt - 1) * (kChan / 4);
-                const f32x4_t* src = reinterpret_cast<const f32x4_t*>(us + TR * kChan);
-                __syncthreads();  // every wave is done with the previous tile
+                auto at = [&](int row0, int x) {
+                    return reinterpret_cast<f32x4_t*>(us + (row0 + x / (kChan / 4)) * kStride) + x % (kChan / 4);
+                };
+                // all of it at once where its old and new places overlap, else in parts (fewer registers)
+                constexpr int kPart = TR >= kSeg - 1 && kMove > 2 ? 2 : kMove;
 #pragma unroll
-                for (int i = 0; i < kMove; ++i) mv[i] = src[tid + i * kThreads < nmv ? tid + i * kThreads : 0];
-                __syncthreads();
+                for (int i0 = 0; i0 < kMove; i0 += kPart) {
 #pragma unroll
-                for (int i = 0; i < kMove; ++i)
-                    if (tid + i * kThreads < nmv) reinterpret_cast<f32x4_t*>(us)[tid + i * kThreads] = mv[i];
+                    for (int i = i0; i < i0 + kPart && i < kMove; ++i)
+                        mv[i] = *at(TR, tid + i * kThreads < nmv ? tid + i * kThreads : 0);
+                    if (i0 == 0) __syncthreads();  // (nobody reads the previous tile's outputs in rows 0 .. TR - 1 any more)
+#pragma unroll
+                    for (int i = i0; i < i0 + kPart && i < kMove; ++i)
+                        if (tid + i * kThreads < nmv) *at(0, tid + i * kThreads) = mv[i];
+                }
                 if constexpr (kAhead) {
-                    write_rows(nt - 1, nrow);
+                    write_rows(tb + nt - 1, nt - 1, nrow);
                 } else {
                     for (int rw = nt - 1; rw < nrow; rw += kBatch) {
                         load_rows(tb + rw);
-                        write_rows(rw, nrow);
+                        write_rows(tb + rw, rw, nrow);
                     }
                 }
             } else {
-                if (t0 > t_first || sg > 0) __syncthreads();
                 for (int rw = 0; rw < nrow; rw += kBatch) {
                     load_rows(tb + rw);
-                    write_rows(rw, nrow);
+                    write_rows(tb + rw, rw, nrow);
                 }
+                for (int x = nrow * kStride + tid; x < kRows * kStride; x += kThreads) us[x] = 0.0f;  // meet zero taps
             }
-            write_taps(tp);
+            const bool wave_bad = __builtin_amdgcn_ballot_w64(bad) != 0;
+            if (lane == 0) flags[par][w] = wave_bad;
             __syncthreads();
-            staged = nseg == 1 && t0 + TR < t_stop;
+            bool new_bad = false;
+#pragma unroll
+            for (int i = 0; i < kWaves; ++i) new_bad |= flags[par][i] != 0;
+            par ^= 1;
+            const bool exact = __builtin_amdgcn_readfirstlane(new_bad || prev_bad);
+            prev_bad = kOne && new_bad;
             if constexpr (kAhead)
-                if (staged) load_rows(tb + TR + nt - 1);  // the next tile's rows
+                if (t0 + TR < t_stop) load_rows(tb + TR + nt - 1);  // the next tile's rows
 
-            // staged rows [vlo, vhi) hold data
-            const int64_t vlo64 = pr.lo - tb, vhi64 = pr.hi - tb;
-            const int vlo = vlo64 > 0 ? (vlo64 < nrow ? (int)vlo64 : nrow) : 0;
-            const int vhi = vhi64 < nrow ? (vhi64 > 0 ? (int)vhi64 : 0) : nrow;
-            for (int st = 0; st < nt; st += kStage) {
-                const int n = nt - st < kStage ? nt - st : kStage;
-                const bool more = st + kStage < nt;
-                if (more) load_taps(st + kStage, tp);
-                const int rs = r0 + st;  // row that output 0 of this wave meets with tap 0 of the stage
-                const float* up = us + rs * kChan + lane;
-                const float* hp = ts + lane;
-                int j = 0;
-                auto tap_block = [&](auto nb_c, auto whole_c) {  // the next nb taps of the stage
-                    constexpr int NB = decltype(nb_c)::value;
-                    float uw[kR + NB - 1], hw[NB];
+            if (sg == 0) {
 #pragma unroll
-                    for (int i = 0; i < NB; ++i) hw[i] = hp[i * kTapStride];
+                for (int k = 0; k < NT; ++k) acc[k] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            }
+            if (c0 + 16 * w < D) {
+                if (!exact) {
+                    // kX rows at a time, the next ones read while these are multiplied; the fences keep the scheduler
+                    // from reading them all at once
+                    constexpr int kX = 4, kAll = 16 * (NT - 1) + kSeg + 3;
+                    float u[2][kX];
 #pragma unroll
-                    for (int i = 0; i < kR + NB - 1; ++i) uw[i] = up[i * kChan];
-                    if constexpr (decltype(whole_c)::value) {
+                    for (int i = 0; i < kX; ++i) u[0][i] = up[i * kStride];
+                    auto rows = [&](auto xb_c) {
+                        constexpr int XB = decltype(xb_c)::value;
 #pragma unroll
-                        for (int i = 0; i < NB; ++i)
+                        for (int i = 0; i < kX; ++i)
+                            if ((XB + 1) * kX + i < kAll) u[(XB + 1) & 1][i] = up[((XB + 1) * kX + i) * kStride];
 #pragma unroll
-                            for (int r = 0; r < kR; ++r) acc[r] = __builtin_fmaf(hw[i], uw[r + i], acc[r]);
-                    } else {  // rows outside [vlo, vhi) have no term
-                        const int lo = vlo - rs - j, hi = vhi - rs - j;
+                        for (int i = 0; i < kX; ++i) {
 #pragma unroll
-                        for (int x = 0; x < kR + NB - 1; ++x) {
-                            const bool has = x >= lo && x < hi;
-#pragma unroll
-                            for (int i = 0; i < NB; ++i)
-                                if (x - i >= 0 && x - i < kR) {
-                                    const float y = __builtin_fmaf(hw[i], uw[x], acc[x - i]);
-                                    acc[x - i] = has ? y : acc[x - i];
-                                }
+                            for (int k = 0; k < NT; ++k) {
+                                const int m = XB * kX + i - 16 * k;
+                                if (m >= 0 && m < kSeg + 3)
+                                    acc[k] = __builtin_amdgcn_mfma_f32_4x4x1f32(wt[m], u[XB & 1][i], acc[k], 0, 0, 0);
+                            }
                         }
+                        __builtin_amdgcn_sched_barrier(0);
+                    };
+                    each_index(rows, std::make_integer_sequence<int, (kAll + kX - 1) / kX>{});
+                } else {
+                    // not everything is finite: the sums term by term, without the products' structural zeros and
+                    // without the rows that hold no data
+                    const int64_t vlo = pr.lo - tb, vhi = pr.hi - tb;
+                    const float* hp = h0 + (int64_t)__shfl(gstep, ch) * lh;
+                    for (int jp = 0; jp < nt; ++jp) {
+                        const float h1 = hp[pr.rev ? ja + jp : jb - 1 - jp];
+#pragma unroll
+                        for (int k = 0; k < NT; ++k)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const int row = 16 * k + i + jp;
+                                const float x = __builtin_fmaf(h1, up[row * kStride], acc[k][i]);
+                                acc[k][i] = (row + 4 * l4 >= vlo && row + 4 * l4 < vhi) ? x : acc[k][i];
+                            }
                     }
-                    j += NB;
-                    hp += NB * kTapStride;
-                    up += NB * kChan;
-                };
-                using Blk = std::integral_constant<int, kBlk>;
-                using One = std::integral_constant<int, 1>;
-                while (j + kBlk <= n && rs + j + kR + kBlk - 2 < vlo) {  // no row of the block holds data
-                    j += kBlk;
-                    hp += kBlk * kTapStride;
-                    up += kBlk * kChan;
-                }
-                while (j + kBlk <= n && rs + j < vlo) tap_block(Blk{}, std::false_type{});
-                while (j + kBlk <= n && rs + j + kR + kBlk - 2 < vhi) tap_block(Blk{}, std::true_type{});
-                while (j + kBlk <= n && rs + j < vhi) tap_block(Blk{}, std::false_type{});
-                while (j < n && rs + j < vhi) tap_block(One{}, std::false_type{});
-                if (more) {
-                    __syncthreads();
-                    write_taps(tp);
-                    __syncthreads();
                 }
             }
         }
 
-        put(t0 + r0, acc, pr.gate, pr.out);
-        if (pr.out2) put(t0 + r0, acc, pr.gate2, pr.out2);
+        // ---- outputs: through rows 0 .. TR - 1 (the halo of the next tile lies behind them), then as whole row pieces
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NT; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                us[(16 * k + 4 * l4 + i) * kStride + 16 * w + ch] = acc[k][i];
+        __syncthreads();
+        auto put = [&](const void* gate, void* out) {
+            const char* gp = static_cast<const char*>(gate) + (b * pr.stride_gate + col) * T::kBytes;
+            char* op = static_cast<char*>(out) + (b * pr.stride_out + col) * T::kBytes;
+            constexpr int kPut = kPassAll < 2 ? kPassAll : 2;  // pieces in flight
+#pragma unroll
+            for (int i0 = 0; i0 < kPassAll; i0 += kPut) {
+                typename PV::Raw gr[kPut];
+                if (gate) {
+#pragma unroll
+                    for (int i = 0; i < kPut; ++i) {
+                        int64_t t = t0 + (i0 + i) * RPP + pr0;
+                        t = t < L ? t : L - 1;
+                        gr[i] = PV::load_nt(gp + t * row_bytes);
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < kPut; ++i) {
+                    const int row = (i0 + i) * RPP + pr0;
+                    float z[VEC], gf[VEC];
+                    const float* zp = us + (row < TR ? row : 0) * kStride + pc * VEC;
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) z[e] = zp[e];
+                    if (gate) {
+                        PV::unpack(gr[i], gf);
+#pragma unroll
+                        for (int e = 0; e < VEC; ++e) z[e] *= gf[e];
+                    }
+                    if (own && row < TR && t0 + row < L) PV::store_nt(op + (t0 + row) * row_bytes, PV::pack(z));
+                }
+            }
+        };
+        put(pr.gate, pr.out);
+        if (pr.out2) put(pr.gate2, pr.out2);
+        if constexpr (!kOne) __syncthreads();  // before the next tile's taps
     }
 }
 
-template <typename T, int VEC, int kR>
-hy_status launch_r(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
-    constexpr int TR = kWaves * kR;
+template <typename T, int VEC, int kSeg, int NT, bool kOne>
+hy_status launch_nt(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
+    constexpr int TR = 16 * NT;
     const int64_t tiles = (a.L + TR - 1) / TR;
-    // two workgroups per compute unit where there are tiles enough: each then walks its share of a sequence, loading the
-    // next tile's rows while it computes
+    // two workgroups per compute unit; where there are tiles enough each walks its share of a sequence
     int64_t walks = 512 / (B * a.ncb * nprob);
     if (walks < 1) walks = 1;
     if (walks > tiles) walks = tiles;
@@ -300,15 +352,25 @@ hy_status launch_r(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
     if (steps > 0x7fffffffLL || B > 0x7fffffffLL || B * walks > 0x7fffffffLL / a.ncb) return HY_ERR_UNSUPPORTED;
     a.steps = (int32_t)steps;
     a.walks_per_seq = (int32_t)walks;
-    return launch_kernel((fir_kernel<T, VEC, kR>), dim3((uint32_t)(B * walks * a.ncb), (uint32_t)nprob), dim3(kThreads), st, a);
+    return launch_kernel((fir_kernel<T, VEC, kSeg, NT, kOne>), dim3((uint32_t)(B * walks * a.ncb), (uint32_t)nprob),
+                         dim3(kThreads), st, a);
+}
+
+template <typename T, int VEC, int NT>
+hy_status launch_seg(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
+    if (a.lh <= 32) return launch_nt<T, VEC, 32, NT, true>(a, nprob, B, st);
+    if (a.lh <= 64) return launch_nt<T, VEC, 64, NT, true>(a, nprob, B, st);
+    if (a.lh <= 128) return launch_nt<T, VEC, 128, NT, true>(a, nprob, B, st);
+    return launch_nt<T, VEC, 128, NT, false>(a, nprob, B, st);
 }
 
 template <typename T, int VEC>
 hy_status launch_vec(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
     // 128-row tiles amortise the 127 halo rows of a 128-tap filter; a problem that leaves compute units without a
-    // workgroup that way is cut into 32-row tiles instead
-    const int64_t wg = B * ((a.L + 127) / 128) * a.ncb * nprob;
-    return wg >= 256 ? launch_r<T, VEC, 32>(a, nprob, B, st) : launch_r<T, VEC, 8>(a, nprob, B, st);
+    // workgroup that way is cut into 32-row tiles instead.  (Eight waves over 128 channels, one workgroup per compute
+    // unit, measured the same on long sequences and 13% slower at 2 x 2048 x 1024.)
+    const bool wide = B * ((a.L + 127) / 128) * a.ncb * nprob >= 256;
+    return wide ? launch_seg<T, VEC, 8>(a, nprob, B, st) : launch_seg<T, VEC, 2>(a, nprob, B, st);
 }
 
 template <typename T>
