@@ -637,7 +637,7 @@ static hy_status gated_bwd(const void* dy, const void* q, const void* k, const v
         rc = check_workspace(workspace, workspace_bytes, need, others, 9);
         if (rc != HY_OK) return rc;
         if (walk) return launch_bwd_walk(p, s, workspace, st);
-        if (stencil) return launch_bwd_stencil(&p, 1, s, workspace, st);
+        if (stencil) return launch_bwd_stencil(p, s, workspace, st);
         if (mfma) return launch_mr_bwd(p, s, workspace, st);  // medium grouped filters: one pass on the matrix cores
         return launch_cp4_bwd(p, s, workspace, st);           // medium filters of single channels or small groups
     }
@@ -691,7 +691,7 @@ hy_status hyena_featurize_bwd(const void* dy, const void* x, const float* h, voi
         const Range others[5] = {{dy, bytes}, {x, bytes}, {dx, bytes}, {h, nh}, {dh, nh}};
         rc = check_workspace(workspace, workspace_bytes, bwd_stencil_workspace_bytes(s), others, 5);
         if (rc != HY_OK) return rc;
-        return launch_bwd_stencil(&p, 1, s, workspace, st);
+        return launch_bwd_stencil(p, s, workspace, st);
     }
     return launch_bwd_direct(p, s, st);
 }
@@ -775,11 +775,12 @@ hy_status hyena_chain_bwd(const void* dy, const void* q, const void* k, const vo
     // the three featurizers: one launch where q', k', v' (dead by now) have room for its partial filter gradients
     BwdShape fs{B, L, D, lf, feat_group, static_cast<hy_dtype>(dtype)};
     fs.gated = false;
-    if (bwd_stencil_supported(fs) && 3 * bwd_stencil_workspace_bytes(fs, 3) <= 3 * slot) {
+    fs.nprob = 3;
+    if (bwd_stencil_supported(fs) && bwd_stencil_workspace_bytes(fs) <= slot) {
         const BwdPtrs fp[3] = {{gq, nullptr, q, nullptr, hq, nullptr, dq, nullptr, dhq},
                                {gk, nullptr, k, nullptr, hk, nullptr, dk, nullptr, dhk},
                                {gv, nullptr, v, nullptr, hv, nullptr, dv, nullptr, dhv}};
-        return launch_bwd_stencil(fp, 3, fs, ws, static_cast<hipStream_t>(hip_stream));
+        return launch_bwd_stencil(fp[0], fs, ws, static_cast<hipStream_t>(hip_stream));
     }
     rc = hyena_featurize_bwd(gq, q, hq, dq, dhq, iw, inner, B, L, D, lf, feat_group, dtype, hip_stream);
     if (rc != HY_OK) return rc;

@@ -605,10 +605,10 @@ hy_status launch_dh_tile(const BwdPtrs& p, const BwdShape& s, hipStream_t st) {
                          st, a, s.B);
 }
 
-int stencil_rows(const BwdShape& s, int64_t nvec, int nprob) {
+int stencil_rows(const BwdShape& s, int64_t nvec) {
     int rows = tuning().se_rows;
     if (rows <= 0) {
-        const int64_t waves_per_row = (nvec * nprob + kWave - 1) / kWave;
+        const int64_t waves_per_row = (nvec * s.nprob + kWave - 1) / kWave;
         // Measured on MI355X (L = 8192, D = 4096): 256-step tiles run 10% faster than 128-step ones (half the
         // halo rows and half the partial filter gradients), as long as four waves per CU are left.
         // The featurizer variant holds half the loads and windows per lane and wants eight waves per CU (same
@@ -637,14 +637,14 @@ hy_status launch_reduce(const ReduceArgs& r, int nprob, int64_t nsets, int64_t n
 }
 
 template <typename T, int LH>
-hy_status launch_stencil_lh(const BwdPtrs* p, int nprob, const BwdShape& s, void* ws, hipStream_t st) {
+hy_status launch_stencil_lh(const BwdPtrs* p, const BwdShape& s, void* ws, hipStream_t st) {
     constexpr int VEC = stencil_vec<T>();
     constexpr int R = 4;
     BwdStencilArgs a;
     for (int i = 0; i < kMaxProb; ++i) {
-        const int x = i < nprob ? i : 0;
+        const int x = i < s.nprob ? i : 0;
         a.p[i] = p[x];
-        a.partial[i] = reinterpret_cast<float*>(static_cast<char*>(ws) + x * bwd_stencil_workspace_bytes(s, nprob));
+        a.partial[i] = reinterpret_cast<float*>(static_cast<char*>(ws) + x * bwd_stencil_workspace_bytes(s));
     }
     a.L = s.L;
     a.D = s.D;
@@ -655,14 +655,14 @@ hy_status launch_stencil_lh(const BwdPtrs* p, int nprob, const BwdShape& s, void
     a.fut = s.future;
     a.group = s.group;
     a.nvec = s.D / VEC;
-    a.rows = stencil_rows(s, a.nvec, nprob);
+    a.rows = stencil_rows(s, a.nvec);
     a.tiles_per_seq = (int32_t)((s.L + a.rows - 1) / a.rows);
     a.nitems = s.B * a.tiles_per_seq * a.nvec;
     const int64_t nb = (a.nitems + kBlock - 1) / kBlock;
     if (nb > 0x7fffffffLL) return HY_ERR_UNSUPPORTED;
     const hy_status rc = s.gated
-        ? launch_kernel((bwd_stencil_kernel<T, VEC, LH, R, true>), dim3((uint32_t)nb, (uint32_t)nprob), dim3(kBlock), st, a)
-        : launch_kernel((bwd_stencil_kernel<T, VEC, LH, R, false>), dim3((uint32_t)nb, (uint32_t)nprob), dim3(kBlock), st, a);
+        ? launch_kernel((bwd_stencil_kernel<T, VEC, LH, R, true>), dim3((uint32_t)nb, (uint32_t)s.nprob), dim3(kBlock), st, a)
+        : launch_kernel((bwd_stencil_kernel<T, VEC, LH, R, false>), dim3((uint32_t)nb, (uint32_t)s.nprob), dim3(kBlock), st, a);
     if (rc != HY_OK) return rc;
     const int64_t nsets = s.B * a.tiles_per_seq;
     ReduceArgs r;
@@ -670,20 +670,20 @@ hy_status launch_stencil_lh(const BwdPtrs* p, int nprob, const BwdShape& s, void
         r.partial[i] = a.partial[i];
         r.dh[i] = a.p[i].dh;
     }
-    return launch_reduce(r, nprob, nsets, s.D, s.lh, s.group, st);
+    return launch_reduce(r, s.nprob, nsets, s.D, s.lh, s.group, st);
 }
 
 template <typename T>
-hy_status launch_stencil_t(const BwdPtrs* p, int nprob, const BwdShape& s, void* ws, hipStream_t st) {
+hy_status launch_stencil_t(const BwdPtrs* p, const BwdShape& s, void* ws, hipStream_t st) {
     switch (s.lh) {
-        case 1: return launch_stencil_lh<T, 1>(p, nprob, s, ws, st);
-        case 2: return launch_stencil_lh<T, 2>(p, nprob, s, ws, st);
-        case 3: return launch_stencil_lh<T, 3>(p, nprob, s, ws, st);
-        case 4: return launch_stencil_lh<T, 4>(p, nprob, s, ws, st);
-        case 5: return launch_stencil_lh<T, 5>(p, nprob, s, ws, st);
-        case 6: return launch_stencil_lh<T, 6>(p, nprob, s, ws, st);
-        case 7: return launch_stencil_lh<T, 7>(p, nprob, s, ws, st);
-        case 8: return launch_stencil_lh<T, 8>(p, nprob, s, ws, st);
+        case 1: return launch_stencil_lh<T, 1>(p, s, ws, st);
+        case 2: return launch_stencil_lh<T, 2>(p, s, ws, st);
+        case 3: return launch_stencil_lh<T, 3>(p, s, ws, st);
+        case 4: return launch_stencil_lh<T, 4>(p, s, ws, st);
+        case 5: return launch_stencil_lh<T, 5>(p, s, ws, st);
+        case 6: return launch_stencil_lh<T, 6>(p, s, ws, st);
+        case 7: return launch_stencil_lh<T, 7>(p, s, ws, st);
+        case 8: return launch_stencil_lh<T, 8>(p, s, ws, st);
         default: return HY_ERR_UNSUPPORTED;
     }
 }
@@ -742,16 +742,16 @@ bool bwd_stencil_supported(const BwdShape& s) {
     return s.lh <= 8 && s.D % vec == 0;
 }
 
-int64_t bwd_stencil_workspace_bytes(const BwdShape& s, int nprob) {
+int64_t bwd_stencil_workspace_bytes(const BwdShape& s) {
     const int vec = s.dtype == HY_BF16 ? 2 : 1;
-    const int rows = stencil_rows(s, s.D / vec, nprob);
+    const int rows = stencil_rows(s, s.D / vec);
     const int64_t tiles = (s.L + rows - 1) / rows;
     return s.B * tiles * s.D * s.lh * (int64_t)sizeof(float);
 }
 
-hy_status launch_bwd_stencil(const BwdPtrs* p, int nprob, const BwdShape& s, void* ws, hipStream_t st) {
-    if (!bwd_stencil_supported(s) || nprob < 1 || nprob > kMaxProb) return HY_ERR_UNSUPPORTED;
-    return s.dtype == HY_BF16 ? launch_stencil_t<BF16>(p, nprob, s, ws, st) : launch_stencil_t<F32>(p, nprob, s, ws, st);
+hy_status launch_bwd_stencil(const BwdPtrs& p, const BwdShape& s, void* ws, hipStream_t st) {
+    if (!bwd_stencil_supported(s) || s.nprob < 1 || s.nprob > kMaxProb) return HY_ERR_UNSUPPORTED;
+    return s.dtype == HY_BF16 ? launch_stencil_t<BF16>(&p, s, ws, st) : launch_stencil_t<F32>(&p, s, ws, st);
 }
 
 hy_status launch_dh_reduce(const float* partial, float* dh, int64_t nsets, int64_t n_rows, int32_t lh, int32_t group,

@@ -95,6 +95,7 @@ struct BwdShape {
     int32_t history = 0, future = 0;
     bool gated = true;        // false: backward of the ungated featurizer convolution (x = k, dx = dk; no q, v, dq, dv);
                               // stencil and general kernels only
+    int32_t nprob = 1;        // problems of this shape in one launch, up to 3; launch_bwd_stencil only
     bool shard_call = false;  // came in through a shard entry point: the kernels' shard variants, whatever the values
     int64_t stride_kv() const { return bstride_kv > 0 ? bstride_kv : L * D; }
     int64_t stride_gq() const { return bstride_gq > 0 ? bstride_gq : L * D; }
@@ -210,9 +211,9 @@ hy_status launch_li_state_fold(const float* states, int64_t n, int64_t steps, co
 hy_status launch_li_direct(const LiPtrs& p, const LiShape& s, hipStream_t st);
 // Backward, short filters: fused streaming pass + reduction of partial filter gradients held in `ws`.
 bool bwd_stencil_supported(const BwdShape& s);
-// Up to three problems of one shape per launch; `ws` holds bwd_stencil_workspace_bytes(s, nprob) bytes for each.
-int64_t bwd_stencil_workspace_bytes(const BwdShape& s, int nprob = 1);
-hy_status launch_bwd_stencil(const BwdPtrs* p, int nprob, const BwdShape& s, void* ws, hipStream_t st);
+// `p` is the first of s.nprob problems; `ws` holds bwd_stencil_workspace_bytes(s) bytes for each.
+int64_t bwd_stencil_workspace_bytes(const BwdShape& s);
+hy_status launch_bwd_stencil(const BwdPtrs& p, const BwdShape& s, void* ws, hipStream_t st);
 // Backward, short bf16 filters on long stretches of time: the same arithmetic on the tile-walking data movement
 // (256 channels per workgroup, 16-row chunks through LDS); bwd_walk_preferred() says when the dispatcher takes it.
 bool bwd_walk_preferred(const BwdShape& s);
