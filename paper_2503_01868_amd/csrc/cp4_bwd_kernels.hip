@@ -274,9 +274,8 @@ int64_t dh_rows(const BwdShape& s) {
     const int64_t ncb = s.D / kC;
     int64_t rows = tuning().mr_rows;
     if (rows <= 0) {
-        const int64_t tiles = tiles_filling_rounds(s.B * ncb, s.L, 4 * kT);  // one workgroup per CU
-        rows = (s.L + tiles - 1) / tiles;
-        if (rows < 4 * kT) rows = 4 * kT;
+        rows = one_round_rows(s.B * ncb, s.L, 4 * kT, kT);
+        if (rows < 2 * kT) rows = 2 * kT;  // as short as the history a tile starts with (each also leaves partial rows)
     }
     rows = (rows + kT - 1) / kT * kT;
     const int64_t cap = (s.L + kT - 1) / kT * kT;

@@ -569,9 +569,7 @@ hy_status launch_cp4_nw(const ConvPtrs& p, const ConvShape& s, hipStream_t st) {
     a.hist = s.history;
     int64_t rows = tuning().mr_rows;
     if (rows <= 0) {
-        const int64_t tiles = tiles_filling_rounds(s.B * a.ncb, s.L, 4 * kT);  // one workgroup per CU
-        rows = (s.L + tiles - 1) / tiles;
-        if (rows < 4 * kT) rows = 4 * kT;
+        rows = one_round_rows(s.B * a.ncb, s.L, 4 * kT, kT);
     }
     rows = (rows + kT - 1) / kT * kT;
     if (rows > (s.L + kT - 1) / kT * kT) rows = (s.L + kT - 1) / kT * kT;
@@ -605,9 +603,7 @@ hy_status launch_cp4_ws(const ConvPtrs& p, const ConvShape& s, hipStream_t st) {
     a.hist = s.history;
     int64_t rows = tuning().mr_rows;
     if (rows <= 0) {
-        const int64_t tiles = tiles_filling_rounds(s.B * a.ncb, s.L, 4 * kT);  // one workgroup per CU
-        rows = (s.L + tiles - 1) / tiles;
-        if (rows < 4 * kT) rows = 4 * kT;
+        rows = one_round_rows(s.B * a.ncb, s.L, 4 * kT, kT);
     }
     rows = (rows + kT - 1) / kT * kT;
     if (rows > (s.L + kT - 1) / kT * kT) rows = (s.L + kT - 1) / kT * kT;

@@ -456,7 +456,8 @@ int64_t li_rows(const LiShape& s, int nw) {
         int64_t tiles = 256 / (s.B * ncb);
         if (tiles < 1) tiles = 1;
         rows = (s.L + tiles - 1) / tiles;
-        if (rows < 4 * kChunk) rows = 4 * kChunk;
+        const int64_t min_rows = (nw == 4 ? 2 : 4) * kChunk;
+        if (rows < min_rows) rows = min_rows;
     }
     rows = (rows + kChunk - 1) / kChunk * kChunk;
     const int64_t cap = (s.L + kChunk - 1) / kChunk * kChunk;
@@ -468,7 +469,10 @@ int li_waves(const LiShape& s) {
     // Left to itself, a problem that gives a 256-channel workgroup fewer than 512 steps takes 128-channel workgroups
     // (half as many tiles per sequence, twice as long): measured at B = 1, D = 4096: L = 2048 29.8 against 32.5 us,
     // L = 4096 45.8 against 48.6; from L = 8192 on the wide workgroup wins (76.2 against 79.2 us).
-    if (tuning().mr_waves == 0 && tuning().mr_rows == 0 && s.D % 256 == 0 && li_rows(s, 16) < 512) return 8;
+    // Where those would be at their shortest (four chunks) as well, 64-channel workgroups: B = 1, L = 512: D = 256 17.7 ->
+    // 15.0 us, D = 4096 20.0 -> 18.4; L = 2048, D = 1024 19.9 -> 18.5; L = 2048, D = 4096 stays (29.5 against 31.3).
+    if (tuning().mr_waves == 0 && tuning().mr_rows == 0 && s.D % 256 == 0 && li_rows(s, 16) < 512)
+        return li_rows(s, 8) <= 4 * kChunk ? 4 : 8;
     // A batch that fills the chip with narrower workgroups of ONE tile per sequence takes them: a single pass moves
     // 8 bytes per output where the two-pass scan moves 12 (measured at L = 8192, D = 4096: B = 8 400 us with 8
     // waves against 445 with 16, B = 4 197 us with 4 waves against 241; B = 16 fills it with 16 waves: 695 us, 77%).

@@ -423,11 +423,10 @@ int64_t mr_bwd_rows(const BwdShape& s) {
     const int nkb = (s.lh - 1 + 31) / 32 + 1;
     int64_t rows = tuning().mr_rows;
     if (rows <= 0) {
-        const int64_t base = s.B * ncb;
-        const int64_t min_rows = 4LL * kChunk * (nkb > 1 ? nkb - 1 : 1);
-        const int64_t tiles = tiles_filling_rounds(base, s.L, min_rows);  // one wave per SIMD: per-CU bound
-        rows = (s.L + tiles - 1) / tiles;
-        if (rows < min_rows) rows = min_rows;
+        const int64_t halo = (int64_t)kChunk * (nkb > 1 ? nkb - 1 : 1);
+        rows = one_round_rows(s.B * ncb, s.L, 4 * halo, kChunk);
+        // (a tile as short as its halo: each one also leaves a row of partial filter gradients per slice)
+        if (rows < halo) rows = halo;
     }
     rows = (rows + kChunk - 1) / kChunk * kChunk;
     const int64_t cap = (s.L + kChunk - 1) / kChunk * kChunk;
