@@ -51,10 +51,18 @@ __global__ __launch_bounds__(kBlock) void bwd_stencil_kernel(BwdStencilArgs a) {
     const BwdPtrs pr = a.p[blockIdx.y];
     const int64_t item = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (item >= a.nitems) return;
-    const int64_t cv = item % a.nvec;
-    const int64_t tile = item / a.nvec;
-    const int64_t b = tile / a.tiles_per_seq;
-    const int64_t t0 = (tile % a.tiles_per_seq) * (int64_t)a.rows;
+    int64_t cv, tile, b, t0;
+    if (a.nitems <= 0xffffffffLL) {  // 32-bit divisions: those of 64 bits are a good part of a small launch
+        tile = (uint32_t)item / (uint32_t)a.nvec;
+        cv = (uint32_t)item - (uint32_t)tile * (uint32_t)a.nvec;
+        b = (uint32_t)tile / (uint32_t)a.tiles_per_seq;
+        t0 = (int64_t)((uint32_t)tile - (uint32_t)b * (uint32_t)a.tiles_per_seq) * a.rows;
+    } else {
+        cv = item % a.nvec;
+        tile = item / a.nvec;
+        b = tile / a.tiles_per_seq;
+        t0 = (tile % a.tiles_per_seq) * (int64_t)a.rows;
+    }
     const int64_t t1 = (t0 + a.rows < a.L) ? t0 + a.rows : a.L;
     const int64_t L = a.L, D = a.D;
     const int64_t c = cv * VEC;
@@ -70,7 +78,8 @@ __global__ __launch_bounds__(kBlock) void bwd_stencil_kernel(BwdStencilArgs a) {
     float taps[VEC][LH], dh[VEC][LH];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
-        const float* hp = pr.h + ((c + e) / a.group) * (int64_t)LH;
+        const int64_t g = D <= 0xffffffffLL ? (int64_t)((uint32_t)(c + e) / (uint32_t)a.group) : (c + e) / a.group;
+        const float* hp = pr.h + g * (int64_t)LH;
 #pragma unroll
         for (int j = 0; j < LH; ++j) {
             taps[e][j] = hp[j];
@@ -615,7 +624,13 @@ int stencil_rows(const BwdShape& s, int64_t nvec) {
         // shape: 48.5 us with 128-step tiles, 66 us with 256).
         rows = 256;
         const int64_t want = s.gated ? 1024 : 2048;
-        while (rows > 32 && s.B * ((s.L + rows - 1) / rows) * waves_per_row < want) rows >>= 1;
+        auto waves = [&] { return s.B * ((s.L + rows - 1) / rows) * waves_per_row; };
+        while (rows > 32 && waves() < want) rows >>= 1;
+        // With two waves per CU or fewer a launch is as long as one lane's chain of batches: shorter tiles still, for the
+        // price of halo rows and partial filter gradients (rows 32 / 16 / 8, bf16, 7 taps: 512 x 256 18.2 / 13.7 / 12.3
+        // us, 512 x 4096 19.5 / 16.7 / 18.6, 2 x 1000 x 768 17.8 / 15.0 / 17.2; 2048 x 1024 20.1 / 20.0 / 24.2).  Three
+        // problems at a time stop at 16, where their partial sums still fit the chain's workspace.
+        while (rows > (s.nprob > 1 ? 16 : 8) && waves() <= 512) rows >>= 1;
     }
     if (rows > s.L) rows = (int)s.L;
     if (rows < 1) rows = 1;
