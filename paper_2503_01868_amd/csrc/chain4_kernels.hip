@@ -124,28 +124,16 @@ __global__ __launch_bounds__((kWM + kWV) * 64, 3) void chain4_kernel(Chain4Args 
                 }
             }
         }
-        // ---- Toeplitz operands of the medium filter: operand i serves d = 16 i; lane (li = output step, lq = source
-        // octet), element e holds h[d + li - 8 lq - e], zero outside [0, lh).  The filter is staged in the wave's
-        // own q' lines, which nothing else touches before the first iteration.
+        // ---- Toeplitz operands of the medium filter, staged in the wave's own q' lines, which nothing else touches
+        // before the first iteration
         bf16x8_t tz[2 * NKB];
         {
             float* hsw = reinterpret_cast<float*>(qst + (16 * w) * kQS);
             const float* hp = a.h + ((cblock0 + 16 * w) / a.group) * (int64_t)a.lh;
-            for (int j = lane; j < kTaps; j += 64) hsw[j] = (j < a.lh) ? hp[j] : 0.0f;
+            static_assert((kTapPad + kTaps) * 4 <= 16 * kQS, "the filter fits the wave's q' lines");
+            stage_filter<kTaps>(hsw, hp, a.lh, lane);
             __syncthreads();
-#pragma unroll
-            for (int i = 0; i < 2 * NKB; ++i) {
-                Words<4> wds;
-#pragma unroll
-                for (int e2 = 0; e2 < 4; ++e2) {
-                    const int i0 = 16 * i + li - 8 * lq - 2 * e2;
-                    const int i1 = i0 - 1;
-                    const float f0 = (i0 >= 0 && i0 < kTaps) ? hsw[i0] : 0.0f;
-                    const float f1 = (i1 >= 0 && i1 < kTaps) ? hsw[i1] : 0.0f;
-                    wds.w[e2] = pack_bf16x2(f0, f1);
-                }
-                tz[i] = __builtin_bit_cast(bf16x8_t, wds);
-            }
+            toeplitz_operands(tz, hsw, li, lq);
         }
         bf16x8_t uw[NKB];  // window of the last NKB source blocks of 32 steps
         {

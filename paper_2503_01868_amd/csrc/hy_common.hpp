@@ -179,6 +179,36 @@ struct Pack {
     }
 };
 
+// A wave's medium filter and its Toeplitz operands.  stage_filter leaves kTapPad zeros and then kTaps taps (zero from lh
+// on) in `hs`, all loads in flight at once; after a barrier toeplitz_operands reads operand i, which serves the offset
+// d = (output tile start) - (source block start) = 16 i: lane (li = output step, lq = source octet), element e holds
+// h[d + li - 8 lq - e] as bf16, zero outside [0, lh).  The zeros in front replace a test per element.
+constexpr int kTapPad = 32;  // 8 lq + e <= 31 taps reach below tap 0
+template <int kTaps>
+__device__ __forceinline__ void stage_filter(float* hs, const float* hp, int lh, int lane) {
+    constexpr int N = (kTaps + kWave - 1) / kWave;
+    float f[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) f[i] = hp[i * kWave + lane < lh ? i * kWave + lane : 0];
+    if (lane < kTapPad) hs[lane] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int j = i * kWave + lane;
+        if (j < kTaps) hs[kTapPad + j] = j < lh ? f[i] : 0.0f;
+    }
+}
+template <int N>
+__device__ __forceinline__ void toeplitz_operands(bf16x8_t (&tz)[N], const float* hs, int li, int lq) {
+    const float* p = hs + kTapPad + li - 8 * lq;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        Words<4> wds;
+#pragma unroll
+        for (int e2 = 0; e2 < 4; ++e2) wds.w[e2] = pack_bf16x2(p[16 * i - 2 * e2], p[16 * i - 2 * e2 - 1]);
+        tz[i] = __builtin_bit_cast(bf16x8_t, wds);
+    }
+}
+
 // Note on workgroup order: workgroups are dealt to the 8 XCDs round-robin by launch index.  Every kernel
 // here keeps the plain launch order with the fastest-varying tile index along a row, so that all XCDs
 // sweep one compact address window together; giving each XCD its own contiguous range of tiles was

@@ -72,7 +72,7 @@ __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
     __shared__ uint4 dyring[NR][kChunk * PPR];         // raw dy pieces, written and read back by the same lane
     __shared__ __attribute__((aligned(16))) char zst[2][kChunk * ZROW];   // du, fp32 rows
     __shared__ __attribute__((aligned(16))) char zst2[2][kChunk * ZROW];  // z, fp32 rows
-    __shared__ float hs[NW][kTaps];
+    __shared__ float hs[NW][kTapPad + kTaps];
 
     const int tid = threadIdx.x;
     const int w = tid / 64, lane = tid % 64;
@@ -146,21 +146,9 @@ __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
     bf16x8_t tz[2 * NKB];
     {
         const float* hp = a.h + (c0 / a.group) * (int64_t)a.lh;
-        for (int j = lane; j < kTaps; j += 64) hs[w][j] = (j < a.lh) ? hp[j] : 0.0f;
+        stage_filter<kTaps>(hs[w], hp, a.lh, lane);
         __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 2 * NKB; ++i) {
-            Words<4> wds;
-#pragma unroll
-            for (int e2 = 0; e2 < 4; ++e2) {
-                const int i0 = 16 * i + li - 8 * lq - 2 * e2;
-                const int i1 = i0 - 1;
-                const float f0 = (i0 >= 0 && i0 < kTaps) ? hs[w][i0] : 0.0f;
-                const float f1 = (i1 >= 0 && i1 < kTaps) ? hs[w][i1] : 0.0f;
-                wds.w[e2] = pack_bf16x2(f0, f1);
-            }
-            tz[i] = __builtin_bit_cast(bf16x8_t, wds);
-        }
+        toeplitz_operands(tz, hs[w], li, lq);
     }
     // gw[m]: g block of chunk ci - m, source steps in walk order; uw[m]: u block of chunk ci - m, source steps in
     // reversed order (element e of octet lq = step 31 - 8 lq - e of the chunk)
@@ -358,11 +346,11 @@ __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
             const int delta = lane - 15;  // i - n
             const int j = 16 * x + delta;
             if (j >= 0 && j < a.lh) {
-                float s = 0.0f;
-                for (int i = 0; i < 16; ++i) {
-                    const int n = i - delta;
-                    if (n >= 0 && n < 16) s += tilebuf[i * 17 + n];
-                }
+                float v[16], s = 0.0f;  // all reads in flight, then the diagonal in order
+#pragma unroll
+                for (int i = 0; i < 16; ++i) v[i] = tilebuf[i * 17 + ((i - delta) & 15)];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) s += (i - delta >= 0 && i - delta < 16) ? v[i] : 0.0f;
                 dhw[j] += s;
             }
         }

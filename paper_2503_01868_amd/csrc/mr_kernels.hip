@@ -57,7 +57,7 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : (NKB > 13 ? 1 : 2)) void mr
     static_assert(NW % 4 == 0, "the LDS swizzle needs 8 pieces per row");
     __shared__ uint4 stage[2][kChunk * PPR];
     __shared__ __attribute__((aligned(16))) char zst[2][kChunk * ZROW];
-    __shared__ float hs[NW][kTaps];
+    __shared__ float hs[NW][kTapPad + kTaps];
 
     const int tid = threadIdx.x;
     const int w = tid / 64, lane = tid % 64;
@@ -125,27 +125,13 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : (NKB > 13 ? 1 : 2)) void mr
         if (i + 1 < kPrefetch) load_q(i, qpre[i]);  // the last q stage is filled by the first iteration
     }
 
-    // ---- Toeplitz operands: operand i serves d = (output tile start) - (source block start) = 16 i; in it
-    // lane (li = output step, lq = source octet), element e holds h[d + li - 8 lq - e] (zero outside
-    // [0, lh)), rounded to bf16.  The wave's filter goes through LDS once so the gather is not 80 global loads.
+    // ---- Toeplitz operands; the wave's filter goes through LDS once so the gather is not 80 global loads
     bf16x8_t tz[2 * NKB];
     {
         const float* hp = a.h + (c0 / a.group) * (int64_t)a.lh;
-        for (int j = lane; j < kTaps; j += 64) hs[w][j] = (j < a.lh) ? hp[j] : 0.0f;
+        stage_filter<kTaps>(hs[w], hp, a.lh, lane);
         __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 2 * NKB; ++i) {
-            Words<4> wds;
-#pragma unroll
-            for (int e2 = 0; e2 < 4; ++e2) {
-                const int i0 = 16 * i + li - 8 * lq - 2 * e2;
-                const int i1 = i0 - 1;
-                const float f0 = (i0 >= 0 && i0 < kTaps) ? hs[w][i0] : 0.0f;
-                const float f1 = (i1 >= 0 && i1 < kTaps) ? hs[w][i1] : 0.0f;
-                wds.w[e2] = pack_bf16x2(f0, f1);
-            }
-            tz[i] = __builtin_bit_cast(bf16x8_t, wds);
-        }
+        toeplitz_operands(tz, hs[w], li, lq);
     }
 
     // ---- register window of the last NKB source blocks (block m starts 32 m steps before the chunk)
