@@ -611,7 +611,15 @@ hy_status launch_cp4_ws(const ConvPtrs& p, const ConvShape& s, hipStream_t st) {
     a.tiles_per_seq = (int32_t)((s.L + rows - 1) / rows);
     const int64_t nb = s.B * a.tiles_per_seq * a.ncb;
     if (nb > 0x7fffffffLL) return HY_ERR_UNSUPPORTED;
-    if (dual) return launch_kernel((cp4ws_kernel<NBK, PF, true>), dim3((uint32_t)nb), dim3((kWM + kWV) * 64), st, a);
+    if (dual) {
+        // With four tensors per step two iterations in flight spill registers.  That pays only in long tiles, where it
+        // is the stream and not the start of a tile that counts (dk, dv launch within the ungrouped backward, 128 taps:
+        // one against two: 2 x 3000 x 2048, tiles of 384 steps, 105 against 110 us in all; 1 x 8192 x 4096, 1024 steps,
+        // 223 against 228; 1 x 32768 x 4096, 4096 steps, 737 against 725).
+        if (rows <= 2048)
+            return launch_kernel((cp4ws_kernel<NBK, 1, true>), dim3((uint32_t)nb), dim3((kWM + kWV) * 64), st, a);
+        return launch_kernel((cp4ws_kernel<NBK, PF, true>), dim3((uint32_t)nb), dim3((kWM + kWV) * 64), st, a);
+    }
     return launch_kernel((cp4ws_kernel<NBK, PF, false>), dim3((uint32_t)nb), dim3((kWM + kWV) * 64), st, a);
 }
 
