@@ -184,7 +184,7 @@ __global__ __launch_bounds__(kThreads, 2) void fir_kernel(FirArgs a) {
     const int nseg = kOne ? 1 : (lh + kSeg - 1) / kSeg;
     if constexpr (kOne) load_taps(0, lh);
     const int64_t t_stop = t_first + (int64_t)a.steps * TR < L ? t_first + (int64_t)a.steps * TR : L;
-    bool prev_bad = false;
+    int clean = 1 << 30;  // tiles since values that are not finite were staged
     int par = 0;
     for (int64_t t0 = t_first; t0 < t_stop; t0 += TR) {
         f32x4_t acc[NT];
@@ -240,8 +240,10 @@ __global__ __launch_bounds__(kThreads, 2) void fir_kernel(FirArgs a) {
 #pragma unroll
             for (int i = 0; i < kWaves; ++i) new_bad |= flags[par][i] != 0;
             par ^= 1;
-            const bool exact = __builtin_amdgcn_readfirstlane(new_bad || prev_bad);
-            prev_bad = kOne && new_bad;
+            // rows of this tile's halo were staged up to kBack tiles ago
+            constexpr int kBack = kOne ? (kSeg - 1 + TR - 1) / TR : 0;
+            clean = new_bad ? 0 : (clean < kBack + 1 ? clean + 1 : clean);
+            const bool exact = __builtin_amdgcn_readfirstlane(clean <= kBack);
             if constexpr (kAhead)
                 if (t0 + TR < t_stop) load_rows(tb + TR + nt - 1);  // the next tile's rows
 
