@@ -470,9 +470,10 @@ int li_waves(const LiShape& s) {
     // (half as many tiles per sequence, twice as long): measured at B = 1, D = 4096: L = 2048 29.8 against 32.5 us,
     // L = 4096 45.8 against 48.6; from L = 8192 on the wide workgroup wins (76.2 against 79.2 us).
     // Where those would be at their shortest (four chunks) as well, 64-channel workgroups: B = 1, L = 512: D = 256 17.7 ->
-    // 15.0 us, D = 4096 20.0 -> 18.4; L = 2048, D = 1024 19.9 -> 18.5; L = 2048, D = 4096 stays (29.5 against 31.3).
+    // 15.0 us, D = 4096 20.0 -> 18.4; L = 2048, D = 1024 19.9 -> 18.5, unless their tiles would
+    // be much longer (L = 1000, D = 4096: 256 steps 22.2 us, 128 steps of 8 waves 21.4).
     if (tuning().mr_waves == 0 && tuning().mr_rows == 0 && s.D % 256 == 0 && li_rows(s, 16) < 512)
-        return li_rows(s, 8) <= 4 * kChunk ? 4 : 8;
+        return li_rows(s, 8) <= 4 * kChunk && li_rows(s, 4) <= 6 * kChunk ? 4 : 8;
     // A batch that fills the chip with narrower workgroups of ONE tile per sequence takes them: a single pass moves
     // 8 bytes per output where the two-pass scan moves 12 (measured at L = 8192, D = 4096: B = 8 400 us with 8
     // waves against 445 with 16, B = 4 197 us with 4 waves against 241; B = 16 fills it with 16 waves: 695 us, 77%).
