@@ -772,11 +772,14 @@ hy_status hyena_chain_bwd(const void* dy, const void* q, const void* k, const vo
     if (rc != HY_OK) return rc;
     rc = hyena_mr_bwd(dy, qf, kf, vf, h, gq, gk, gv, dh, iw, inner, B, L, D, lh, group, dtype, hip_stream);
     if (rc != HY_OK) return rc;
-    // the three featurizers: one launch where q', k', v' (dead by now) have room for its partial filter gradients
+    // The three featurizers: one launch where q', k', v' (dead by now) have room for its partial filter gradients.  It
+    // saves the ramps of two launches and loses a little locality between the tensors, so not for the longest inputs
+    // (whole call, three launches -> one: 1 x 8192 x 4096 343 -> 318 us, 1 x 32768 x 4096 1131 -> 1113, 4 x 32768 x 4096
+    // 4302 -> 4418).
     BwdShape fs{B, L, D, lf, feat_group, static_cast<hy_dtype>(dtype)};
     fs.gated = false;
     fs.nprob = 3;
-    if (bwd_stencil_supported(fs) && bwd_stencil_workspace_bytes(fs) <= slot) {
+    if (B * L * D <= (1LL << 27) && bwd_stencil_supported(fs) && bwd_stencil_workspace_bytes(fs) <= slot) {
         const BwdPtrs fp[3] = {{gq, nullptr, q, nullptr, hq, nullptr, dq, nullptr, dhq},
                                {gk, nullptr, k, nullptr, hk, nullptr, dk, nullptr, dhk},
                                {gv, nullptr, v, nullptr, hv, nullptr, dv, nullptr, dhv}};
