@@ -188,6 +188,10 @@ __global__ __launch_bounds__(kThreads, 2) void fir_kernel(FirArgs a) {
     int par = 0;
     for (int64_t t0 = t_first; t0 < t_stop; t0 += TR) {
         f32x4_t acc[NT];
+        if constexpr (!kOne) {
+#pragma unroll
+            for (int k = 0; k < NT; ++k) acc[k] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        }
         for (int sg = 0; sg < nseg; ++sg) {
             const int si = pr.rev ? sg : nseg - 1 - sg;
             const int ja = si * kSeg, jb = ja + kSeg < lh ? ja + kSeg : lh;
@@ -195,7 +199,8 @@ __global__ __launch_bounds__(kThreads, 2) void fir_kernel(FirArgs a) {
             const int64_t tb = pr.rev ? t0 + ja : t0 - (jb - 1);
             const int nrow = TR + nt - 1;
             if constexpr (!kOne) {
-                if (sg > 0) __syncthreads();  // every wave is done with the previous segment's rows
+                if (tb + nrow <= pr.lo || tb >= pr.hi) continue;  // a filter longer than the sequence: no row holds data
+                __syncthreads();  // every wave is done with the previous segment's rows
                 load_taps(ja, nt);
             }
             bad = bad_tap;
@@ -247,7 +252,7 @@ __global__ __launch_bounds__(kThreads, 2) void fir_kernel(FirArgs a) {
             if constexpr (kAhead)
                 if (t0 + TR < t_stop) load_rows(tb + TR + nt - 1);  // the next tile's rows
 
-            if (sg == 0) {
+            if constexpr (kOne) {
 #pragma unroll
                 for (int k = 0; k < NT; ++k) acc[k] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
             }
