@@ -211,7 +211,8 @@ __global__ __launch_bounds__(kThreads, 2) void fir_kernel(FirArgs a) {
                 auto at = [&](int row0, int x) {
                     return reinterpret_cast<f32x4_t*>(us + (row0 + x / (kChan / 4)) * kStride) + x % (kChan / 4);
                 };
-                // all of it at once where its old and new places overlap, else in parts (fewer registers)
+                // all of it at once where its old and new places overlap, else in parts (fewer registers).  The rows written
+                // after this are among its old places, so parts that are read behind the first barrier need another.
                 constexpr int kPart = TR >= kSeg - 1 && kMove > 2 ? 2 : kMove;
 #pragma unroll
                 for (int i0 = 0; i0 < kMove; i0 += kPart) {
@@ -223,6 +224,7 @@ __global__ __launch_bounds__(kThreads, 2) void fir_kernel(FirArgs a) {
                     for (int i = i0; i < i0 + kPart && i < kMove; ++i)
                         if (tid + i * kThreads < nmv) *at(0, tid + i * kThreads) = mv[i];
                 }
+                if constexpr (kPart < kMove) __syncthreads();
                 if constexpr (kAhead) {
                     write_rows(tb + nt - 1, nt - 1, nrow);
                 } else {

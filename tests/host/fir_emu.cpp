@@ -1,0 +1,108 @@
+// The general FIR kernel, run on the CPU: values and barriers of walks over several tiles.  Every output has to be the
+// bits of a plain loop over its terms (the order the kernel states), whichever wave of a workgroup runs ahead.
+#include <math.h>
+#include <stdio.h>
+
+#include "direct_kernels.hip"
+
+static uint16_t to_bf16(float x) {  // round to nearest even, finite values
+    const uint32_t u = __builtin_bit_cast(uint32_t, x);
+    return (uint16_t)((u + 0x7fff + ((u >> 16) & 1)) >> 16);
+}
+extern "C" __bf16 __truncsfbf2(float x) { return __builtin_bit_cast(__bf16, to_bf16(x)); }  // the compiler's conversion
+
+using namespace hy;
+
+namespace {
+
+uint32_t g_state = 1;
+float draw() {
+    g_state = g_state * 1664525u + 1013904223u;
+    return (float)(int32_t)g_state * 4.6566129e-10f;
+}
+float bf16_value(float x) { return __builtin_bit_cast(float, (uint32_t)to_bf16(x) << 16); }
+
+struct Tensor {  // [B, L, D]
+    int64_t L, D;
+    bool bf16;
+    void* p;
+    Tensor(int64_t B, int64_t L_, int64_t D_, bool bf) : L(L_), D(D_), bf16(bf), p(nullptr) {
+        if (posix_memalign(&p, 64, (size_t)(B * L * D * (bf ? 2 : 4)))) abort();
+        memset(p, 0xff, (size_t)(B * L * D * (bf ? 2 : 4)));  // NaN where a test leaves it
+    }
+    ~Tensor() { free(p); }
+    float get(int64_t t, int64_t c) const {
+        return bf16 ? __builtin_bit_cast(float, (uint32_t)static_cast<uint16_t*>(p)[t * D + c] << 16)
+                    : static_cast<float*>(p)[t * D + c];
+    }
+    void set(int64_t t, int64_t c, float x) {
+        if (bf16) static_cast<uint16_t*>(p)[t * D + c] = to_bf16(x);
+        else static_cast<float*>(p)[t * D + c] = x;
+    }
+};
+
+// All outputs of one workgroup of the second walk (the last, possibly ragged channel block), against the plain loop.
+// `infinite`: one sample in front of the walk is.
+int check(int64_t L, int64_t D, int lh, int group, bool bf16, bool rev, bool descending, bool infinite) {
+    constexpr int kTile = 128;
+    const int64_t ncb = (D + 63) / 64, tiles = (L + kTile - 1) / kTile;
+    const int64_t walks = 512 / ncb, steps = (tiles + walks - 1) / walks;
+    const int64_t c0 = (ncb - 1) * 64, t0 = steps * kTile, t1 = 2 * steps * kTile < L ? 2 * steps * kTile : L;
+    if (tiles * ncb < 256 || steps < 3 || t1 - t0 != steps * kTile) return printf("not the walk this is meant for\n"), 1;
+    Tensor a(1, L, D, bf16), b(1, L, D, bf16), gate(1, L, D, bf16), out(1, L, D, bf16);
+    float* h = static_cast<float*>(malloc((size_t)(D / group * lh * 4)));
+    for (int64_t i = 0; i < D / group * lh; ++i) h[i] = draw();
+    for (int64_t t = t0 > lh ? t0 - lh : 0; t < (t1 + lh < L ? t1 + lh : L); ++t)
+        for (int64_t c = c0; c < D; ++c) {
+            a.set(t, c, draw());
+            b.set(t, c, draw());
+            gate.set(t, c, draw());
+        }
+    if (infinite) a.set(rev ? t1 + 3 : t0 - 3, c0 + 5, INFINITY);
+    FirProblem p;
+    p.a = a.p; p.b = b.p; p.h = h; p.gate = gate.p; p.out = out.p;
+    p.stride_ab = p.stride_gate = p.stride_out = L * D;
+    p.lo = 0; p.hi = L; p.rev = rev;
+    emu::wanted = [&](dim3 i) { return i.x == ncb + (ncb - 1); };
+    emu::wave_order = [&](int i, int n) { return descending ? n - 1 - i : i; };
+    if (launch_fir(&p, 1, 1, L, D, lh, group, bf16 ? HY_BF16 : HY_F32, nullptr) != HY_OK) return printf("launch\n"), 1;
+    int64_t wrong = 0;
+    for (int64_t t = t0; t < t1; ++t)
+        for (int64_t c = c0; c < D; ++c) {
+            float s = 0.0f;
+            for (int i = 0; i < lh; ++i) {  // ascending tap (transposed) or source (causal) order
+                const int j = rev ? i : lh - 1 - i;
+                const int64_t src = rev ? t + j : t - j;
+                if (src >= 0 && src < L) s = fmaf(h[c / group * lh + j], a.get(src, c) * b.get(src, c), s);
+            }
+            s *= gate.get(t, c);
+            const float want = bf16 && isfinite(s) ? bf16_value(s) : s, got = out.get(t, c);
+            wrong += isnan(want) ? !isnan(got) : !(want == got);
+        }
+    free(h);
+    printf("L=%lld D=%lld lh=%d group=%d %s %s%s, %s wave first, %lld tiles: %lld of %lld outputs wrong\n", (long long)L,
+           (long long)D, lh, group, bf16 ? "bf16" : "f32", rev ? "transposed" : "causal", infinite ? ", one sample infinite" : "",
+           descending ? "last" : "first", (long long)steps, (long long)wrong, (long long)((t1 - t0) * (D - c0)));
+    return wrong != 0;
+}
+
+}  // namespace
+
+int main() {
+    const int64_t L = 128 * 3 * 64 - 50;  // three tiles of 128 rows to a walk
+    int bad = 0;
+    for (int lh : {20, 40, 65, 128})  // one segment of 32, 64, 128 taps
+        for (int i = 0; i < 4; ++i) {
+            const int64_t D = i / 2 ? 509 : 512;  // rows of single elements, of 16-byte pieces
+            const int group = i / 2 ? 1 : 8;
+            bad += check(L, D, lh, group, i % 2, lh == 40 || lh == 65, false, false);
+            bad += check(L, D, lh, group, i % 2, lh == 20 || lh == 128, true, false);
+        }
+    bad += check(L, 512, 150, 8, true, false, false, false);  // two segments
+    bad += check(L, 509, 129, 1, false, true, true, false);
+    bad += check(L, 512, 128, 8, true, false, true, true);
+    bad += check(L, 512, 40, 1, false, true, false, true);
+    bad += check(L, 512, 150, 8, false, false, true, true);
+    printf("fir emulation: %d problem(s)\n", bad);
+    return bad != 0;
+}
