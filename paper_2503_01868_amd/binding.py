@@ -114,7 +114,11 @@ def _dtype_code(t: torch.Tensor) -> int:
 
 
 # A call of a small problem is shorter on the GPU (7 us for 1024 x 256) than its checks used to take here (12 us with
-# device objects, a device context and a stream object per call), so these helpers ask for plain flags and numbers.
+# device objects, a device context and a stream object per call), so these helpers ask for plain flags and numbers.  Two of
+# them are torch's own bindings behind the public calls, which stand in where a torch does not have them by these names.
+_current_gpu = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+_current_raw_stream = (getattr(torch._C, "_cuda_getCurrentRawStream", None)
+                       or (lambda gpu: torch.cuda.current_stream(gpu).cuda_stream))
 
 
 def _check_act(name: str, t: torch.Tensor, ref: torch.Tensor | None = None) -> None:
@@ -141,7 +145,7 @@ def _check_filter(name: str, h: torch.Tensor, x: torch.Tensor, group: int) -> in
 
 def _stream(x: torch.Tensor, stream) -> int:
     if stream is None:
-        return torch._C._cuda_getCurrentRawStream(x.get_device())
+        return _current_raw_stream(x.get_device())
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
 
@@ -160,7 +164,7 @@ _HERE = _Here()
 
 def _on(x: torch.Tensor):
     """Context in which x's GPU is the current one."""
-    if x.is_cuda and x.get_device() == torch._C._cuda_getDevice():
+    if x.is_cuda and x.get_device() == _current_gpu():
         return _HERE
     return torch.cuda.device(x.device)
 
