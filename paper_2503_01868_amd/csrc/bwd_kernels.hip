@@ -221,12 +221,11 @@ __global__ __launch_bounds__(kBlock) void bwd_stencil_kernel(BwdStencilArgs a) {
         for (int j = 0; j < LH; ++j) pp[e * LH + j] = dh[e][j];
 }
 
-// second pass: dh[g][j] = sum over partial sets and over the channels of group g.  A workgroup owns 64 outputs;
-// its four waves each sum a contiguous quarter of the terms (fixed order: set, then channel of the group), wave 0
-// adds the four quarters in order.  Deterministic, no atomics.  The sums run in fp64 (the adds are a negligible
-// part of this kernel), so the reduction adds no rounding of its own to the fp32 partials.  With few terms per
-// output (up to 8: single channels and a handful of tiles) a lane sums all of them for one of 256 outputs instead:
-// a quarter of the workgroups, all loads of a lane in flight at once, no exchange.
+// second pass: dh[g][j] = sum over partial sets and over the channels of group g.  kRedParts lanes share an output: each
+// sums a contiguous share of the terms (fixed order: set, then channel of the group), the first adds the shares in
+// order.  Deterministic, no atomics.  The sums run in fp64 (the adds are a negligible part of this kernel), so the
+// reduction adds no rounding of its own to the fp32 partials.  With few terms per output (up to 8: single channels and
+// a handful of tiles) one lane sums them all, all its loads in flight at once, no exchange.
 struct ReduceArgs {
     const float* partial[kMaxProb];
     float* dh[kMaxProb];
@@ -282,7 +281,7 @@ __global__ __launch_bounds__(kBlock) void dh_reduce_kernel(ReduceArgs a, int64_t
     __syncthreads();
     if (part == 0 && idx < n) {
         double t = red[0][o];
-#pragma unroll
+#pragma unroll 8
         for (int r = 1; r < kRedParts; ++r) t += red[r][o];
         dh[idx] = (float)t;
     }
@@ -644,11 +643,21 @@ hy_status launch_reduce(const ReduceArgs& r, int nprob, int64_t nsets, int64_t n
                         hipStream_t st) {
     const int64_t nout = (n_rows / group) * lh;
     if (nout == 0) return HY_OK;
-    const int64_t per = nsets * group <= 8 ? kBlock : kBlock / 4;
-    const dim3 grid((uint32_t)((nout + per - 1) / per), (uint32_t)nprob);
-    if (nsets * group <= 8)
-        return launch_kernel(dh_reduce_kernel<1>, grid, dim3(kBlock), st, r, nsets, n_rows, lh, group);
-    return launch_kernel(dh_reduce_kernel<4>, grid, dim3(kBlock), st, r, nsets, n_rows, lh, group);
+    auto go = [&](void (*kernel)(ReduceArgs, int64_t, int64_t, int32_t, int32_t), int64_t parts) {
+        const int64_t per = kBlock / parts;
+        return launch_kernel(kernel, dim3((uint32_t)((nout + per - 1) / per), (uint32_t)nprob), dim3(kBlock), st, r, nsets,
+                             n_rows, lh, group);
+    };
+    // Few outputs of many terms (a filter shared by many channels, many short tiles) are one long chain per lane, so more
+    // lanes share them; many outputs fill the chip by themselves and read whole lines with four (featurizer backward,
+    // 7 taps, whole call with 4 / 32 / 256 lanes; outputs x terms: 7 x 65536 1073 / 155 / 58 us, 448 x 2048 50 / 18 / 22,
+    // 448 x 16384 399 / 128 / 133, 1792 x 512 21.8 / 17.6 / 25, 7168 x 512 31 / 27 / 57, 28672 x 512 66 / 90 / 202,
+    // 448 x 256 17.1 / 17.0 / 17.3).
+    const int64_t terms = nsets * group;
+    if (terms <= 8) return go(dh_reduce_kernel<1>, 1);
+    if (terms > 4096 && nout <= 512) return go(dh_reduce_kernel<256>, 256);
+    if (terms > 256 && nout <= 8192) return go(dh_reduce_kernel<32>, 32);
+    return go(dh_reduce_kernel<4>, 4);
 }
 
 template <typename T, int LH>
