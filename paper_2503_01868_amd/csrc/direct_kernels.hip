@@ -57,15 +57,19 @@ __device__ __forceinline__ void each_index(F&& f, std::integer_sequence<int, I..
 
 // VEC: elements per row access (16 bytes where the rows allow it, else one element); kSeg: taps per segment;
 // NT: 16-row output blocks per tile
+constexpr int per_cu(int seg, int nt) { return seg <= 32 && nt <= 2 ? 4 : 2; }  // workgroups a compute unit holds
+
 template <typename T, int VEC, int kSeg, int NT, bool kOne>
-__global__ __launch_bounds__(kThreads, 2) void fir_kernel(FirArgs a) {
+__global__ __launch_bounds__(kThreads, per_cu(kSeg, NT)) void fir_kernel(FirArgs a) {
     constexpr int TR = 16 * NT;                    // output rows per tile
     constexpr int kRows = TR + kSeg - 1;           // staged rows
     constexpr int PPR = kChan / VEC;               // pieces per staged row
     constexpr int RPP = kThreads / PPR;            // rows per pass over the workgroup's lanes
     constexpr int kPassAll = (TR + RPP - 1) / RPP;  // passes that cover one tile's rows
     constexpr bool kAhead = kOne && T::kBytes == 2 && VEC > 1;  // the next tile's rows are loaded while this one is computed
-    constexpr int kPass = kAhead || kPassAll < 4 ? kPassAll : 4;  // passes in flight
+    // passes in flight: 16-byte pieces take eight registers per pass, single elements (a quarter of the rows per pass) two
+    constexpr int kPassFew = VEC == 1 ? (kSeg == 64 ? 16 : 8) : 4;
+    constexpr int kPass = kAhead || kPassAll < kPassFew ? kPassAll : kPassFew;
     constexpr int kBatch = kPass * RPP < TR ? kPass * RPP : TR;  // rows they cover
     static_assert(!kAhead || kPass == kPassAll, "a tile's rows in flight at once");
     constexpr int kMove = ((kSeg - 1) * (kChan / 4) + kThreads - 1) / kThreads;  // float4s of halo per lane
@@ -314,7 +318,8 @@ __global__ __launch_bounds__(kThreads, 2) void fir_kernel(FirArgs a) {
         auto put = [&](const void* gate, void* out) {
             const char* gp = static_cast<const char*>(gate) + (b * pr.stride_gate + col) * T::kBytes;
             char* op = static_cast<char*>(out) + (b * pr.stride_out + col) * T::kBytes;
-            constexpr int kPut = kPassAll < 2 ? kPassAll : 2;  // pieces in flight
+            constexpr int kPutFew = VEC == 1 ? 8 : 4;
+            constexpr int kPut = kPassAll < kPutFew ? kPassAll : kPutFew;  // pieces in flight
 #pragma unroll
             for (int i0 = 0; i0 < kPassAll; i0 += kPut) {
                 typename PV::Raw gr[kPut];
@@ -352,10 +357,19 @@ template <typename T, int VEC, int kSeg, int NT, bool kOne>
 hy_status launch_nt(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
     constexpr int TR = 16 * NT;
     const int64_t tiles = (a.L + TR - 1) / TR;
-    // two workgroups per compute unit; where there are tiles enough each walks its share of a sequence
-    int64_t walks = 512 / (B * a.ncb * nprob);
-    if (walks < 1) walks = 1;
-    if (walks > tiles) walks = tiles;
+    // Where there are tiles enough a workgroup walks its share of a sequence: as long as lets every workgroup be resident
+    // at once, or in whole rounds where one round would be half empty (a walk's start, its halo and taps, is priced as
+    // one tile).  With several segments nothing is kept from one tile to the next, so there every tile is a workgroup of
+    // its own (3 x 2730 x 1024 fp32, 200 taps: 119 -> 99 us).
+    int64_t walks = tiles;
+    if (kOne) {
+        constexpr int64_t resident = 256 * per_cu(kSeg, NT);
+        const int64_t units = B * a.ncb * nprob;
+        auto cost = [&](int64_t w) { return (units * w + resident - 1) / resident * ((tiles + w - 1) / w + 1); };
+        walks = 1;
+        for (int64_t w = 2; w <= tiles && units * (w - 1) < 4 * resident; ++w)
+            if (cost(w) < cost(walks)) walks = w;
+    }
     const int64_t steps = (tiles + walks - 1) / walks;
     walks = (tiles + steps - 1) / steps;
     if (steps > 0x7fffffffLL || B > 0x7fffffffLL || B * walks > 0x7fffffffLL / a.ncb) return HY_ERR_UNSUPPORTED;
@@ -367,6 +381,8 @@ hy_status launch_nt(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
 
 template <typename T, int VEC, int NT>
 hy_status launch_seg(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
+    if constexpr (NT <= 2)  // (3 x 2730 x 1024 fp32, 9 taps, against a segment of 32: 28.5 -> 26.4 us)
+        if (a.lh <= 16) return launch_nt<T, VEC, 16, NT, true>(a, nprob, B, st);
     if (a.lh <= 32) return launch_nt<T, VEC, 32, NT, true>(a, nprob, B, st);
     if (a.lh <= 64) return launch_nt<T, VEC, 64, NT, true>(a, nprob, B, st);
     if (a.lh <= 128) return launch_nt<T, VEC, 128, NT, true>(a, nprob, B, st);
@@ -376,9 +392,20 @@ hy_status launch_seg(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
 template <typename T, int VEC>
 hy_status launch_vec(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
     // 128-row tiles amortise the 127 halo rows of a 128-tap filter; a problem that leaves compute units without a
-    // workgroup that way is cut into 32-row tiles instead.  (Eight waves over 128 channels, one workgroup per compute
-    // unit, measured the same on long sequences and 13% slower at 2 x 2048 x 1024.)
-    const bool wide = B * ((a.L + 127) / 128) * a.ncb * nprob >= 256;
+    // workgroup that way is cut into 32-row tiles instead, and so is one whose last tile would be mostly padding.  (Eight
+    // waves over 128 channels, one workgroup per compute unit, measured the same on long sequences and 13% slower at
+    // 2 x 2048 x 1024.)  Up to 32 taps the halo is small and short tiles, four workgroups to a compute unit, hide more
+    // of each other's loads, unless one long tile holds the whole sequence and there is no halo at all; rows of single
+    // bf16 elements, which take the most load instructions per byte, gain from that at any length.  Rows 128 / 32, us:
+    // 57 x 30 x 2048 fp32 34.4 / 17.8, 8 x 60 x 2048, 128 taps 11.1 / 9.0; 9 taps: 2 x 1500 x 1001 fp32 23.5 / 16.4,
+    // 3 x 2730 x 1024 fp32 34.1 / 26.4, 3 x 5003 x 1000 bf16 44.8 / 44.1, but 40 x 102 x 2048 fp32 32.2 / 36; 33 and 128
+    // taps: 2 x 1500 x 1001 bf16 28 / 21 and 35 / 30, 4 x 8000 x 1001 bf16 161 / 151 and 216 / 202, fp32 152 / 162 and
+    // 212 / 210.  Several segments: 3 x 5003 x 1000 bf16, 200 taps 154 / 319.
+    const int64_t rows = (a.L + 127) / 128 * 128;
+    const bool full = B * (rows / 128) * a.ncb * nprob >= 256;
+    const bool padded = 4 * rows > 5 * ((a.L + 31) / 32 * 32);
+    const bool short_tiles = a.lh <= 32 ? a.L > 128 : VEC == 1 && T::kBytes == 2;
+    const bool wide = full && (a.lh > 128 || !(padded || short_tiles));
     return wide ? launch_seg<T, VEC, 8>(a, nprob, B, st) : launch_seg<T, VEC, 2>(a, nprob, B, st);
 }
 

@@ -44,11 +44,17 @@ struct Tensor {  // [B, L, D]
 // All outputs of one workgroup of the second walk (the last, possibly ragged channel block), against the plain loop.
 // `infinite`: one sample in front of the walk is.
 int check(int64_t L, int64_t D, int lh, int group, bool bf16, bool rev, bool descending, bool infinite) {
-    constexpr int kTile = 128;
-    const int64_t ncb = (D + 63) / 64, tiles = (L + kTile - 1) / kTile;
-    const int64_t walks = 512 / ncb, steps = (tiles + walks - 1) / walks;
-    const int64_t c0 = (ncb - 1) * 64, t0 = steps * kTile, t1 = 2 * steps * kTile < L ? 2 * steps * kTile : L;
-    if (tiles * ncb < 256 || steps < 3 || t1 - t0 != steps * kTile) return printf("not the walk this is meant for\n"), 1;
+    FirProblem p;
+    p.stride_ab = p.stride_gate = p.stride_out = L * D;
+    p.lo = 0; p.hi = L; p.rev = rev;
+    auto launch = [&] { return launch_fir(&p, 1, 1, L, D, lh, group, bf16 ? HY_BF16 : HY_F32, nullptr); };
+    emu::wanted = [](dim3) { return false; };  // only the launch's grid
+    if (launch() != HY_OK) return printf("launch\n"), 1;
+    const int tile = lh <= 32 || (bf16 && D % 8 != 0 && lh <= 128) ? 32 : 128;
+    const int64_t ncb = (D + 63) / 64, tiles = (L + tile - 1) / tile, walks = emu::grid_dim.x / ncb;
+    const int64_t steps = (tiles + walks - 1) / walks;
+    const int64_t c0 = (ncb - 1) * 64, t0 = steps * tile, t1 = 2 * steps * tile < L ? 2 * steps * tile : L;
+    if ((steps < 3 && lh <= 128) || t1 - t0 != steps * tile) return printf("not the walk this is meant for\n"), 1;
     Tensor a(1, L, D, bf16), b(1, L, D, bf16), gate(1, L, D, bf16), out(1, L, D, bf16);
     float* h = static_cast<float*>(malloc((size_t)(D / group * lh * 4)));
     for (int64_t i = 0; i < D / group * lh; ++i) h[i] = draw();
@@ -59,13 +65,10 @@ int check(int64_t L, int64_t D, int lh, int group, bool bf16, bool rev, bool des
             gate.set(t, c, draw());
         }
     if (infinite) a.set(rev ? t1 + 3 : t0 - 3, c0 + 5, INFINITY);
-    FirProblem p;
     p.a = a.p; p.b = b.p; p.h = h; p.gate = gate.p; p.out = out.p;
-    p.stride_ab = p.stride_gate = p.stride_out = L * D;
-    p.lo = 0; p.hi = L; p.rev = rev;
     emu::wanted = [&](dim3 i) { return i.x == ncb + (ncb - 1); };
     emu::wave_order = [&](int i, int n) { return descending ? n - 1 - i : i; };
-    if (launch_fir(&p, 1, 1, L, D, lh, group, bf16 ? HY_BF16 : HY_F32, nullptr) != HY_OK) return printf("launch\n"), 1;
+    if (launch() != HY_OK) return printf("launch\n"), 1;
     int64_t wrong = 0;
     for (int64_t t = t0; t < t1; ++t)
         for (int64_t c = c0; c < D; ++c) {
@@ -89,9 +92,9 @@ int check(int64_t L, int64_t D, int lh, int group, bool bf16, bool rev, bool des
 }  // namespace
 
 int main() {
-    const int64_t L = 128 * 3 * 64 - 50;  // three tiles of 128 rows to a walk
+    const int64_t L = 128 * 3 * 64 - 50;  // three tiles of 128 rows or more of 32 to a walk
     int bad = 0;
-    for (int lh : {20, 40, 65, 128})  // one segment of 32, 64, 128 taps
+    for (int lh : {12, 20, 40, 65, 128})  // one segment of 16, 32, 64, 128 taps
         for (int i = 0; i < 4; ++i) {
             const int64_t D = i / 2 ? 509 : 512;  // rows of single elements, of 16-byte pieces
             const int group = i / 2 ? 1 : 8;
