@@ -41,7 +41,8 @@ constexpr int kStride = kChan + 4;  // floats per staged row: the operand reads 
 struct FirArgs {
     FirProblem p[3];
     int64_t L, D;
-    int32_t lh, group;
+    int32_t lh, group;       // lh: the taps that can meet data
+    int32_t row_taps;        // taps per filter in memory
     int32_t ncb;             // channel blocks
     int32_t steps;           // tiles a workgroup walks
     int32_t walks_per_seq;
@@ -92,7 +93,7 @@ __global__ __launch_bounds__(kThreads, per_cu(kSeg, NT)) void fir_kernel(FirArgs
     const int64_t g0 = c0 / a.group;
     const int cw = 16 * w + lane % 16;
     const uint32_t gstep = ((uint32_t)(c0 - g0 * a.group) + (uint32_t)(c0 + cw < D ? cw : D - 1 - c0)) / (uint32_t)a.group;
-    const float* const h0 = pr.h + g0 * (int64_t)lh;
+    const float* const h0 = pr.h + g0 * (int64_t)a.row_taps;
     const int64_t row_bytes = D * T::kBytes;
 
     // ---- rows of 64 channels: this lane's piece of the rows it loads and stores (a piece past the last channel reads
@@ -160,7 +161,7 @@ __global__ __launch_bounds__(kThreads, per_cu(kSeg, NT)) void fir_kernel(FirArgs
             float f[kCh][kX];
 #pragma unroll
             for (int c = 0; c < kCh; ++c) {
-                const float* hp = h0 + (int64_t)__builtin_amdgcn_readlane(gstep, i0 + c) * lh;
+                const float* hp = h0 + (int64_t)__builtin_amdgcn_readlane(gstep, i0 + c) * a.row_taps;
 #pragma unroll
                 for (int x = 0; x < kX; ++x) {  // unconditional loads: outside the segment its first tap, not used
                     const int jp = x * kWave + lane - 3;
@@ -291,7 +292,7 @@ __global__ __launch_bounds__(kThreads, per_cu(kSeg, NT)) void fir_kernel(FirArgs
                     // not everything is finite: the sums term by term, without the products' structural zeros and
                     // without the rows that hold no data
                     const int64_t vlo = pr.lo - tb, vhi = pr.hi - tb;
-                    const float* hp = h0 + (int64_t)__shfl(gstep, ch) * lh;
+                    const float* hp = h0 + (int64_t)__shfl(gstep, ch) * a.row_taps;
                     for (int jp = 0; jp < nt; ++jp) {
                         const float h1 = hp[pr.rev ? ja + jp : jb - 1 - jp];
 #pragma unroll
@@ -386,6 +387,9 @@ hy_status launch_seg(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
     if (a.lh <= 32) return launch_nt<T, VEC, 32, NT, true>(a, nprob, B, st);
     if (a.lh <= 64) return launch_nt<T, VEC, 64, NT, true>(a, nprob, B, st);
     if (a.lh <= 128) return launch_nt<T, VEC, 128, NT, true>(a, nprob, B, st);
+    // three segments of 64 are 201 products per output block, two of 128 are 262 (3 x 5003 x 1000 fp32, 150 taps: 152
+    // against 166 us); beyond 192 taps staging the rows once more costs what the products save (400 taps: 304 / 285)
+    if (a.lh <= 192) return launch_nt<T, VEC, 64, NT, false>(a, nprob, B, st);
     return launch_nt<T, VEC, 128, NT, false>(a, nprob, B, st);
 }
 
@@ -424,7 +428,15 @@ hy_status launch_fir(const FirProblem* p, int nprob, int64_t B, int64_t L, int64
     for (int i = 0; i < 3; ++i) a.p[i] = p[i < nprob ? i : 0];
     a.L = L;
     a.D = D;
-    a.lh = lh;
+    // taps beyond the first row with data (causal) or the last (transposed) meet none: a filter longer than its sequence
+    // is one of its length (15 x 31 x 333 fp32 featurizers, 800 taps: 28 -> 12 us)
+    int64_t reach = 1;
+    for (int i = 0; i < nprob; ++i) {
+        const int64_t r = p[i].rev ? p[i].hi : L - p[i].lo;
+        if (r > reach) reach = r;
+    }
+    a.lh = lh < reach ? lh : (int32_t)reach;
+    a.row_taps = lh;
     a.group = group;
     const int64_t ncb = (D + kChan - 1) / kChan;
     if (ncb > 0x7fffffffLL) return HY_ERR_UNSUPPORTED;

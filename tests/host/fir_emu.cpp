@@ -101,7 +101,8 @@ int main() {
             bad += check(L, D, lh, group, i % 2, lh == 40 || lh == 65, false, false);
             bad += check(L, D, lh, group, i % 2, lh == 20 || lh == 128, true, false);
         }
-    bad += check(L, 512, 150, 8, true, false, false, false);  // two segments
+    bad += check(L, 512, 150, 8, true, false, false, false);  // three segments of 64
+    bad += check(L, 512, 200, 8, true, true, false, false);   // two segments of 128
     bad += check(L, 509, 129, 1, false, true, true, false);
     bad += check(L, 512, 128, 8, true, false, true, true);
     bad += check(L, 512, 40, 1, false, true, false, true);

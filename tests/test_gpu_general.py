@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 # B, L, D, lh, group
 SHAPES = [
     (1, 1, 1, 9, 1), (2, 31, 3, 16, 3), (1, 33, 30, 17, 1), (1, 127, 64, 63, 2), (2, 128, 65, 64, 5), (1, 129, 72, 65, 8),
-    (1, 200, 40, 127, 4), (3, 300, 24, 128, 1), (1, 300, 100, 129, 20), (1, 700, 8, 257, 8), (1, 90, 16, 400, 16),
+    (1, 200, 40, 127, 4), (3, 300, 24, 128, 1), (1, 300, 100, 129, 20), (1, 600, 24, 192, 1), (1, 600, 24, 193, 1), (1, 700, 8, 257, 8), (1, 90, 16, 400, 16),
     (2, 4200, 200, 40, 8), (1, 9000, 136, 130, 1),  # 128-row tiles, several to a walk
 ]
 
@@ -85,6 +85,19 @@ def test_non_finite_values_reach_what_the_definition_says(L, at, D):
     assert np.array_equal(~np.isfinite(dh), bad_h)
 
 
+def us_per_call(call):
+    times = []
+    for _ in range(9):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(20):
+            call()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 50)
+    return statistics.median(times)
+
+
 def test_odd_widths_keep_up():
     """Rows of single elements (an odd width) against rows of 16-byte pieces, 9 taps: 1.7 (fp32) and 2.1 (bf16) times as
     long with 16 rows of a workgroup's 64 channels in flight, in tiles of 128; 1.2 and 1.3 times with 32, in tiles of 32."""
@@ -92,18 +105,24 @@ def test_odd_widths_keep_up():
     def us(D, dtype):
         x = [torch.randn((2, 1500, D), device="cuda:0").to(dtype) for _ in range(3)]
         h = torch.randn((D, 9), device="cuda:0")
-        times = []
-        for _ in range(9):
-            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
-            a.record()
-            for _ in range(20):
-                binding.hyena_mr_fwd(*x, h, 1)
-            b.record()
-            torch.cuda.synchronize()
-            times.append(a.elapsed_time(b) * 50)
-        return statistics.median(times)
+        return us_per_call(lambda: binding.hyena_mr_fwd(*x, h, 1))
 
     for dtype in (torch.float32, torch.bfloat16):
         even, odd = us(1000, dtype), us(1001, dtype)
         say("hyena_mr_fwd 2 x 1500, 9 taps, %s: D = 1000 %.1f us, D = 1001 %.1f us" % (dtype, even, odd))
         assert odd < 1.6 * even
+
+
+def test_taps_beyond_the_sequence_cost_nothing():
+    """A filter longer than the sequence (history included) is one of its length: 2.3 times as long where its empty
+    segments are walked through."""
+    x = [torch.randn((15, 31, 333), device="cuda:0") for _ in range(3)]
+    h = torch.randn((111, 800), device="cuda:0")
+    short = h[:, :31].contiguous()
+    a, b = (us_per_call(lambda f=f: binding.hyena_featurize3_fwd(*x, f, f, f, 3)) for f in (short, h))
+    say("hyena_featurize3_fwd 15 x 31 x 333: 31 taps %.1f us, 800 taps %.1f us" % (a, b))
+    assert b < 1.5 * a
+    for y, z in zip(binding.hyena_featurize3_fwd(*x, short, short, short, 3), binding.hyena_featurize3_fwd(*x, h, h, h, 3)):
+        assert torch.equal(y, z)
+    dx = [binding.hyena_featurize_bwd(x[0], x[1], f, 3)[0] for f in (short, h)]
+    assert torch.equal(*dx)
