@@ -543,29 +543,69 @@ __global__ __launch_bounds__(kDhThreads, 1) void dh_tile_kernel(DhArgs a) {
     }
 }
 
-// dh[g][j] = sum over batch items, tiles and the group's partial rows, in that order; four lanes share an output
-template <typename T>
+// dh[g][j] = sum over batch items, tiles and the group's partial rows, in that order, by kParts lanes per output as in
+// dh_reduce_kernel
+template <typename T, int kParts>
 __global__ __launch_bounds__(kBlock) void dh_tile_reduce_kernel(DhArgs a, int64_t B) {
-    constexpr int kParts = 4, kOut = kBlock / kParts;
+    constexpr int kOut = kBlock / kParts;
     __shared__ double red[kParts][kOut];
     const int o = threadIdx.x % kOut, part = threadIdx.x / kOut;
     const int64_t n = (a.D / a.group) * a.lh;
     const int64_t idx = (int64_t)blockIdx.x * kOut + o;
     const int64_t idc = idx < n ? idx : n - 1;
     const int64_t g = idc / a.lh, j = idc % a.lh;
-    const int64_t rpg = a.group / a.fold;               // partial rows per group
+    const int32_t rpg = a.group / a.fold;               // partial rows per group
     const int64_t tile_len = (a.D / a.fold) * a.lh;
-    const int64_t per = (a.tiles_per_seq + kParts - 1) / kParts;
-    const int64_t lo = part * per, hi = lo + per < a.tiles_per_seq ? lo + per : a.tiles_per_seq;
+    const int64_t per_item = (int64_t)a.tiles_per_seq * rpg, total = B * per_item;
+    const int64_t per = (total + kParts - 1) / kParts;
+    const int64_t lo = part * per, hi = lo + per < total ? lo + per : total;
+    auto tile_row = [&](int64_t b, int32_t t) { return dh_scratch<T>(a.p.dk, b, a.sout) + t * tile_len + g * rpg * a.lh + j; };
     double s = 0.0;
-    for (int64_t b = 0; b < B; ++b) {
-        const double* base = dh_scratch<T>(a.p.dk, b, a.sout) + g * rpg * a.lh + j;
-        for (int64_t t = lo; t < hi; ++t)
-            for (int64_t c = 0; c < rpg; ++c) s += base[t * tile_len + c * a.lh];
+    if (lo < hi) {
+        int64_t b = lo / per_item;
+        int32_t t = (int32_t)((lo - b * per_item) / rpg), c = (int32_t)(lo - b * per_item - (int64_t)t * rpg);
+        const double* cur = tile_row(b, t) + (int64_t)c * a.lh;
+        for (int64_t x0 = lo; x0 < hi; x0 += 8) {  // past the end the last term is read again, not added
+            double v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                v[i] = *cur;
+                if (x0 + i + 1 < hi) {
+                    if (++c < rpg) {
+                        cur += a.lh;
+                    } else {
+                        c = 0;
+                        if (++t == a.tiles_per_seq) {
+                            t = 0;
+                            ++b;
+                        }
+                        cur = tile_row(b, t);
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s += x0 + i < hi ? v[i] : 0.0;
+        }
     }
     red[part][o] = s;
     __syncthreads();
-    if (part == 0 && idx < n) a.p.dh[idx] = (float)(red[0][o] + red[1][o] + red[2][o] + red[3][o]);
+    if (part == 0 && idx < n) {
+        double t = red[0][o];
+#pragma unroll 8
+        for (int r = 1; r < kParts; ++r) t += red[r][o];
+        a.p.dh[idx] = (float)t;
+    }
+}
+
+// Lanes per output of a reduction: few outputs of many terms (a filter shared by many channels, many short tiles) are one
+// long chain per lane, so more lanes share them; many outputs fill the chip by themselves and read whole lines with four
+// (featurizer backward, 7 taps, whole call with 4 / 32 / 256 lanes; outputs x terms: 7 x 65536 1073 / 155 / 58 us,
+// 448 x 2048 50 / 18 / 22, 448 x 16384 399 / 128 / 133, 1792 x 512 21.8 / 17.6 / 25, 7168 x 512 31 / 27 / 57, 28672 x 512
+// 66 / 90 / 202, 448 x 256 17.1 / 17.0 / 17.3).
+int reduce_parts(int64_t nout, int64_t terms) {
+    if (terms > 4096 && nout <= 512) return 256;
+    if (terms > 256 && nout <= 8192) return 32;
+    return 4;
 }
 
 // HY_ERR_UNSUPPORTED where dk cannot hold the partial sums of one tile
@@ -609,8 +649,15 @@ hy_status launch_dh_tile(const BwdPtrs& p, const BwdShape& s, hipStream_t st) {
     const hy_status rc = s.gated ? go(std::true_type{}) : go(std::false_type{});
     if (rc != HY_OK) return rc;
     const int64_t nout = (s.D / s.group) * s.lh;
-    return launch_kernel((dh_tile_reduce_kernel<T>), dim3((uint32_t)((nout + kBlock / 4 - 1) / (kBlock / 4))), dim3(kBlock),
-                         st, a, s.B);
+    auto reduce = [&](void (*kernel)(DhArgs, int64_t), int64_t parts) {
+        const int64_t per = kBlock / parts;
+        return launch_kernel(kernel, dim3((uint32_t)((nout + per - 1) / per)), dim3(kBlock), st, a, s.B);
+    };
+    switch (reduce_parts(nout, s.B * tiles * (s.group / a.fold))) {
+        case 256: return reduce(dh_tile_reduce_kernel<T, 256>, 256);
+        case 32: return reduce(dh_tile_reduce_kernel<T, 32>, 32);
+        default: return reduce(dh_tile_reduce_kernel<T, 4>, 4);
+    }
 }
 
 int stencil_rows(const BwdShape& s, int64_t nvec) {
@@ -648,16 +695,13 @@ hy_status launch_reduce(const ReduceArgs& r, int nprob, int64_t nsets, int64_t n
         return launch_kernel(kernel, dim3((uint32_t)((nout + per - 1) / per), (uint32_t)nprob), dim3(kBlock), st, r, nsets,
                              n_rows, lh, group);
     };
-    // Few outputs of many terms (a filter shared by many channels, many short tiles) are one long chain per lane, so more
-    // lanes share them; many outputs fill the chip by themselves and read whole lines with four (featurizer backward,
-    // 7 taps, whole call with 4 / 32 / 256 lanes; outputs x terms: 7 x 65536 1073 / 155 / 58 us, 448 x 2048 50 / 18 / 22,
-    // 448 x 16384 399 / 128 / 133, 1792 x 512 21.8 / 17.6 / 25, 7168 x 512 31 / 27 / 57, 28672 x 512 66 / 90 / 202,
-    // 448 x 256 17.1 / 17.0 / 17.3).
     const int64_t terms = nsets * group;
     if (terms <= 8) return go(dh_reduce_kernel<1>, 1);
-    if (terms > 4096 && nout <= 512) return go(dh_reduce_kernel<256>, 256);
-    if (terms > 256 && nout <= 8192) return go(dh_reduce_kernel<32>, 32);
-    return go(dh_reduce_kernel<4>, 4);
+    switch (reduce_parts(nout, terms)) {
+        case 256: return go(dh_reduce_kernel<256>, 256);
+        case 32: return go(dh_reduce_kernel<32>, 32);
+        default: return go(dh_reduce_kernel<4>, 4);
+    }
 }
 
 template <typename T, int LH>

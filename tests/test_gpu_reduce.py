@@ -1,4 +1,4 @@
-"""The reduction of partial filter gradients: 1, 4, 32 or 256 lanes per output, by the number of outputs and of terms."""
+"""The reductions of partial filter gradients: 1, 4, 32 or 256 lanes per output, by the number of outputs and of terms."""
 import statistics
 
 import numpy as np
@@ -39,25 +39,53 @@ def test_filter_gradient(case):
     assert oracle.rel_err(host(dx), rx) <= TOL["f32"] and oracle.rel_err(host(dh), rh) <= TOL["f32"]
 
 
+def us_per_call(call):
+    times = []
+    for _ in range(9):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(10):
+            call()
+        b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b) * 100)
+    return statistics.median(times)
+
+
 def test_a_filter_shared_by_all_channels_is_no_serial_sum():
     """65536 terms of 6 outputs: 47 times the call with a filter per channel when four lanes add them, 3 to 4 times with
     256 lanes."""
     B, L, D, lh = 2, 57, 4096, 6
     x = [torch.randn((B, L, D), device="cuda:0").bfloat16() for _ in range(4)]
 
-    def us(group):
-        h = torch.randn((D // group, lh), device="cuda:0")
-        times = []
-        for _ in range(9):
-            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
-            a.record()
-            for _ in range(10):
-                binding.hyena_se_bwd(*x, h, group)
-            b.record()
-            torch.cuda.synchronize()
-            times.append(a.elapsed_time(b) * 100)
-        return statistics.median(times)
-
-    one, shared = us(1), us(D)
+    one, shared = (us_per_call(lambda h=torch.randn((D // g, lh), device="cuda:0"), g=g: binding.hyena_se_bwd(*x, h, g))
+                   for g in (1, D))
     say("hyena_se_bwd 2 x 57 x 4096: a filter per channel %.1f us, one filter %.1f us" % (one, shared))
     assert shared < 12 * one
+
+
+# B, L, D, lh, group on the general path, whose tiles of time leave B * tiles * (the group's odd part) terms per output
+TILED = [(8, 43, 333, 12, 333), (2, 700, 36, 40, 9), (3, 130, 600, 9, 75), (1, 2100, 7, 20, 7), (5, 64, 260, 17, 65)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", TILED, ids=lambda c: "B%dL%dD%dlh%dg%d" % c)
+def test_filter_gradient_of_the_general_path(case, dtype):
+    B, L, D, lh, group = case
+    say("hyena_mr_bwd %s %s" % (case, dtype))
+    rng = np.random.Generator(np.random.PCG64(9950 + L))
+    dy, q, k, v = (synth.normal_tensor(rng, (B, L, D), dtype) for _ in range(4))
+    h = synth.decay_filter(rng, D // group, lh)
+    dh = binding.hyena_mr_bwd(dev(dy), dev(q), dev(k), dev(v), dev(h), group)[3]
+    assert oracle.rel_err(host(dh), oracle.gated_conv_bwd(dy, q, k, v, h, group=group)[3]) <= TOL["f32"]
+
+
+def test_a_general_filter_shared_by_all_channels_is_no_serial_sum():
+    """2664 terms of 12 outputs: 21 times the call with a filter per channel when a lane walks each tile's rows alone, about
+    as long with 32 lanes."""
+    B, L, D, lh = 8, 43, 333, 12
+    x = [torch.randn((B, L, D), device="cuda:0") for _ in range(4)]
+    one, shared = (us_per_call(lambda h=torch.randn((D // g, lh), device="cuda:0"), g=g: binding.hyena_mr_bwd(*x, h, g))
+                   for g in (1, D))
+    say("hyena_mr_bwd 8 x 43 x 333: a filter per channel %.1f us, one filter %.1f us" % (one, shared))
+    assert shared < 5 * one
