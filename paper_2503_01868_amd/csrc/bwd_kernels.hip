@@ -608,7 +608,7 @@ int reduce_parts(int64_t nout, int64_t terms) {
     return 4;
 }
 
-// HY_ERR_UNSUPPORTED where dk cannot hold the partial sums of one tile
+// HY_ERR_UNSUPPORTED where dk cannot hold the partial sums of one tile and where dh_direct_kernel is quicker
 template <typename T, int VEC>
 hy_status launch_dh_tile(const BwdPtrs& p, const BwdShape& s, hipStream_t st) {
     DhArgs a;
@@ -625,13 +625,24 @@ hy_status launch_dh_tile(const BwdPtrs& p, const BwdShape& s, hipStream_t st) {
     while (a.fold < 64 && s.group % (2 * a.fold) == 0) a.fold *= 2;
     const int64_t ncb = (s.D + 63) / 64, nlag = (s.lh + kDhLags - 1) / kDhLags;
     const int64_t fit = (s.L * s.D * T::kBytes - 8) / ((s.D / a.fold) * (int64_t)s.lh * 8);
-    // one workgroup per compute unit; tiles of 256 steps or more keep the 128 rows of history they start with small
+    // one workgroup per compute unit, in tiles of a staging or more (256 steps against 64: 3 x 1058 x 256 fp32, 100 taps,
+    // whole call 55 / 39 us, 9 x 490 x 136 bf16, 9 taps 36 / 23)
     int64_t tiles = 256 / (s.B * ncb * nlag);
-    if (tiles > s.L / 256) tiles = s.L / 256;
+    if (tiles > s.L / kDhT) tiles = s.L / kDhT;
     if (tiles < 1) tiles = 1;
     if (tiles > fit) tiles = fit;
     if (tiles < 1) return HY_ERR_UNSUPPORTED;
     int64_t rows = ((s.L + tiles - 1) / tiles + kDhT - 1) / kDhT * kDhT;
+    // A few samples per lane of dh_direct_kernel are done before a tile is staged.  In units of 0.25 us: its chain of loads
+    // (2048 workgroups at a time) or the lines it reads, against two launches and the products of a tile's stagings.
+    // Plain kernel / tiles, whole call, us: 1 x 85 x 72 fp32, 100 taps, group 72 19 / 40, 1 x 319 x 72 bf16, 65 taps 20 / 50,
+    // 6 x 132 x 3 fp32, 9 taps 13 / 22; beyond the line 4 x 317 x 72 bf16, 64 taps 30 / 25, 9 x 490 x 136 bf16, 9 taps 44 / 23.
+    const int64_t filters = s.D / s.group, blocks = filters * s.lh;
+    const int64_t chain = s.B * ((s.L * s.group + kBlock - 1) / kBlock) * (blocks > 2048 ? blocks / 2048 : 1);
+    const int64_t line = s.group * T::kBytes > 64 ? s.group * T::kBytes : 64;
+    const double lines = (double)blocks * (double)(s.B * s.L) * (double)line * (s.gated ? 4 : 2) / 5.5e6;
+    const int64_t products = rows / kDhT * (s.lh <= 32 ? 1 : s.lh <= 64 ? 2 : 4);
+    if (chain < 24 + 6 * products && lines < (double)(24 + 6 * products)) return HY_ERR_UNSUPPORTED;
     if (rows > 0x7fffffffLL || ncb > 0x7fffffffLL || nlag > 65535) return HY_ERR_UNSUPPORTED;
     tiles = (s.L + rows - 1) / rows;
     if (s.B > 0x7fffffffLL || s.B * tiles > 0x7fffffffLL / ncb) return HY_ERR_UNSUPPORTED;

@@ -89,3 +89,17 @@ def test_a_general_filter_shared_by_all_channels_is_no_serial_sum():
                    for g in (1, D))
     say("hyena_mr_bwd 8 x 43 x 333: a filter per channel %.1f us, one filter %.1f us" % (one, shared))
     assert shared < 5 * one
+
+
+def test_tiny_filter_gradients_stay_short():
+    """85 steps of 72 channels in one filter of 100 taps: 2.4 times the call with 8 steps when two workgroups walk them in
+    tiles, 1.2 times when a workgroup per tap sums them."""
+
+    def call(L):
+        x = [torch.randn((1, L, 72), device="cuda:0") for _ in range(4)]
+        h = torch.randn((1, 100), device="cuda:0")
+        return us_per_call(lambda: binding.hyena_mr_bwd(*x, h, 72))
+
+    short, long = call(8), call(85)
+    say("hyena_mr_bwd 1 x L x 72, 100 taps: L = 8 %.1f us, L = 85 %.1f us" % (short, long))
+    assert long < 1.8 * short
