@@ -456,7 +456,8 @@ int64_t li_rows(const LiShape& s, int nw) {
         int64_t tiles = 256 / (s.B * ncb);
         if (tiles < 1) tiles = 1;
         rows = (s.L + tiles - 1) / tiles;
-        const int64_t min_rows = (nw == 4 ? 2 : 4) * kChunk;
+        // (up to four chunks stay one tile: a second pass costs more than their chain; 3 x 114 x 1536 11.5 against 15.0 us)
+        const int64_t min_rows = (nw == 4 && s.L > 4 * kChunk ? 2 : 4) * kChunk;
         if (rows < min_rows) rows = min_rows;
     }
     rows = (rows + kChunk - 1) / kChunk * kChunk;

@@ -429,3 +429,9 @@ def test_chain_shard_entry_point_rejects_bad_layouts():
     assert call(y=Q[0] - 133 * 128 * 2) == 4          # y inside q's history rows
     assert call(dtype=0) == 5 and call(group=8) == 5 and call(lh=130) == 5 and call(lf=10) == 5   # single-kernel path only
     assert call(B=0) == 0 and call(L=0) == 0
+
+
+@pytest.mark.parametrize("B,L,D", [(1, 65, 64), (1, 100, 192), (3, 114, 1536), (1, 128, 4096), (7, 72, 256)])
+def test_long_implicit_calls_of_one_tile_need_no_workspace(B, L, D):
+    """Up to four chunks of 32 steps are one tile whatever the width: a single pass, callable without a workspace."""
+    assert binding.lib().hyena_li_workspace_bytes(B, L, D, 16, 16, 1) == 0
