@@ -1,7 +1,7 @@
-"""The general FIR kernels (fp32, and bf16 shapes no matrix-core path takes) at the edges of their tiles: segments of 128
-taps, stages of 64, register blocks of 16, tiles of 32 and 128 rows, walks of several tiles, 64-channel blocks with idle
-lanes, rows of 16-byte pieces and of single elements; forward, gradients, featurizers; and the reach of non-finite
-samples and taps."""
+"""The general FIR kernel (fp32, and bf16 shapes no matrix-core path takes) at the edges of its tiles: segments of 16 to 128
+taps, tiles of 32 and 128 rows, walks of several tiles, 64-channel blocks with idle lanes, rows of 16-byte pieces and of
+single elements; forward, gradients, featurizers; the reach of non-finite samples and taps; and what calls cost next to
+their neighbours."""
 import statistics
 
 import numpy as np
@@ -18,8 +18,9 @@ pytestmark = pytest.mark.gpu
 # B, L, D, lh, group
 SHAPES = [
     (1, 1, 1, 9, 1), (2, 31, 3, 16, 3), (1, 33, 30, 17, 1), (1, 127, 64, 63, 2), (2, 128, 65, 64, 5), (1, 129, 72, 65, 8),
-    (1, 200, 40, 127, 4), (3, 300, 24, 128, 1), (1, 300, 100, 129, 20), (1, 600, 24, 192, 1), (1, 600, 24, 193, 1), (1, 700, 8, 257, 8), (1, 90, 16, 400, 16),
-    (2, 4200, 200, 40, 8), (1, 9000, 136, 130, 1),  # 128-row tiles, several to a walk
+    (1, 200, 40, 127, 4), (3, 300, 24, 128, 1), (1, 300, 100, 129, 20), (1, 600, 24, 192, 1), (1, 600, 24, 193, 1),
+    (1, 700, 8, 257, 8), (1, 90, 16, 400, 16),
+    (2, 4200, 200, 40, 8), (1, 9000, 136, 130, 1),  # a 128-row tile per workgroup; three segments in 32-row tiles
 ]
 
 
@@ -85,6 +86,84 @@ def test_non_finite_values_reach_what_the_definition_says(L, at, D):
     assert np.array_equal(~np.isfinite(dh), bad_h)
 
 
+def tile_walk(B, L, D, lh, dtype, problems):
+    """(rows per tile, tiles per workgroup) of a launch with up to 128 taps, as direct_kernels.hip chooses them."""
+    units = B * -(-D // 64) * problems
+    single = D % (4 if dtype == "f32" else 8) != 0
+    padded = 4 * 128 * -(-L // 128) > 5 * 32 * -(-L // 32)
+    short_tiles = L > 128 if lh <= 32 else single and dtype == "bf16"
+    rows = 128 if units * -(-L // 128) >= 256 and not padded and not short_tiles else 32
+    tiles, resident = -(-L // rows), 1024 if lh <= 32 and rows == 32 else 512
+
+    def cost(w):
+        return -(-units * w // resident) * (-(-tiles // w) + 1)
+
+    walks = 1
+    for w in range(2, tiles + 1):
+        if units * (w - 1) >= 4 * resident:
+            break
+        if cost(w) < cost(walks):
+            walks = w
+    return rows, -(-tiles // walks)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D,group", [(1000, 8), (1001, 1)], ids=["pieces", "elements"])
+@pytest.mark.parametrize("lh", [12, 20, 40, 65, 100, 128])
+def test_walks_of_several_tiles(lh, D, group, dtype):
+    """Walks of three tiles or more, whose halo stays in LDS: forward and gradients, on the first and the last channels."""
+    B, L = 3, 5003
+    for problems in (1, 2):
+        rows, steps = tile_walk(B, L, D, lh, dtype, problems)
+        assert steps >= 3 and rows == (32 if lh <= 32 or (dtype == "bf16" and D % 8) else 128)
+    say("hyena_mr_fwd / bwd %d x %d x %d lh=%d group=%d %s" % (B, L, D, lh, group, dtype))
+    q, k, v, h = draw(9500 + lh, B, L, D, lh, group, dtype, kind="mr")
+    dy = synth.normal_tensor(np.random.Generator(np.random.PCG64(9501)), (B, L, D), dtype)
+    y = host(binding.hyena_mr_fwd(dev(q), dev(k), dev(v), dev(h), group))
+    grads = [host(x) for x in binding.hyena_mr_bwd(dev(dy), dev(q), dev(k), dev(v), dev(h), group)]
+    for c in (slice(0, 32), slice(D - 32 - D % 8, D)):
+        g = slice(c.start // group, c.stop // group)
+        a = [x[..., c].contiguous() if torch.is_tensor(x) else np.ascontiguousarray(x[..., c]) for x in (dy, q, k, v)]
+        f = np.ascontiguousarray(h[g])
+        assert oracle.rel_err(y[..., c], oracle.gated_conv(*a[1:], f, group=group)) <= TOL[dtype]
+        for name, got, want in zip(("dq", "dk", "dv", "dh"), grads, oracle.gated_conv_bwd(*a, f, group=group)):
+            got = got[g] if name == "dh" else got[..., c]
+            assert oracle.rel_err(got, want) <= (TOL["f32"] if name == "dh" else TOL[dtype]), name
+
+
+# lh, L, D, position of the infinite sample: one segment of each length, several, more taps than steps; short and long walks
+NON_FINITE = [(12, 700, 24, 40), (20, 9000, 520, 4321), (64, 300, 24, 31), (64, 9000, 520, 4500), (128, 9000, 520, 129),
+              (150, 700, 24, 600), (300, 900, 24, 250), (300, 90, 24, 10)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", NON_FINITE, ids=lambda c: "lh%dL%dD%dat%d" % c)
+def test_non_finite_values_leave_the_other_outputs(case, dtype):
+    """As above for every segment length and both storage types, and the outputs that stay finite are right."""
+    lh, L, D, at = case
+    say("non-finite %s %s" % (case, dtype))
+    q, k, v, h = draw(9450 + at, 1, L, D, lh, 1, dtype, kind="mr")
+    k[0, at, 3] = float("inf")
+    h = h.copy()
+    h[5, lh // 3] = np.inf
+    dy = synth.normal_tensor(np.random.Generator(np.random.PCG64(9451)), (1, L, D), dtype)
+    y = host(binding.hyena_mr_fwd(dev(q), dev(k), dev(v), dev(h), 1))
+    dq, dk, dv, dh = (host(x) for x in binding.hyena_mr_bwd(dev(dy), dev(q), dev(k), dev(v), dev(h), 1))
+    bad_y, bad_k = np.zeros((1, L, D), dtype=bool), np.zeros((1, L, D), dtype=bool)
+    bad_y[0, at:at + lh, 3] = True
+    bad_y[0, lh // 3:, 5] = True
+    bad_k[0, :max(0, L - lh // 3), 5] = True
+    bad_v = bad_k.copy()
+    bad_v[0, at, 3] = True  # dv = du * k
+    bad_h = np.zeros((D, lh), dtype=bool)
+    bad_h[3, :min(lh, L - at)] = True
+    ref = (oracle.gated_conv(q, k, v, h, group=1), *oracle.gated_conv_bwd(dy, q, k, v, h, group=1))
+    for name, got, want, bad in zip(("y", "dq", "dk", "dv", "dh"), (y, dq, dk, dv, dh), ref, (bad_y, bad_y, bad_k, bad_v, bad_h)):
+        assert np.array_equal(~np.isfinite(got), bad), name
+        err = oracle.rel_err(np.where(bad, 0.0, got), np.where(bad, 0.0, np.asarray(want)))
+        assert err <= (TOL["f32"] if name == "dh" else TOL[dtype]), (name, err)
+
+
 def us_per_call(call):
     times = []
     for _ in range(9):
@@ -114,7 +193,7 @@ def test_odd_widths_keep_up():
 
 
 def test_taps_beyond_the_sequence_cost_nothing():
-    """A filter longer than the sequence (history included) is one of its length: 2.3 times as long where its empty
+    """A filter longer than the sequence (history included) is one of its length: 2.2 times as long where its empty
     segments are walked through."""
     x = [torch.randn((15, 31, 333), device="cuda:0") for _ in range(3)]
     h = torch.randn((111, 800), device="cuda:0")
