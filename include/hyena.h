@@ -328,9 +328,11 @@ int64_t hyena_featurize_bwd_workspace_bytes(int64_t B, int64_t L, int64_t D, int
 /*
  * Backward of hyena_chain_fwd (Eq. 1 as a whole: q' = hq * q, k' = hk * k, v' = hv * v, y = q' (.) (h * (k' (.) v')))
  * by the chain rule, as a composition of the calls above on the caller's stream: hyena_featurize3_fwd recomputes
- * q', k', v'; hyena_mr_bwd gives dq', dk', dv' and dh; the operation of hyena_featurize_bwd on the three tensors (one
- * launch for filters of up to 8 taps) gives dq, dk, dv and dhq, dhk, dhv.  The intermediate tensors live in the workspace in the activations' dtype (for bf16 they are
- * rounded to bf16 between the steps, as the forward's two-kernel path rounds q', k', v').
+ * q', k', v'; hyena_mr_bwd gives dq', dk', dv' and dh; the operation of hyena_featurize_bwd on the three tensors gives
+ * dq, dk, dv and dhq, dhk, dhv (in one launch for filters of up to 8 taps, in bf16 on even widths, on tensors of up to 2^27
+ * elements whose partial filter gradients fit the memory of q', k', v', else in three).  The intermediate tensors live in the workspace in the
+ * activations' dtype (for bf16 they are rounded to bf16 between the steps, as the forward's two-kernel path rounds
+ * q', k', v').
  * dy, q, k, v, dq, dk, dv: device, [B, L, D] of `dtype`; hq, hk, hv, dhq, dhk, dhv: fp32 [D/feat_group, lf];
  * h, dh: fp32 [D/group, lh]; the usual alignment and overlap rules (every gradient distinct from everything else).
  * workspace: hyena_chain_bwd_workspace_bytes(...) bytes (six tensors plus what the inner calls need), 16-byte

@@ -774,8 +774,8 @@ hy_status hyena_chain_bwd(const void* dy, const void* q, const void* k, const vo
     if (rc != HY_OK) return rc;
     // The three featurizers: one launch where q', k', v' (dead by now) have room for its partial filter gradients.  It
     // saves the ramps of two launches and loses a little locality between the tensors, so not for the longest inputs
-    // (whole call, three launches -> one: 1 x 8192 x 4096 343 -> 318 us, 1 x 32768 x 4096 1131 -> 1113, 4 x 32768 x 4096
-    // 4302 -> 4418).
+    // (whole call, three launches -> one: 1 x 8192 x 4096 329 -> 297 us, 1 x 32768 x 4096 1097 -> 1089, 4 x 32768 x 4096
+    // 4373 -> 4481).
     BwdShape fs{B, L, D, lf, feat_group, static_cast<hy_dtype>(dtype)};
     fs.gated = false;
     fs.nprob = 3;

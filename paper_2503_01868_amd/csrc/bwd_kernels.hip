@@ -15,7 +15,7 @@
 //    arrived), a delay line of k and v for that lag, and VEC*lh partial sums for dh.  A tile reads lh-1
 //    halo rows of k, v before its start and lh-1 halo rows of dy, q after its end.
 //  * any other lh, group or width, both dtypes: dq, dk, dv by the general FIR kernel (direct_kernels.hip) in both time
-//    directions, dh by dh_tile_kernel (sequences too short for its partial sums: dh_direct_kernel).
+//    directions, dh by dh_tile_kernel (where its partial sums do not fit or samples are few: dh_direct_kernel).
 //
 // kGated = false turns both paths into the backward of the featurizer convolutions of Eq. 1 (x' = h * x, no
 // gates): u = x (the k pointer), g = dy, the only activation gradient is dx = du (the dk pointer); q, v, dq, dv are
@@ -346,11 +346,11 @@ __global__ __launch_bounds__(kBlock) void dh_direct_kernel(BwdDirectArgs a) {
 // a wave holds 16 lags: 16 steps of g against 16 + 15 rows of u are 256 FMAs per 48 LDS reads.  Filters of fewer than
 // 128 taps leave waves without lags: those take a share of the steps instead (kLagWaves lag blocks of 16).
 // The partial sums of a tile lie in the memory of dk, which the FIR launch behind these two overwrites: the shapes that
-// come here are the ones whose callers bring no workspace, and a tile is long enough for its sums to fit (the channels
-// of a group are summed in the wave first, as far as its size has powers of two).
+// come here are the ones whose callers bring no workspace, and tiles are no more than their sums fit (the channels of a
+// group are summed in the wave first, as far as its size has powers of two).
 // Pairs the definition does not have are left out, not multiplied by zeros (see the FIR kernel).
 // Measured at B = 2, L = 2048, D = 1024, 128 taps, groups of 16, fp32: 1160 us with one workgroup per (group, tap), which
-// read all samples of the group once per tap; 38 + 5 us in these two.
+// read all samples of the group once per tap; 35 + 5 us in these two.
 struct DhArgs {
     BwdPtrs p;
     int64_t L, D;

@@ -155,9 +155,9 @@ inline int64_t tiles_filling_rounds(int64_t base, int64_t L, int64_t min_rows) {
 // Time steps per workgroup of a kernel whose workgroups are bound by what one compute unit can do: one workgroup per
 // compute unit (or the finer cut above, down to `long_rows` steps), in multiples of `step`, however short that makes a
 // tile.  Until the launch fills the chip a tile's halo costs nothing but its own time, and the time of a launch is that
-// of one tile.  Measured at B = 1, lh = 128, D = 1024, L = 2048 against floors of 256 to 1024 steps: MR backward 45 -> 30
-// us, ungrouped 67 -> 46, ungrouped forward 17 -> 10, fused chain 41 -> 11.5; L = 512, D = 4096: 43 -> 29, 68 -> 47,
-// 17 -> 10, 25 -> 11.6.  Tiles shorter than this (more than one round of workgroups) lose again: with 32 steps the first
+// of one tile.  Measured at B = 1, lh = 128, D = 1024, L = 2048 against floors of 256 to 1024 steps: MR backward 45 -> 25
+// us, ungrouped 63 -> 43, ungrouped forward 17 -> 9.4, fused chain 38 -> 12; L = 512, D = 4096: 42 -> 25, 64 -> 43,
+// 16 -> 9.4, 23 -> 12.  Tiles shorter than this (more than one round of workgroups) lose again: with 32 steps the first
 // of these shapes takes 85 us in the MR backward and 18.5 in the chain.
 inline int64_t one_round_rows(int64_t base, int64_t L, int64_t long_rows, int64_t step) {
     const int64_t tiles = tiles_filling_rounds(base, L, long_rows);

@@ -246,7 +246,7 @@ int64_t tile_rows(const ConvShape& s, int nw, int64_t* workgroups) {
         if (tiles < 1) tiles = 1;
         rows = (s.L + tiles - 1) / tiles;
         // Four waves are the narrowest workgroup, what is left when wider ones would leave compute units idle: its tiles
-        // may be as short as one workgroup per CU makes them (L = 512: D = 256 11.1 -> 5.3 us, D = 4096 12.5 -> 7.8 us).
+        // may be as short as one workgroup per CU makes them (L = 512, D = 4096: 12.1 -> 7.5 us).
         const int64_t min_rows = nw == 4 ? kChunk : 4LL * kChunk * (NKB > 1 ? NKB - 1 : 1);
         if (rows < min_rows) rows = min_rows;
     }
@@ -294,7 +294,7 @@ hy_status launch_nkb(const ConvPtrs& p, const ConvShape& s, hipStream_t st) {
             // Small problems: a wide workgroup's tile is not shorter than four times its halo, so it may leave
             // compute units idle.  Take the widest workgroup that still gives every compute unit one (measured
             // at B = 1, D = 4096, lh = 128: L = 4096 28.9 us with 8 waves against 33.0 with 16; L = 2048 16.3 us
-            // with 4 waves against 19.8 / 28.3; L = 512 7.8 against 14.3 / 22.5; from L = 8192 on 16 waves win).
+            // with 4 waves against 19.8 / 28.3; L = 512 7.5 against 14.4 / 22.5; from L = 8192 on 16 waves win).
             // "Every" means three quarters of them: a batch of 3 gives 240 wide workgroups, which beat 192 narrow
             // ones by far (B = 3, L = 8192: 161 us with 4 waves, the old choice at a threshold of 256).
             constexpr int64_t kEnough = 192;
