@@ -364,11 +364,13 @@ hy_status launch_nt(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
     int64_t walks = tiles;
     if (kOne) {
         constexpr int64_t resident = 256 * per_cu(kSeg, NT);
-        const int64_t units = B * a.ncb * nprob;
+        const int64_t units = B * a.ncb * nprob, least = (units + resident - 1) / resident;
         auto cost = [&](int64_t w) { return (units * w + resident - 1) / resident * ((tiles + w - 1) / w + 1); };
         walks = 1;
-        for (int64_t w = 2; w <= tiles && units * (w - 1) < 4 * resident; ++w)
+        for (int64_t rounds = least; rounds < least + 4; ++rounds) {
+            const int64_t w = rounds * resident / units < tiles ? rounds * resident / units : tiles;
             if (cost(w) < cost(walks)) walks = w;
+        }
     }
     const int64_t steps = (tiles + walks - 1) / walks;
     walks = (tiles + steps - 1) / steps;

@@ -98,10 +98,9 @@ def tile_walk(B, L, D, lh, dtype, problems):
     def cost(w):
         return -(-units * w // resident) * (-(-tiles // w) + 1)
 
-    walks = 1
-    for w in range(2, tiles + 1):
-        if units * (w - 1) >= 4 * resident:
-            break
+    walks, least = 1, -(-units // resident)
+    for rounds in range(least, least + 4):
+        w = min(rounds * resident // units, tiles)
         if cost(w) < cost(walks):
             walks = w
     return rows, -(-tiles // walks)
