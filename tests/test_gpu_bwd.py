@@ -208,6 +208,26 @@ def test_chunk_parallel_backward_exact_case():
         assert np.array_equal(host(got), want), name
 
 
+@pytest.mark.parametrize("lh", [9, 65, 66, 129])
+@pytest.mark.parametrize("L,rows", [(1, 0), (3, 0), (63, 64), (64, 64), (66, 64), (126, 64), (129, 64), (192, 128), (253, 64)])
+def test_chunk_parallel_backward_edges_of_tiles(L, rows, lh):
+    """Ends of the sequence at every place of a 4-step piece, a 16-step group and a 64-step chunk, tiles shorter than the
+    filter, both window lengths; exactly representable values, so all gradients must match bit for bit."""
+    B, D, group = 2, 128, 2
+    say("cp4 bwd edges L=%d rows=%d lh=%d" % (L, rows, lh))
+    binding.set_option("mr_rows", rows)
+    rng = np.random.Generator(np.random.PCG64(80))
+    h = (rng.integers(-4, 5, size=(D // group, lh)) / 8.0 * (rng.random((D // group, lh)) < 0.3)).astype(np.float32)
+    dy, q, k, v = (torch.from_numpy((rng.integers(-1, 2, (B, L, D)) * (rng.random((B, L, D)) < 0.5)).astype(np.float32)).bfloat16()
+                   for _ in range(4))
+    ref = oracle.gated_conv_bwd(dy, q, k, v, h, group=group)
+    for r in ref[:3]:
+        assert np.array_equal(r, torch.from_numpy(r).bfloat16().double().numpy())
+    outs = binding.hyena_mr_bwd(dev(dy), dev(q), dev(k), dev(v), dev(h), group)
+    for name, got, want in zip(("dq", "dk", "dv", "dh"), outs, ref):
+        assert np.array_equal(host(got), want), name
+
+
 def test_matrix_core_backward_exact_case():
     """Sparse signed inputs and dyadic taps: every product and partial sum is exactly representable, so
     dq, dk, dv and dh must match the oracle bit for bit."""
