@@ -16,10 +16,6 @@ struct ConvPtrs {
     const void* v;   // pre-gate operand, unused when not gated
     const float* h;  // [D/group, lh] fp32
     void* y;
-    // optional second post-gate and output, y2 = q2 * (h * (k*v)), from the same convolution (only where
-    // cp4_dual_supported says so)
-    const void* q2 = nullptr;
-    void* y2 = nullptr;
 };
 
 struct ConvShape {
@@ -27,22 +23,16 @@ struct ConvShape {
     int32_t lh, group;
     hy_dtype dtype;
     bool gated;
-    // true: the convolution runs towards the past, y[t] = q[t] * sum_j h[j] k[t+j] v[t+j] (terms with t+j >= L
-    // vanish): the transposed operator the backward pass needs.  Only launch_cp4 implements it.
-    bool reversed = false;
     // One rank's share of a sequence-sharded call (Sec. 4, point-to-point scheme): consecutive batch items are
     // `bstride_kv` elements apart in k and v and `bstride_qy` in q and y (0: L * D, dense), and `history` rows of
     // k and v in front of row 0 hold the steps that precede the shard (the left neighbour's last rows); what lies
     // before them is zero.  Implemented by launch_stencil, launch_se_walk (history 0 or >= 8), launch_mr_mfma,
-    // launch_cp4 and launch_direct.  In reversed time the history rows lie BEHIND row L - 1.  `bstride_y` (0: as
-    // q) gives y a batch stride of its own; only launch_cp4 takes it.
+    // launch_cp4 and launch_direct.
     int64_t bstride_kv = 0, bstride_qy = 0;
     int32_t history = 0;
-    int64_t bstride_y = 0;
     int64_t stride_kv() const { return bstride_kv > 0 ? bstride_kv : L * D; }
     int64_t stride_qy() const { return bstride_qy > 0 ? bstride_qy : L * D; }
-    int64_t stride_y() const { return bstride_y > 0 ? bstride_y : stride_qy(); }
-    bool sharded() const { return history != 0 || stride_kv() != L * D || stride_qy() != L * D || stride_y() != L * D; }
+    bool sharded() const { return history != 0 || stride_kv() != L * D || stride_qy() != L * D; }
 };
 
 // The operator chain: featurize q, k, v (filters hq, hk, hv), then the gated medium convolution with h.
@@ -203,8 +193,6 @@ bool cp_mfma_supported(const ConvShape& s);
 hy_status launch_cp_mfma(const ConvPtrs& p, const ConvShape& s, hipStream_t st);
 // The same on the batched 4x4x4 MFMA: 256 channels per workgroup, lh <= 129.  HY_ERR_UNSUPPORTED outside cp4_supported().
 bool cp4_supported(const ConvShape& s);
-// whether launch_cp4 also takes ConvPtrs::q2 / y2 for this shape (the long-filter kernel does)
-bool cp4_dual_supported(const ConvShape& s);
 hy_status launch_cp4(const ConvPtrs& p, const ConvShape& s, hipStream_t st);
 // Whole chain in one pass over q, k, v, featurizers on the matrix cores too (batched 4x4x4 products, taps as bf16
 // head + remainder).  HY_ERR_UNSUPPORTED outside chain4_supported().
@@ -238,9 +226,8 @@ bool mr_bwd_supported(const BwdShape& s);
 int64_t mr_bwd_rows(const BwdShape& s);
 int64_t mr_bwd_workspace_bytes(const BwdShape& s);
 hy_status launch_mr_bwd(const BwdPtrs& p, const BwdShape& s, void* ws, hipStream_t st);
-// Backward on the matrix cores for medium bf16 filters not shared by 16 channels (any group): dq and dk, dv from the
-// chunk-parallel forward kernel (forwards, and twice towards the past), dh as a per-channel correlation on the
-// batched 4x4x4 products; `ws` holds the partial filter gradients.
+// Backward on the matrix cores for medium bf16 filters not shared by 16 channels (any group): dq, dk, dv and dh in one
+// pass on the batched 4x4x4 products; `ws` holds the partial filter gradients.
 bool cp4_bwd_supported(const BwdShape& s);
 int64_t cp4_bwd_workspace_bytes(const BwdShape& s);
 hy_status launch_cp4_bwd(const BwdPtrs& p, const BwdShape& s, void* ws, hipStream_t st);
