@@ -441,12 +441,11 @@ __global__ __launch_bounds__(2 * kNW * 64, 2) void cp4_bwd_kernel(Cp4BwdArgs a) 
 
 int64_t bwd_rows(const BwdShape& s) {
     const int64_t ncb = s.D / kC;
-    const int64_t halo = s.lh <= 65 ? kT : 2 * kT;
     int64_t rows = tuning().mr_rows;
     if (rows <= 0) {
-        rows = one_round_rows(s.B * ncb, s.L, 4 * halo, kT);
-        // as short as the halo: each tile also leaves partial rows (half or twice that: the same times within 5%)
-        if (rows < halo) rows = halo;
+        rows = one_round_rows(s.B * ncb, s.L, 8 * kT, kT);
+        // as short as the longer halo: each tile also leaves partial rows (half or twice that: the same times within 5%)
+        if (rows < 2 * kT) rows = 2 * kT;
     }
     rows = (rows + kT - 1) / kT * kT;
     const int64_t cap = (s.L + kT - 1) / kT * kT;
