@@ -327,15 +327,17 @@ int64_t hyena_featurize_bwd_workspace_bytes(int64_t B, int64_t L, int64_t D, int
 
 /*
  * Backward of hyena_chain_fwd (Eq. 1 as a whole: q' = hq * q, k' = hk * k, v' = hv * v, y = q' (.) (h * (k' (.) v')))
- * by the chain rule, as a composition of the calls above on the caller's stream: hyena_featurize3_fwd recomputes
- * q', k', v'; hyena_mr_bwd gives dq', dk', dv' and dh; the operation of hyena_featurize_bwd on the three tensors gives
- * dq, dk, dv and dhq, dhk, dhv (in one launch for filters of up to 8 taps, in bf16 on even widths, on tensors of up to 2^27
- * elements whose partial filter gradients fit the memory of q', k', v', else in three).  The intermediate tensors live in the workspace in the
- * activations' dtype (for bf16 they are rounded to bf16 between the steps, as the forward's two-kernel path rounds
- * q', k', v').
+ * by the chain rule.  bf16 with an inner filter of 9 to 129 taps shared by a multiple of 16 channels, featurizers of up to 8
+ * taps and D % 64 == 0 (D < 2^23): one kernel that reads dy, q, k, v and writes dq, dk, dv once; u = k' (.) v', g = dy (.) q',
+ * dq', dk', dv' and, where they gate du, k' and v' are rounded to bf16 on chip.  Everything else is a composition of the calls
+ * above on the caller's stream: hyena_featurize3_fwd recomputes q', k', v'; hyena_mr_bwd gives dq', dk', dv' and dh; the
+ * operation of hyena_featurize_bwd on the three tensors gives dq, dk, dv and dhq, dhk, dhv (in one launch for filters of up to
+ * 8 taps, in bf16 on even widths, on tensors of up to 2^27 elements whose partial filter gradients fit the memory of
+ * q', k', v', else in three).  Its intermediate tensors live in the workspace in the activations' dtype (for bf16 they are
+ * rounded to bf16 between the steps, as the forward's two-kernel path rounds q', k', v').
  * dy, q, k, v, dq, dk, dv: device, [B, L, D] of `dtype`; hq, hk, hv, dhq, dhk, dhv: fp32 [D/feat_group, lf];
  * h, dh: fp32 [D/group, lh]; the usual alignment and overlap rules (every gradient distinct from everything else).
- * workspace: hyena_chain_bwd_workspace_bytes(...) bytes (six tensors plus what the inner calls need), 16-byte
+ * workspace: hyena_chain_bwd_workspace_bytes(...) bytes (six tensors plus what the inner calls need, whichever way), 16-byte
  * aligned, disjoint from every argument; too small: HY_ERR_SHAPE.  An empty problem writes zero filter gradients.
  */
 hy_status hyena_chain_bwd(const void *dy, const void *q, const void *k, const void *v, const float *hq,

@@ -705,7 +705,9 @@ int64_t chain_bwd_inner_ws(int64_t B, int64_t L, int64_t D, int32_t lf, int32_t 
     const int64_t a = hyena_bwd_workspace_bytes(B, L, D, lh, group, dtype);
     const int64_t b = hyena_featurize_bwd_workspace_bytes(B, L, D, lf, feat_group, dtype);
     if (a < 0 || b < 0) return -1;
-    return a > b ? a : b;
+    const ChainShape s{B, L, D, lf, feat_group, lh, group, static_cast<hy_dtype>(dtype)};
+    const int64_t c = chain_bwd_supported(s) ? chain_bwd_workspace_bytes(s) : 0;  // one pass: nothing but this
+    return a > b ? (a > c ? a : c) : (b > c ? b : c);
 }
 }  // namespace
 
@@ -765,6 +767,10 @@ hy_status hyena_chain_bwd(const void* dy, const void* q, const void* k, const vo
     rc = check_workspace(workspace, workspace_bytes, 6 * slot + inner, all, 15);
     if (rc != HY_OK) return rc;
     char* const ws = static_cast<char*>(workspace);
+    const ChainShape cs{B, L, D, lf, feat_group, lh, group, static_cast<hy_dtype>(dtype)};
+    if (chain_bwd_supported(cs))
+        return launch_chain_bwd(ChainBwdPtrs{dy, q, k, v, hq, hk, hv, h, dq, dk, dv, dhq, dhk, dhv, dh}, cs, ws,
+                                static_cast<hipStream_t>(hip_stream));
     void* const qf = ws, * const kf = ws + slot, * const vf = ws + 2 * slot;               // q', k', v'
     void* const gq = ws + 3 * slot, * const gk = ws + 4 * slot, * const gv = ws + 5 * slot;  // dq', dk', dv'
     void* const iw = inner > 0 ? ws + 6 * slot : nullptr;

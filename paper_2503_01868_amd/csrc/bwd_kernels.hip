@@ -838,6 +838,11 @@ hy_status launch_dh_reduce(const float* partial, float* dh, int64_t nsets, int64
     return launch_reduce(ReduceArgs{{partial, partial, partial}, {dh, dh, dh}}, 1, nsets, n_rows, lh, group, st);
 }
 
+hy_status launch_dh_reduce3(const float* const (&partial)[3], float* const (&dh)[3], int64_t nsets, int64_t n_rows, int32_t lh,
+                            int32_t group, hipStream_t st) {
+    return launch_reduce(ReduceArgs{{partial[0], partial[1], partial[2]}, {dh[0], dh[1], dh[2]}}, 3, nsets, n_rows, lh, group, st);
+}
+
 hy_status launch_bwd_zero_dh(float* dh, int64_t D, int32_t lh, int32_t group, hipStream_t st) {
     // a reduction over zero partial sets writes zeros (a fill kernel, not a memset, so that callers may
     // capture the call in a HIP graph)

@@ -60,6 +60,14 @@ struct ChainShape {
     int64_t stride_y() const { return bstride_y > 0 ? bstride_y : L * D; }
 };
 
+// Backward of the operator chain.
+struct ChainBwdPtrs {
+    const void *dy, *q, *k, *v;
+    const float *hq, *hk, *hv, *h;
+    void *dq, *dk, *dv;
+    float *dhq, *dhk, *dhv, *dh;
+};
+
 // Backward of the gated convolution.
 struct BwdPtrs {
     const void* dy;
@@ -231,9 +239,17 @@ hy_status launch_mr_bwd(const BwdPtrs& p, const BwdShape& s, void* ws, hipStream
 bool cp4_bwd_supported(const BwdShape& s);
 int64_t cp4_bwd_workspace_bytes(const BwdShape& s);
 hy_status launch_cp4_bwd(const BwdPtrs& p, const BwdShape& s, void* ws, hipStream_t st);
+// Backward of the whole chain in one pass (medium grouped bf16 filters, featurizers of up to 8 taps); `ws` holds the partial
+// filter gradients.
+bool chain_bwd_supported(const ChainShape& s);
+int64_t chain_bwd_workspace_bytes(const ChainShape& s);
+hy_status launch_chain_bwd(const ChainBwdPtrs& p, const ChainShape& s, void* ws, hipStream_t st);
 // dh[g][j] = sum over nsets partial sets and over `group` adjacent rows of a set; a set is [n_rows][lh].
 hy_status launch_dh_reduce(const float* partial, float* dh, int64_t nsets, int64_t n_rows, int32_t lh, int32_t group,
                            hipStream_t st);
+// The same for three problems of one shape in one launch.
+hy_status launch_dh_reduce3(const float* const (&partial)[3], float* const (&dh)[3], int64_t nsets, int64_t n_rows, int32_t lh,
+                            int32_t group, hipStream_t st);
 // dh := 0 (the filter gradient of an empty batch).
 hy_status launch_bwd_zero_dh(float* dh, int64_t D, int32_t lh, int32_t group, hipStream_t st);
 // Bandwidth yardstick y = q*k*v (bf16): strip = 0 streams linearly, 64 / 128 / 256 walks column strips of that many

@@ -38,6 +38,12 @@ hy_status launch_mr_bwd(const BwdPtrs&, const BwdShape&, void*, hipStream_t) { r
 bool cp4_bwd_supported(const BwdShape& s) { return s.dtype == HY_BF16 && s.D % 128 == 0 && s.lh > 8 && s.lh <= 129; }
 int64_t cp4_bwd_workspace_bytes(const BwdShape& s) { return s.B * s.D * s.lh * 4; }
 hy_status launch_cp4_bwd(const BwdPtrs&, const BwdShape&, void*, hipStream_t) { return HY_OK; }
+bool chain_bwd_supported(const ChainShape& s) {
+    return s.dtype == HY_BF16 && s.group % 16 == 0 && s.D % 64 == 0 && s.lh > 8 && s.lh <= 129 && s.lf <= 8;
+}
+int64_t chain_bwd_workspace_bytes(const ChainShape& s) { return s.B * (s.D / 16 * s.lh + 3 * s.D * s.lf) * 4; }
+hy_status launch_chain_bwd(const ChainBwdPtrs&, const ChainShape&, void*, hipStream_t) { return HY_OK; }
+hy_status launch_dh_reduce3(const float* const (&)[3], float* const (&)[3], int64_t, int64_t, int32_t, int32_t, hipStream_t) { return HY_OK; }
 hy_status launch_dh_reduce(const float*, float*, int64_t, int64_t, int32_t, int32_t, hipStream_t) { return HY_OK; }
 hy_status launch_stream_gate(const void*, const void*, const void*, void*, int64_t, int64_t, int64_t, int32_t, int64_t,
                              int32_t, int32_t, hipStream_t) { return HY_OK; }

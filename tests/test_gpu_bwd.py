@@ -414,6 +414,26 @@ def test_chain_backward_matches_oracle(case):
         assert err <= tol, (name, err)
 
 
+@pytest.mark.parametrize("lh,lf", [(9, 7), (65, 1), (66, 8), (129, 5)])
+@pytest.mark.parametrize("L,rows", [(1, 0), (3, 0), (31, 32), (32, 32), (34, 32), (63, 32), (129, 32), (250, 96), (517, 256)])
+def test_one_pass_chain_backward_edges_of_tiles(L, rows, lh, lf):
+    """Ends of the sequence at every place of a 4-step piece, a 16-step group and a 32-step chunk, tiles shorter than the inner
+    filter, both window lengths, the shortest and longest featurizers, shared ones too.  The bars are the chain's (bf16 u, g,
+    dq', dk', dv' and outputs: 2^-9 each, in sums of independent terms)."""
+    B, D, group, fg = 2, 128, 16, 2 if lf == 5 else 1
+    say("one-pass chain bwd L=%d rows=%d lh=%d lf=%d" % (L, rows, lh, lf))
+    binding.set_option("mr_rows", rows)
+    rng = np.random.Generator(np.random.PCG64(9300 + L + lh))
+    dy, q, k, v = (synth.normal_tensor(rng, (B, L, D), "bf16") for _ in range(4))
+    hq, hk, hv = (synth.short_filter(rng, D // fg, lf) for _ in range(3))
+    h = synth.decay_filter(rng, D // group, lh)
+    got = binding.hyena_chain_bwd(*[dev(x) for x in (dy, q, k, v, hq, hk, hv, h)], group, fg)
+    ref = oracle.chain_bwd(dy, q, k, v, hq, hk, hv, h, group=group, feat_group=fg)
+    for name, g, want, tol in zip(("dq", "dk", "dv", "dhq", "dhk", "dhv", "dh"), got, ref, (TOL["bf16"],) * 3 + (DH_TOL_MFMA,) * 4):
+        err = oracle.rel_err(host(g), want)
+        assert err <= tol, (name, err)
+
+
 @pytest.mark.timeout(900)
 def test_chain_backward_at_the_chain_config_on_a_channel_slab():
     """c4_bwd as bench.py times it (B=4, L=32768, D=4096, featurizers of 7 taps, lh=128, groups of 16): the whole

@@ -79,7 +79,7 @@ def test_the_checker_sees_a_planted_pair_and_accepts_a_distant_one():
     assert hazards(reverse)[0] == []
 
 
-@pytest.mark.parametrize("unit", ["li_kernels.hip", "mr_bwd_kernels.hip"])
+@pytest.mark.parametrize("unit", ["li_kernels.hip", "mr_bwd_kernels.hip", "chain_bwd_kernels.hip"])
 def test_no_short_product_accumulates_onto_a_fresh_long_product(unit, tmp_path):
     lines = assemble(os.path.join(CSRC, unit), tmp_path)
     found, n = hazards(lines)
