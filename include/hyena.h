@@ -413,6 +413,8 @@ hy_status hyena_stream_gate(const void *q, const void *k, const void *v, void *y
  *   "mr_waves" waves (= 16-channel groups) per workgroup in the MR and Hyena-LI kernels (4, 8 or 16)
  *   "se_walk"  which kernel hyena_se_fwd takes for bf16 filters of up to 8 taps: 0 = by problem size,
  *              1 = always the long-sequence kernel (where D is a multiple of 128), 2 = always the stencil
+ *   "li_wait"  how Hyena-LI's tiles come by the states of the tiles before them, where it can do them in one pass:
+ *              0 = wait for them (for a bounded time), 1 = compute them again, 2 = two passes everywhere
  * Unknown names return HY_ERR_UNSUPPORTED.  Results depend on these only through rounding, within the
  * documented precision of each entry point.
  */

@@ -525,8 +525,8 @@ hy_status hyena_li_fwd_static(const void* q, const void* k, const void* v, const
         rc = static_scratch(&ws);
         if (rc != HY_OK) return rc;
     }
-    // Nothing has to be cleared: pass 1 writes the end state of every tile but the last of each sequence, and pass 2
-    // reads exactly those records, so no byte is read that this call has not written.
+    // Nothing has to be cleared here: the launches of this call write (or, for the one-pass form, mark as unset) the record
+    // of every tile but the last of each sequence, and read exactly those, so no byte is read that this call has not written.
     return launch_li_mfma(p, s, ws, st);
 }
 
@@ -870,6 +870,9 @@ hy_status hyena_set_option(const char* name, int32_t value) {
     } else if (strcmp(name, "se_walk") == 0) {
         if (value > 2) return HY_ERR_SHAPE;
         t.se_walk = value;
+    } else if (strcmp(name, "li_wait") == 0) {
+        if (value > 2) return HY_ERR_SHAPE;
+        t.li_wait = value;
     } else {
         return HY_ERR_UNSUPPORTED;
     }

@@ -128,6 +128,7 @@ struct Tuning {
     int mr_rows = 0;
     int mr_waves = 0;
     int se_walk = 0;  // 0: by size, 1: always the walking SE kernel where it applies, 2: never
+    int li_wait = 0;  // Hyena-LI in one pass: 0: wait for earlier tiles' states, 1: recompute them, 2: never in one pass
 };
 // The options as the calling thread's current entry point sees them.  Every extern "C" function that sizes or
 // launches anything starts with a TuningSnapshot, which copies the process-wide options under a lock into a
@@ -206,7 +207,7 @@ hy_status launch_cp4(const ConvPtrs& p, const ConvShape& s, hipStream_t st);
 // head + remainder).  HY_ERR_UNSUPPORTED outside chain4_supported().
 bool chain4_supported(const ChainShape& s);
 hy_status launch_chain4(const ChainPtrs& p, const ChainShape& s, hipStream_t st);
-// Hyena-LI as a two-pass chunked scan on bf16 MFMA (end-of-tile states in `ws`), and the plain recurrence.
+// Hyena-LI as a chunked scan on bf16 MFMA, in one pass or two (end-of-tile states in `ws`), and the plain recurrence.
 bool li_mfma_supported(const LiShape& s);
 int64_t li_workspace_bytes(const LiShape& s);
 hy_status launch_li_mfma(const LiPtrs& p, const LiShape& s, void* ws, hipStream_t st);

@@ -17,8 +17,11 @@
 // into tiles and scanned in two passes (the classic chunked scan): pass 1 walks every tile but the last of
 // each sequence with a zero start and leaves the tile's final state in a workspace (reads k and v only);
 // pass 2 rebuilds its start state from the tiles before it, s_in = sum_tau Lambda^(rows * (tile-1-tau)) s_tau
-// (a short Horner loop over 1 KiB records), and computes y.  With a single tile per sequence pass 1 is skipped.
+// (a short Horner loop over 1 KiB records), and computes y.  With a single tile per sequence pass 1 is skipped;
+// tiles short enough to be kept on chip between the passes are done in one (li_one_pass_kernel).
 // Data movement per chunk is that of mr_kernels.hip: whole row pieces, u and z through LDS, one barrier.
+#include <type_traits>
+
 #include "hy_common.hpp"
 #include "hy_launch.hpp"
 
@@ -42,6 +45,7 @@ struct LiArgs {
     int32_t rows;           // time steps per workgroup, multiple of 32
     int32_t tiles_per_seq;  // ceil(L / rows)
     int32_t ncb;            // channel blocks = D / (16 NW)
+    int32_t polls;          // li_one_pass_kernel: looks at an earlier tile's state before a wave computes it itself
 };
 
 constexpr int kChunk = 32;
@@ -55,6 +59,152 @@ __device__ __forceinline__ float powi(float x, int e) {  // x^e, e >= 0, by squa
         e >>= 1;
     }
     return r;
+}
+
+// T operands: tile x (steps 16x..16x+15 of the chunk) against the chunk's 32 source steps; lane (li = step,
+// lq = source octet), element e = h[16x + li - 8lq - e].  `h` holds the filter's first 32 values.
+__device__ __forceinline__ void t_operands(bf16x8_t (&tz)[2], const float* h, int li, int lq) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        Words<4> wds;
+#pragma unroll
+        for (int e2 = 0; e2 < 4; ++e2) {
+            const int i0 = 16 * x + li - 8 * lq - 2 * e2;
+            const int i1 = i0 - 1;
+            const float f0 = (i0 >= 0 && i0 < kChunk) ? h[i0] : 0.0f;
+            const float f1 = (i1 >= 0 && i1 < kChunk) ? h[i1] : 0.0f;
+            wds.w[e2] = pack_bf16x2(f0, f1);
+        }
+        tz[x] = __builtin_bit_cast(bf16x8_t, wds);
+    }
+}
+
+// P operand: lane (li = n, lq = source octet), element e = lambda_n^(31 - 8lq - e), as a bf16 head and a bf16
+// remainder.  The exponentials of a filter may nearly cancel (close poles, residues of opposite sign); each
+// one's running sum therefore has to be accurate well beyond bf16, or the error of the individual terms shows
+// at full size in their small difference.  The same holds for the Q operands below.
+__device__ __forceinline__ void p_operands(bf16x8_t& pop, bf16x8_t& pop_lo, const float* lam, int li, int lq) {
+    const float ln = lam[li];
+    Words<4> wds, wlo;
+    float pw = powi(ln, 31 - 8 * lq - 7);  // smallest exponent of the lane (element 7), then multiply up
+    float pe[8];
+#pragma unroll
+    for (int e = 7; e >= 0; --e) {
+        pe[e] = pw;
+        pw *= ln;
+    }
+#pragma unroll
+    for (int e2 = 0; e2 < 4; ++e2) {
+        wds.w[e2] = pack_bf16x2(pe[2 * e2], pe[2 * e2 + 1]);
+        wlo.w[e2] = pack_bf16x2(pe[2 * e2] - bf16_lo(wds.w[e2]), pe[2 * e2 + 1] - bf16_hi(wds.w[e2]));
+    }
+    pop = __builtin_bit_cast(bf16x8_t, wds);
+    pop_lo = __builtin_bit_cast(bf16x8_t, wlo);
+}
+
+// Q operands: lane (li = step of tile x, lq), element e = R_n lambda_n^(16x + li + 1), n = 4lq + e
+__device__ __forceinline__ void q_operands(s16x4_t (&qop)[2], s16x4_t (&qop_lo)[2], const float* res, const float* lam, int li,
+                                           int lq) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        float qe[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) qe[e] = res[4 * lq + e] * powi(lam[4 * lq + e], 16 * x + li + 1);
+        Words<2> wds, wlo;
+        wds.w[0] = pack_bf16x2(qe[0], qe[1]);
+        wds.w[1] = pack_bf16x2(qe[2], qe[3]);
+        wlo.w[0] = pack_bf16x2(qe[0] - bf16_lo(wds.w[0]), qe[1] - bf16_hi(wds.w[0]));
+        wlo.w[1] = pack_bf16x2(qe[2] - bf16_lo(wds.w[1]), qe[3] - bf16_hi(wds.w[1]));
+        qop[x] = __builtin_bit_cast(s16x4_t, wds);
+        qop_lo[x] = __builtin_bit_cast(s16x4_t, wlo);
+    }
+}
+
+// z of a chunk: steps 16x + li of channels 4 lq .. 4 lq + 3 of the wave in acc[x].
+// The state enters in two bf16 parts, head and remainder; smallest terms first: head of the state against the remainder
+// of Q, remainder of the state against the head of Q, then the heads, then the chunk's own Toeplitz block.  The order of
+// the two instruction shapes matters beyond rounding: a 16x16x16 product that accumulates onto the result of a 16x16x32
+// product issued fewer than 5 wait states earlier reads the register's previous contents on gfx950 (measured), and the
+// compiler does not always leave that distance; 16x16x16 results feeding a 16x16x32 product are interlocked by the
+// hardware.  Every 16x16x16 product below accumulates onto zero or onto another 16x16x16 result, so the unsafe pair cannot
+// arise from this source by data dependence; tests/test_isa_hazards.py checks the generated code of this file for the pair
+// on every build.
+__device__ __forceinline__ void chunk_outputs(f32x4_t (&acc)[2], const f32x4_t& s, const bf16x8_t& uw, const bf16x8_t (&tz)[2],
+                                              const s16x4_t (&qop)[2], const s16x4_t (&qop_lo)[2]) {
+    const uint32_t h01 = pack_bf16x2(s[0], s[1]), h23 = pack_bf16x2(s[2], s[3]);
+    const uint32_t l01 = pack_bf16x2(s[0] - bf16_lo(h01), s[1] - bf16_hi(h01));
+    const uint32_t l23 = pack_bf16x2(s[2] - bf16_lo(h23), s[3] - bf16_hi(h23));
+    Words<2> hw, lw;
+    hw.w[0] = h01; hw.w[1] = h23;
+    lw.w[0] = l01; lw.w[1] = l23;
+    const s16x4_t shi = __builtin_bit_cast(s16x4_t, hw), slo = __builtin_bit_cast(s16x4_t, lw);
+    acc[0] = acc[1] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int x = 0; x < 2; ++x) acc[x] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(shi, qop_lo[x], acc[x], 0, 0, 0);
+#pragma unroll
+    for (int x = 0; x < 2; ++x) acc[x] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(slo, qop[x], acc[x], 0, 0, 0);
+#pragma unroll
+    for (int x = 0; x < 2; ++x) acc[x] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(shi, qop[x], acc[x], 0, 0, 0);
+#pragma unroll
+    for (int x = 0; x < 2; ++x) acc[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(uw, tz[x], acc[x], 0, 0, 0);
+}
+
+// The same products in 16x16x32 shape alone: head and remainder of the state side by side in one operand, remainder and head
+// of Q in the other, and once more with the state's parts exchanged (which adds the product of the remainders).  No product
+// here feeds one of another shape: in an unrolled loop the compiler left 4 wait states and no other product between a
+// 16x16x16 product and the 16x16x32 product that accumulated onto it, and the upper two registers of the result came out
+// wrong in some waves (other distances, and other products in between, do not show it; tests/test_isa_hazards.py checks the
+// kernels above for that pair).
+__device__ __forceinline__ void chunk_outputs_wide(f32x4_t (&acc)[2], const f32x4_t& s, const bf16x8_t& uw,
+                                                   const bf16x8_t (&tz)[2], const bf16x8_t (&qop)[2]) {
+    Words<4> a, b;
+    a.w[0] = b.w[2] = pack_bf16x2(s[0], s[1]);
+    a.w[1] = b.w[3] = pack_bf16x2(s[2], s[3]);
+    a.w[2] = b.w[0] = pack_bf16x2(s[0] - bf16_lo(a.w[0]), s[1] - bf16_hi(a.w[0]));
+    a.w[3] = b.w[1] = pack_bf16x2(s[2] - bf16_lo(a.w[1]), s[3] - bf16_hi(a.w[1]));
+    const bf16x8_t s1 = __builtin_bit_cast(bf16x8_t, a), s2 = __builtin_bit_cast(bf16x8_t, b);
+    acc[0] = acc[1] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int x = 0; x < 2; ++x) acc[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(s1, qop[x], acc[x], 0, 0, 0);
+#pragma unroll
+    for (int x = 0; x < 2; ++x) acc[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(s2, qop[x], acc[x], 0, 0, 0);
+#pragma unroll
+    for (int x = 0; x < 2; ++x) acc[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(uw, tz[x], acc[x], 0, 0, 0);
+}
+
+// s' = Lambda^32 s + P u
+__device__ __forceinline__ void advance(f32x4_t& s, const float (&lam32)[4], const bf16x8_t& pop, const bf16x8_t& pop_lo,
+                                        const bf16x8_t& uw) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s[r] *= lam32[r];
+    s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pop, uw, s, 0, 0, 0);
+    s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pop_lo, uw, s, 0, 0, 0);
+}
+
+// k*v of 8 channels of a row, rounded to bf16
+__device__ __forceinline__ uint4 products(const Words<4>& kk, const Words<4>& vv) {
+    float kf[8], vf[8];
+    Pack<BF16, 8>::unpack(kk, kf);
+    Pack<BF16, 8>::unpack(vv, vf);
+    uint32_t x[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = pack_bf16x2(kf[2 * e] * vf[2 * e], kf[2 * e + 1] * vf[2 * e + 1]);
+    return make_uint4(x[0], x[1], x[2], x[3]);
+}
+
+// element e of a lane = u[row 8 lq + e][channel 16 w + li] of a staged chunk (rd_piece: the lane's piece of a row)
+template <int PPR>
+__device__ __forceinline__ bf16x8_t transposed(const uint4* stage, int rd_piece, int li, int lq) {
+    const uint16_t* s16 = reinterpret_cast<const uint16_t*>(stage);
+    Words<4> wds;
+#pragma unroll
+    for (int e2 = 0; e2 < 4; ++e2) {
+        const int r0 = 8 * lq + 2 * e2;
+        const uint32_t lo = s16[((r0 * PPR + rd_piece) << 3) + (li & 7)];
+        const uint32_t hi = s16[(((r0 + 1) * PPR + rd_piece) << 3) + (li & 7)];
+        wds.w[e2] = lo | (hi << 16);
+    }
+    return __builtin_bit_cast(bf16x8_t, wds);
 }
 
 // kStateOnly: pass 1 (no q, no output, the tile's final state goes to the workspace).
@@ -164,67 +314,15 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 2) void li_mfma_kernel(LiAr
     }
     __syncthreads();
 
-    // T operands: tile x (steps 16x..16x+15 of the chunk) against the chunk's 32 source steps; lane (li = step,
-    // lq = source octet), element e = h[16x + li - 8lq - e]
     bf16x8_t tz[2];
-    if constexpr (!kStateOnly) {
-#pragma unroll
-        for (int x = 0; x < 2; ++x) {
-            Words<4> wds;
-#pragma unroll
-            for (int e2 = 0; e2 < 4; ++e2) {
-                const int i0 = 16 * x + li - 8 * lq - 2 * e2;
-                const int i1 = i0 - 1;
-                const float f0 = (i0 >= 0 && i0 < kChunk) ? hs[w][i0] : 0.0f;
-                const float f1 = (i1 >= 0 && i1 < kChunk) ? hs[w][i1] : 0.0f;
-                wds.w[e2] = pack_bf16x2(f0, f1);
-            }
-            tz[x] = __builtin_bit_cast(bf16x8_t, wds);
-        }
-    }
-    // P operand: lane (li = n, lq = source octet), element e = lambda_n^(31 - 8lq - e), as a bf16 head and a bf16
-    // remainder.  The exponentials of a filter may nearly cancel (close poles, residues of opposite sign); each
-    // one's running sum therefore has to be accurate well beyond bf16, or the error of the individual terms shows
-    // at full size in their small difference.  The same holds for the Q operands below.
+    if constexpr (!kStateOnly) t_operands(tz, hs[w], li, lq);
     bf16x8_t pop, pop_lo;
-    {
-        const float ln = ls[w][li];
-        Words<4> wds, wlo;
-        float pw = powi(ln, 31 - 8 * lq - 7);  // smallest exponent of the lane (element 7), then multiply up
-        float pe[8];
-#pragma unroll
-        for (int e = 7; e >= 0; --e) {
-            pe[e] = pw;
-            pw *= ln;
-        }
-#pragma unroll
-        for (int e2 = 0; e2 < 4; ++e2) {
-            wds.w[e2] = pack_bf16x2(pe[2 * e2], pe[2 * e2 + 1]);
-            wlo.w[e2] = pack_bf16x2(pe[2 * e2] - bf16_lo(wds.w[e2]), pe[2 * e2 + 1] - bf16_hi(wds.w[e2]));
-        }
-        pop = __builtin_bit_cast(bf16x8_t, wds);
-        pop_lo = __builtin_bit_cast(bf16x8_t, wlo);
-    }
+    p_operands(pop, pop_lo, ls[w], li, lq);
     float lam32[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) lam32[r] = powi(ls[w][4 * lq + r], kChunk);
-    // Q operands: lane (li = step of tile x, lq), element e = R_n lambda_n^(16x + li + 1), n = 4lq + e
     s16x4_t qop[2], qop_lo[2];
-    if constexpr (!kStateOnly) {
-#pragma unroll
-        for (int x = 0; x < 2; ++x) {
-            float qe[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) qe[e] = rs[w][4 * lq + e] * powi(ls[w][4 * lq + e], 16 * x + li + 1);
-            Words<2> wds, wlo;
-            wds.w[0] = pack_bf16x2(qe[0], qe[1]);
-            wds.w[1] = pack_bf16x2(qe[2], qe[3]);
-            wlo.w[0] = pack_bf16x2(qe[0] - bf16_lo(wds.w[0]), qe[1] - bf16_hi(wds.w[0]));
-            wlo.w[1] = pack_bf16x2(qe[2] - bf16_lo(wds.w[1]), qe[3] - bf16_hi(wds.w[1]));
-            qop[x] = __builtin_bit_cast(s16x4_t, wds);
-            qop_lo[x] = __builtin_bit_cast(s16x4_t, wlo);
-        }
-    }
+    if constexpr (!kStateOnly) q_operands(qop, qop_lo, rs[w], ls[w], li, lq);
 
     const int swz = ((lr >> 3) & 3) << 1;
     const int st_idx = lr * PPR + (lp ^ swz);
@@ -251,74 +349,22 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 2) void li_mfma_kernel(LiAr
         for (int sgi = 0; sgi < kPrefetch; ++sgi) {
             const int ci = base + sgi;
             const bool live = ci < nchunks;
-            {
-                float kf[8], vf[8];
-                Pack<BF16, 8>::unpack(kpre[sgi], kf);
-                Pack<BF16, 8>::unpack(vpre[sgi], vf);
-                Words<4> uu;
-#pragma unroll
-                for (int e2 = 0; e2 < 4; ++e2)
-                    uu.w[e2] = pack_bf16x2(kf[2 * e2] * vf[2 * e2], kf[2 * e2 + 1] * vf[2 * e2 + 1]);
-                stage[ci & 1][st_idx] = make_uint4(uu.w[0], uu.w[1], uu.w[2], uu.w[3]);
-            }
+            stage[ci & 1][st_idx] = products(kpre[sgi], vpre[sgi]);
             load_kv(ci + kPrefetch, kpre[sgi], vpre[sgi]);
 
             __syncthreads();
 
-            // transposed read: element e of this lane = u[row 8 lq + e][channel 16 w + li]
-            bf16x8_t uw;
-            {
-                const uint16_t* s16 = reinterpret_cast<const uint16_t*>(stage[ci & 1]);
-                Words<4> wds;
-#pragma unroll
-                for (int e2 = 0; e2 < 4; ++e2) {
-                    const int r0 = 8 * lq + 2 * e2;
-                    const uint32_t lo = s16[((r0 * PPR + rd_piece) << 3) + (li & 7)];
-                    const uint32_t hi = s16[(((r0 + 1) * PPR + rd_piece) << 3) + (li & 7)];
-                    wds.w[e2] = lo | (hi << 16);
-                }
-                uw = __builtin_bit_cast(bf16x8_t, wds);
-            }
+            const bf16x8_t uw = transposed<PPR>(stage[ci & 1], rd_piece, li, lq);
 
             if (live) {
                 if constexpr (!kStateOnly) {
-                    // carry-in: the state in two bf16 parts, head and remainder
-                    const uint32_t h01 = pack_bf16x2(s[0], s[1]), h23 = pack_bf16x2(s[2], s[3]);
-                    const uint32_t l01 = pack_bf16x2(s[0] - bf16_lo(h01), s[1] - bf16_hi(h01));
-                    const uint32_t l23 = pack_bf16x2(s[2] - bf16_lo(h23), s[3] - bf16_hi(h23));
-                    Words<2> hw, lw;
-                    hw.w[0] = h01; hw.w[1] = h23;
-                    lw.w[0] = l01; lw.w[1] = l23;
-                    const s16x4_t shi = __builtin_bit_cast(s16x4_t, hw), slo = __builtin_bit_cast(s16x4_t, lw);
-                    // smallest terms first: head of the state against the remainder of Q, remainder of the state
-                    // against the head of Q, then the heads, then the chunk's own Toeplitz block.  The order of the
-                    // two instruction shapes matters beyond rounding: a 16x16x16 product that accumulates onto the
-                    // result of a 16x16x32 product issued fewer than 5 wait states earlier reads the register's
-                    // previous contents on gfx950 (measured), and the compiler does not always leave that distance;
-                    // 16x16x16 results feeding a 16x16x32 product are interlocked by the hardware.  Every 16x16x16
-                    // product below accumulates onto zero or onto another 16x16x16 result, so the unsafe pair cannot
-                    // arise from this source by data dependence; tests/test_isa_hazards.py checks the generated code
-                    // of this file for the pair on every build.
-                    f32x4_t acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = {0.0f, 0.0f, 0.0f, 0.0f};
-                    acc0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(shi, qop_lo[0], acc0, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(shi, qop_lo[1], acc1, 0, 0, 0);
-                    acc0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(slo, qop[0], acc0, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(slo, qop[1], acc1, 0, 0, 0);
-                    acc0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(shi, qop[0], acc0, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(shi, qop[1], acc1, 0, 0, 0);
-                    acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(uw, tz[0], acc0, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(uw, tz[1], acc1, 0, 0, 0);
+                    f32x4_t acc[2];
+                    chunk_outputs(acc, s, uw, tz, qop, qop_lo);
                     char* zp = zst[ci & 1] + zwr_off;
-                    *reinterpret_cast<float4*>(zp) = make_float4(acc0[0], acc0[1], acc0[2], acc0[3]);
-                    *reinterpret_cast<float4*>(zp + 16 * ZROW) = make_float4(acc1[0], acc1[1], acc1[2], acc1[3]);
+                    *reinterpret_cast<float4*>(zp) = make_float4(acc[0][0], acc[0][1], acc[0][2], acc[0][3]);
+                    *reinterpret_cast<float4*>(zp + 16 * ZROW) = make_float4(acc[1][0], acc[1][1], acc[1][2], acc[1][3]);
                 }
-                // state update: s' = Lambda^32 s + P u
-                s[0] *= lam32[0];
-                s[1] *= lam32[1];
-                s[2] *= lam32[2];
-                s[3] *= lam32[3];
-                s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pop, uw, s, 0, 0, 0);
-                s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pop_lo, uw, s, 0, 0, 0);
+                advance(s, lam32, pop, pop_lo, uw);
             }
             if constexpr (!kStateOnly) {
                 const int prev = (sgi + kPrefetch - 1) % kPrefetch;
@@ -338,6 +384,267 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 2) void li_mfma_kernel(LiAr
         float* wp = a.ws + (b * (a.tiles_per_seq - 1) + tile) * ws_tile + ws_wave;
         *reinterpret_cast<float4*>(wp) = make_float4(s[0], s[1], s[2], s[3]);
     }
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// One pass, for tiles of up to kOneTile steps: a workgroup forms u of its whole tile once and keeps it (LDS and registers,
+// 4 VGPRs per chunk), walks the tile's state from zero and leaves it in the workspace, waits for the states of the tiles
+// before it and only then reads q and computes y, from the u it kept.  k and v are read once: 8 bytes per output instead of
+// 12.  The states are those of the two passes above, bit for bit.
+//
+// What bounds it: the 4-tensor stream through 512-byte strips (44.4 us at 8192 x 4096) in two phases, and between them the
+// wait, the operands of the second and the records' launch: 56.7 us where two passes take 75.1.
+//
+// The wait is per wave and per record, without flags or fences: li_mark_kernel has filled the records with kUnset, a NaN that
+// no state ever is (a producer that holds it stores the plain NaN), every word is stored and loaded as an atomic at device
+// scope, and a record counts as there when none of its words is kUnset.  A workgroup waits only for workgroups with a lower
+// index, which are dealt out before it; and the wait is bounded all the same (each XCD starts its share on its own, so one
+// that is busy with another stream's kernel may start it late): after kPolls looks, about 2 ms, a wave walks the missing tile
+// itself, to the same bits.
+constexpr int kOneTileChunks = 16;
+constexpr uint32_t kUnset = 0xffffdeadu;
+constexpr int kPolls = 1024;
+
+__global__ __launch_bounds__(256) void li_mark_kernel(uint4* rec, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) rec[i] = make_uint4(kUnset, kUnset, kUnset, kUnset);
+}
+
+__device__ __forceinline__ uint64_t device_load(const float* p) {
+    return __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void publish(float* p, const f32x4_t& s) {
+    uint32_t x[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        x[r] = __float_as_uint(s[r]);
+        if (x[r] == kUnset) x[r] = 0x7fc00000u;
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+        __hip_atomic_store(reinterpret_cast<uint64_t*>(p) + r, x[2 * r] | (uint64_t)x[2 * r + 1] << 32, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// KL: chunks of u kept in LDS (the first ones), the others in registers.  PF, QF: chunks of k, v and of q in flight.
+template <int NW, int KL, int PF, int QF>
+__global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 2) void li_one_pass_kernel(LiArgs a) {
+    constexpr int PPR = 2 * NW;
+    constexpr int ZROW = 16 * NW * 4 + 16;
+    constexpr int KR = kOneTileChunks - KL;
+    using std::integral_constant;
+    __shared__ uint4 keep[KL > 0 ? KL : 1][kChunk * PPR];
+    __shared__ __attribute__((aligned(16))) char zst[2][kChunk * ZROW];  // z, fp32 rows; u of the other chunks before that
+    __shared__ float rs[NW][kMaxOrder], ls[NW][kMaxOrder], hs[NW][kChunk];
+    static_assert(kChunk * ZROW >= kChunk * PPR * 16, "a chunk of u fits a chunk of z");
+
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
+    const int li = lane % 16, lq = lane / 16;
+
+    const uint32_t lb = blockIdx.x;
+    const int cb = lb % (uint32_t)a.ncb;
+    const uint32_t tl = lb / (uint32_t)a.ncb;
+    const int64_t b = tl / (uint32_t)a.tiles_per_seq;
+    const int tile = (int)(tl % (uint32_t)a.tiles_per_seq);
+    const int64_t t_start = (int64_t)tile * a.rows;
+    const int nrows = (int)((t_start + a.rows < a.L ? t_start + a.rows : a.L) - t_start);
+    const int nchunks = (nrows + kChunk - 1) / kChunk;
+
+    const int64_t D = a.D;
+    const int64_t cblock0 = (int64_t)cb * 16 * NW;
+    const int64_t c0 = cblock0 + 16 * w;
+    const int64_t tile0 = (b * a.L + t_start) * D + cblock0;
+
+    // A lane moves 8 channels of one row of a chunk; rows past the tile re-read its last row, chunks past the tile one
+    // 16-byte location (their values are not used)
+    const int lr = tid / PPR, lp = tid % PPR;
+    const uint32_t row_bytes = (uint32_t)D * 2;
+    auto offset = [&](int ci) {
+        int row = ci * kChunk + lr;
+        row = row < nrows ? row : nrows - 1;
+        return ci < nchunks ? (uint32_t)row * row_bytes + 16u * lp : 0u;
+    };
+    auto load = [&](const uint16_t* p, uint32_t off) { return load_words_nt<4>(reinterpret_cast<const char*>(p + tile0) + off); };
+    Words<4> kpre[PF], vpre[PF], qpre[QF];
+#pragma unroll
+    for (int i = 0; i < PF; ++i) {
+        const uint32_t off = offset(i);
+        kpre[i] = load(a.k, off);
+        vpre[i] = load(a.v, off);
+    }
+
+    // ---- residues and poles of the wave's group
+    {
+        const int64_t g = c0 / a.group;
+        if (lane < kMaxOrder) {
+            rs[w][lane] = lane < a.order ? a.R[g * a.order + lane] : 0.0f;
+            ls[w][lane] = lane < a.order ? a.lam[g * a.order + lane] : 0.0f;
+        }
+    }
+    __syncthreads();
+    bf16x8_t pop, pop_lo;
+    p_operands(pop, pop_lo, ls[w], li, lq);
+    float lam32[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) lam32[r] = powi(ls[w][4 * lq + r], kChunk);
+
+    const int st_idx = lr * PPR + (lp ^ (((lr >> 3) & 3) << 1));
+    const int rd_piece = (2 * w + (li >> 3)) ^ (lq << 1);
+
+    // ---- phase 1: u of the tile, and its state from zero
+    bf16x8_t ukeep[KR];
+    f32x4_t s = {0.0f, 0.0f, 0.0f, 0.0f};
+    auto staged = [&](int ci) { return ci < KL ? keep[ci] : reinterpret_cast<uint4*>(zst[ci & 1]); };
+    auto phase1 = [&](auto self, auto chunk) {
+        constexpr int ci = decltype(chunk)::value;
+        if constexpr (ci < kOneTileChunks) {
+            if (ci >= nchunks) return;
+            staged(ci)[st_idx] = products(kpre[ci % PF], vpre[ci % PF]);
+            const uint32_t off = offset(ci + PF);
+            kpre[ci % PF] = load(a.k, off);
+            vpre[ci % PF] = load(a.v, off);
+            __syncthreads();
+            const bf16x8_t uw = transposed<PPR>(staged(ci), rd_piece, li, lq);
+            if constexpr (ci >= KL) ukeep[ci - KL] = uw;
+            advance(s, lam32, pop, pop_lo, uw);
+            self(self, integral_constant<int, ci + 1>{});
+        }
+    };
+    phase1(phase1, integral_constant<int, 0>{});
+
+    const int64_t ws_wave = (c0 / 16) * 256;  // this wave's 1 KiB inside the records of a (b, tile); a lane's 4 floats
+    const int64_t ws_tile = (D / 16) * 256;   // hold s[n = 4lq + r][channel li], r = 0..3
+    float* const rec = a.ws + b * (a.tiles_per_seq - 1) * ws_tile + ws_wave;
+    if (tile < a.tiles_per_seq - 1) publish(rec + tile * ws_tile + 4 * lane, s);
+
+#pragma unroll
+    for (int i = 0; i < QF; ++i) qpre[i] = load(a.q, offset(i));
+    if (lane < kChunk) {
+        float hj = 0.0f;
+        for (int n = 0; n < kMaxOrder; ++n) hj += rs[w][n] * powi(ls[w][n], lane);
+        hs[w][lane] = hj;
+    }
+    __syncthreads();  // hs; and the last chunk of u has been read from where z goes
+    // ---- start state: the Horner sum over the earlier tiles' end states (li_mfma_kernel's)
+    s = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    if (a.s_in) {
+        const float4 c4 = *reinterpret_cast<const float4*>(a.s_in + b * ws_tile + ws_wave + 4 * lane);
+        s = f32x4_t{c4.x, c4.y, c4.z, c4.w};
+    }
+    if (tile > 0) {
+        float lam_rows[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) lam_rows[r] = powi(ls[w][4 * lq + r], a.rows);
+        int looks = a.polls;
+        // one word of every record first, a lane each: most of the waiting costs one load per look
+        for (int base = 0; base < tile; base += 64) {
+            const int mine = base + lane < tile ? base + lane : tile - 1;
+            const uint32_t* p = reinterpret_cast<const uint32_t*>(rec + mine * ws_tile);
+            while (looks > 0 && __any(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kUnset)) {
+                --looks;
+                __builtin_amdgcn_s_sleep(4);
+            }
+        }
+        auto horner = [&](const f32x4_t& x) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s[r] = lam_rows[r] * s[r] + x[r];
+        };
+        constexpr int NB = 4;  // records in flight (with 16: 4096 x 4096 33.8 -> 36.7 us)
+        for (int tau = 0; tau < tile;) {
+            uint64_t x[NB][2];
+            bool there = a.polls > 0;
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const float* p = rec + (tau + i < tile ? tau + i : tile - 1) * ws_tile + 4 * lane;
+                x[i][0] = device_load(p);
+                x[i][1] = device_load(p + 2);
+            }
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int r = 0; r < 2; ++r) there = there && (uint32_t)x[i][r] != kUnset && (uint32_t)(x[i][r] >> 32) != kUnset;
+            if (__all(there)) {
+#pragma unroll
+                for (int i = 0; i < NB; ++i)
+                    if (tau + i < tile)
+                        horner(f32x4_t{__uint_as_float((uint32_t)x[i][0]), __uint_as_float((uint32_t)(x[i][0] >> 32)),
+                                       __uint_as_float((uint32_t)x[i][1]), __uint_as_float((uint32_t)(x[i][1] >> 32))});
+                tau += NB;
+            } else if (looks > 0) {
+                --looks;
+                __builtin_amdgcn_s_sleep(4);
+            } else {  // walk tile `tau` (all its rows exist: it is not the sequence's last)
+                f32x4_t e = {0.0f, 0.0f, 0.0f, 0.0f};
+                const uint32_t at = 8u * lq * row_bytes + 2u * li;
+                for (int t0 = 0; t0 < a.rows; t0 += kChunk) {
+                    const int64_t chunk0 = (b * a.L + (int64_t)tau * a.rows + t0) * D + c0;
+                    auto u_at = [&](int row) {
+                        const char *pk = reinterpret_cast<const char*>(a.k + chunk0 + row * D),
+                                   *pv = reinterpret_cast<const char*>(a.v + chunk0 + row * D);
+                        return bf16_lo(*reinterpret_cast<const uint16_t*>(pk + at)) *
+                               bf16_lo(*reinterpret_cast<const uint16_t*>(pv + at));
+                    };
+                    Words<4> u;
+#pragma unroll
+                    for (int e2 = 0; e2 < 4; ++e2) {
+                        u.w[e2] = pack_bf16x2(u_at(2 * e2), u_at(2 * e2 + 1));
+                        __builtin_amdgcn_sched_barrier(0);  // (few registers are free here)
+                    }
+                    advance(e, lam32, pop, pop_lo, __builtin_bit_cast(bf16x8_t, u));
+                }
+                horner(e);
+                ++tau;
+            }
+        }
+    }
+
+    // ---- phase 2: y of the tile
+    bf16x8_t tz[2];
+    t_operands(tz, hs[w], li, lq);
+    bf16x8_t qop[2];  // remainder of Q, then its head
+    {
+        s16x4_t hi[2], lo[2];
+        q_operands(hi, lo, rs[w], ls[w], li, lq);
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+            qop[x] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo[x], hi[x], 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+    const int zwr_off = li * ZROW + (16 * w + 4 * lq) * 4;
+    const int zrd_off = lr * ZROW + 8 * lp * 4;
+    auto phase2 = [&](auto self, auto chunk) {
+        constexpr int ci = decltype(chunk)::value;
+        if constexpr (ci < kOneTileChunks) {
+            if (ci >= nchunks) return;
+            bf16x8_t uw;
+            if constexpr (ci < KL)
+                uw = transposed<PPR>(keep[ci], rd_piece, li, lq);
+            else
+                uw = ukeep[ci - KL];
+            f32x4_t acc[2];
+            chunk_outputs_wide(acc, s, uw, tz, qop);
+            char* zw = zst[ci & 1] + zwr_off;
+            *reinterpret_cast<float4*>(zw) = make_float4(acc[0][0], acc[0][1], acc[0][2], acc[0][3]);
+            *reinterpret_cast<float4*>(zw + 16 * ZROW) = make_float4(acc[1][0], acc[1][1], acc[1][2], acc[1][3]);
+            advance(s, lam32, pop, pop_lo, uw);
+            __syncthreads();
+            if (ci * kChunk + lr < nrows) {
+                const char* zp = zst[ci & 1] + zrd_off;
+                const float4 za = *reinterpret_cast<const float4*>(zp);
+                const float4 zb = *reinterpret_cast<const float4*>(zp + 16);
+                float qf[8];
+                Pack<BF16, 8>::unpack(qpre[ci % QF], qf);
+                float y8[8] = {za.x * qf[0], za.y * qf[1], za.z * qf[2], za.w * qf[3],
+                               zb.x * qf[4], zb.y * qf[5], zb.z * qf[6], zb.w * qf[7]};
+                store_words_nt<4>(reinterpret_cast<char*>(a.y + tile0) + offset(ci), Pack<BF16, 8>::pack(y8));
+            }
+            qpre[ci % QF] = load(a.q, offset(ci + QF));
+            self(self, integral_constant<int, ci + 1>{});
+        }
+    };
+    phase2(phase2, integral_constant<int, 0>{});
+    if (a.s_out && tile == a.tiles_per_seq - 1)  // (the launcher admits this only for L % 32 == 0: no padded rows)
+        *reinterpret_cast<float4*>(a.s_out + b * ws_tile + ws_wave + 4 * lane) = make_float4(s[0], s[1], s[2], s[3]);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -465,11 +772,29 @@ int64_t li_rows(const LiShape& s, int nw) {
     return rows > cap ? cap : rows;
 }
 
-int li_waves(const LiShape& s) {
+// One pass where a workgroup can keep its tile's u and the tiles are long against their number (a wave adds up the states
+// of all earlier tiles while nothing else goes on), the more so the fewer channels a workgroup moves per step.  Us, two
+// passes / one: 16 waves 8192 x 4096 (16 tiles of 512 steps) 75.1 / 56.7, 20001 x 1536 (42 of 480) 83.1 / 64.0, 65536 x 512
+// (128 of 512) 97 / 84, 131072 x 256 (256 of 512) 98 / 117; 8 waves 4096 x 4096 (8 of 512) 43.8 / 34, 32768 x 512 (64 of
+// 512) 54 / 44, 65536 x 256 (128 of 512) 51.8 / 53.7, 4096 x 1024 (32 of 128) 21.4 / 23.0, 16384 x 256 (128 of 128)
+// 31 / 43; 4 waves 512 x 256 (4 of 128) 15.4 / 14.4, 3 x 1333 x 1024 (5 of 288) 21.5 / 19.1.
+bool li_one_pass(const LiShape& s, int nw) {
+    const int64_t rows = li_rows(s, nw), tiles = (s.L + rows - 1) / rows;
+    return tiles > 1 && rows <= kOneTileChunks * kChunk && rows * nw >= 64 * tiles && s.D <= (1 << 21) && tuning().li_wait != 2;
+}
+
+// `state_only`: no outputs are wanted, one pass over k and v in any case
+int li_waves(const LiShape& s, bool state_only = false) {
     const int nw = tuning().mr_waves > 0 ? tuning().mr_waves : 16;
+    // One pass with tiles that only fit it with the widest workgroup (narrower ones have half as many, twice as long): us
+    // with the choice below / with 16 waves in one pass, 5500 x 4096 54 / 43, 7000 x 4096 69 / 51, 2 x 12000 x 1024
+    // 62 / 52, 3 x 2500 x 4096 57 / 52.  Up to 256 steps 8 waves keep theirs as well: 4096 x 4096 34 against 37.
+    if (!state_only && tuning().mr_waves == 0 && tuning().mr_rows == 0 && s.D % 256 == 0 && li_rows(s, 16) > 8 * kChunk &&
+        li_one_pass(s, 16))
+        return 16;
     // Left to itself, a problem that gives a 256-channel workgroup fewer than 512 steps takes 128-channel workgroups
-    // (half as many tiles per sequence, twice as long): measured at B = 1, D = 4096: L = 2048 29.8 against 32.5 us,
-    // L = 4096 45.8 against 48.6; from L = 8192 on the wide workgroup wins (76.2 against 79.2 us).
+    // (half as many tiles per sequence, twice as long): measured at B = 1, D = 4096: L = 2048 23.2 against 28.4 us,
+    // L = 4096 34 against 37.
     // Where those would be at their shortest (four chunks) as well, 64-channel workgroups: B = 1, L = 512: D = 256 17.7 ->
     // 15.0 us, D = 4096 20.0 -> 18.4; L = 2048, D = 1024 19.9 -> 18.5, unless their tiles would
     // be much longer (L = 1000, D = 4096: 256 steps 22.2 us, 128 steps of 8 waves 21.4).
@@ -519,6 +844,7 @@ hy_status launch_li_state_nw(const LiPtrs& p, const LiShape& s, void* ws, hipStr
     a.D = s.D;
     a.order = s.order;
     a.group = s.group;
+    a.polls = 0;
     a.ncb = (int32_t)(s.D / (16 * NW));
     const int64_t rows = li_rows(s, NW);
     a.rows = (int32_t)rows;
@@ -550,6 +876,7 @@ hy_status launch_li_nw(const LiPtrs& p, const LiShape& s, void* ws, hipStream_t 
     a.D = s.D;
     a.order = s.order;
     a.group = s.group;
+    a.polls = 0;
     a.ncb = (int32_t)(s.D / (16 * NW));
     const int64_t rows = li_rows(s, NW);
     a.rows = (int32_t)rows;
@@ -557,6 +884,14 @@ hy_status launch_li_nw(const LiPtrs& p, const LiShape& s, void* ws, hipStream_t 
     const int64_t nb2 = s.B * a.tiles_per_seq * a.ncb;
     const int64_t nb1 = s.B * (a.tiles_per_seq - 1) * a.ncb;
     if (nb2 > 0x7fffffffLL) return HY_ERR_UNSUPPORTED;
+    if (nb1 > 0 && li_one_pass(s, NW)) {
+        a.polls = tuning().li_wait == 1 ? 0 : kPolls;
+        const int64_t n16 = s.B * (a.tiles_per_seq - 1) * (s.D / 16) * 64;
+        const hy_status rc = launch_kernel(li_mark_kernel, dim3((uint32_t)((n16 + 255) / 256)), dim3(256), st,
+                                           static_cast<uint4*>(ws), n16);
+        if (rc != HY_OK) return rc;
+        return launch_kernel((li_one_pass_kernel<NW, NW == 16 ? 5 : 0, 3, 3>), dim3((uint32_t)nb2), dim3(NW * 64), st, a);
+    }
     if (nb1 > 0) {
         const hy_status rc = launch_kernel((li_mfma_kernel<NW, PF, true>), dim3((uint32_t)nb1), dim3(NW * 64), st, a);
         if (rc != HY_OK) return rc;
@@ -591,14 +926,14 @@ hy_status launch_li_mfma(const LiPtrs& p, const LiShape& s, void* ws, hipStream_
 
 int64_t li_state_workspace_bytes(const LiShape& s) {
     if (!li_mfma_supported(s) || s.B == 0 || s.L == 0 || s.D == 0) return 0;
-    const int64_t rows = li_rows(s, li_waves(s));
+    const int64_t rows = li_rows(s, li_waves(s, true));
     const int64_t tiles = (s.L + rows - 1) / rows;
     return s.B * tiles * (s.D / 16) * 256 * (int64_t)sizeof(float);
 }
 
 hy_status launch_li_state(const LiPtrs& p, const LiShape& s, void* ws, hipStream_t st) {
     if (!li_mfma_supported(s) || s.L % kChunk != 0 || !p.state_out) return HY_ERR_UNSUPPORTED;
-    switch (li_waves(s)) {
+    switch (li_waves(s, true)) {
         case 16: return launch_li_state_nw<16>(p, s, ws, st);
         case 8: return launch_li_state_nw<8>(p, s, ws, st);
         default: return launch_li_state_nw<4>(p, s, ws, st);

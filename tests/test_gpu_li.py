@@ -377,3 +377,53 @@ def test_state_calls_refuse_what_they_cannot_do():
     s = binding.hyena_li_state(k, v, lam, group)
     same = binding.hyena_li_state_fold([], 512, lam, B, D, group, state_in=s)    # nothing to fold: the state itself
     assert torch.equal(same, s)
+
+
+# (B, L, D, order, waves, rows): the one-pass form at the edges of its tiles: every workgroup width; one chunk more than
+# those kept in LDS and fewer; a last tile of one step and of one whole chunk; more tiles than one look or batch of records
+ONE_PASS_CASES = [
+    (1, 1025, 256, 16, 16, 512),
+    (2, 160 * 3, 512, 7, 16, 160),
+    (1, 192 * 2 + 33, 256, 16, 16, 192),
+    (1, 300, 64, 16, 4, 256),
+    (3, 512 * 6 - 1, 64, 3, 4, 512),
+    (1, 416 * 9 + 32, 128, 16, 8, 416),
+    (1, 320 * 70 + 1, 256, 16, 16, 320),
+]
+
+
+@pytest.mark.parametrize("case", ONE_PASS_CASES)
+def test_one_pass_waits_for_states_or_walks_to_the_same_ones(case):
+    """One pass against the definition (a row past the last chunk's included), and bit for bit against the same pass with
+    every wave computing the earlier tiles' states itself; against the two passes up to rounding."""
+    B, L, D, order, waves, rows = case
+    binding.set_option("mr_waves", waves)
+    binding.set_option("mr_rows", rows)
+    say("one pass B=%d L=%d D=%d order=%d waves=%d rows=%d" % case)
+    q, k, v, R, lam = draw_li(71, B, L, D, order, 16, "bf16")
+    args = [dev(x) for x in (q, k, v, R, lam)]
+    y = {}
+    try:
+        for wait in (0, 1, 2):
+            binding.set_option("li_wait", wait)
+            y[wait] = binding.hyena_li_fwd(*args, 16)
+    finally:
+        binding.set_option("li_wait", 0)
+    assert torch.equal(y[0], y[1])
+    ref = oracle.li_recurrent(q, k, v, R, lam, group=16)
+    assert oracle.rel_err(host(y[0]), ref) <= TOL["bf16"]
+    # the same states, their products with Q added in another order: a few outputs in a hundred round to the other
+    # neighbour, one bf16 unit = at most 2^-7 of a value, and so of the largest output
+    assert oracle.rel_err(host(y[0]), host(y[2]).astype(np.float64)) <= 2.0 ** -7
+
+
+def test_one_pass_with_values_that_are_not_finite():
+    """A record of NaNs is a record like any other: outputs after a NaN are NaN, those before it and of other channels of
+    other blocks are what they were."""
+    B, L, D = 1, 2048, 256
+    q, k, v, R, lam = draw_li(72, B, L, D, 16, 16, "bf16")
+    clean = host(binding.hyena_li_fwd(*[dev(x) for x in (q, k, v, R, lam)], 16))
+    k[0, 700, 5] = float("nan")
+    y = host(binding.hyena_li_fwd(*[dev(x) for x in (q, k, v, R, lam)], 16))
+    assert np.isnan(y[0, 704:, 5]).all()
+    assert np.array_equal(y[0, :672], clean[0, :672]) and np.array_equal(y[0, :, 16:], clean[0, :, 16:])
