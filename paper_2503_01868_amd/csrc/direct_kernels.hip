@@ -9,10 +9,10 @@
 //     D[i][j] += w[m - i] * x[x0 + 4 j],   output row 16 k + 4 j + i, staged row x0 + 4 j = output row + tap (m = x0 - 16 k),
 // so one operand of taps per m (lane = channel, i) serves every output block k, and one read of u per lane and x0 serves
 // all output blocks whose taps it meets.  The kSeg + 3 tap operands stay in registers; a wave owns 16 channels x 128 rows
-// (8 output blocks; small problems and short filters 32 rows, 2 blocks), a workgroup 4 waves = 64 channels.  The operand product u = a*b is formed once per workgroup into
+// (8 output blocks; small problems and short filters 32 rows, 2 blocks; whole bf16 pieces 64 rows), a workgroup 4 waves = 64 channels.  The operand product u = a*b is formed once per workgroup into
 // LDS as fp32 rows; 255 rows take 68 KiB, so two workgroups share a compute unit.  A workgroup walks several tiles of
-// its sequence where there are enough of them, keeping the halo in LDS (bf16: with the next tile's rows in flight while
-// it computes; in fp32 they do not fit the registers beside the operands).  Outputs go back through LDS so that gates
+// its sequence where there are enough of them, keeping the halo in LDS (bf16: with the next tile's rows and the tile's gate
+// in flight while it computes; in fp32 they do not fit the registers beside the operands).  Outputs go back through LDS so that gates
 // are read and outputs stored as whole row pieces.  Filters of more than 128 taps go through in segments, the sums staying
 // where they are.  Every output adds its terms in ascending source order for the causal direction and ascending
 // tap order for the transposed one, as a plain loop over the definition does.
@@ -20,7 +20,7 @@
 // finite values: a workgroup that stages anything else takes the sums of that tile term by term on the vector ALUs,
 // without the terms the definition does not have, so a non-finite tap or sample reaches exactly the outputs it reaches
 // in the definition.
-// Measured, 128 taps: B = 3, L = 5003, D = 1000 bf16 79 us, B = 2, L = 2048, D = 1024 fp32 25 us, B = 1, L = 8192,
+// Measured, 128 taps: B = 3, L = 5003, D = 1000 bf16 70 us (79 with 128-row tiles and the gate loaded behind the products), B = 2, L = 2048, D = 1024 fp32 25 us, B = 1, L = 8192,
 // D = 4096 fp32 159 us (a filter of 32 taps there: 86); the same walk with vector FMAs, a lane one channel and 32
 // outputs: 100, 30, 198 us; 8 outputs per lane straight from global memory: 259, 64, 519 us.
 #include <type_traits>
@@ -72,6 +72,9 @@ __global__ __launch_bounds__(kThreads, per_cu(kSeg, NT)) void fir_kernel(FirArgs
     constexpr int kPass = kAhead || kPassAll < kPassFew ? kPassAll : kPassFew;
     constexpr int kBatch = kPass * RPP < TR ? kPass * RPP : TR;  // rows they cover
     static_assert(!kAhead || kPass == kPassAll, "a tile's rows in flight at once");
+    constexpr int kPutFew = VEC == 1 ? 8 : 4;
+    constexpr int kPut = kPassAll < kPutFew ? kPassAll : kPutFew;  // pieces of a gate in flight
+    constexpr bool kGateAhead = kAhead && NT <= 4 && kPut == kPassAll;  // ... loaded before the products
     constexpr int kMove = ((kSeg - 1) * (kChan / 4) + kThreads - 1) / kThreads;  // float4s of halo per lane
     constexpr int kTapStride = kSeg + 8;           // a channel's taps with three zeros on either side
     static_assert(kChan * kTapStride <= kRows * kStride, "the taps pass through the rows' memory");
@@ -191,6 +194,16 @@ __global__ __launch_bounds__(kThreads, per_cu(kSeg, NT)) void fir_kernel(FirArgs
     int clean = 1 << 30;  // tiles since values that are not finite were staged
     int par = 0;
     for (int64_t t0 = t_first; t0 < t_stop; t0 += TR) {
+        typename PV::Raw gahead[kGateAhead ? kPut : 1];
+        auto load_gate = [&](typename PV::Raw* gr, const void* gate, int i0) {  // kPut pieces of the tile's rows
+            const char* gp = static_cast<const char*>(gate) + (b * pr.stride_gate + col) * T::kBytes;
+#pragma unroll
+            for (int i = 0; i < kPut; ++i) {
+                int64_t t = t0 + (i0 + i) * RPP + pr0;
+                t = t < L ? t : L - 1;
+                gr[i] = PV::load_nt(gp + t * row_bytes);
+            }
+        };
         f32x4_t acc[NT];
         if constexpr (!kOne) {
 #pragma unroll
@@ -258,6 +271,8 @@ __global__ __launch_bounds__(kThreads, per_cu(kSeg, NT)) void fir_kernel(FirArgs
             if constexpr (kAhead)
                 if (t0 + TR < t_stop) load_rows(tb + TR + nt - 1);  // the next tile's rows
 
+            if constexpr (kGateAhead)
+                if (pr.gate) load_gate(gahead, pr.gate, 0);
             if constexpr (kOne) {
 #pragma unroll
                 for (int k = 0; k < NT; ++k) acc[k] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
@@ -315,21 +330,16 @@ __global__ __launch_bounds__(kThreads, per_cu(kSeg, NT)) void fir_kernel(FirArgs
             for (int i = 0; i < 4; ++i)
                 us[(16 * k + 4 * l4 + i) * kStride + 16 * w + ch] = acc[k][i];
         __syncthreads();
-        auto put = [&](const void* gate, void* out) {
-            const char* gp = static_cast<const char*>(gate) + (b * pr.stride_gate + col) * T::kBytes;
+        auto put = [&](const void* gate, void* out, auto ahead) {
             char* op = static_cast<char*>(out) + (b * pr.stride_out + col) * T::kBytes;
-            constexpr int kPutFew = VEC == 1 ? 8 : 4;
-            constexpr int kPut = kPassAll < kPutFew ? kPassAll : kPutFew;  // pieces in flight
 #pragma unroll
             for (int i0 = 0; i0 < kPassAll; i0 += kPut) {
                 typename PV::Raw gr[kPut];
-                if (gate) {
+                if constexpr (decltype(ahead)::value) {
 #pragma unroll
-                    for (int i = 0; i < kPut; ++i) {
-                        int64_t t = t0 + (i0 + i) * RPP + pr0;
-                        t = t < L ? t : L - 1;
-                        gr[i] = PV::load_nt(gp + t * row_bytes);
-                    }
+                    for (int i = 0; i < kPut; ++i) gr[i] = gahead[i];
+                } else {
+                    if (gate) load_gate(gr, gate, i0);
                 }
 #pragma unroll
                 for (int i = 0; i < kPut; ++i) {
@@ -347,8 +357,8 @@ __global__ __launch_bounds__(kThreads, per_cu(kSeg, NT)) void fir_kernel(FirArgs
                 }
             }
         };
-        put(pr.gate, pr.out);
-        if (pr.out2) put(pr.gate2, pr.out2);
+        put(pr.gate, pr.out, std::bool_constant<kGateAhead>{});
+        if (pr.out2) put(pr.gate2, pr.out2, std::false_type{});
         if constexpr (!kOne) __syncthreads();  // before the next tile's taps
     }
 }
@@ -381,13 +391,20 @@ hy_status launch_nt(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
                          dim3(kThreads), st, a);
 }
 
+// Rows of 16-byte bf16 pieces: 64-row tiles leave the registers to load both the next tile's rows and this tile's gate before
+// the products, for any problem size.
+template <typename T, int VEC>
+constexpr bool half_tiles() { return T::kBytes == 2 && VEC > 1; }
+
 template <typename T, int VEC, int NT>
 hy_status launch_seg(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
     if constexpr (NT <= 2)  // (3 x 2730 x 1024 fp32, 9 taps, against a segment of 32: 28.5 -> 26.4 us)
         if (a.lh <= 16) return launch_nt<T, VEC, 16, NT, true>(a, nprob, B, st);
     if (a.lh <= 32) return launch_nt<T, VEC, 32, NT, true>(a, nprob, B, st);
-    if (a.lh <= 64) return launch_nt<T, VEC, 64, NT, true>(a, nprob, B, st);
-    if (a.lh <= 128) return launch_nt<T, VEC, 128, NT, true>(a, nprob, B, st);
+    if constexpr (!half_tiles<T, VEC>()) {  // (else launch_vec's)
+        if (a.lh <= 64) return launch_nt<T, VEC, 64, NT, true>(a, nprob, B, st);
+        if (a.lh <= 128) return launch_nt<T, VEC, 128, NT, true>(a, nprob, B, st);
+    }
     // three segments of 64 are 201 products per output block, two of 128 are 262 (3 x 5003 x 1000 fp32, 150 taps: 152
     // against 166 us); beyond 192 taps staging the rows once more costs what the products save (400 taps: 304 / 285)
     if (a.lh <= 192) return launch_nt<T, VEC, 64, NT, false>(a, nprob, B, st);
@@ -396,6 +413,14 @@ hy_status launch_seg(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
 
 template <typename T, int VEC>
 hy_status launch_vec(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
+    // (rows 128 or 32 by the rules below / 64, bf16, 128 taps, us: 3 x 5003 x 1000 84.0 / 68.4, 4 x 4096 x 2056 189 / 153,
+    // 6 x 690 x 1000 42.3 / 29.3, 1 x 700 x 1000 13.5 / 11.1, gradients 3 x 1300 x 1000 103 / 89; 50 taps 3 x 5003 x 1000
+    // 51.3 / 51.1, 40 taps 1 x 4000 x 1000 17.8 / 16.4; but 30 taps 3 x 5003 x 1000 39.7 / 40.6.)  fp32 rows are twice as
+    // many registers: they do not fit.
+    if constexpr (half_tiles<T, VEC>()) {
+        if (a.lh > 64 && a.lh <= 128) return launch_nt<T, VEC, 128, 4, true>(a, nprob, B, st);
+        if (a.lh > 32 && a.lh <= 64) return launch_nt<T, VEC, 64, 4, true>(a, nprob, B, st);
+    }
     // 128-row tiles amortise the 127 halo rows of a 128-tap filter; a problem that leaves compute units without a
     // workgroup that way is cut into 32-row tiles instead, and so is one whose last tile would be mostly padding.  (Eight
     // waves over 128 channels, one workgroup per compute unit, measured the same on long sequences and 13% slower at

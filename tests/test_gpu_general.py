@@ -204,3 +204,24 @@ def test_taps_beyond_the_sequence_cost_nothing():
         assert torch.equal(y, z)
     dx = [binding.hyena_featurize_bwd(x[0], x[1], f, 3)[0] for f in (short, h)]
     assert torch.equal(*dx)
+
+
+@pytest.mark.parametrize("lh", [33, 64, 65, 128])
+@pytest.mark.parametrize("B,L,D", [(1, 63, 72), (2, 64, 8), (1, 65, 136), (3, 129, 200), (2, 4097, 1000), (5, 6464, 264)],
+                         ids=lambda x: str(x))
+def test_tiles_of_64_rows(B, L, D, lh):
+    """bf16 rows of whole pieces go in 64-row tiles from 33 to 128 taps: a step less than a tile, one more, walks that end
+    inside a tile and with one, channel blocks cut off by the width."""
+    say("64-row tiles %d x %d x %d lh=%d" % (B, L, D, lh))
+    q, k, v, h = draw(9600 + L + lh, B, L, D, lh, 8, "bf16", kind="mr")
+    dy = synth.normal_tensor(np.random.Generator(np.random.PCG64(9601)), (B, L, D), "bf16")
+    y = host(binding.hyena_mr_fwd(dev(q), dev(k), dev(v), dev(h), 8))
+    grads = [host(x) for x in binding.hyena_mr_bwd(dev(dy), dev(q), dev(k), dev(v), dev(h), 8)]
+    c = slice(0, D) if D <= 264 and L < 1000 else slice(D - 24, D)  # (the last channel block where the oracle is slow)
+    g = slice(c.start // 8, c.stop // 8)
+    a = [x[..., c].contiguous() for x in (dy, q, k, v)]
+    hc = np.ascontiguousarray(h[g])
+    assert oracle.rel_err(y[..., c], oracle.gated_conv(*a[1:], hc, group=8)) <= TOL["bf16"]
+    for name, got, want in zip(("dq", "dk", "dv", "dh"), grads, oracle.gated_conv_bwd(*a, hc, group=8)):
+        got = got[g] if name == "dh" else got[..., c]
+        assert oracle.rel_err(got, want) <= (TOL["f32"] if name == "dh" else TOL["bf16"]), name
