@@ -140,10 +140,11 @@ __global__ __launch_bounds__(2 * kNW * 64, 2) void cp4_bwd_kernel(Cp4BwdArgs a) 
     // ---- the filters go through LDS (whole rows, all loads in flight), zeros around the taps instead of tests
     {
         constexpr int N = (kTapStride + 63) / 64, CW = kC / (2 * kNW);
+        const uint32_t row = ((uint32_t)cblock0 + CW * wave + lane % CW) / (uint32_t)a.group;  // one division for all
         float f[CW][N];
 #pragma unroll
         for (int c = 0; c < CW; ++c) {
-            const float* hp = a.h + (int64_t)(((uint32_t)cblock0 + CW * wave + c) / (uint32_t)a.group) * a.lh;
+            const float* hp = a.h + (int64_t)(uint32_t)__builtin_amdgcn_readlane(row, c) * a.lh;
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 const int tap = 64 * i + lane - 3;

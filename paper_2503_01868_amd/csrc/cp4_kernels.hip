@@ -54,6 +54,28 @@ constexpr int kR = 192;   // ring length in steps = 3 kT >= kT + history
 constexpr int kLS = 416;  // bytes per ring line (>= 2 kR, multiple of 32)
 constexpr int kQS = 128;  // bytes per q/y line (2 kT)
 
+// Toeplitz operands of a lane, row i = l4: element k of operand m = h[4m + i - k], from the channel's filter in memory
+template <int NBK>
+__device__ __forceinline__ void gather_operands(s16x4_t (&ares)[NBK], const float* hp, int32_t lh, int l4) {
+    auto tapv = [&](int idx) { return (idx >= 0 && idx < lh) ? hp[idx] : 0.0f; };
+#pragma unroll
+    for (int m = 0; m < NBK; ++m) {
+        float t4[4];  // t4[k] = h[4m + i - k]
+        if (m >= 1 && 4 * m + 3 < lh) {
+            // wholly inside [0, lh): h[4m + i - 3 .. 4m + i], four adjacent floats (4-byte aligned)
+            const float* p = hp + 4 * m + l4 - 3;
+            t4[3] = p[0]; t4[2] = p[1]; t4[1] = p[2]; t4[0] = p[3];
+        } else {
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) t4[kk] = tapv(4 * m + l4 - kk);
+        }
+        Words<2> wd;
+        wd.w[0] = pack_bf16x2(t4[0], t4[1]);
+        wd.w[1] = pack_bf16x2(t4[2], t4[3]);
+        ares[m] = __builtin_bit_cast(s16x4_t, wd);
+    }
+}
+
 // PF = iterations of k, v, q in flight per lane (register stages).
 template <int NBK, int NW, int PF>
 __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 2) void cp4_kernel(Cp4Args a) {
@@ -128,26 +150,7 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 2) void cp4_kernel(Cp4Args 
     // A_m[i][k] = h[4m + i - k]
     const int blk = lane >> 2, l4 = lane & 3;
     s16x4_t ares[NBK];
-    {
-        const float* hp = a.h + ((cblock0 + 16 * w + blk) / a.group) * (int64_t)a.lh;
-        auto tapv = [&](int idx) { return (idx >= 0 && idx < a.lh) ? hp[idx] : 0.0f; };
-#pragma unroll
-        for (int m = 0; m < NBK; ++m) {
-            float t4[4];  // t4[k] = h[4m + i - k]
-            if (m >= 1 && 4 * m + 3 < a.lh) {
-                // wholly inside [0, lh): h[4m + i - 3 .. 4m + i], four adjacent floats (4-byte aligned)
-                const float* p = hp + 4 * m + l4 - 3;
-                t4[3] = p[0]; t4[2] = p[1]; t4[1] = p[2]; t4[0] = p[3];
-            } else {
-#pragma unroll
-                for (int kk = 0; kk < 4; ++kk) t4[kk] = tapv(4 * m + l4 - kk);
-            }
-            Words<2> wd;
-            wd.w[0] = pack_bf16x2(t4[0], t4[1]);
-            wd.w[1] = pack_bf16x2(t4[2], t4[3]);
-            ares[m] = __builtin_bit_cast(s16x4_t, wd);
-        }
-    }
+    gather_operands(ares, a.h + ((cblock0 + 16 * w + blk) / a.group) * (int64_t)a.lh, a.lh, l4);
 
     // ---- history: the kH steps before the tile; steps ts32 - 128 + x sit at ring position (x + 128) % 192
     {
@@ -284,8 +287,7 @@ constexpr int kQS4 = 288;  // bytes per q/y line (2 slots x 2 kT + 32)
 
 // A wave's filter operands, A_m[i][k] = h_c[4m + i - k] for the channels c0 .. c0 + 15 (block = lane / 4, i = lane % 4).
 // The filters go through LDS as bf16 lines with zeros around the taps: whole rows from memory with all loads in flight,
-// where a gather takes 4 NBK loads per lane that meet 16 rows each (1 x 8192 x 4096, 128 taps: 61.8 us -> 59.2; shapes of up
-// to 2^25 elements, 100 taps: 1% to 17% less, 9% on average; with the 5 to 17 operands of cp4_kernel the gather is faster,
+// where a gather takes 4 NBK loads per lane that meet 16 rows each (1 x 8192 x 4096, 128 taps: 58.2 us -> 56.4; with the 5 to 17 operands of cp4_kernel the gather is faster,
 // by 5%).  kTapLine entries per line: the 16 lines' entries of one index then lie in 16 different pairs of banks.
 template <int NBK>
 constexpr int kTapLine = 4 * NBK + 8;
@@ -293,10 +295,11 @@ template <int NBK>
 __device__ __forceinline__ void filter_operands(s16x4_t (&ares)[NBK], __bf16* lines, const float* h, uint32_t c0, uint32_t group,
                                                 int32_t lh, int lane) {
     constexpr int W = kTapLine<NBK>, N = (W + kWave - 1) / kWave;
+    const uint32_t row = (c0 + (lane & 15)) / group;  // one division for the 16 filters
     float f[16][N];
 #pragma unroll
     for (int c = 0; c < 16; ++c) {
-        const float* hp = h + (int64_t)((c0 + c) / group) * lh;
+        const float* hp = h + (int64_t)(uint32_t)__builtin_amdgcn_readlane(row, c) * lh;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const int tap = kWave * i + lane - 3;
@@ -359,7 +362,12 @@ __global__ __launch_bounds__((kWM + kWV) * 64, 3) void cp4ws_kernel(Cp4Args a) {
         // ================= multiplier waves
         const int blk = lane >> 2, l4 = lane & 3;
         s16x4_t ares[NBK];
-        filter_operands(ares, taps + 16 * w * kTapLine<NBK>, a.h, (uint32_t)cblock0 + 16 * w, (uint32_t)a.group, a.lh, lane);
+        // (tiles of one iteration wait for the operands: with 25 of them the gather is there first, 2 x 443 x 768, 96 taps
+        // 6.8 us against 7.2)
+        if (NBK <= 25 && a.rows == kT)
+            gather_operands(ares, a.h + (int64_t)(((uint32_t)cblock0 + 16 * w + blk) / (uint32_t)a.group) * a.lh, a.lh, l4);
+        else
+            filter_operands(ares, taps + 16 * w * kTapLine<NBK>, a.h, (uint32_t)cblock0 + 16 * w, (uint32_t)a.group, a.lh, lane);
         const int cw = 16 * w + blk;
         const char* const rl = ring + line_off(cw, kLS4);
         const char* const ring_lane = rl + 8 * l4;                    // position 4 j
