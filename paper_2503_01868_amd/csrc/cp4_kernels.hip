@@ -287,8 +287,9 @@ constexpr int kQS4 = 288;  // bytes per q/y line (2 slots x 2 kT + 32)
 
 // A wave's filter operands, A_m[i][k] = h_c[4m + i - k] for the channels c0 .. c0 + 15 (block = lane / 4, i = lane % 4).
 // The filters go through LDS as bf16 lines with zeros around the taps: whole rows from memory with all loads in flight,
-// where a gather takes 4 NBK loads per lane that meet 16 rows each (1 x 8192 x 4096, 128 taps: 58.2 us -> 56.4; with the 5 to 17 operands of cp4_kernel the gather is faster,
-// by 5%).  kTapLine entries per line: the 16 lines' entries of one index then lie in 16 different pairs of banks.
+// where a gather takes 4 NBK loads per lane that meet 16 rows each (1 x 8192 x 4096, 128 taps: 58.2 us -> 56.4, 96 taps 57.3
+// -> 55.0; with the 5 to 17 operands of cp4_kernel the gather is faster, by 5%).  kTapLine entries per line: the 16 lines'
+// entries of one index then lie in 16 different pairs of banks.
 template <int NBK>
 constexpr int kTapLine = 4 * NBK + 8;
 template <int NBK>

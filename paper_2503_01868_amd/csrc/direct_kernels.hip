@@ -9,7 +9,8 @@
 //     D[i][j] += w[m - i] * x[x0 + 4 j],   output row 16 k + 4 j + i, staged row x0 + 4 j = output row + tap (m = x0 - 16 k),
 // so one operand of taps per m (lane = channel, i) serves every output block k, and one read of u per lane and x0 serves
 // all output blocks whose taps it meets.  The kSeg + 3 tap operands stay in registers; a wave owns 16 channels x 128 rows
-// (8 output blocks; small problems and short filters 32 rows, 2 blocks; whole bf16 pieces 64 rows), a workgroup 4 waves = 64 channels.  The operand product u = a*b is formed once per workgroup into
+// (8 output blocks; small problems and short filters 32 rows, 2 blocks; whole bf16 pieces 64 rows), a workgroup 4 waves = 64
+// channels.  The operand product u = a*b is formed once per workgroup into
 // LDS as fp32 rows; 255 rows take 68 KiB, so two workgroups share a compute unit.  A workgroup walks several tiles of
 // its sequence where there are enough of them, keeping the halo in LDS (bf16: with the next tile's rows and the tile's gate
 // in flight while it computes; in fp32 they do not fit the registers beside the operands).  Outputs go back through LDS so that gates
@@ -20,9 +21,10 @@
 // finite values: a workgroup that stages anything else takes the sums of that tile term by term on the vector ALUs,
 // without the terms the definition does not have, so a non-finite tap or sample reaches exactly the outputs it reaches
 // in the definition.
-// Measured, 128 taps: B = 3, L = 5003, D = 1000 bf16 70 us (79 with 128-row tiles and the gate loaded behind the products), B = 2, L = 2048, D = 1024 fp32 25 us, B = 1, L = 8192,
-// D = 4096 fp32 159 us (a filter of 32 taps there: 86); the same walk with vector FMAs, a lane one channel and 32
-// outputs: 100, 30, 198 us; 8 outputs per lane straight from global memory: 259, 64, 519 us.
+// Measured, 128 taps: B = 3, L = 5003, D = 1000 bf16 70 us (79 with 128-row tiles and the gate loaded behind the products),
+// B = 2, L = 2048, D = 1024 fp32 25 us, B = 1, L = 8192, D = 4096 fp32 159 us (a filter of 32 taps there: 86); the same walk
+// with vector FMAs, a lane one channel and 32 outputs: 100, 30, 198 us; 8 outputs per lane straight from global memory: 259,
+// 64, 519 us.
 #include <type_traits>
 #include <utility>
 
