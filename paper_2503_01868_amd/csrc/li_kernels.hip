@@ -393,7 +393,7 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 2) void li_mfma_kernel(LiAr
 // 12.  The states are those of the two passes above, bit for bit.
 //
 // What bounds it: the 4-tensor stream through 512-byte strips (44.4 us at 8192 x 4096) in two phases, and between them the
-// wait, the operands of the second and the records' launch: 56.7 us where two passes take 75.1.
+// wait, the operands of the second and the records' launch: 57 us where two passes take 76.
 //
 // The wait is per wave and per record, without flags or fences: li_mark_kernel has filled the records with kUnset, a NaN that
 // no state ever is (a producer that holds it stores the plain NaN), every word is stored and loaded as an atomic at device
@@ -405,9 +405,12 @@ constexpr int kOneTileChunks = 16;
 constexpr uint32_t kUnset = 0xffffdeadu;
 constexpr int kPolls = 1024;
 
+constexpr int kMarks = 4;  // 16-byte pieces per lane
 __global__ __launch_bounds__(256) void li_mark_kernel(uint4* rec, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) rec[i] = make_uint4(kUnset, kUnset, kUnset, kUnset);
+    const int64_t i0 = (int64_t)blockIdx.x * 256 * kMarks + threadIdx.x;
+#pragma unroll
+    for (int x = 0; x < kMarks; ++x)
+        if (i0 + 256 * x < n) store_words_nt<4>(rec + i0 + 256 * x, Words<4>{{kUnset, kUnset, kUnset, kUnset}});
 }
 
 __device__ __forceinline__ uint64_t device_load(const float* p) {
@@ -887,8 +890,9 @@ hy_status launch_li_nw(const LiPtrs& p, const LiShape& s, void* ws, hipStream_t 
     if (nb1 > 0 && li_one_pass(s, NW)) {
         a.polls = tuning().li_wait == 1 ? 0 : kPolls;
         const int64_t n16 = s.B * (a.tiles_per_seq - 1) * (s.D / 16) * 64;
-        const hy_status rc = launch_kernel(li_mark_kernel, dim3((uint32_t)((n16 + 255) / 256)), dim3(256), st,
-                                           static_cast<uint4*>(ws), n16);
+        const int64_t marks = (n16 + 256 * kMarks - 1) / (256 * kMarks);
+        const hy_status rc =
+            launch_kernel(li_mark_kernel, dim3((uint32_t)marks), dim3(256), st, static_cast<uint4*>(ws), n16);
         if (rc != HY_OK) return rc;
         return launch_kernel((li_one_pass_kernel<NW, NW == 16 ? 5 : 0, 3, 3>), dim3((uint32_t)nb2), dim3(NW * 64), st, a);
     }
