@@ -54,24 +54,30 @@ constexpr int kR = 192;   // ring length in steps = 3 kT >= kT + history
 constexpr int kLS = 416;  // bytes per ring line (>= 2 kR, multiple of 32)
 constexpr int kQS = 128;  // bytes per q/y line (2 kT)
 
-// Toeplitz operands of a lane, row i = l4: element k of operand m = h[4m + i - k], from the channel's filter in memory
+// Toeplitz operands of a lane, row i = l4: element k of operand m = h[4m + i - k], from the channel's filter in memory.  All
+// loads go out before the first value is rounded: with the rounding in the loop of the loads the compiler may put it into
+// their branches, behind a wait for each (65 taps, 1 x 3667 x 1024: 12.3 -> 14.8 us; 4 x 217 x 4096 11.1 -> 13.4).
 template <int NBK>
 __device__ __forceinline__ void gather_operands(s16x4_t (&ares)[NBK], const float* hp, int32_t lh, int l4) {
     auto tapv = [&](int idx) { return (idx >= 0 && idx < lh) ? hp[idx] : 0.0f; };
+    float t4[NBK][4];  // t4[m][k] = h[4m + i - k]
 #pragma unroll
     for (int m = 0; m < NBK; ++m) {
-        float t4[4];  // t4[k] = h[4m + i - k]
         if (m >= 1 && 4 * m + 3 < lh) {
             // wholly inside [0, lh): h[4m + i - 3 .. 4m + i], four adjacent floats (4-byte aligned)
             const float* p = hp + 4 * m + l4 - 3;
-            t4[3] = p[0]; t4[2] = p[1]; t4[1] = p[2]; t4[0] = p[3];
+            t4[m][3] = p[0]; t4[m][2] = p[1]; t4[m][1] = p[2]; t4[m][0] = p[3];
         } else {
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) t4[kk] = tapv(4 * m + l4 - kk);
+            for (int kk = 0; kk < 4; ++kk) t4[m][kk] = tapv(4 * m + l4 - kk);
         }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int m = 0; m < NBK; ++m) {
         Words<2> wd;
-        wd.w[0] = pack_bf16x2(t4[0], t4[1]);
-        wd.w[1] = pack_bf16x2(t4[2], t4[3]);
+        wd.w[0] = pack_bf16x2(t4[m][0], t4[m][1]);
+        wd.w[1] = pack_bf16x2(t4[m][2], t4[m][3]);
         ares[m] = __builtin_bit_cast(s16x4_t, wd);
     }
 }
@@ -330,7 +336,8 @@ __device__ __forceinline__ void filter_operands(s16x4_t (&ares)[NBK], __bf16* li
     }
 }
 
-template <int NBK, int PF>
+// kGather: operands gathered from memory instead of passing through LDS
+template <int NBK, int PF, bool kGather>
 __global__ __launch_bounds__((kWM + kWV) * 64, 3) void cp4ws_kernel(Cp4Args a) {
     constexpr int kH = 4 * (NBK - 1);
     static_assert(kH <= 2 * kT, "history must fit two ring slots");
@@ -339,7 +346,7 @@ __global__ __launch_bounds__((kWM + kWV) * 64, 3) void cp4ws_kernel(Cp4Args a) {
     constexpr int PPR = C / 8;   // 16-byte pieces per row
     __shared__ __attribute__((aligned(16))) char ring[C * kLS4 + (C / 8) * 8];
     __shared__ __attribute__((aligned(16))) char qy[C * kQS4 + (C / 8) * 8];
-    __shared__ __attribute__((aligned(4))) __bf16 taps[C * kTapLine<NBK>];
+    __shared__ __attribute__((aligned(4))) __bf16 taps[kGather ? 2 : C * kTapLine<NBK>];
 
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -363,9 +370,10 @@ __global__ __launch_bounds__((kWM + kWV) * 64, 3) void cp4ws_kernel(Cp4Args a) {
         // ================= multiplier waves
         const int blk = lane >> 2, l4 = lane & 3;
         s16x4_t ares[NBK];
-        // (tiles of one iteration wait for the operands: with 25 of them the gather is there first, 2 x 443 x 768, 96 taps
-        // 6.8 us against 7.2)
-        if (NBK <= 25 && a.rows == kT)
+        // the mover waves' loads go out first: what they bring has the longer way (through LDS and a barrier) to the first
+        // product (8 x 60 x 1024, 128 taps, gathered operands: kernel 8.3 -> 7.2 us)
+        __builtin_amdgcn_s_barrier();
+        if constexpr (kGather)
             gather_operands(ares, a.h + (int64_t)(((uint32_t)cblock0 + 16 * w + blk) / (uint32_t)a.group) * a.lh, a.lh, l4);
         else
             filter_operands(ares, taps + 16 * w * kTapLine<NBK>, a.h, (uint32_t)cblock0 + 16 * w, (uint32_t)a.group, a.lh, lane);
@@ -515,6 +523,7 @@ __global__ __launch_bounds__((kWM + kWV) * 64, 3) void cp4ws_kernel(Cp4Args a) {
                 }
             }
             load_rows(1, kw[0], vw[0], qw[0]);
+            __builtin_amdgcn_s_barrier();  // (the multiplier waves', before their operands)
 #pragma unroll
             for (int hb = (kH <= kT ? 1 : 0); hb < 2; ++hb) {
 #pragma unroll
@@ -606,7 +615,11 @@ hy_status launch_cp4_ws(const ConvPtrs& p, const ConvShape& s, hipStream_t st) {
     a.tiles_per_seq = (int32_t)((s.L + rows - 1) / rows);
     const int64_t nb = s.B * a.tiles_per_seq * a.ncb;
     if (nb > 0x7fffffffLL) return HY_ERR_UNSUPPORTED;
-    return launch_kernel((cp4ws_kernel<NBK, PF>), dim3((uint32_t)nb), dim3((kWM + kWV) * 64), st, a);
+    // tiles of one iteration wait for the operands, and a gather has them sooner (LDS / gather, kernel: 8 x 60 x 1024, 128 taps
+    // 8.0 / 7.2 us, 97 taps 7.4 / 6.7)
+    if (rows == kT)
+        return launch_kernel((cp4ws_kernel<NBK, PF, true>), dim3((uint32_t)nb), dim3((kWM + kWV) * 64), st, a);
+    return launch_kernel((cp4ws_kernel<NBK, PF, false>), dim3((uint32_t)nb), dim3((kWM + kWV) * 64), st, a);
 }
 
 template <int NBK>
