@@ -394,7 +394,7 @@ hy_status launch_nt(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
 }
 
 // Rows of 16-byte bf16 pieces: 64-row tiles leave the registers to load both the next tile's rows and this tile's gate before
-// the products, for any problem size.
+// the products.
 template <typename T, int VEC>
 constexpr bool half_tiles() { return T::kBytes == 2 && VEC > 1; }
 
@@ -403,7 +403,7 @@ hy_status launch_seg(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
     if constexpr (NT <= 2)  // (3 x 2730 x 1024 fp32, 9 taps, against a segment of 32: 28.5 -> 26.4 us)
         if (a.lh <= 16) return launch_nt<T, VEC, 16, NT, true>(a, nprob, B, st);
     if (a.lh <= 32) return launch_nt<T, VEC, 32, NT, true>(a, nprob, B, st);
-    if constexpr (!half_tiles<T, VEC>()) {  // (else launch_vec's)
+    if constexpr (NT <= 2 || !half_tiles<T, VEC>()) {  // (else launch_vec's)
         if (a.lh <= 64) return launch_nt<T, VEC, 64, NT, true>(a, nprob, B, st);
         if (a.lh <= 128) return launch_nt<T, VEC, 128, NT, true>(a, nprob, B, st);
     }
@@ -418,10 +418,16 @@ hy_status launch_vec(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
     // (rows 128 or 32 by the rules below / 64, bf16, 128 taps, us: 3 x 5003 x 1000 84.0 / 68.4, 4 x 4096 x 2056 189 / 153,
     // 6 x 690 x 1000 42.3 / 29.3, 1 x 700 x 1000 13.5 / 11.1, gradients 3 x 1300 x 1000 103 / 89; 50 taps 3 x 5003 x 1000
     // 51.3 / 51.1, 40 taps 1 x 4000 x 1000 17.8 / 16.4; but 30 taps 3 x 5003 x 1000 39.7 / 40.6.)  fp32 rows are twice as
-    // many registers: they do not fit.
+    // many registers: they do not fit.  A problem for whose 32-row tiles the compute units take no more turns than for 64-row
+    // ones has the shorter turns (32 / 64: 1 x 65 x 1000, 33 taps 6.9 / 8.1, 6 x 158 x 1000, 65 taps 12.4 / 14.4; with
+    // twice the turns 6 x 84 x 2056, 50 taps 13.0 / 10.7).
     if constexpr (half_tiles<T, VEC>()) {
-        if (a.lh > 64 && a.lh <= 128) return launch_nt<T, VEC, 128, 4, true>(a, nprob, B, st);
-        if (a.lh > 32 && a.lh <= 64) return launch_nt<T, VEC, 64, 4, true>(a, nprob, B, st);
+        if (a.lh > 32 && a.lh <= 128) {
+            auto turns = [&](int64_t rows) { return (B * a.ncb * nprob * ((a.L + rows - 1) / rows) + 255) / 256; };
+            if (turns(32) == turns(64)) return launch_seg<T, VEC, 2>(a, nprob, B, st);
+            if (a.lh > 64) return launch_nt<T, VEC, 128, 4, true>(a, nprob, B, st);
+            return launch_nt<T, VEC, 64, 4, true>(a, nprob, B, st);
+        }
     }
     // 128-row tiles amortise the 127 halo rows of a 128-tap filter; a problem that leaves compute units without a
     // workgroup that way is cut into 32-row tiles instead, and so is one whose last tile would be mostly padding.  (Eight

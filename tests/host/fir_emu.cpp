@@ -42,15 +42,17 @@ struct Tensor {  // [B, L, D]
 };
 
 // All outputs of one workgroup of the second walk (the last, possibly ragged channel block), against the plain loop.
-// `infinite`: one sample in front of the walk is.
-int check(int64_t L, int64_t D, int lh, int group, bool bf16, bool rev, bool descending, bool infinite) {
+// `infinite`: the step, counted from the walk's first one in its direction, of a sample that is (kFinite: none).
+constexpr int kFinite = 1 << 20;
+int check(int64_t L, int64_t D, int lh, int group, bool bf16, bool rev, bool descending, int infinite) {
     FirProblem p;
     p.stride_ab = p.stride_gate = p.stride_out = L * D;
     p.lo = 0; p.hi = L; p.rev = rev;
     auto launch = [&] { return launch_fir(&p, 1, 1, L, D, lh, group, bf16 ? HY_BF16 : HY_F32, nullptr); };
     emu::wanted = [](dim3) { return false; };  // only the launch's grid
     if (launch() != HY_OK) return printf("launch\n"), 1;
-    const int tile = lh <= 32 || (bf16 && D % 8 != 0 && lh <= 128) ? 32 : 128;
+    const bool pieces = bf16 && D % 8 == 0;  // rows of 16-byte bf16 pieces
+    const int tile = lh <= 32 || (bf16 && !pieces && lh <= 128) ? 32 : pieces && lh <= 128 ? 64 : 128;
     const int64_t ncb = (D + 63) / 64, tiles = (L + tile - 1) / tile, walks = emu::grid_dim.x / ncb;
     const int64_t steps = (tiles + walks - 1) / walks;
     const int64_t c0 = (ncb - 1) * 64, t0 = steps * tile, t1 = 2 * steps * tile < L ? 2 * steps * tile : L;
@@ -64,7 +66,7 @@ int check(int64_t L, int64_t D, int lh, int group, bool bf16, bool rev, bool des
             b.set(t, c, draw());
             gate.set(t, c, draw());
         }
-    if (infinite) a.set(rev ? t1 + 3 : t0 - 3, c0 + 5, INFINITY);
+    if (infinite != kFinite) a.set(rev ? t1 - 1 - infinite : t0 + infinite, c0 + 5, INFINITY);
     p.a = a.p; p.b = b.p; p.h = h; p.gate = gate.p; p.out = out.p;
     emu::wanted = [&](dim3 i) { return i.x == ncb + (ncb - 1); };
     emu::wave_order = [&](int i, int n) { return descending ? n - 1 - i : i; };
@@ -84,9 +86,24 @@ int check(int64_t L, int64_t D, int lh, int group, bool bf16, bool rev, bool des
         }
     free(h);
     printf("L=%lld D=%lld lh=%d group=%d %s %s%s, %s wave first, %lld tiles: %lld of %lld outputs wrong\n", (long long)L,
-           (long long)D, lh, group, bf16 ? "bf16" : "f32", rev ? "transposed" : "causal", infinite ? ", one sample infinite" : "",
+           (long long)D, lh, group, bf16 ? "bf16" : "f32", rev ? "transposed" : "causal", infinite != kFinite ? ", one sample infinite" : "",
            descending ? "last" : "first", (long long)steps, (long long)wrong, (long long)((t1 - t0) * (D - c0)));
     return wrong != 0;
+}
+
+// Rows of a tile, by the launch's workgroups.
+int check_rows(int64_t B, int64_t L, int64_t D, int lh, int rows) {
+    Tensor a(1, 8, 8, true);
+    FirProblem p;
+    p.a = p.b = p.gate = p.out = a.p;
+    p.h = static_cast<float*>(a.p);
+    p.stride_ab = p.stride_gate = p.stride_out = L * D;
+    p.lo = 0; p.hi = L; p.rev = false;
+    emu::wanted = [](dim3) { return false; };
+    if (launch_fir(&p, 1, B, L, D, lh, 1, HY_BF16, nullptr) != HY_OK) return printf("launch\n"), 1;
+    const int64_t want = B * ((L + rows - 1) / rows) * ((D + 63) / 64), got = emu::grid_dim.x;
+    printf("B=%lld L=%lld D=%lld lh=%d: %lld workgroups\n", (long long)B, (long long)L, (long long)D, lh, (long long)got);
+    return got != want;
 }
 
 }  // namespace
@@ -98,15 +115,25 @@ int main() {
         for (int i = 0; i < 4; ++i) {
             const int64_t D = i / 2 ? 509 : 512;  // rows of single elements, of 16-byte pieces
             const int group = i / 2 ? 1 : 8;
-            bad += check(L, D, lh, group, i % 2, lh == 40 || lh == 65, false, false);
-            bad += check(L, D, lh, group, i % 2, lh == 20 || lh == 128, true, false);
+            bad += check(L, D, lh, group, i % 2, lh == 40 || lh == 65, false, kFinite);
+            bad += check(L, D, lh, group, i % 2, lh == 20 || lh == 128, true, kFinite);
         }
-    bad += check(L, 512, 150, 8, true, false, false, false);  // three segments of 64
-    bad += check(L, 512, 200, 8, true, true, false, false);   // two segments of 128
-    bad += check(L, 509, 129, 1, false, true, true, false);
-    bad += check(L, 512, 128, 8, true, false, true, true);
-    bad += check(L, 512, 40, 1, false, true, false, true);
-    bad += check(L, 512, 150, 8, false, false, true, true);
+    bad += check(L, 512, 150, 8, true, false, false, kFinite);  // three segments of 64
+    bad += check(L, 512, 200, 8, true, true, false, kFinite);   // two segments of 128
+    bad += check(L, 509, 129, 1, false, true, true, kFinite);
+    bad += check(L, 512, 128, 8, true, false, true, -3);
+    bad += check(L, 512, 40, 1, false, true, false, -4);
+    bad += check(L, 512, 150, 8, false, false, true, -3);
+    // inside the walk's first 64-row tile, in reach of the third
+    bad += check(L, 512, 128, 8, true, false, false, 60);
+    bad += check(L, 512, 128, 8, true, true, true, 60);
+    bad += check(L, 512, 64, 8, true, false, true, 63);
+    // bf16 rows of whole pieces: 64-row tiles, 32-row ones where the compute units take no more turns for them
+    bad += check_rows(1, 65, 1000, 33, 32);
+    bad += check_rows(6, 158, 1000, 65, 32);
+    bad += check_rows(2, 256, 1024, 64, 32);
+    bad += check_rows(2, 288, 1024, 64, 64);
+    bad += check_rows(6, 84, 2056, 50, 64);
     printf("fir emulation: %d problem(s)\n", bad);
     return bad != 0;
 }
