@@ -48,6 +48,17 @@ def test_version_and_status_strings():
     assert len(seen) == 8 and "ok" in seen
 
 
+def test_hyena_li_tiles_where_one_tile_or_fewer_records_are_better():
+    """Two tiles per sequence are not taken where a narrower workgroup fills the chip with one (no records), and the widest
+    workgroup's many short tiles only where they are long against their number (records of twice as many steps)."""
+    wb = binding.lib().hyena_li_workspace_bytes
+    for B, L, D in ((3, 562, 8192), (8, 549, 3072), (5, 613, 5120)):
+        assert wb(B, L, D, 16, 16, 1) == 0
+    for B, L, D, rows in ((1, 27593, 768, 672), (3, 28733, 256, 704)):   # 352 steps with the widest
+        assert wb(B, L, D, 16, 16, 1) == B * ((L + rows - 1) // rows - 1) * (D // 16) * 1024
+    assert wb(1, 24680, 1024, 16, 16, 1) == ((24680 + 415) // 416 - 1) * 64 * 1024
+
+
 # fake but well-formed device addresses: validation must finish before any of them is dereferenced
 P = [0x10000 * (i + 1) for i in range(9)]
 
