@@ -6,12 +6,12 @@
 //   z_chunk = T u_chunk + Q s,        T[t, i] = h[t - i] (lower triangular, 32 x 32: the H_0 of Sec. 3.1),
 //                                      Q[t, n] = R_n lambda_n^(t+1),
 //   s'      = Lambda^32 s + P u_chunk, P[n, i] = lambda_n^(31-i),   s[n, c] = sum_{i<=end} lambda_n^(end-i) u[i, c].
-// With 16 channels of one filter group on a matrix tile (as in mr_kernels.hip) these are two
-// v_mfma_f32_16x16x32_bf16 for T, one for P and two pairs of v_mfma_f32_16x16x16_bf16 for Q; s stays in fp32
-// accumulators and enters the Q product split into a bf16 head and a bf16 remainder, so carrying the state
-// over 10^5 steps costs no precision beyond the bf16 rounding of the coefficients.  The state product comes
-// out with 4 consecutive n of one channel per lane, which is exactly the operand layout of the Q product:
-// the state never leaves its registers.
+// With 16 channels of one filter group on a matrix tile (as in mr_kernels.hip) these are v_mfma_f32_16x16x32_bf16,
+// two for T, two for P and four for Q; s stays in fp32 accumulators and enters the Q product split into a bf16 head
+// and a bf16 remainder, as do the coefficients of P and Q, so carrying the state over 10^5 steps costs no precision
+// beyond 16 bits of the coefficients.  The state product comes out with 4 consecutive n of one channel per lane:
+// head and remainder of the state, side by side, are the operand of the Q product, and the state never leaves its
+// registers.
 //
 // The recurrence runs along time, and one GPU needs more than B * D / 256 workgroups, so the sequence is cut
 // into tiles and scanned in two passes (the classic chunked scan): pass 1 walks every tile but the last of
@@ -27,8 +27,6 @@
 
 namespace hy {
 namespace {
-
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
 struct LiArgs {
     const uint16_t* q;
@@ -102,61 +100,33 @@ __device__ __forceinline__ void p_operands(bf16x8_t& pop, bf16x8_t& pop_lo, cons
     pop_lo = __builtin_bit_cast(bf16x8_t, wlo);
 }
 
-// Q operands: lane (li = step of tile x, lq), element e = R_n lambda_n^(16x + li + 1), n = 4lq + e
-__device__ __forceinline__ void q_operands(s16x4_t (&qop)[2], s16x4_t (&qop_lo)[2], const float* res, const float* lam, int li,
-                                           int lq) {
+// Q operands: lane (li = step of tile x, lq), R_n lambda_n^(16x + li + 1), n = 4lq + e: remainders in the elements 0..3, heads
+// in 4..7
+__device__ __forceinline__ void q_operands(bf16x8_t (&qop)[2], const float* res, const float* lam, int li, int lq) {
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
         float qe[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) qe[e] = res[4 * lq + e] * powi(lam[4 * lq + e], 16 * x + li + 1);
-        Words<2> wds, wlo;
-        wds.w[0] = pack_bf16x2(qe[0], qe[1]);
-        wds.w[1] = pack_bf16x2(qe[2], qe[3]);
-        wlo.w[0] = pack_bf16x2(qe[0] - bf16_lo(wds.w[0]), qe[1] - bf16_hi(wds.w[0]));
-        wlo.w[1] = pack_bf16x2(qe[2] - bf16_lo(wds.w[1]), qe[3] - bf16_hi(wds.w[1]));
-        qop[x] = __builtin_bit_cast(s16x4_t, wds);
-        qop_lo[x] = __builtin_bit_cast(s16x4_t, wlo);
+        Words<4> wds;
+        wds.w[2] = pack_bf16x2(qe[0], qe[1]);
+        wds.w[3] = pack_bf16x2(qe[2], qe[3]);
+        wds.w[0] = pack_bf16x2(qe[0] - bf16_lo(wds.w[2]), qe[1] - bf16_hi(wds.w[2]));
+        wds.w[1] = pack_bf16x2(qe[2] - bf16_lo(wds.w[3]), qe[3] - bf16_hi(wds.w[3]));
+        qop[x] = __builtin_bit_cast(bf16x8_t, wds);
     }
 }
 
 // z of a chunk: steps 16x + li of channels 4 lq .. 4 lq + 3 of the wave in acc[x].
-// The state enters in two bf16 parts, head and remainder; smallest terms first: head of the state against the remainder
-// of Q, remainder of the state against the head of Q, then the heads, then the chunk's own Toeplitz block.  The order of
-// the two instruction shapes matters beyond rounding: a 16x16x16 product that accumulates onto the result of a 16x16x32
-// product issued fewer than 5 wait states earlier reads the register's previous contents on gfx950 (measured), and the
-// compiler does not always leave that distance; 16x16x16 results feeding a 16x16x32 product are interlocked by the
-// hardware.  Every 16x16x16 product below accumulates onto zero or onto another 16x16x16 result, so the unsafe pair cannot
-// arise from this source by data dependence; tests/test_isa_hazards.py checks the generated code of this file for the pair
-// on every build.
+// Head and remainder of the state lie side by side in one operand, remainder and head of Q in the other: one product adds head
+// times remainder and remainder times head, a second one, with the state's parts exchanged, the heads and the remainders.
+// All products of this file have one shape, 16x16x32, and no 16x16x16 product feeds one of them or takes its sum: on gfx950
+// a 16x16x16 product that accumulates onto the result of a 16x16x32 product fewer than 5 wait states old read the register's
+// previous contents, and a 16x16x32 product that accumulates onto the result of a 16x16x16 product 4 wait states old, with no
+// other product between, left the upper two registers of its result wrong in some waves (both measured).  The compiler does
+// not always keep such a distance; tests/test_isa_hazards.py looks for either pair in the generated code.
 __device__ __forceinline__ void chunk_outputs(f32x4_t (&acc)[2], const f32x4_t& s, const bf16x8_t& uw, const bf16x8_t (&tz)[2],
-                                              const s16x4_t (&qop)[2], const s16x4_t (&qop_lo)[2]) {
-    const uint32_t h01 = pack_bf16x2(s[0], s[1]), h23 = pack_bf16x2(s[2], s[3]);
-    const uint32_t l01 = pack_bf16x2(s[0] - bf16_lo(h01), s[1] - bf16_hi(h01));
-    const uint32_t l23 = pack_bf16x2(s[2] - bf16_lo(h23), s[3] - bf16_hi(h23));
-    Words<2> hw, lw;
-    hw.w[0] = h01; hw.w[1] = h23;
-    lw.w[0] = l01; lw.w[1] = l23;
-    const s16x4_t shi = __builtin_bit_cast(s16x4_t, hw), slo = __builtin_bit_cast(s16x4_t, lw);
-    acc[0] = acc[1] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int x = 0; x < 2; ++x) acc[x] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(shi, qop_lo[x], acc[x], 0, 0, 0);
-#pragma unroll
-    for (int x = 0; x < 2; ++x) acc[x] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(slo, qop[x], acc[x], 0, 0, 0);
-#pragma unroll
-    for (int x = 0; x < 2; ++x) acc[x] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(shi, qop[x], acc[x], 0, 0, 0);
-#pragma unroll
-    for (int x = 0; x < 2; ++x) acc[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(uw, tz[x], acc[x], 0, 0, 0);
-}
-
-// The same products in 16x16x32 shape alone: head and remainder of the state side by side in one operand, remainder and head
-// of Q in the other, and once more with the state's parts exchanged (which adds the product of the remainders).  No product
-// here feeds one of another shape: in an unrolled loop the compiler left 4 wait states and no other product between a
-// 16x16x16 product and the 16x16x32 product that accumulated onto it, and the upper two registers of the result came out
-// wrong in some waves (other distances, and other products in between, do not show it; tests/test_isa_hazards.py checks the
-// kernels above for that pair).
-__device__ __forceinline__ void chunk_outputs_wide(f32x4_t (&acc)[2], const f32x4_t& s, const bf16x8_t& uw,
-                                                   const bf16x8_t (&tz)[2], const bf16x8_t (&qop)[2]) {
+                                              const bf16x8_t (&qop)[2]) {
     Words<4> a, b;
     a.w[0] = b.w[2] = pack_bf16x2(s[0], s[1]);
     a.w[1] = b.w[3] = pack_bf16x2(s[2], s[3]);
@@ -321,8 +291,8 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 2) void li_mfma_kernel(LiAr
     float lam32[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) lam32[r] = powi(ls[w][4 * lq + r], kChunk);
-    s16x4_t qop[2], qop_lo[2];
-    if constexpr (!kStateOnly) q_operands(qop, qop_lo, rs[w], ls[w], li, lq);
+    bf16x8_t qop[2];
+    if constexpr (!kStateOnly) q_operands(qop, rs[w], ls[w], li, lq);
 
     const int swz = ((lr >> 3) & 3) << 1;
     const int st_idx = lr * PPR + (lp ^ swz);
@@ -359,7 +329,7 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 2) void li_mfma_kernel(LiAr
             if (live) {
                 if constexpr (!kStateOnly) {
                     f32x4_t acc[2];
-                    chunk_outputs(acc, s, uw, tz, qop, qop_lo);
+                    chunk_outputs(acc, s, uw, tz, qop);
                     char* zp = zst[ci & 1] + zwr_off;
                     *reinterpret_cast<float4*>(zp) = make_float4(acc[0][0], acc[0][1], acc[0][2], acc[0][3]);
                     *reinterpret_cast<float4*>(zp + 16 * ZROW) = make_float4(acc[1][0], acc[1][1], acc[1][2], acc[1][3]);
@@ -605,14 +575,8 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 2) void li_one_pass_kernel(
     // ---- phase 2: y of the tile
     bf16x8_t tz[2];
     t_operands(tz, hs[w], li, lq);
-    bf16x8_t qop[2];  // remainder of Q, then its head
-    {
-        s16x4_t hi[2], lo[2];
-        q_operands(hi, lo, rs[w], ls[w], li, lq);
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-            qop[x] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo[x], hi[x], 0, 1, 2, 3, 4, 5, 6, 7));
-    }
+    bf16x8_t qop[2];
+    q_operands(qop, rs[w], ls[w], li, lq);
     const int zwr_off = li * ZROW + (16 * w + 4 * lq) * 4;
     const int zrd_off = lr * ZROW + 8 * lp * 4;
     auto phase2 = [&](auto self, auto chunk) {
@@ -625,7 +589,7 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 2) void li_one_pass_kernel(
             else
                 uw = ukeep[ci - KL];
             f32x4_t acc[2];
-            chunk_outputs_wide(acc, s, uw, tz, qop);
+            chunk_outputs(acc, s, uw, tz, qop);
             char* zw = zst[ci & 1] + zwr_off;
             *reinterpret_cast<float4*>(zw) = make_float4(acc[0][0], acc[0][1], acc[0][2], acc[0][3]);
             *reinterpret_cast<float4*>(zw + 16 * ZROW) = make_float4(acc[1][0], acc[1][1], acc[1][2], acc[1][3]);
