@@ -15,8 +15,9 @@
 // (h is zero outside [0, lh)).  A_m and B_m stay in registers for the whole tile, 2 VGPRs per m.  A column of a right operand
 // is one aligned quad (4 steps of a channel): the operand of shift i of group gamma holds quad 4 gamma + j - i in column j.
 // du of group gamma takes the operands (gamma - a, i) of g for m = 4a + i, dh the same ones for T = 16 gamma + 4(3 - i), and z
-// of group gamma - NG, which is complete when group gamma is there, those of u at group gamma - NG + a for m = 4a - i.  So a
-// group's four operands are read from LDS once (8 bytes per lane each) and stay in a register window of NG + 1 groups.
+// of group gamma - 4 LAG, which is complete when group gamma is there, those of u at group gamma - 4 LAG + a for m = 4a - i.
+// So a group's four operands are read from LDS once (8 bytes per lane each) and stay in a register window of up to 4 LAG + 1
+// groups.
 //
 // What bounds it: 7 tensor passes through 128-byte row pieces (three launches, dq, then dk and dv, then dh, made 13).  A
 // workgroup owns 64 channels with 8 waves, two per SIMD and of two kinds: four run du and dh (filter operands 66 registers,
@@ -85,12 +86,14 @@ struct Quad {
 __device__ __forceinline__ s16x4_t operand(const Quad& x) { return __builtin_bit_cast(s16x4_t, x); }
 __device__ __forceinline__ Quad quad_at(const char* p) { return __builtin_bit_cast(Quad, *reinterpret_cast<const uint2*>(p)); }
 
-// LAG = chunks between a chunk's arrival and its complete z; filters of up to 64 LAG + 1 taps.  PF = chunks of loads in
-// flight.  kShard: the call is one rank's share of a sequence (halo rows next to the tensors, batch strides).
-template <int LAG, int PF, bool kShard>
+// NG = groups of 16 steps a filter reaches back; filters of up to 16 NG + 1 taps.  A product with a tap of zero carries a value
+// that is not finite as far as NG reaches, so NG follows the filter (calls with 9 to 33 and 66 to 97 taps are also up to 11%
+// faster than with the 4 or 8 groups of the window).  PF = chunks of loads in flight.  kShard: the call is one rank's share of
+// a sequence (halo rows next to the tensors, batch strides).
+template <int NG, int PF, bool kShard>
 __global__ __launch_bounds__(2 * kNW * 64, 2) void cp4_bwd_kernel(Cp4BwdArgs a) {
-    constexpr int NG = 4 * LAG;      // groups of 16 steps a filter reaches back
-    constexpr int NBK = 4 * NG + 1;  // products per group and convolution
+    constexpr int LAG = (NG + 3) / 4;  // chunks between a chunk's arrival and its complete z
+    constexpr int NBK = 4 * NG + 1;    // products per group and convolution
     constexpr int PPR = kC / 8;      // 16-byte pieces per row
     static_assert(kNW * 64 == PPR * (kT / 2), "one lane per (row pair, piece)");
     static_assert(LAG == 1 || LAG == 2, "the window and the dy ring hold up to two chunks");
@@ -411,7 +414,7 @@ __global__ __launch_bounds__(2 * kNW * 64, 2) void cp4_bwd_kernel(Cp4BwdArgs a) 
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
                             if (x > 0 || i == 0)
-                                z[i & 1] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ares[x > 0 ? 4 * x - i : 0], win[(G - NG + x) & 15][i], z[i & 1], 0, 0, 0);
+                                z[i & 1] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ares[x > 0 ? 4 * x - i : 0], win[(G - 4 * LAG + x) & 15][i], z[i & 1], 0, 0, 0);
                     *reinterpret_cast<uint2*>(yl) = gated(z[0] + z[1], y4);  // dq
                 }
             };
@@ -495,16 +498,20 @@ hy_status launch_cp4_bwd(const BwdPtrs& p, const BwdShape& s, void* ws, hipStrea
     const int64_t nb = nsets * a.ncb;
     if (nb > 0x7fffffffLL) return HY_ERR_UNSUPPORTED;
     const dim3 grid((uint32_t)nb), block(2 * kNW * 64);
-    // Up to 65 taps one chunk of history instead of two: half the halo, 54 products per group instead of 102, and room for
-    // a second chunk of loads in flight (LAG = 2 spills with one).  Against the three launches on 40 shapes of 64 to 8192
-    // channels and up to 2^25 elements: 1.4 to 2.6 times as fast, nothing slower.
-    hy_status rc;
-    if (s.lh <= 65)
-        rc = s.sharded() ? launch_kernel((cp4_bwd_kernel<1, 2, true>), grid, block, st, a)
-                         : launch_kernel((cp4_bwd_kernel<1, 2, false>), grid, block, st, a);
-    else
-        rc = s.sharded() ? launch_kernel((cp4_bwd_kernel<2, 1, true>), grid, block, st, a)
-                         : launch_kernel((cp4_bwd_kernel<2, 1, false>), grid, block, st, a);
+    // Up to 65 taps one chunk of history instead of two: half the halo, and room for a second chunk of loads in flight
+    // (with two chunks of history and 8 groups one chunk in flight already spills 4 registers).  Against the three launches
+    // (dq; dk and dv; dh) on 40 shapes of 64 to 8192 channels and up to 2^25 elements: 1.4 to 2.6 times as fast, nothing slower.
+    auto launch = [&](auto ng) {
+        constexpr int NG = decltype(ng)::value, PF = NG <= 4 ? 2 : 1;
+        return s.sharded() ? launch_kernel((cp4_bwd_kernel<NG, PF, true>), grid, block, st, a)
+                           : launch_kernel((cp4_bwd_kernel<NG, PF, false>), grid, block, st, a);
+    };
+    using std::integral_constant;
+    const hy_status rc = s.lh <= 17   ? launch(integral_constant<int, 1>{})
+                         : s.lh <= 33 ? launch(integral_constant<int, 2>{})
+                         : s.lh <= 65 ? launch(integral_constant<int, 4>{})
+                         : s.lh <= 97 ? launch(integral_constant<int, 6>{})
+                                      : launch(integral_constant<int, 8>{});
     if (rc != HY_OK) return rc;
     return launch_dh_reduce(static_cast<const float*>(ws), p.dh, nsets, s.D, s.lh, s.group, st);
 }

@@ -228,6 +228,45 @@ def test_chunk_parallel_backward_edges_of_tiles(L, rows, lh):
         assert np.array_equal(host(got), want), name
 
 
+@pytest.mark.parametrize("lh", [17, 18, 33, 34, 97, 98])
+@pytest.mark.parametrize("L,rows", [(66, 64), (129, 64), (253, 64)])
+def test_chunk_parallel_backward_edges_of_filters(L, rows, lh):
+    """The longest and shortest filters of each number of 16-step groups."""
+    test_chunk_parallel_backward_edges_of_tiles(L, rows, lh)
+
+
+@pytest.mark.parametrize("lh", [9, 17, 18, 33, 34, 65, 66, 97, 98, 129])
+def test_chunk_parallel_backward_reach_of_non_finite_values(lh):
+    """A product spans 4 steps and multiplies its zeros, and a filter's products come in groups of 16 taps, from 34 taps on in
+    pairs of groups: a NaN in u or g reaches z or du of its own channel from 3 steps on the wrong side to the end of the last
+    group and 3 steps, and the filter gradient of its own filter; everything else keeps its bits."""
+    B, L, D, at, c = 2, 700, 128, 400, 70
+    say("cp4 bwd non-finite lh=%d" % lh)
+    groups = {9: 1, 17: 1, 18: 2, 33: 2, 34: 4, 65: 4, 66: 6, 97: 6, 98: 8, 129: 8}[lh]
+    dy, q, k, v, h = draw(9700 + lh, B, L, D, lh, 1, "bf16", "mr")
+    clean = binding.hyena_mr_bwd(dev(dy), dev(q), dev(k), dev(v), dev(h), 1)
+    span = {"u": (at, at + 16 * groups + 3), "g": (at - 16 * groups, at + 3)}
+    for where, x in (("u", k), ("g", q)):
+        keep = x[1, at, c].clone()
+        x[1, at, c] = float("nan")
+        got = binding.hyena_mr_bwd(dev(dy), dev(q), dev(k), dev(v), dev(h), 1)
+        x[1, at, c] = keep
+        lo, hi = span[where]
+        lo -= 3
+        for name, a, b in zip(("dq", "dk", "dv", "dh"), got, clean):
+            a, b = a.float().cpu(), b.float().cpu()
+            same = torch.ones_like(a, dtype=torch.bool)
+            if name == "dh":
+                same[c] = False
+            else:
+                same[1, lo:hi + 1, c] = False
+            assert torch.equal(a[same], b[same]), (where, name)
+        # what the definition makes NaN is NaN
+        reach = slice(at, at + lh) if where == "u" else slice(at - lh + 1, at + 1)
+        outs = (got[0],) if where == "u" else got[1:3]
+        assert all(torch.isnan(o[1, reach, c]).all() for o in outs) and torch.isnan(got[3][c]).all(), where
+
+
 def test_matrix_core_backward_exact_case():
     """Sparse signed inputs and dyadic taps: every product and partial sum is exactly representable, so
     dq, dk, dv and dh must match the oracle bit for bit."""
