@@ -20,7 +20,10 @@
 //    dx'[T+k-4(3-j)], H[i][k] = x[T+i+k]: entry (i, j) collects the lag 4(3-j)+i;
 //  * four run z in the same way, then dq, and the inner filter gradient as products over channels
 //    (v_mfma_f32_16x16x16_bf16, operands read transposed).
-// The intermediates enter products rounded to bf16 (u, g, dx', and k', v' as gates) and are otherwise fp32 on chip.
+// The intermediates enter products rounded to bf16 (u, g, dx', and k', v' as gates) and are otherwise fp32 on chip.  A product
+// also multiplies its structural zeros, so a value that is not finite would reach 3 steps to the wrong side of a featurizer and up
+// to 11 to the other; a lane whose featurizer products gave such a value takes its steps term by term instead (1 to 2% of the
+// time, most of it the test for it; doing the same for the inner filter, whose blocks are 32 steps, would not fit the registers).
 //
 // Everything lies in one 2400-byte LDS record per channel, time contiguous.  Results take the place of what is dead: dk, dv
 // that of the raw k, v of their chunk, dq that of the raw q (rings of 8 chunks for q and dy, which wait for z, and of 4 for k
@@ -91,6 +94,14 @@ __device__ __forceinline__ void put_quad(char* p, const Quad& x) { *reinterpret_
 __device__ __forceinline__ Quad pack_quad(const f32x4_t& x) { return Quad{{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3])}}; }
 __device__ __forceinline__ f32x4_t unpack_quad(const Quad& x) {
     return f32x4_t{bf16_lo(x.w[0]), bf16_hi(x.w[0]), bf16_lo(x.w[1]), bf16_hi(x.w[1])};
+}
+// z, or not zero any more if one of the four steps is not finite
+__device__ __forceinline__ float probe(float z, const Quad& x) {
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        z = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, x.w[i]), __builtin_bit_cast(bf16x2_t, 0u), z, false);
+    return z;
 }
 // four taps as bf16 heads and remainders
 __device__ __forceinline__ void split_taps(const float (&t)[4], s16x4_t (&o)[2]) {
@@ -178,8 +189,9 @@ __global__ __launch_bounds__(kKinds * kNW * 64, kKinds) void chain_bwd_kernel(Ch
         for (int i = 0; i < 4; ++i) r.w[i] = operand(quad_at(rc4 + kDx + x * kDxSize + kFront + 32 * n - 8 * i));
         return r;
     };
-    // dx of 16 steps and their share of its filter gradient
-    auto unit = [&](const s16x4_t (&fa)[NF][2], const Steps& x, const Shifts& r, f32x4_t& facc) {
+    // dx of 16 steps and their share of its filter gradient.  `first`: the walk's first steps, where the quad before them, column
+    // 2 of the first product, is no steps of the sequence: its zeros are not multiplied with x
+    auto unit = [&](const s16x4_t (&fa)[NF][2], const Steps& x, const Shifts& r, bool first, f32x4_t& facc) {
         const uint32_t sh = (l4 & 1) * 16;
         f32x4_t dx = {0.0f, 0.0f, 0.0f, 0.0f};
         uint32_t d[9];
@@ -188,7 +200,8 @@ __global__ __launch_bounds__(kKinds * kNW * 64, kKinds) void chain_bwd_kernel(Ch
         auto dh_product = [&](int kq) {
             const Quad hk{{__builtin_amdgcn_alignbit(d[2 * kq + 1], d[2 * kq], sh),
                            __builtin_amdgcn_alignbit(d[2 * kq + 2], d[2 * kq + 1], sh)}};
-            facc = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(operand(hk), r.w[3 - kq], facc, 0, 0, 0);
+            const f32x4_t sum = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(operand(hk), r.w[3 - kq], facc, 0, 0, 0);
+            if (kq > 0 || !first || l4 == 3) facc = sum;
         };
         auto dx_product = [&](int m, int part) { dx = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(fa[m][part], r.w[m], dx, 0, 0, 0); };
         dx_product(2, 1); dh_product(0);
@@ -205,6 +218,26 @@ __global__ __launch_bounds__(kKinds * kNW * 64, kKinds) void chain_bwd_kernel(Ch
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             if (4 * (3 - l4) + i < a.lf) out[4 * (3 - l4) + i] = facc[i];
+    };
+    // ---- the definition's terms alone, one by one with fp32 taps, for a lane whose products gave something that is not finite:
+    // a product also multiplies its structural zeros, and the remainder of an infinite tap is none.  (What this needs beside
+    // its arguments is formed from a value that the compiler cannot move out of the rare branch.)
+    auto taps_of = [&](int x) {
+        int c = 16 * w + blk;
+        asm volatile("" : "+v"(c));
+        return a.hx[x] + (int64_t)(((uint32_t)cblock0 + c) / (uint32_t)a.feat_group) * a.lf;
+    };
+    auto step_at = [&](int at) { return bf16_lo(*reinterpret_cast<const lds16_t*>(rc4 + at)); };
+    auto put_step = [&](int at, float x) { *reinterpret_cast<lds16_t*>(rc4 + at) = (uint16_t)pack_bf16x2(x, 0.0f); };
+    auto exact_dx = [&](int x, int at) {  // of the lane's steps of a chunk
+        const float* const hp = taps_of(x);
+#pragma unroll 1
+        for (int o = 0; o < kSlot; o = (o & 7) == 6 ? o + 26 : o + 2) {
+            float sum = 0.0f;
+#pragma unroll 1
+            for (int j = 0; j < a.lf; ++j) sum = __builtin_fmaf(hp[j], step_at(kDx + x * kDxSize + kFront + o - 2 * j), sum);
+            put_step(at + o, sum);
+        }
     };
     // body(slot, j) for the chunks j = 0 .. ntot - 1, slot = j % 8; then last(slot, ntot)
     auto walk = [&](auto&& body, auto&& last) {
@@ -271,6 +304,7 @@ __global__ __launch_bounds__(kKinds * kNW * 64, kKinds) void chain_bwd_kernel(Ch
                 if (in_tile(j)) {
                     // four units of 16 steps of a tensor, the next one's reads under way during one's products
                     Shifts sh[2];
+                    float z[2] = {0.0f, 0.0f};
                     sh[0] = read_shifts(1, 0);
 #pragma unroll
                     for (int un = 0; un < 4; ++un) {
@@ -280,8 +314,13 @@ __global__ __launch_bounds__(kKinds * kNW * 64, kKinds) void chain_bwd_kernel(Ch
                             steps[(un + 1) & 1] = read_steps(at[(un + 1) >> 1] + 32 * ((un + 1) & 1));
                             sh[(un + 1) & 1] = read_shifts(1 + ((un + 1) >> 1), (un + 1) & 1);
                         }
-                        put_quad(rc4 + at[x] + 32 * n, unit(fa[x], steps[un & 1], sh[un & 1], facc[x]));
+                        const Quad dx = unit(fa[x], steps[un & 1], sh[un & 1], n == 0 && chunk_start(j) == 0, facc[x]);
+                        put_quad(rc4 + at[x] + 32 * n, dx);
+                        z[x] = probe(z[x], dx);
                     }
+#pragma unroll
+                    for (int x = 0; x < 2; ++x)
+                        if (__builtin_expect(!(z[x] == 0.0f), 0)) exact_dx(1 + x, at[x]);
                 }
             }
             __syncthreads();
@@ -356,14 +395,18 @@ __global__ __launch_bounds__(kKinds * kNW * 64, kKinds) void chain_bwd_kernel(Ch
                     put_quad(rc16 + kDx + kFront + 32 * p + 8 * (3 - lq),
                              pack_quad(__builtin_shufflevector(acc[p], acc[p], 3, 2, 1, 0) * unpack_quad(y4[p])));
                 if (in_tile(j - LAG)) {
+                    float z = 0.0f;
 #pragma unroll
                     for (int n = 0; n < 2; ++n) {
                         const Steps steps = read_steps(kQ + SZ * kSlot + 32 * n);
                         const Shifts sh = read_shifts(0, n);
                         __builtin_amdgcn_sched_barrier(0);
                         if (own) products_dh(n);  // while the reads are under way
-                        put_quad(rc4 + kQ + SZ * kSlot + 32 * n, unit(fa, steps, sh, facc));
+                        const Quad dx = unit(fa, steps, sh, n == 0 && chunk_start(j - LAG) == 0, facc);
+                        put_quad(rc4 + kQ + SZ * kSlot + 32 * n, dx);
+                        z = probe(z, dx);
                     }
+                    if (__builtin_expect(!(z == 0.0f), 0)) exact_dx(0, kQ + SZ * kSlot);
                 }
             }
             if (own && !(j >= LAG && in_tile(j - LAG))) {
@@ -521,9 +564,10 @@ __global__ __launch_bounds__(kKinds * kNW * 64, kKinds) void chain_bwd_kernel(Ch
             if (j > LAG && in_tile(j - 1 - LAG)) store_rows(kQ + DQ * kSlot, a.out[0], j - 1 - LAG);
         };
         // q', k', v' of chunk c, and from them g and u
-        auto featurize = [&](auto slot_c) {
+        auto featurize = [&](auto slot_c, int c) {
             constexpr int SL = decltype(slot_c)::value, S4 = SL & 3, two = (SL & 1) * kSlot;  // SL = c % 8
             constexpr int at[3] = {kQ + SL * kSlot, kK + S4 * kSlot, kV + S4 * kSlot};
+            float z = 0.0f;
 #pragma unroll
             for (int n = 0; n < 2; ++n) {
                 s16x4_t xq[3][NF];
@@ -540,10 +584,30 @@ __global__ __launch_bounds__(kKinds * kNW * 64, kKinds) void chain_bwd_kernel(Ch
 #pragma unroll
                         for (int x = 0; x < 3; ++x)
                             f[x] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(fb[x][m][part], xq[x][m], f[x], 0, 0, 0);
-                put_quad(rc4 + kG + two + 32 * n, pack_quad(y4 * f[0]));
-                put_quad(rc4 + kU + two + 32 * n, pack_quad(f[1] * f[2]));
+                const Quad g4 = pack_quad(y4 * f[0]), u4 = pack_quad(f[1] * f[2]);
+                put_quad(rc4 + kG + two + 32 * n, g4);
+                put_quad(rc4 + kU + two + 32 * n, u4);
                 put_quad(rc4 + kKf + two + 32 * n, pack_quad(f[1]));
                 put_quad(rc4 + kVf + two + 32 * n, pack_quad(f[2]));
+                z = probe(probe(z, g4), u4);
+            }
+            if (__builtin_expect(!(z == 0.0f), 0)) {
+                const float *const h0 = taps_of(0), *const h1 = taps_of(1), *const h2 = taps_of(2);
+                const int T = chunk_start(c) + 4 * l4;
+#pragma unroll 1
+                for (int o = 0; o < kSlot; o = (o & 7) == 6 ? o + 26 : o + 2) {
+                    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
+#pragma unroll 1
+                    for (int j = 0; j < a.lf && T + (o >> 1) + j < L; ++j) {
+                        s0 = __builtin_fmaf(h0[j], step_at(at[0] + o + 2 * j), s0);
+                        s1 = __builtin_fmaf(h1[j], step_at(at[1] + o + 2 * j), s1);
+                        s2 = __builtin_fmaf(h2[j], step_at(at[2] + o + 2 * j), s2);
+                    }
+                    put_step(kG + two + o, step_at(kY + SL * kSlot + o) * s0);
+                    put_step(kU + two + o, s1 * s2);
+                    put_step(kKf + two + o, s1);
+                    put_step(kVf + two + o, s2);
+                }
             }
         };
         auto step = [&](auto slot_c, int j) {
@@ -553,7 +617,7 @@ __global__ __launch_bounds__(kKinds * kNW * 64, kKinds) void chain_bwd_kernel(Ch
                 write_chunk(integral_constant<int, (SL + 3) & 7>{}, j + 3);
                 load_chunk(integral_constant<int, (SL + 3) & 7>{}, j + 3 + PF);
             }
-            if (j + 1 < ntot) featurize(integral_constant<int, (SL + 1) & 7>{});
+            if (j + 1 < ntot) featurize(integral_constant<int, (SL + 1) & 7>{}, j + 1);
             __syncthreads();
         };
         write_chunk(integral_constant<int, 0>{}, 0);
@@ -563,7 +627,7 @@ __global__ __launch_bounds__(kKinds * kNW * 64, kKinds) void chain_bwd_kernel(Ch
         write_chunk(integral_constant<int, 2>{}, 2);
         load_chunk(integral_constant<int, 2>{}, 2 + PF);
         __syncthreads();
-        featurize(integral_constant<int, 0>{});
+        featurize(integral_constant<int, 0>{}, 0);
         __syncthreads();
         walk(step, store_chunk);
     }
@@ -624,9 +688,15 @@ hy_status launch_chain_bwd(const ChainBwdPtrs& p, const ChainShape& s, void* ws,
     const int64_t nb = nsets * a.ncb;
     if (nb > 0x7fffffffLL) return HY_ERR_UNSUPPORTED;
     const dim3 grid((uint32_t)nb), block(kKinds * kNW * 64);
-    // up to 65 taps the window and z's delay are 2 chunks instead of 4
-    hy_status rc = s.lh <= 65 ? launch_kernel((chain_bwd_kernel<3>), grid, block, st, a)
-                              : launch_kernel((chain_bwd_kernel<5>), grid, block, st, a);
+    // the window and z's delay are as many chunks as the filter reaches back (mr_bwd_kernels.hip's, and so is the reach of a
+    // value that is not finite)
+    hy_status rc;
+    switch ((s.lh + 30) / 32 + 1) {
+        case 2: rc = launch_kernel((chain_bwd_kernel<2>), grid, block, st, a); break;
+        case 3: rc = launch_kernel((chain_bwd_kernel<3>), grid, block, st, a); break;
+        case 4: rc = launch_kernel((chain_bwd_kernel<4>), grid, block, st, a); break;
+        default: rc = launch_kernel((chain_bwd_kernel<5>), grid, block, st, a);
+    }
     if (rc != HY_OK) return rc;
     // partial rows of dh are per 16-channel slice, those of dhq, dhk, dhv per channel
     rc = launch_dh_reduce(a.partial, p.dh, nsets, s.D / 16, s.lh, s.group / 16, st);

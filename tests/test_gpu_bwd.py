@@ -473,6 +473,52 @@ def test_one_pass_chain_backward_edges_of_tiles(L, rows, lh, lf):
         assert err <= tol, (name, err)
 
 
+@pytest.mark.parametrize("lh,lf", [(9, 1), (33, 5), (65, 8), (97, 4), (129, 7)])
+@pytest.mark.parametrize("L,where", [(700, 400), (700, 1), (700, 698), (64, 0), (31, 30)])
+def test_one_pass_chain_backward_reach_of_non_finite_values(L, where, lh, lf):
+    """A value that is not finite reaches no more of the one-pass kernel's results than of the composition's (the featurizers
+    by their definition, the inner operator in whole 32-step blocks); both windows' lengths and every number of taps' quads, an
+    infinite tap too.  What it does not reach keeps its bits."""
+    B, D, group = 2, 128, 16
+    say("one-pass chain bwd non-finite L=%d at %d lh=%d lf=%d" % (L, where, lh, lf))
+    rng = np.random.Generator(np.random.PCG64(9800 + L + lh))
+    dy, q, k, v = (synth.normal_tensor(rng, (B, L, D), "bf16") for _ in range(4))
+    hq, hk, hv = (torch.from_numpy(synth.short_filter(rng, D, lf)) for _ in range(3))
+    h = dev(synth.decay_filter(rng, D // group, lh))
+    names = ("dq", "dk", "dv", "dhq", "dhk", "dhv", "dh")
+
+    def one_pass():
+        return [x.float().cpu() for x in binding.hyena_chain_bwd(*[dev(x) for x in (dy, q, k, v, hq, hk, hv)], h, group, 1)]
+
+    def composed():
+        x = [dev(t) for t in (q, k, v)]
+        f = [dev(t) for t in (hq, hk, hv)]
+        g = binding.hyena_mr_bwd(dev(dy), *binding.hyena_featurize3_fwd(*x, *f, 1), h, group)
+        parts = [binding.hyena_featurize_bwd(gx, xx, fx, 1) for gx, xx, fx in zip(g, x, f)]
+        return [p[0].float().cpu() for p in parts] + [p[1].float().cpu() for p in parts] + [g[3].float().cpu()]
+
+    clean = one_pass()
+    for bad in (float("nan"), float("inf")):
+        for t, at in ((dy, (1, where, 37)), (q, (1, where, 37)), (k, (1, where, 37)), (v, (1, where, 37)), (hk, (37, lf - 1))):
+            keep = t[at].clone()
+            t[at] = bad
+            got, want = one_pass(), composed()
+            t[at] = keep
+            for name, a, b, c in zip(names, got, want, clean):
+                reached = ~torch.isfinite(a)
+                assert not (reached & torch.isfinite(b)).any(), (name, at, bad)
+                # channels of other groups, and the other batch item
+                rows = a.dim() == 2
+                n = a.shape[0] // (D // 16) if rows else 16  # rows or channels of a group of 16 channels
+                group_of = slice(37 // 16 * n, (37 // 16 + 1) * n)
+                same = torch.ones_like(a, dtype=torch.bool)
+                if rows:
+                    same[group_of] = False
+                else:
+                    same[1 if t is not hk else slice(None), :, group_of] = False
+                assert torch.equal(a[same], c[same]), (name, at, bad)
+
+
 @pytest.mark.timeout(900)
 def test_chain_backward_at_the_chain_config_on_a_channel_slab():
     """c4_bwd as bench.py times it (B=4, L=32768, D=4096, featurizers of 7 taps, lh=128, groups of 16): the whole
