@@ -89,8 +89,8 @@ __device__ __forceinline__ Quad quad_at(const char* p) { return __builtin_bit_ca
 // NG = groups of 16 steps a filter reaches back; filters of up to 16 NG + 1 taps.  A product with a tap of zero carries a value
 // that is not finite as far as NG reaches, so NG follows the filter (calls with 9 to 33 and 66 to 97 taps are also up to 11%
 // faster than with the 4 or 8 groups of the window).  PF = chunks of loads in flight.  kShard: the call is one rank's share of
-// a sequence (halo rows next to the tensors, batch strides).
-template <int NG, int PF, bool kShard>
+// a sequence (halo rows next to the tensors, batch strides).  kWide: a row is too long for the 24-bit products that place one.
+template <int NG, int PF, bool kShard, bool kWide>
 __global__ __launch_bounds__(2 * kNW * 64, 2) void cp4_bwd_kernel(Cp4BwdArgs a) {
     constexpr int LAG = (NG + 3) / 4;  // chunks between a chunk's arrival and its complete z
     constexpr int NBK = 4 * NG + 1;    // products per group and convolution
@@ -125,7 +125,8 @@ __global__ __launch_bounds__(2 * kNW * 64, 2) void cp4_bwd_kernel(Cp4BwdArgs a) 
     const int ntot = (t_end - t_begin + kT - 1) / kT + LAG;
 
     const int64_t D = a.D;
-    const uint32_t row_bytes = (uint32_t)D * 2;
+    using Off = std::conditional_t<kWide, uint64_t, uint32_t>;  // bytes between rows of a chunk
+    const Off row_bytes = (Off)D * 2;
     const int64_t cblock0 = (int64_t)cb * kC;
     const int64_t seq0 = (kShard ? b * a.sout : b * a.L * D) + cblock0;
     const int64_t seq0kv = kShard ? b * a.skv + cblock0 : seq0, seq0gq = kShard ? b * a.sgq + cblock0 : seq0;
@@ -270,11 +271,11 @@ __global__ __launch_bounds__(2 * kNW * 64, 2) void cp4_bwd_kernel(Cp4BwdArgs a) 
         // ================= z, and all data movement: rows 2 rp, 2 rp + 1 of a chunk, channels 8 lp .. 8 lp + 7
         const int mt = tid - kNW * 64;
         const int lp = mt % PPR, rp = mt / PPR;
-        // Addresses are a uniform base, the first row of a chunk in memory, and a 32-bit byte offset per lane; rows outside
-        // [lo, hi] become the nearest one, so a chunk that lies wholly outside reads one row piece.
+        // Addresses are a uniform base, the first row of a chunk in memory, and a byte offset per lane (of 32 bits, see kWide);
+        // rows outside [lo, hi] become the nearest one, so a chunk that lies wholly outside reads one row piece.
         struct Rows {
-            int64_t base;     // elements from the batch item's start
-            uint32_t off[2];  // bytes
+            int64_t base;  // elements from the batch item's start
+            Off off[2];    // bytes
         };
         auto rows_at = [&](int T, int lo, int hi) {
             int first = L - kT - T;
@@ -287,12 +288,13 @@ __global__ __launch_bounds__(2 * kNW * 64, 2) void cp4_bwd_kernel(Cp4BwdArgs a) 
                 int t = L - 1 - T - 2 * rp - i;
                 t = t > first ? t : first;
                 t = t < hi ? t : hi;
-                r.off[i] = __umul24((uint32_t)(t - first), row_bytes) + 16 * lp;
+                if constexpr (kWide) r.off[i] = (Off)(t - first) * row_bytes + 16 * lp;
+                else r.off[i] = __umul24((uint32_t)(t - first), row_bytes) + 16 * lp;
             }
             return r;
         };
-        auto ld = [](const uint16_t* p, uint32_t off) { return load_words_nt<4>(reinterpret_cast<const char*>(p) + off); };
-        auto st = [](uint16_t* p, uint32_t off, const Words<4>& x) { store_words_nt<4>(reinterpret_cast<char*>(p) + off, x); };
+        auto ld = [](const uint16_t* p, Off off) { return load_words_nt<4>(reinterpret_cast<const char*>(p) + off); };
+        auto st = [](uint16_t* p, Off off, const Words<4>& x) { store_words_nt<4>(reinterpret_cast<char*>(p) + off, x); };
 
         Words<4> yw[PF][2], qw[PF][2], kw[PF][2], vw[PF][2];  // chunk it in stage it % PF
         const int u_lo = t_start > 4 ? t_start - 4 : 0;
@@ -460,7 +462,7 @@ int64_t bwd_rows(const BwdShape& s) {
 }  // namespace
 
 bool cp4_bwd_supported(const BwdShape& s) {
-    return s.gated && s.dtype == HY_BF16 && s.D % 128 == 0 && s.lh > 8 && s.lh <= 129 && s.L <= 0x7fff0000LL && s.D < (1 << 23);
+    return s.gated && s.dtype == HY_BF16 && s.D % 128 == 0 && s.lh > 8 && s.lh <= 129 && s.L <= 0x7fff0000LL && s.D <= 0x7fff0000LL;
 }
 
 int64_t cp4_bwd_workspace_bytes(const BwdShape& s) {
@@ -503,8 +505,10 @@ hy_status launch_cp4_bwd(const BwdPtrs& p, const BwdShape& s, void* ws, hipStrea
     // (dq; dk and dv; dh) on 40 shapes of 64 to 8192 channels and up to 2^25 elements: 1.4 to 2.6 times as fast, nothing slower.
     auto launch = [&](auto ng) {
         constexpr int NG = decltype(ng)::value, PF = NG <= 4 ? 2 : 1;
-        return s.sharded() ? launch_kernel((cp4_bwd_kernel<NG, PF, true>), grid, block, st, a)
-                           : launch_kernel((cp4_bwd_kernel<NG, PF, false>), grid, block, st, a);
+        // rows of 2^24 bytes and more: the shards' kernel (1 x 70 x 2^23, 65 taps 6.4 ms; the general kernel 26.7)
+        if (s.D >= 1 << 23) return launch_kernel((cp4_bwd_kernel<NG, PF, true, true>), grid, block, st, a);
+        return s.sharded() ? launch_kernel((cp4_bwd_kernel<NG, PF, true, false>), grid, block, st, a)
+                           : launch_kernel((cp4_bwd_kernel<NG, PF, false, false>), grid, block, st, a);
     };
     using std::integral_constant;
     const hy_status rc = s.lh <= 17   ? launch(integral_constant<int, 1>{})
