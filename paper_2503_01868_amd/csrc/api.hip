@@ -705,9 +705,7 @@ int64_t chain_bwd_inner_ws(int64_t B, int64_t L, int64_t D, int32_t lf, int32_t 
     const int64_t a = hyena_bwd_workspace_bytes(B, L, D, lh, group, dtype);
     const int64_t b = hyena_featurize_bwd_workspace_bytes(B, L, D, lf, feat_group, dtype);
     if (a < 0 || b < 0) return -1;
-    const ChainShape s{B, L, D, lf, feat_group, lh, group, static_cast<hy_dtype>(dtype)};
-    const int64_t c = chain_bwd_supported(s) ? chain_bwd_workspace_bytes(s) : 0;  // one pass: nothing but this
-    return a > b ? (a > c ? a : c) : (b > c ? b : c);
+    return a > b ? a : b;
 }
 }  // namespace
 
@@ -722,7 +720,10 @@ int64_t hyena_chain_bwd_workspace_bytes(int64_t B, int64_t L, int64_t D, int32_t
     if (L > INT64_MAX / D || B > INT64_MAX / (L * D) || B * L * D > (INT64_MAX / 8) / esz) return -1;
     const int64_t inner = chain_bwd_inner_ws(B, L, D, lf, feat_group, lh, group, dtype);
     if (inner < 0) return -1;
-    return 6 * align256(B * L * D * esz) + inner;
+    const int64_t composition = 6 * align256(B * L * D * esz) + inner;
+    const ChainShape s{B, L, D, lf, feat_group, lh, group, static_cast<hy_dtype>(dtype)};
+    const int64_t one_pass = chain_bwd_supported(s) ? chain_bwd_workspace_bytes(s) : 0;
+    return one_pass > composition ? one_pass : composition;
 }
 
 hy_status hyena_chain_bwd(const void* dy, const void* q, const void* k, const void* v, const float* hq, const float* hk,
@@ -768,7 +769,8 @@ hy_status hyena_chain_bwd(const void* dy, const void* q, const void* k, const vo
     if (rc != HY_OK) return rc;
     char* const ws = static_cast<char*>(workspace);
     const ChainShape cs{B, L, D, lf, feat_group, lh, group, static_cast<hy_dtype>(dtype)};
-    if (chain_bwd_supported(cs))
+    // one pass where its partial filter gradients fit (on sequences of a few steps they are more than the composition needs)
+    if (chain_bwd_supported(cs) && chain_bwd_workspace_bytes(cs) <= workspace_bytes)
         return launch_chain_bwd(ChainBwdPtrs{dy, q, k, v, hq, hk, hv, h, dq, dk, dv, dhq, dhk, dhv, dh}, cs, ws,
                                 static_cast<hipStream_t>(hip_stream));
     void* const qf = ws, * const kf = ws + slot, * const vf = ws + 2 * slot;               // q', k', v'

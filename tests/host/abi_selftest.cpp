@@ -44,6 +44,22 @@ int main() {
     EXPECT(hyena_mr_bwd(P[0], P[1], P[2], P[3], H[0], P[4], P[5], P[4], DH, nullptr, 0, 1, 8, 40, 50, 1, HY_BF16, nullptr), HY_ERR_ALIGN);
     EXPECT(hyena_mr_bwd(P[0], P[1], P[2], P[3], H[0], P[4], P[5], P[6], DH, nullptr, 0, 0, 8, 40, 50, 1, HY_BF16, nullptr), HY_OK);
     if (hyena_bwd_workspace_bytes(1, 8, 16, 3, 1, HY_BF16) != 16 * 3 * 4) ++bad;
+    // the composition's workspace is enough for the chain backward where the one-pass kernel would like more
+    {
+        float* G[4];
+        for (int i = 0; i < 4; ++i) G[i] = DH + 0x40000 * i;
+        const int64_t six = 6 * 256, inner = hyena_featurize_bwd_workspace_bytes(1, 1, 64, 8, 1, HY_BF16);
+        auto chain_bwd = [&](int64_t bytes) {
+            return hyena_chain_bwd(P[0], P[1], P[2], P[3], H[0], H[1], H[2], H[3], P[4], P[5], P[6], G[0], G[1], G[2], G[3], P[7],
+                                   bytes, 1, 1, 64, 8, 1, 9, 16, HY_BF16, nullptr);
+        };
+        const int before = bad;
+        if (hyena_chain_bwd_workspace_bytes(1, 1, 64, 8, 1, 9, 16, HY_BF16) <= six + inner) ++bad;
+        EXPECT(chain_bwd(hyena_chain_bwd_workspace_bytes(1, 1, 64, 8, 1, 9, 16, HY_BF16)), HY_OK);
+        EXPECT(chain_bwd(six + inner), HY_OK);
+        EXPECT(chain_bwd(six + inner - 1), HY_ERR_SHAPE);
+        std::printf("chain backward's workspace: %d problem(s)\n", bad - before);
+    }
     // a filter table or the filter gradient inside a written activation
     EXPECT(hyena_se_fwd(P[0], P[1], P[2], reinterpret_cast<const float*>(P[3]), P[3], 1, 8, 16, 3, 1, HY_BF16, nullptr), HY_ERR_ALIGN);
     EXPECT(hyena_se_bwd(P[0], P[1], P[2], P[3], H[0], P[4], P[5], P[6], reinterpret_cast<float*>(P[5]), P[7], 1 << 16, 1, 8, 16, 3, 1, HY_BF16, nullptr), HY_ERR_ALIGN);

@@ -251,6 +251,11 @@ def test_chain_backward_rejects_bad_arguments_and_sizes_its_workspace():
     wb = lib.hyena_chain_bwd_workspace_bytes
     assert wb(0, 8, 16, 3, 1, 5, 1, 1) == 0 and wb(1, 8, 16, 0, 1, 5, 1, 1) == -1 and wb(1, 8, 16, 3, 5, 5, 1, 1) == -1
     assert wb(1, 8, 16, 3, 1, 5, 1, 9) == -1
+    # the one-pass kernel's shapes need no more than the composition, but for sequences of a few steps
+    for B, L, D, lf, lh, group in ((2, 33, 128, 7, 9, 16), (1, 8192, 4096, 7, 128, 16), (3, 700, 64, 5, 65, 32)):
+        slot = (B * L * D * 2 + 255) // 256 * 256
+        assert wb(B, L, D, lf, 1, lh, group, 1) == 6 * slot + max(lib.hyena_bwd_workspace_bytes(B, L, D, lh, group, 1),
+                                                                  lib.hyena_featurize_bwd_workspace_bytes(B, L, D, lf, 1, 1))
     # six tensors of 2 GiB-ish each plus the inner calls' share
     assert wb(4, 32768, 4096, 7, 1, 128, 16, 1) >= 6 * 4 * 32768 * 4096 * 2
 
