@@ -397,6 +397,15 @@ int64_t hyena_li_workspace_bytes(int64_t B, int64_t L, int64_t D, int32_t order,
     return li_workspace_bytes(s);
 }
 
+namespace {
+// The problem as the scan takes it with `bytes` of workspace: where its usual choice of tiles needs more records, the one with
+// the fewest.
+LiShape li_within(LiShape s, int64_t bytes) {
+    s.fewest = li_workspace_bytes(s) > bytes;
+    return s;
+}
+}  // namespace
+
 hy_status hyena_li_fwd(const void* q, const void* k, const void* v, const float* R, const float* lambda, void* y,
                        void* workspace, int64_t workspace_bytes, int64_t B, int64_t L, int64_t D, int32_t order,
                        int32_t group, int32_t dtype, void* hip_stream) {
@@ -410,6 +419,7 @@ hy_status hyena_li_fwd(const void* q, const void* k, const void* v, const float*
     LiPtrs p{q, k, v, R, lambda, y};
     LiShape s{B, L, D, order, group, static_cast<hy_dtype>(dtype)};
     if (li_mfma_supported(s)) {
+        s = li_within(s, workspace_bytes);
         const int64_t bytes = B * L * D * 2;
         const int64_t nf = filter_bytes(D, group, order);
         const Range others[6] = {{q, bytes}, {k, bytes}, {v, bytes}, {y, bytes}, {R, nf}, {lambda, nf}};
@@ -434,6 +444,7 @@ hy_status hyena_li_fwd_carry(const void* q, const void* k, const void* v, const 
     // states exist in the matrix-core scan only; an empty call would have to copy state_in to state_out
     if (!li_mfma_supported(s) || empty(B, L, D)) return HY_ERR_UNSUPPORTED;
     if (state_out && L % 32 != 0) return HY_ERR_UNSUPPORTED;
+    s = li_within(s, workspace_bytes);
     const int64_t bytes = B * L * D * 2;
     const int64_t nf = filter_bytes(D, group, order);
     const int64_t sb = B * D * 64;  // bytes of a state: B * (D / 16) records of 256 floats

@@ -120,6 +120,7 @@ struct LiShape {
     int64_t B, L, D;
     int32_t order, group;
     hy_dtype dtype;
+    bool fewest = false;  // the choice of tiles with the fewest records, where a faster one needs more workspace
 };
 
 struct Tuning {

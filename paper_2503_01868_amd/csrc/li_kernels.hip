@@ -758,7 +758,7 @@ int li_waves(const LiShape& s, bool state_only = false) {
     // 62 / 52, 3 x 2500 x 4096 57 / 52; but not while they are short against their number (27593 x 768, 79 tiles of 352 steps,
     // 57 / 62; 13375 x 1280, 47 of 288, 48 / 51; but 24680 x 1024, 60 of 416, 64 / 57), nor two of them where 128-channel workgroups walk the sequence as one tile
     // (3 x 562 x 8192 29 / 32, 5 x 746 x 5120 37 / 40).  Up to 256 steps 8 waves keep theirs as well: 4096 x 4096 34 against 37.
-    if (!state_only && tuning().mr_waves == 0 && tuning().mr_rows == 0 && s.D % 256 == 0 && li_rows(s, 16) > 8 * kChunk &&
+    if (!state_only && !s.fewest && tuning().mr_waves == 0 && tuning().mr_rows == 0 && s.D % 256 == 0 && li_rows(s, 16) > 8 * kChunk &&
         li_one_pass(s, 16)) {
         const int64_t rows = li_rows(s, 16), tiles = (s.L + rows - 1) / rows;
         if (rows >= 160 + 3 * tiles && (tiles > 2 || li_rows(s, 8) < s.L)) return 16;

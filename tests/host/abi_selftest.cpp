@@ -60,6 +60,22 @@ int main() {
         EXPECT(chain_bwd(six + inner - 1), HY_ERR_SHAPE);
         std::printf("chain backward's workspace: %d problem(s)\n", bad - before);
     }
+    // Hyena-LI: enough for the choice with the fewest records is enough
+    {
+        const int before = bad;
+        auto li = [&](int64_t bytes, int64_t L) {
+            return hyena_li_fwd(P[0], P[1], P[2], H[0], H[1], P[3], bytes > 0 ? P[7] : nullptr, bytes, 1, L, 64, 16, 16, HY_BF16, nullptr);
+        };
+        if (hyena_li_workspace_bytes(1, 2048, 64, 16, 16, HY_BF16) != 3 * 4096) ++bad;
+        EXPECT(li(3 * 4096, 2048), HY_OK);
+        EXPECT(li(3 * 4096 - 1, 2048), HY_OK);
+        EXPECT(li(4096, 2048), HY_OK);
+        EXPECT(li(4095, 2048), HY_ERR_SHAPE);
+        EXPECT(li(0, 1024), HY_OK);  // (one tile)
+        EXPECT(hyena_li_fwd_carry(P[0], P[1], P[2], H[0], H[1], P[3], nullptr, nullptr, P[7], 4096, 1, 2048, 64, 16, 16, HY_BF16, nullptr), HY_OK);
+        EXPECT(hyena_li_fwd_carry(P[0], P[1], P[2], H[0], H[1], P[3], nullptr, nullptr, P[7], 4095, 1, 2048, 64, 16, 16, HY_BF16, nullptr), HY_ERR_SHAPE);
+        std::printf("Hyena-LI's workspace: %d problem(s)\n", bad - before);
+    }
     // a filter table or the filter gradient inside a written activation
     EXPECT(hyena_se_fwd(P[0], P[1], P[2], reinterpret_cast<const float*>(P[3]), P[3], 1, 8, 16, 3, 1, HY_BF16, nullptr), HY_ERR_ALIGN);
     EXPECT(hyena_se_bwd(P[0], P[1], P[2], P[3], H[0], P[4], P[5], P[6], reinterpret_cast<float*>(P[5]), P[7], 1 << 16, 1, 8, 16, 3, 1, HY_BF16, nullptr), HY_ERR_ALIGN);

@@ -14,7 +14,10 @@ hy_status launch_cp4(const ConvPtrs&, const ConvShape& s, hipStream_t) { return 
 bool cp_mfma_supported(const ConvShape& s) { return s.dtype == HY_BF16 && s.gated && s.D % 64 == 0 && s.lh <= 145; }
 hy_status launch_cp_mfma(const ConvPtrs&, const ConvShape& s, hipStream_t) { return cp_mfma_supported(s) ? HY_OK : HY_ERR_UNSUPPORTED; }
 bool li_mfma_supported(const LiShape& s) { return s.dtype == HY_BF16 && s.group % 16 == 0 && s.D % 64 == 0 && s.order <= 16; }
-int64_t li_workspace_bytes(const LiShape& s) { return li_mfma_supported(s) ? s.B * ((s.L + 511) / 512 - 1) * (s.D / 16) * 1024 : 0; }
+int64_t li_workspace_bytes(const LiShape& s) {
+    const int64_t rows = s.fewest ? 1024 : 512;
+    return li_mfma_supported(s) ? s.B * ((s.L + rows - 1) / rows - 1) * (s.D / 16) * 1024 : 0;
+}
 hy_status launch_li_mfma(const LiPtrs&, const LiShape&, void*, hipStream_t) { return HY_OK; }
 hy_status launch_li_direct(const LiPtrs&, const LiShape& s, hipStream_t) { return s.order <= 64 ? HY_OK : HY_ERR_UNSUPPORTED; }
 int64_t li_state_workspace_bytes(const LiShape& s) { return li_mfma_supported(s) ? s.B * ((s.L + 511) / 512) * (s.D / 16) * 1024 : 0; }

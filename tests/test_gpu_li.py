@@ -425,3 +425,30 @@ def test_one_pass_with_values_that_are_not_finite():
     y = host(binding.hyena_li_fwd(*[dev(x) for x in (q, k, v, R, lam)], 16))
     assert np.isnan(y[0, 704:, 5]).all()
     assert np.array_equal(y[0, :672], clean[0, :672]) and np.array_equal(y[0, :, 16:], clean[0, :, 16:])
+
+
+@pytest.mark.parametrize("B,L,D,most,least", [(8, 2533, 1536, 8 * 4, 0), (1, 5500, 4096, 15, 7)])
+def test_a_workspace_for_the_fewest_records_is_enough(B, L, D, most, least):
+    """Where the usual choice of tiles needs more records than another one, a call with room for the other's takes that."""
+    need = binding.lib().hyena_li_workspace_bytes(B, L, D, 16, 16, binding.HY_BF16)
+    record = D // 16 * 1024
+    say("li workspace %d x %d x %d: %d records" % (B, L, D, need // record))
+    assert need == most * record
+    g = torch.Generator(device="cuda").manual_seed(73)
+    q, k, v = (torch.randn((B, L, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    R = torch.randn((D // 16, 16), generator=g, device="cuda") / 4
+    lam = torch.rand((D // 16, 16), generator=g, device="cuda")
+    want = binding.hyena_li_fwd(q, k, v, R, lam, 16)
+    y = torch.full_like(q, float("nan"))
+    ws = torch.empty(max(16, least * record), dtype=torch.uint8, device="cuda")
+
+    def call(records):
+        return binding.lib().hyena_li_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), R.data_ptr(), lam.data_ptr(), y.data_ptr(),
+                                          ws.data_ptr() if records else None, records * record, B, L, D, 16, 16, binding.HY_BF16,
+                                          torch.cuda.current_stream().cuda_stream)
+
+    if least:
+        assert call(least - 1) == 2
+    assert call(least) == 0
+    # other tiles, the same sums in another order: a bf16 unit of the largest output at most
+    assert oracle.rel_err(host(y), host(want).astype(np.float64)) <= 2.0 ** -7

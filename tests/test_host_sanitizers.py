@@ -46,3 +46,4 @@ def test_abi_host_logic_under_asan_ubsan(tmp_path):
     assert "AddressSanitizer" not in out and "runtime error" not in out, out[-3000:]
     assert "abi selftest:" in res.stdout, out[-3000:]
     assert "chain backward's workspace: 0 problem(s)" in res.stdout, out[-3000:]
+    assert "Hyena-LI's workspace: 0 problem(s)" in res.stdout, out[-3000:]
