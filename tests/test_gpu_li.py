@@ -392,6 +392,13 @@ ONE_PASS_CASES = [
 ]
 
 
+def is_one_pass(B, L, D, waves, rows):
+    """The dispatch's rule, as li_kernels.hip states it, where the options give the workgroup's width and the tile's length."""
+    tiles = (L + rows - 1) // rows
+    assert binding.lib().hyena_li_workspace_bytes(B, L, D, 16, 16, binding.HY_BF16) == B * (tiles - 1) * (D // 16) * 1024
+    return tiles > 1 and rows <= 512 and rows * waves >= 64 * tiles
+
+
 @pytest.mark.parametrize("case", ONE_PASS_CASES)
 def test_one_pass_waits_for_states_or_walks_to_the_same_ones(case):
     """One pass against the definition (a row past the last chunk's included), and bit for bit against the same pass with
@@ -399,6 +406,7 @@ def test_one_pass_waits_for_states_or_walks_to_the_same_ones(case):
     B, L, D, order, waves, rows = case
     binding.set_option("mr_waves", waves)
     binding.set_option("mr_rows", rows)
+    assert is_one_pass(B, L, D, waves, rows)
     say("one pass B=%d L=%d D=%d order=%d waves=%d rows=%d" % case)
     q, k, v, R, lam = draw_li(71, B, L, D, order, 16, "bf16")
     args = [dev(x) for x in (q, k, v, R, lam)]
@@ -415,16 +423,30 @@ def test_one_pass_waits_for_states_or_walks_to_the_same_ones(case):
     assert torch.equal(y[0], y[2])  # the same states and the same products
 
 
-def test_one_pass_with_values_that_are_not_finite():
-    """A record of NaNs is a record like any other: outputs after a NaN are NaN, those before it and of other channels of
-    other blocks are what they were."""
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_one_pass_with_values_that_are_not_finite(bad):
+    """A record of NaNs or infinities is a record like any other, whether waited for or computed again: outputs after such a
+    value are not finite, those before its chunk and of other groups are what they were."""
     B, L, D = 1, 2048, 256
+    binding.set_option("mr_waves", 16)
+    binding.set_option("mr_rows", 256)
+    assert is_one_pass(B, L, D, 16, 256)
     q, k, v, R, lam = draw_li(72, B, L, D, 16, 16, "bf16")
-    clean = host(binding.hyena_li_fwd(*[dev(x) for x in (q, k, v, R, lam)], 16))
-    k[0, 700, 5] = float("nan")
-    y = host(binding.hyena_li_fwd(*[dev(x) for x in (q, k, v, R, lam)], 16))
-    assert np.isnan(y[0, 704:, 5]).all()
-    assert np.array_equal(y[0, :672], clean[0, :672]) and np.array_equal(y[0, :, 16:], clean[0, :, 16:])
+    lam[:, 0] = 1.0  # (an infinity does not decay)
+    args = [dev(x) for x in (q, k, v, R, lam)]
+    clean = host(binding.hyena_li_fwd(*args, 16))
+    args[1][0, 700, 5] = bad
+    y = {}
+    try:
+        for wait in (0, 1, 2):
+            binding.set_option("li_wait", wait)
+            y[wait] = host(binding.hyena_li_fwd(*args, 16))
+    finally:
+        binding.set_option("li_wait", 0)
+    assert not np.isfinite(y[0][0, 704:, 5]).any()
+    assert np.array_equal(y[0][0, :672], clean[0, :672]) and np.array_equal(y[0][0, :, 16:], clean[0, :, 16:])
+    for wait in (1, 2):
+        assert np.array_equal(y[0], y[wait], equal_nan=True)
 
 
 @pytest.mark.parametrize("B,L,D,most,least", [(8, 2533, 1536, 8 * 4, 0), (1, 5500, 4096, 15, 7)])
