@@ -288,9 +288,10 @@ hy_status hyena_chain_fwd_shard(const void *q, const void *k, const void *v, con
  * from the same Toeplitz operands applied to a window of u blocks, a few chunks late; dh is a second MFMA
  * contraction over the channels of a group (u and g = dy*q are rounded to bf16 for it, partial sums stay fp32).
  * Medium bf16 filters that are not shared by 16 channels (any other group size, D a multiple of 128, 8 < lh <= 129)
- * run chunk-parallel on the matrix cores (App. A.1): dq is the forward operator applied to (dy, k, v), dk and dv the
- * same kernel walking towards the past on g = dy*q (one launch each), dh a per-channel correlation of g and u on
- * the batched 4x4 matrix instruction (g and u rounded to bf16, partial sums fp32).
+ * run chunk-parallel on the matrix cores (App. A.1), in ONE pass as well: du, z and the correlation for dh are per-channel
+ * products on the batched 4x4 matrix instruction (u, g and the filter rounded to bf16, partial sums fp32).
+ * On both a value that is not finite also meets structural zeros: it reaches as far as the filter, rounded up to blocks of 32
+ * steps and 16 channels, or of 16 steps of its own channel.
  * Everything else runs a general fp32 kernel.
  * hyena_se_bwd and hyena_mr_bwd are the same operation and differ only in which shapes they are tuned for.
  */
@@ -329,16 +330,18 @@ int64_t hyena_featurize_bwd_workspace_bytes(int64_t B, int64_t L, int64_t D, int
  * Backward of hyena_chain_fwd (Eq. 1 as a whole: q' = hq * q, k' = hk * k, v' = hv * v, y = q' (.) (h * (k' (.) v')))
  * by the chain rule.  bf16 with an inner filter of 9 to 129 taps shared by a multiple of 16 channels, featurizers of up to 8
  * taps and D % 64 == 0 (D < 2^23): one kernel that reads dy, q, k, v and writes dq, dk, dv once; u = k' (.) v', g = dy (.) q',
- * dq', dk', dv' and, where they gate du, k' and v' are rounded to bf16 on chip.  Everything else is a composition of the calls
- * above on the caller's stream: hyena_featurize3_fwd recomputes q', k', v'; hyena_mr_bwd gives dq', dk', dv' and dh; the
+ * dq', dk', dv' and, where they gate du, k' and v' are rounded to bf16 on chip, h is rounded to bf16, and a tap of hq, hk, hv
+ * enters as in hyena_chain_fwd, as a bf16 head plus a bf16 remainder (16 mantissa bits).  Everything else is a composition of
+ * the calls above on the caller's stream: hyena_featurize3_fwd recomputes q', k', v'; hyena_mr_bwd gives dq', dk', dv' and dh; the
  * operation of hyena_featurize_bwd on the three tensors gives dq, dk, dv and dhq, dhk, dhv (in one launch for filters of up to
  * 8 taps, in bf16 on even widths, on tensors of up to 2^27 elements whose partial filter gradients fit the memory of
  * q', k', v', else in three).  Its intermediate tensors live in the workspace in the activations' dtype (for bf16 they are
  * rounded to bf16 between the steps, as the forward's two-kernel path rounds q', k', v').
  * dy, q, k, v, dq, dk, dv: device, [B, L, D] of `dtype`; hq, hk, hv, dhq, dhk, dhv: fp32 [D/feat_group, lf];
  * h, dh: fp32 [D/group, lh]; the usual alignment and overlap rules (every gradient distinct from everything else).
- * workspace: hyena_chain_bwd_workspace_bytes(...) bytes (six tensors plus what the inner calls need, whichever way), 16-byte
- * aligned, disjoint from every argument; too small: HY_ERR_SHAPE.  An empty problem writes zero filter gradients.
+ * workspace: hyena_chain_bwd_workspace_bytes(...) bytes, 16-byte aligned, disjoint from every argument: what the composition
+ * needs (six tensors plus the inner calls' share) or, on sequences of a few steps where they are more, the one kernel's partial
+ * filter gradients; less than the composition needs: HY_ERR_SHAPE; in between the call runs as the composition.  An empty problem writes zero filter gradients.
  */
 hy_status hyena_chain_bwd(const void *dy, const void *q, const void *k, const void *v, const float *hq,
                           const float *hk, const float *hv, const float *h, void *dq, void *dk, void *dv,
