@@ -9,8 +9,8 @@ A step is one pass of the hot path over one synthetic batch that already sits in
   c3  Hyena-MR  bf16 B1 L131072 D4096 lh128 group16  hyena_mr_fwd
   c4  chain     bf16 B4 L32768  D4096                hyena_chain_fwd (featurizers + MR in one kernel)
   c1_bwd / c2_bwd / c3_bwd / c2u_bwd: the backward entry points (hyena_se_bwd / hyena_mr_bwd) on the shapes of
-      c1 / c2 / c3 / c2u; c4_bwd: hyena_chain_bwd on c4's shape (featurizers recomputed, inner backward, three
-      featurizer backward calls; 6 tensors of workspace); c4_feat: the three featurizer convolutions of c4 alone
+      c1 / c2 / c3 / c2u; c4_bwd: hyena_chain_bwd on c4's shape (one kernel, the reductions of the
+      filter gradients, and a workspace of 6 tensors, the composition's); c4_feat: the three featurizer convolutions of c4 alone
       (hyena_featurize3_fwd, 12 bytes per element: three tensors read and written)
   c1_shards / c2_shards / c3_shards: c1 / c2 / c3 computed as four consecutive sequence shards (hyena_se_fwd_shard /
       hyena_mr_fwd_shard: each call sees its quarter of the steps plus the lh - 1 rows of k and v before it), the
@@ -373,7 +373,7 @@ def entry_point(wl):
     if wl.feat:
         return "hyena_featurize3_fwd"
     name = {"se": "hyena_se_fwd", "mr": "hyena_mr_fwd", "chain": "hyena_chain_fwd",
-            "li": "hyena_li_fwd (both passes of the scan)"}[wl.cfg["kind"]]
+            "li": "hyena_li_fwd (all launches of the entry point)"}[wl.cfg["kind"]]
     if wl.bwd:
         name = name.replace("_fwd", "_bwd")
     if wl.shards:
