@@ -31,10 +31,12 @@
 // same places and runs the featurizers of chunk j+1; the second runs chunk j and the third z, dq of chunk j-LAG; one barrier.
 //
 // What bounds it: 7 tensor passes through 128-byte row pieces (98 us at the rate of a large copy), and the LDS, whose pipe is
-// busy for half of the time: every value crosses it several times.  1 x 8192 x 4096, 128 and 7 taps, whole call: 300 us as a
-// composition, 135 here; 4 x 32768 x 4096 4448 -> 1962.  On the way there: 8 waves of two kinds 162 us (too few waves to
-// cover LDS latency between dependent products), twelve 156, record skews that keep the three ways of reading apart 143,
-// whole quads instead of each row's own dwords for H 139, transposed instead of 2-byte reads for the filter gradient 135.
+// the busiest unit on chip (42% of the time at 1 x 8192 x 4096, 55% at 4 x 32768 x 4096; vector ALUs 37 and 47%, matrix cores 25
+// and 35%): every value crosses it several times.  128 and 7 taps, whole call: 1 x 8192 x 4096 301 us as a composition, 140 here;
+// 4 x 32768 x 4096 4448 -> 1953.  On the way there, before values that are not finite had a path of their own: 8 waves of two
+// kinds 162 us (too few waves to cover LDS latency between dependent products), twelve 156, record skews that keep the three
+// ways of reading apart 143, whole quads instead of each row's own dwords for H 139, transposed instead of 2-byte reads for the
+// filter gradient 135.
 #include <type_traits>
 
 #include "hy_common.hpp"

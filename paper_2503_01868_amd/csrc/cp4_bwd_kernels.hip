@@ -24,8 +24,9 @@
 // window 72, accumulators 36), four run z (operands 66, window 72) and move all data; one wave with everything does not
 // fit 512 registers.  The pair issues 102 products per group and SIMD, so vector instructions between them count: windows
 // formed from one read by selects and rotations inside lane quads, and H from neighbouring quads likewise, took 40
-// instructions per group more and 160 us a call against 126 at 1 x 8192 x 4096, 128 taps (three launches: 217); 123 since
-// a wave divides once for all its filters.
+// instructions per group more and 160 us a call against 126 at 1 x 8192 x 4096, 128 taps (three launches: 217); a wave that
+// divides once for all its filters saves 3 more (126 on average over a trace of 970 calls, the reduction's 5 among them; matrix
+// cores 36%, vector ALUs 39%, LDS 29% busy; traffic 1.05 x).
 //
 // Time goes in chunks of 64 steps, one barrier each.  In iteration j the first four waves multiply chunk j and gate du with
 // the chunk's k and v lines, dk and dv over k and v in place; the other four store dk, dv of chunk j - 1 and dq of chunk

@@ -363,7 +363,8 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 2) void li_mfma_kernel(LiAr
 // 12.  The states are those of the two passes above, bit for bit.
 //
 // What bounds it: the 4-tensor stream through 512-byte strips (44.4 us at 8192 x 4096) in two phases, and between them the
-// wait, the operands of the second and the records' launch: 57 us where two passes take 76.
+// wait, the operands of the second and the records' launch (4.9): 57 us a call where two passes take 76, in a row of calls that
+// share their inputs; 60 with inputs that change from call to call.
 //
 // The wait is per wave and per record, without flags or fences: li_mark_kernel has filled the records with kUnset, a NaN that
 // no state ever is (a producer that holds it stores the plain NaN), every word is stored and loaded as an atomic at device
