@@ -14,7 +14,8 @@
 //    (for z), the last lh values of g (du is finished lh-1 steps late, when the newest g it needs has
 //    arrived), a delay line of k and v for that lag, and VEC*lh partial sums for dh.  A tile reads lh-1
 //    halo rows of k, v before its start and lh-1 halo rows of dy, q after its end.
-//  * any other lh, group or width, both dtypes: dq, dk, dv by the general FIR kernel (direct_kernels.hip) in both time
+//  * any other lh, group or width, both dtypes: dq, dk, dv by the general FIR kernels (split_kernels.hip where 8 channels
+//    share a filter of more than 32 taps, else direct_kernels.hip) in both time
 //    directions, dh by dh_tile_kernel (where its partial sums do not fit or samples are few: dh_direct_kernel).
 //
 // kGated = false turns both paths into the backward of the featurizer convolutions of Eq. 1 (x' = h * x, no
@@ -811,6 +812,10 @@ hy_status launch_direct_t(const BwdPtrs& p, const BwdShape& s, hipStream_t st) {
     f[1].stride_out = s.stride_out();
     f[1].lo = -(int64_t)s.history;
     f[1].hi = s.L;
+    if (s.gated) {
+        rc = launch_split_fir(f, 2, s.B, s.L, s.D, s.lh, s.group, s.dtype, st);
+        if (rc != HY_ERR_UNSUPPORTED) return rc;
+    }
     return launch_fir(f, s.gated ? 2 : 1, s.B, s.L, s.D, s.lh, s.group, s.dtype, st);
 }
 

@@ -209,6 +209,13 @@ __device__ __forceinline__ void toeplitz_operands(bf16x8_t (&tz)[N], const float
     }
 }
 
+// Launch index i of n -> tile index such that each XCD (workgroups are dealt to the 8 of them round-robin) has one run of
+// consecutive tiles.
+__device__ __forceinline__ uint32_t xcd_contiguous(uint32_t i, uint32_t n) {
+    const uint32_t x = i % 8, q = n / 8, r = n % 8;
+    return x * q + (x < r ? x : r) + i / 8;
+}
+
 // Note on workgroup order: workgroups are dealt to the 8 XCDs round-robin by launch index.  Every kernel
 // here keeps the plain launch order with the fastest-varying tile index along a row, so that all XCDs
 // sweep one compact address window together; giving each XCD its own contiguous range of tiles was
