@@ -31,6 +31,7 @@ namespace {
 
 // ------------------------------------------------------------------------------------- stencil
 constexpr int kMaxProb = 3;  // problems of one shape per launch (the three featurizers of a chain)
+constexpr int kMaxReduce = 4;  // filter gradients per reduction (those and the inner filter's)
 
 struct BwdStencilArgs {
     BwdPtrs p[kMaxProb];
@@ -227,32 +228,44 @@ __global__ __launch_bounds__(kBlock) void bwd_stencil_kernel(BwdStencilArgs a) {
 // order.  Deterministic, no atomics.  The sums run in fp64 (the adds are a negligible part of this kernel), so the
 // reduction adds no rounding of its own to the fp32 partials.  With few terms per output (up to 8: single channels and
 // a handful of tiles) one lane sums them all, all its loads in flight at once, no exchange.
+// The items of a launch (blockIdx.y) have shapes and lanes per output of their own.
+struct ReduceItem {
+    const float* partial;
+    float* dh;
+    int64_t nsets, rows;  // partial sets; rows of a set
+    int32_t lh, group, parts;
+};
 struct ReduceArgs {
-    const float* partial[kMaxProb];
-    float* dh[kMaxProb];
+    ReduceItem p[kMaxReduce];
 };
 
+// a / b, in 32 bits where a fits them: a 64-bit division is a good part of this kernel
+__device__ __forceinline__ int64_t quotient(int64_t a, int32_t b) {
+    return a <= 0xffffffffLL ? (int64_t)((uint32_t)a / (uint32_t)b) : a / b;
+}
+
 template <int kRedParts>
-__global__ __launch_bounds__(kBlock) void dh_reduce_kernel(ReduceArgs a, int64_t nsets, int64_t D, int32_t lh,
-                                                           int32_t group) {
-    const float* __restrict__ partial = a.partial[blockIdx.y];
-    float* __restrict__ dh = a.dh[blockIdx.y];
+__device__ __forceinline__ void reduce_item(const ReduceItem& it, double* red) {
+    const float* __restrict__ partial = it.partial;
+    float* __restrict__ dh = it.dh;
+    const int64_t D = it.rows;
+    const int32_t lh = it.lh, group = it.group;
     constexpr int kRedOut = kBlock / kRedParts;
-    __shared__ double red[kRedParts][kRedOut];
     const int o = threadIdx.x % kRedOut, part = threadIdx.x / kRedOut;
     const int64_t idx = (int64_t)blockIdx.x * kRedOut + o;  // (g, j)
-    const int64_t n = (D / group) * lh;
+    const int64_t n = quotient(D, group) * lh;
+    if ((int64_t)blockIdx.x * kRedOut >= n) return;
     const int64_t idc = idx < n ? idx : n - 1;  // lanes past the end repeat the last output and do not store
-    const int64_t g = idc / lh, j = idc % lh;
+    const int64_t g = quotient(idc, lh), j = idc - g * lh;
     const float* base = partial + (g * group) * lh + j;
-    const int64_t total = nsets * group;
+    const int64_t total = it.nsets * group;
     const int64_t per = (total + kRedParts - 1) / kRedParts;
     const int64_t lo = part * per, hi = lo + per < total ? lo + per : total;
     double s = 0.0;
     // term x = set * group + c lives at base[set * D * lh + c * lh]; the offset is advanced term by term (one
     // division per lane instead of two per term).  Eight loads in flight at a time (they do not depend on the
     // running sum); past the end the last offset repeats, so that the loads stay unconditional.
-    const int64_t set0 = lo / group;
+    const int64_t set0 = quotient(lo, group);
     int32_t c = (int32_t)(lo - set0 * group);
     int64_t cur = set0 * (D * lh) + (int64_t)c * lh;
     const int64_t wrap = D * lh - (int64_t)(group - 1) * lh;
@@ -278,13 +291,24 @@ __global__ __launch_bounds__(kBlock) void dh_reduce_kernel(ReduceArgs a, int64_t
         if (idx < n) dh[idx] = (float)s;
         return;
     }
-    red[part][o] = s;
+    red[part * kRedOut + o] = s;
     __syncthreads();
     if (part == 0 && idx < n) {
-        double t = red[0][o];
+        double t = red[o];
 #pragma unroll 8
-        for (int r = 1; r < kRedParts; ++r) t += red[r][o];
+        for (int r = 1; r < kRedParts; ++r) t += red[r * kRedOut + o];
         dh[idx] = (float)t;
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void dh_reduce_kernel(ReduceArgs a) {
+    __shared__ double red[kBlock];
+    const ReduceItem it = a.p[blockIdx.y];
+    switch (it.parts) {
+        case 1: return reduce_item<1>(it, red);
+        case 32: return reduce_item<32>(it, red);
+        case 256: return reduce_item<256>(it, red);
+        default: return reduce_item<4>(it, red);
     }
 }
 
@@ -551,20 +575,20 @@ __global__ __launch_bounds__(kBlock) void dh_tile_reduce_kernel(DhArgs a, int64_
     constexpr int kOut = kBlock / kParts;
     __shared__ double red[kParts][kOut];
     const int o = threadIdx.x % kOut, part = threadIdx.x / kOut;
-    const int64_t n = (a.D / a.group) * a.lh;
+    const int64_t n = quotient(a.D, a.group) * a.lh;
     const int64_t idx = (int64_t)blockIdx.x * kOut + o;
     const int64_t idc = idx < n ? idx : n - 1;
-    const int64_t g = idc / a.lh, j = idc % a.lh;
+    const int64_t g = quotient(idc, a.lh), j = idc - g * a.lh;
     const int32_t rpg = a.group / a.fold;               // partial rows per group
-    const int64_t tile_len = (a.D / a.fold) * a.lh;
+    const int64_t tile_len = quotient(a.D, a.fold) * a.lh;
     const int64_t per_item = (int64_t)a.tiles_per_seq * rpg, total = B * per_item;
     const int64_t per = (total + kParts - 1) / kParts;
     const int64_t lo = part * per, hi = lo + per < total ? lo + per : total;
     auto tile_row = [&](int64_t b, int32_t t) { return dh_scratch<T>(a.p.dk, b, a.sout) + t * tile_len + g * rpg * a.lh + j; };
     double s = 0.0;
     if (lo < hi) {
-        int64_t b = lo / per_item;
-        int32_t t = (int32_t)((lo - b * per_item) / rpg), c = (int32_t)(lo - b * per_item - (int64_t)t * rpg);
+        int64_t b = total <= 0xffffffffLL ? (int64_t)((uint32_t)lo / (uint32_t)per_item) : lo / per_item;
+        int32_t t = (int32_t)quotient(lo - b * per_item, rpg), c = (int32_t)(lo - b * per_item - (int64_t)t * rpg);
         const double* cur = tile_row(b, t) + (int64_t)c * a.lh;
         for (int64_t x0 = lo; x0 < hi; x0 += 8) {  // past the end the last term is read again, not added
             double v[8];
@@ -698,22 +722,20 @@ int stencil_rows(const BwdShape& s, int64_t nvec) {
 template <typename T>
 constexpr int stencil_vec() { return T::kBytes == 2 ? 2 : 1; }
 
-hy_status launch_reduce(const ReduceArgs& r, int nprob, int64_t nsets, int64_t n_rows, int32_t lh, int32_t group,
-                        hipStream_t st) {
-    const int64_t nout = (n_rows / group) * lh;
-    if (nout == 0) return HY_OK;
-    auto go = [&](void (*kernel)(ReduceArgs, int64_t, int64_t, int32_t, int32_t), int64_t parts) {
-        const int64_t per = kBlock / parts;
-        return launch_kernel(kernel, dim3((uint32_t)((nout + per - 1) / per), (uint32_t)nprob), dim3(kBlock), st, r, nsets,
-                             n_rows, lh, group);
-    };
-    const int64_t terms = nsets * group;
-    if (terms <= 8) return go(dh_reduce_kernel<1>, 1);
-    switch (reduce_parts(nout, terms)) {
-        case 256: return go(dh_reduce_kernel<256>, 256);
-        case 32: return go(dh_reduce_kernel<32>, 32);
-        default: return go(dh_reduce_kernel<4>, 4);
+hy_status launch_reduce(const DhReduce* items, int n, hipStream_t st) {
+    ReduceArgs r{};
+    int64_t nb = 0;
+    for (int i = 0; i < n; ++i) {
+        const DhReduce& x = items[i];
+        const int64_t nout = (x.rows / x.group) * x.lh, terms = x.nsets * x.group;
+        const int parts = terms <= 8 ? 1 : reduce_parts(nout, terms);
+        r.p[i] = ReduceItem{x.partial, x.dh, x.nsets, x.rows, x.lh, x.group, parts};
+        const int64_t per = kBlock / parts, blocks = (nout + per - 1) / per;
+        nb = blocks > nb ? blocks : nb;
     }
+    if (nb == 0) return HY_OK;
+    if (nb > 0x7fffffffLL) return HY_ERR_UNSUPPORTED;
+    return launch_kernel(dh_reduce_kernel, dim3((uint32_t)nb, (uint32_t)n), dim3(kBlock), st, r);
 }
 
 template <typename T, int LH>
@@ -745,12 +767,9 @@ hy_status launch_stencil_lh(const BwdPtrs* p, const BwdShape& s, void* ws, hipSt
         : launch_kernel((bwd_stencil_kernel<T, VEC, LH, R, false>), dim3((uint32_t)nb, (uint32_t)s.nprob), dim3(kBlock), st, a);
     if (rc != HY_OK) return rc;
     const int64_t nsets = s.B * a.tiles_per_seq;
-    ReduceArgs r;
-    for (int i = 0; i < kMaxProb; ++i) {
-        r.partial[i] = a.partial[i];
-        r.dh[i] = a.p[i].dh;
-    }
-    return launch_reduce(r, s.nprob, nsets, s.D, s.lh, s.group, st);
+    DhReduce r[kMaxProb];
+    for (int i = 0; i < s.nprob; ++i) r[i] = DhReduce{a.partial[i], a.p[i].dh, nsets, s.D, s.lh, s.group};
+    return launch_reduce(r, s.nprob, st);
 }
 
 template <typename T>
@@ -838,20 +857,15 @@ hy_status launch_bwd_stencil(const BwdPtrs& p, const BwdShape& s, void* ws, hipS
     return s.dtype == HY_BF16 ? launch_stencil_t<BF16>(&p, s, ws, st) : launch_stencil_t<F32>(&p, s, ws, st);
 }
 
-hy_status launch_dh_reduce(const float* partial, float* dh, int64_t nsets, int64_t n_rows, int32_t lh, int32_t group,
-                           hipStream_t st) {
-    return launch_reduce(ReduceArgs{{partial, partial, partial}, {dh, dh, dh}}, 1, nsets, n_rows, lh, group, st);
-}
-
-hy_status launch_dh_reduce3(const float* const (&partial)[3], float* const (&dh)[3], int64_t nsets, int64_t n_rows, int32_t lh,
-                            int32_t group, hipStream_t st) {
-    return launch_reduce(ReduceArgs{{partial[0], partial[1], partial[2]}, {dh[0], dh[1], dh[2]}}, 3, nsets, n_rows, lh, group, st);
+hy_status launch_dh_reduce(const DhReduce* items, int n, hipStream_t st) {
+    return n < 1 || n > kMaxReduce ? HY_ERR_UNSUPPORTED : launch_reduce(items, n, st);
 }
 
 hy_status launch_bwd_zero_dh(float* dh, int64_t D, int32_t lh, int32_t group, hipStream_t st) {
     // a reduction over zero partial sets writes zeros (a fill kernel, not a memset, so that callers may
     // capture the call in a HIP graph)
-    return launch_dh_reduce(dh, dh, 0, D, lh, group, st);
+    const DhReduce r{dh, dh, 0, D, lh, group};
+    return launch_dh_reduce(&r, 1, st);
 }
 
 hy_status launch_bwd_direct(const BwdPtrs& p, const BwdShape& s, hipStream_t st) {

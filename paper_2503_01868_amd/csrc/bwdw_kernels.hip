@@ -281,7 +281,8 @@ hy_status launch_walk_lh(const BwdPtrs& p, const BwdShape& s, void* ws, hipStrea
         ? launch_kernel((bwd_walk_kernel<LH, PF, true>), dim3((uint32_t)nb), dim3(kWaves * 64), st, a)
         : launch_kernel((bwd_walk_kernel<LH, PF, false>), dim3((uint32_t)nb), dim3(kWaves * 64), st, a);
     if (rc != HY_OK) return rc;
-    return launch_dh_reduce(static_cast<const float*>(ws), p.dh, nsets, s.D, s.lh, s.group, st);
+    const DhReduce r{static_cast<const float*>(ws), p.dh, nsets, s.D, s.lh, s.group};
+    return launch_dh_reduce(&r, 1, st);
 }
 
 }  // namespace

@@ -701,9 +701,9 @@ hy_status launch_chain_bwd(const ChainBwdPtrs& p, const ChainShape& s, void* ws,
     }
     if (rc != HY_OK) return rc;
     // partial rows of dh are per 16-channel slice, those of dhq, dhk, dhv per channel
-    rc = launch_dh_reduce(a.partial, p.dh, nsets, s.D / 16, s.lh, s.group / 16, st);
-    if (rc != HY_OK) return rc;
-    return launch_dh_reduce3(a.partial_x, dhx, nsets, s.D, s.lf, s.feat_group, st);
+    DhReduce r[4] = {{a.partial, p.dh, nsets, s.D / 16, s.lh, s.group / 16}};
+    for (int i = 0; i < 3; ++i) r[1 + i] = DhReduce{a.partial_x[i], dhx[i], nsets, s.D, s.lf, s.feat_group};
+    return launch_dh_reduce(r, 4, st);
 }
 
 }  // namespace hy

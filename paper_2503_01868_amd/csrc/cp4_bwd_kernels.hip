@@ -518,7 +518,8 @@ hy_status launch_cp4_bwd(const BwdPtrs& p, const BwdShape& s, void* ws, hipStrea
                          : s.lh <= 97 ? launch(integral_constant<int, 6>{})
                                       : launch(integral_constant<int, 8>{});
     if (rc != HY_OK) return rc;
-    return launch_dh_reduce(static_cast<const float*>(ws), p.dh, nsets, s.D, s.lh, s.group, st);
+    const DhReduce r{static_cast<const float*>(ws), p.dh, nsets, s.D, s.lh, s.group};
+    return launch_dh_reduce(&r, 1, st);
 }
 
 }  // namespace hy

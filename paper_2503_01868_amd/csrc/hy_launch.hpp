@@ -252,12 +252,15 @@ hy_status launch_cp4_bwd(const BwdPtrs& p, const BwdShape& s, void* ws, hipStrea
 bool chain_bwd_supported(const ChainShape& s);
 int64_t chain_bwd_workspace_bytes(const ChainShape& s);
 hy_status launch_chain_bwd(const ChainBwdPtrs& p, const ChainShape& s, void* ws, hipStream_t st);
-// dh[g][j] = sum over nsets partial sets and over `group` adjacent rows of a set; a set is [n_rows][lh].
-hy_status launch_dh_reduce(const float* partial, float* dh, int64_t nsets, int64_t n_rows, int32_t lh, int32_t group,
-                           hipStream_t st);
-// The same for three problems of one shape in one launch.
-hy_status launch_dh_reduce3(const float* const (&partial)[3], float* const (&dh)[3], int64_t nsets, int64_t n_rows, int32_t lh,
-                            int32_t group, hipStream_t st);
+// dh[g][j] = sum over nsets partial sets and over `group` adjacent rows of a set; a set is [rows][lh].  Up to four filter
+// gradients in one launch.
+struct DhReduce {
+    const float* partial;
+    float* dh;
+    int64_t nsets, rows;
+    int32_t lh, group;
+};
+hy_status launch_dh_reduce(const DhReduce* items, int n, hipStream_t st);
 // dh := 0 (the filter gradient of an empty batch).
 hy_status launch_bwd_zero_dh(float* dh, int64_t D, int32_t lh, int32_t group, hipStream_t st);
 // Bandwidth yardstick y = q*k*v (bf16): strip = 0 streams linearly, 64 / 128 / 256 walks column strips of that many

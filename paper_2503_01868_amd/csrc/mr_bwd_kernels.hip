@@ -442,7 +442,8 @@ hy_status launch_mr_bwd(const BwdPtrs& p, const BwdShape& s, void* ws, hipStream
     }
     if (rc != HY_OK) return rc;
     // partial rows are per 16-channel slice: a group of `group` channels owns group/16 adjacent slices
-    return launch_dh_reduce(static_cast<const float*>(ws), p.dh, nsets, s.D / 16, s.lh, s.group / 16, st);
+    const DhReduce r{static_cast<const float*>(ws), p.dh, nsets, s.D / 16, s.lh, s.group / 16};
+    return launch_dh_reduce(&r, 1, st);
 }
 
 }  // namespace hy
