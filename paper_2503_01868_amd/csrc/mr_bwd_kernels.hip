@@ -24,7 +24,11 @@
 // partial dh row and writes it to the workspace (App. A.4: partial accumulation by block, written out
 // contiguously); dh_reduce_kernel sums the partials.
 // Four waves (64 channels) per workgroup, one wave per SIMD: operands, two windows, the filter-gradient
-// accumulators and a deep prefetch need ~300 registers per lane.
+// accumulators and the prefetch need ~280 registers per lane.  With one wave per SIMD the instructions between the products
+// are time: the windows' blocks are read transposed (ds_read_b64_tr_b16; 2-byte reads put together by the vector ALUs and
+// 64-bit row offsets per lane were 60 instructions per chunk more), and a row's address is a uniform offset plus 32 bits.
+// Bound: 128-byte row pieces.  Measured, 128 taps, before / now: 3 x 5000 x 2048 117 / 97 us, 1 x 8192 x 4096 105 / 104,
+// 60 taps 111 / 96, 1 x 65536 x 4096 728 / 729.
 #include "hy_common.hpp"
 #include "hy_launch.hpp"
 
@@ -47,7 +51,10 @@ struct MrBwdArgs {
     int64_t skv, sgq, sout;  // elements between batch items in k, v / dy, q / dq, dk, dv
     int32_t hist, fut;       // rows of k, v in front of row 0 / of dy, q behind row L - 1 that hold data
     int32_t lh, group;
-    int32_t rows, tiles_per_seq, ncb;
+    int32_t ncb;
+    // Tile x of a channel block: chunks x % tiles_per_seq * chunks .. of batch item x / tiles_per_seq; with `across`,
+    // chunks x * chunks .. of all batch items in a row, kGap chunks without data between two items (plain calls).
+    int32_t chunks, tiles_per_seq, across, items;
 };
 
 constexpr int kChunk = 32;
@@ -64,7 +71,7 @@ __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
     constexpr int NSLOT = NKB + 1;           // chunks of g kept for the filter gradient (+1: no write/read overlap)
     constexpr int NR = NKB + 1;              // chunks of dy waiting for their z
     constexpr int LAG = NKB - 1;             // chunks between a chunk's arrival and its complete z
-    static_assert(NW % 4 == 0, "the LDS swizzle needs 8 pieces per row");
+    static_assert(NW == 4, "the LDS swizzle is for rows of 8 pieces");
     __shared__ uint4 gst[2][kChunk * PPR];             // g of the newest chunk, swizzled for the transposed read
     __shared__ uint4 utr[2][kChunk * PPR];             // u of the newest chunk, same layout (source of z)
     __shared__ uint2 gring[NSLOT][kChunk * CPR];       // g rows, 8-byte chunks XOR-swizzled by row
@@ -79,66 +86,121 @@ __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
     const int li = lane % 16, lq = lane / 16;
 
     const uint32_t lb = blockIdx.x;
-    const int cb = lb % a.ncb;
-    const int64_t tile = lb / a.ncb;
-    const int64_t b = tile / a.tiles_per_seq;
+    const int cb = (int)(lb % (uint32_t)a.ncb);
+    const uint32_t tile = lb / (uint32_t)a.ncb;
     const int64_t L = a.L, D = a.D;
-    // everything below is in reversed time tau = L - 1 - t
-    const int64_t t_start = (tile % a.tiles_per_seq) * (int64_t)a.rows;
-    const int64_t t_end = (t_start + a.rows < L) ? t_start + a.rows : L;
+    // Everything below is in reversed time tau = L - 1 - t, in chunks of 32 steps: chunk r of a batch item.  What lies
+    // kGap = LAG chunks past the last one is the first one of the next item, so that neither sum reaches over.
+    constexpr int kGap = LAG;
+    const int nseq = (int)((L + kChunk - 1) / kChunk);  // chunks of a batch item
+    const int period = nseq + kGap;
+    int b = kShard || !a.across ? (int)(tile / (uint32_t)a.tiles_per_seq) : 0;
+    int r0 = kShard || !a.across ? (int)(tile % (uint32_t)a.tiles_per_seq) * a.chunks : 0;
+    int ntile = nseq - r0 < a.chunks ? nseq - r0 : a.chunks;  // chunks of the tile
+    if constexpr (!kShard) {
+        if (a.across) {
+            const uint32_t v0 = tile * (uint32_t)a.chunks;  // (the launcher admits fewer than 2^31 chunks in a row)
+            const int left = (int)((uint32_t)a.items * (uint32_t)period - (uint32_t)kGap - v0);
+            b = (int)(v0 / (uint32_t)period);
+            r0 = (int)(v0 % (uint32_t)period);
+            ntile = left < a.chunks ? left : a.chunks;
+        }
+    }
+    const int64_t t_start = (int64_t)r0 * kChunk;                       // (shards)
+    const int64_t t_end = kShard && t_start + (int64_t)ntile * kChunk < L ? t_start + (int64_t)ntile * kChunk : L;
     // dy, q of the chunks before the tile feed its du; before tau = 0 lie the `fut` rows behind the sequence's end
     // that hold data (a shard's right halo), down to the first chunk boundary at or below them
-    int64_t t_begin = t_start - (int64_t)kChunk * LAG;
-    const int64_t t_floor = kShard ? -(((int64_t)a.fut + kChunk - 1) / kChunk) * kChunk : 0;
-    if (t_begin < t_floor) t_begin = t_floor;
+    const int back = kShard ? r0 + (a.fut + kChunk - 1) / kChunk : r0;
+    const int warm = back < LAG ? back : LAG;
     const int64_t tau_lo = kShard ? -(int64_t)a.fut : 0;     // smallest reversed step at which dy and q hold data
     const int64_t tau_hi = kShard ? L + (int64_t)a.hist : L;  // k and v hold data below this reversed step
     // k, v of the LAG chunks after the tile feed its z; the walk always runs LAG chunks past the tile, also where
     // the sequence ends first (those chunks then hold zeros and load nothing)
-    const int ntot = (int)((t_end - t_begin + kChunk - 1) / kChunk) + LAG;
+    const int ntot = warm + ntile + LAG;
+    // Where a walk stands: chunk r of a batch item, and in plain calls the byte offset of the chunk's lowest row in memory
+    // (step 31 of its 32).  A walk that runs past the last item does so with chunk indices that nothing uses.
+    struct At {
+        int r;
+        int64_t row0;
+    };
+    const int64_t step = (int64_t)kChunk * D * 2, jump = L * D * 2 + (int64_t)(period - 1) * step;  // to the next item's first chunk
+    auto forward = [&](At& x) {
+        ++x.r;
+        if constexpr (!kShard) {
+            const bool wrap = x.r == period;
+            x.row0 += wrap ? jump : -step;
+            x.r = wrap ? 0 : x.r;
+        }
+    };
+    auto has_data = [&](const At& x) { return kShard || x.r < nseq; };
+    const int rem = (int)(L - 1 - (int64_t)(nseq - 1) * kChunk);  // last step of the chunk that the sequence ends in
+    auto last_step = [&](const At& x) { return x.r == nseq - 1 ? rem : 31; };
 
     const int64_t cblock0 = (int64_t)cb * 16 * NW;
     const int64_t c0 = cblock0 + 16 * w;
-    const int64_t seq0 = kShard ? b * a.sout : b * L * D;
-    const int64_t seq0kv = kShard ? b * a.skv : seq0, seq0gq = kShard ? b * a.sgq : seq0;
+    const int64_t item0 = b;
+    const int64_t seq0 = kShard ? item0 * a.sout : 0;  // plain calls: in the walk's position
+    const int64_t seq0kv = kShard ? item0 * a.skv : 0, seq0gq = kShard ? item0 * a.sgq : 0;
 
     const int lr = tid / PPR, lp = tid % PPR;
     const int64_t ld_off = cblock0 + 8 * lp;
     // element offset of reversed step tau for this lane, without the batch item's offset
     auto row_off = [&](int64_t tau) { return (L - 1 - tau) * D + ld_off; };
-    auto chunk_start = [&](int ci) { return t_begin + (int64_t)ci * kChunk; };
-    auto in_tile = [&](int ci) {
-        const int64_t t0 = chunk_start(ci);
-        return ci >= 0 && t0 >= t_start && t0 < t_end;
-    };
+    auto in_tile = [&](int ci, const At& x) { return (uint32_t)(ci - warm) < (uint32_t)ntile && has_data(x); };
     // loads whose result is never used (chunk indices past the last chunk; k and v before the tile, dy and q after
-    // it) all go to one 16-byte location of the tile, the same for every lane of the workgroup: one cache line per
-    // wave
-    const int64_t idle_off = (L - t_end) * D + cblock0;
-    auto load_g = [&](int ci, Words<4>& yy, Words<4>& qq) {
-        const int64_t t0 = chunk_start(ci);
-        int64_t tau = t0 + lr;
-        tau = tau < t_end ? tau : t_end - 1;
-        if constexpr (kShard) tau = tau > tau_lo ? tau : tau_lo;  // rows past the data read its last row; their g is zeroed below
-        const int64_t off = seq0gq + ((ci < ntot && t0 < t_end) ? row_off(tau) : idle_off);
-        yy = load_words_nt<4>(a.dy + off);
-        qq = load_words_nt<4>(a.q + off);
+    // it; chunks between batch items) all go to one 16-byte location of the tile, the same for every lane of the workgroup:
+    // one cache line per wave
+    const int64_t idle_off = kShard ? (L - t_end) * D + cblock0
+                                    : item0 * L * D + (L - 1 - (t_start < L ? t_start : L - 1)) * D + cblock0;
+    // plain calls (D < 2^24): a uniform offset and 32 bits per lane
+    const uint32_t lane_off = kShard ? 0u : 2u * ((uint32_t)(31 - lr) * (uint32_t)D + (uint32_t)ld_off);
+    auto bytes_at = [](const uint16_t* p, int64_t base, uint32_t off) { return reinterpret_cast<const char*>(p) + base + off; };
+    auto two_rows = [&](const uint16_t* p1, const uint16_t* p2, const At& x, bool used, Words<4>& r1, Words<4>& r2) {
+        // a chunk that the sequence ends in repeats its last row
+        const int past = lr - last_step(x);
+        const uint32_t off = used ? lane_off + __umul24(past > 0 ? past : 0, (uint32_t)D * 2u) : 0u;
+        const int64_t base = used ? x.row0 : idle_off * 2;
+        r1 = load_words_nt<4>(bytes_at(p1, base, off));
+        r2 = load_words_nt<4>(bytes_at(p2, base, off));
     };
-    auto load_kv = [&](int ci, Words<4>& kk, Words<4>& vv) {
-        const int64_t t0 = chunk_start(ci);
-        int64_t tau = t0 + lr;
-        tau = tau < tau_hi ? tau : tau_hi - 1;
-        const int64_t off = seq0kv + ((ci < ntot && t0 >= t_start && t0 < tau_hi) ? row_off(tau) : idle_off);
-        kk = load_words_nt<4>(a.k + off);
-        vv = load_words_nt<4>(a.v + off);
+    auto load_g = [&](int ci, const At& x, Words<4>& yy, Words<4>& qq) {
+        if constexpr (kShard) {
+            int64_t tau = (int64_t)x.r * kChunk + lr;
+            tau = tau < t_end ? tau : t_end - 1;
+            tau = tau > tau_lo ? tau : tau_lo;  // rows past the data read its last row; their g is zeroed below
+            const int64_t off = seq0gq + (ci < warm + ntile ? row_off(tau) : idle_off);
+            yy = load_words_nt<4>(a.dy + off);
+            qq = load_words_nt<4>(a.q + off);
+        } else {
+            two_rows(a.dy, a.q, x, ci < warm + ntile && has_data(x), yy, qq);
+        }
+    };
+    auto load_kv = [&](int ci, const At& x, Words<4>& kk, Words<4>& vv) {
+        if constexpr (kShard) {
+            const int64_t t0 = (int64_t)x.r * kChunk;
+            int64_t tau = t0 + lr;
+            tau = tau < tau_hi ? tau : tau_hi - 1;
+            const int64_t off = seq0kv + ((ci < ntot && ci >= warm && t0 < tau_hi) ? row_off(tau) : idle_off);
+            kk = load_words_nt<4>(a.k + off);
+            vv = load_words_nt<4>(a.v + off);
+        } else {
+            two_rows(a.k, a.v, x, ci < ntot && ci >= warm && has_data(x), kk, vv);
+        }
     };
 
     Words<4> ypre[PF], qpre[PF], kpre[PF], vpre[PF];
+    At here{r0 - warm, 2 * (item0 * L * D + (L - kChunk - (int64_t)(r0 - warm) * kChunk) * D)};  // the chunk of an iteration, the one before, the one whose dq it stores,
+    At before = here, late = here, late_before = here, ahead = here;  // and the one whose dy and q it requests
 #pragma unroll
     for (int i = 0; i < PF; ++i) {
-        load_g(i, ypre[i], qpre[i]);
-        if (i + 1 < PF) load_kv(i, kpre[i], vpre[i]);  // the last k, v stage is filled by the first iteration
+        load_g(i, ahead, ypre[i], qpre[i]);
+        if (i + 1 < PF) {
+            load_kv(i, ahead, kpre[i], vpre[i]);  // the last k, v stage is filled by the first iteration
+            forward(ahead);
+        }
     }
+    At ahead_kv = ahead;  // one behind
+    forward(ahead);
 
     // zero the g ring: slots of chunks before the start of the walk stand for steps past the end of the sequence
     for (int i = tid; i < NSLOT * kChunk * CPR; i += NW * 64) (&gring[0][0])[i] = make_uint2(0u, 0u);
@@ -165,10 +227,14 @@ __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
 #pragma unroll
     for (int x = 0; x < ND; ++x) cacc[x] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 
-    const int swz = ((lr >> 3) & 3) << 1;
-    const int st_idx = lr * PPR + (lp ^ swz);
-    const int rd_piece = (2 * w + (li >> 3)) ^ (lq << 1);          // rows 8 lq .. 8 lq + 7
-    const int rd_piece_rev = (2 * w + (li >> 3)) ^ ((3 - lq) << 1);  // rows 31 - 8 lq - 7 .. 31 - 8 lq
+    // Rows are permuted by 16-byte pieces so that a wave's transposed reads (for every octet of steps 4 rows x 16 channels)
+    // meet every bank twice, which is what their 512 bytes take.
+    auto skew = [](int row) { return ((row >> 1) & 1) * 2 + ((row >> 3) & 1) * 4; };
+    const int st_idx = lr * PPR + (lp ^ skew(lr));
+    // a lane addresses 4 channels of one row and gets 4 steps of channel li: rows 8 lq .. 8 lq + 3 (and 4 rows on), and for
+    // the reversed order rows 31 - 8 lq down to 28 - 8 lq (and 4 rows back)
+    auto tr_off = [&](int row) { return row * PPR * 16 + ((2 * w + ((li & 3) >> 1)) ^ skew(row)) * 16 + (li & 1) * 8; };
+    const int rd_fwd = tr_off(8 * lq + (li >> 2)), rd_rev = tr_off(31 - 8 * lq - (li >> 2));
     const int zwr_off = li * ZROW + (16 * w + 4 * lq) * 4;           // du: step li of a 16-step tile
     const int zwr_off_rev = (15 - li) * ZROW + (16 * w + 4 * lq) * 4;  // z: step 15 - li
     const int zrd_off = lr * ZROW + 8 * lp * 4;
@@ -178,9 +244,15 @@ __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
     const int rd8 = (4 * w + lq) ^ li;  // this lane's chunk in a row whose index is li (mod 16)
 
     // dk, dv of chunk ci (du staged one iteration earlier)
-    auto gate_store_du = [&](int ci, const Words<4>& kk, const Words<4>& vv) {
-        const int64_t tau = chunk_start(ci) + lr;
-        if (in_tile(ci) && tau < t_end) {
+    auto out_at = [&](uint16_t* p, const At& x) {
+        if constexpr (kShard) return reinterpret_cast<char*>(p + seq0 + row_off((int64_t)x.r * kChunk + lr));
+        else return reinterpret_cast<char*>(p) + x.row0 + lane_off;
+    };
+    auto row_in_tile = [&](int ci, const At& x) {
+        return in_tile(ci, x) && (kShard ? (int64_t)x.r * kChunk + lr < t_end : lr <= last_step(x));
+    };
+    auto gate_store_du = [&](int ci, const At& x, const Words<4>& kk, const Words<4>& vv) {
+        if (row_in_tile(ci, x)) {
             const char* zp = zst[ci & 1] + zrd_off;
             const float4 za = *reinterpret_cast<const float4*>(zp);
             const float4 zb = *reinterpret_cast<const float4*>(zp + 16);
@@ -193,15 +265,13 @@ __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
                 o1[e] = du[e] * vf[e];
                 o2[e] = du[e] * kf[e];
             }
-            const int64_t off = seq0 + row_off(tau);
-            store_words_nt<4>(a.dk + off, Pack<BF16, 8>::pack(o1));
-            store_words_nt<4>(a.dv + off, Pack<BF16, 8>::pack(o2));
+            store_words_nt<4>(out_at(a.dk, x), Pack<BF16, 8>::pack(o1));
+            store_words_nt<4>(out_at(a.dv, x), Pack<BF16, 8>::pack(o2));
         }
     };
     // dq of chunk cq, whose z was staged in iteration cq + LAG (buffer parity of that iteration)
-    auto gate_store_dq = [&](int cq) {
-        const int64_t tau = chunk_start(cq) + lr;
-        if (in_tile(cq) && tau < t_end) {
+    auto gate_store_dq = [&](int cq, const At& x) {
+        if (row_in_tile(cq, x)) {
             const char* zp = zst2[(cq + LAG) & 1] + zrd_off;
             const float4 za = *reinterpret_cast<const float4*>(zp);
             const float4 zb = *reinterpret_cast<const float4*>(zp + 16);
@@ -212,7 +282,7 @@ __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
             Pack<BF16, 8>::unpack(yy, yf);
             float o[8] = {za.x * yf[0], za.y * yf[1], za.z * yf[2], za.w * yf[3],
                           zb.x * yf[4], zb.y * yf[5], zb.z * yf[6], zb.w * yf[7]};
-            store_words_nt<4>(a.dq + seq0 + row_off(tau), Pack<BF16, 8>::pack(o));
+            store_words_nt<4>(out_at(a.dq, x), Pack<BF16, 8>::pack(o));
         }
     };
 
@@ -221,8 +291,9 @@ __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
 #pragma unroll
         for (int sgi = 0; sgi < PF; ++sgi) {
             const int ci = base + sgi;
-            const int64_t t0 = chunk_start(ci);
-            const bool main_chunk = in_tile(ci) && ci < ntot;
+            const int64_t t0 = (int64_t)here.r * kChunk;
+            const bool main_chunk = in_tile(ci, here);
+            const bool in_seq = kShard ? t0 + lr < tau_hi : lr <= (has_data(here) ? last_step(here) : -1);
             const int slot = __builtin_amdgcn_readfirstlane(ci % NSLOT);
 
             // g = dy*q and u = k*v of this lane's row piece, rounded to bf16, into LDS; dy itself into its ring
@@ -233,8 +304,8 @@ __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
                 Words<4> gg;
 #pragma unroll
                 for (int e2 = 0; e2 < 4; ++e2) gg.w[e2] = pack_bf16x2(a8[2 * e2] * b8[2 * e2], a8[2 * e2 + 1] * b8[2 * e2 + 1]);
-                if constexpr (kShard)
-                    if (t0 + lr < tau_lo) gg = zero_words<4>();  // past the rows that hold data: zeros
+                // past the rows that hold data and between batch items: zeros
+                if (kShard ? t0 + lr < tau_lo : !in_seq) gg = zero_words<4>();
                 gst[ci & 1][st_idx] = make_uint4(gg.w[0], gg.w[1], gg.w[2], gg.w[3]);
                 gring[slot][wr8a] = make_uint2(gg.w[0], gg.w[1]);
                 gring[slot][wr8b] = make_uint2(gg.w[2], gg.w[3]);
@@ -246,13 +317,12 @@ __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
                 for (int e2 = 0; e2 < 4; ++e2) uu.w[e2] = pack_bf16x2(a8[2 * e2] * b8[2 * e2], a8[2 * e2 + 1] * b8[2 * e2 + 1]);
                 // z reaches over the end of the tile but not over the end of the sequence; the filter gradient
                 // takes u of the tile only
-                const bool in_seq = t0 + lr < tau_hi;
-                const bool in_own = t0 + lr < t_end;
+                const bool in_own = kShard ? t0 + lr < t_end : in_seq;
                 utr[ci & 1][st_idx] = in_seq ? make_uint4(uu.w[0], uu.w[1], uu.w[2], uu.w[3]) : make_uint4(0u, 0u, 0u, 0u);
                 ust[ci & 1][wr8a] = in_own ? make_uint2(uu.w[0], uu.w[1]) : make_uint2(0u, 0u);
                 ust[ci & 1][wr8b] = in_own ? make_uint2(uu.w[2], uu.w[3]) : make_uint2(0u, 0u);
             }
-            load_g(ci + PF, ypre[sgi], qpre[sgi]);
+            load_g(ci + PF, ahead, ypre[sgi], qpre[sgi]);
 
             __syncthreads();
 
@@ -262,22 +332,16 @@ __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
                 uw[m] = uw[m - 1];
             }
             {
-                const uint16_t* s16 = reinterpret_cast<const uint16_t*>(gst[ci & 1]);
-                const uint16_t* u16 = reinterpret_cast<const uint16_t*>(utr[ci & 1]);
-                Words<4> wds, wdu;
-#pragma unroll
-                for (int e2 = 0; e2 < 4; ++e2) {
-                    const int r0 = 8 * lq + 2 * e2;
-                    const uint32_t lo = s16[((r0 * PPR + rd_piece) << 3) + (li & 7)];
-                    const uint32_t hi = s16[(((r0 + 1) * PPR + rd_piece) << 3) + (li & 7)];
-                    wds.w[e2] = lo | (hi << 16);
-                    const int rr = 31 - 8 * lq - 2 * e2;  // reversed: element 2 e2 = row rr, element 2 e2 + 1 = row rr - 1
-                    const uint32_t ulo = u16[((rr * PPR + rd_piece_rev) << 3) + (li & 7)];
-                    const uint32_t uhi = u16[(((rr - 1) * PPR + rd_piece_rev) << 3) + (li & 7)];
-                    wdu.w[e2] = ulo | (uhi << 16);
-                }
-                gw[0] = __builtin_bit_cast(bf16x8_t, wds);
-                uw[0] = __builtin_bit_cast(bf16x8_t, wdu);
+                typedef __attribute__((address_space(3))) s16x4_t lds_quad_t;
+                auto octet = [&](const uint4* rows, int at, int on) {
+                    const char* p = reinterpret_cast<const char*>(rows) + at;
+                    struct { s16x4_t lo, hi; } x;
+                    x.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_quad_t*)p);
+                    x.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_quad_t*)(p + on));
+                    return __builtin_bit_cast(bf16x8_t, x);
+                };
+                gw[0] = octet(gst[ci & 1], rd_fwd, 4 * PPR * 16);
+                uw[0] = octet(utr[ci & 1], rd_rev, -4 * PPR * 16);
             }
 
             if (main_chunk) {
@@ -311,7 +375,8 @@ __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
             // z of chunk ci - LAG: its source blocks ci - LAG .. ci are all in the window now.  Source block
             // ci - LAG + s sits s chunks after the output chunk: offset 32 s + 16 for the first 16 outputs,
             // 32 s for the second 16.
-            if (ci < ntot && in_tile(ci - LAG)) {
+            // (`late` is chunk ci - LAG here)
+            if (ci < ntot && in_tile(ci - LAG, late)) {
                 f32x4_t acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int s = 0; s < NKB; ++s) {
@@ -324,10 +389,16 @@ __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
             }
             const int prev = (sgi + PF - 1) % PF;  // static after unrolling
             if (ci > 0 && ci <= ntot) {
-                gate_store_du(ci - 1, kpre[prev], vpre[prev]);
-                gate_store_dq(ci - 1 - LAG);
+                gate_store_du(ci - 1, before, kpre[prev], vpre[prev]);
+                gate_store_dq(ci - 1 - LAG, late_before);
             }
-            load_kv(ci - 1 + PF, kpre[prev], vpre[prev]);
+            load_kv(ci - 1 + PF, ahead_kv, kpre[prev], vpre[prev]);
+            ahead_kv = ahead;
+            forward(ahead);
+            before = here;
+            forward(here);
+            late_before = late;
+            if (ci >= LAG) forward(late);
         }
     }
 
@@ -362,9 +433,34 @@ __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
 
 constexpr int kBwdWaves = 4;  // waves (16-channel slices) per workgroup
 
+struct Tiling {
+    int64_t chunks, tiles_per_seq, ntiles;  // ntiles: per channel block
+    bool across;
+};
+
+// Tiles of mr_bwd_rows() steps within a batch item, or tiles of all items in a row, as many as make one round of
+// workgroups, where that takes fewer chunks (a tile's halo and its start priced as chunks): a batch that does not divide the
+// compute units otherwise pays for a round that is partly empty or for two rounds of short tiles (3 x 5000 x 2048, 128 taps:
+// 480 tiles of 32 chunks or 256 of 61, 110 and 97 us).
+Tiling tiling(const BwdShape& s) {
+    const int64_t ncb = s.D / (16 * kBwdWaves), rows = mr_bwd_rows(s);
+    Tiling t{rows / kChunk, (s.L + rows - 1) / rows, 0, false};
+    t.ntiles = s.B * t.tiles_per_seq;
+    if (s.sharded() || s.D >= 1 << 24 || s.B < 2 || tuning().mr_rows > 0) return t;
+    const int64_t lag = (s.lh - 1 + 31) / 32, total = s.B * ((s.L + kChunk - 1) / kChunk + lag) - lag;
+    if (total + lag > 0x7fffffffLL) return t;
+    const int64_t want = ncb < 256 ? 256 / ncb : 1, chunks = (total + want - 1) / want, n = (total + chunks - 1) / chunks;
+    auto cost = [&](int64_t tiles, int64_t each) { return (ncb * tiles + 255) / 256 * (each + lag + 8); };
+    if (n <= t.ntiles && 33 * cost(n, chunks) <= 32 * cost(t.ntiles, t.chunks)) t = Tiling{chunks, n, n, true};
+    return t;
+}
+
 template <int NKB, int NW>
 hy_status launch_nw(const BwdPtrs& p, const BwdShape& s, void* ws, hipStream_t st, int64_t* nsets) {
-    constexpr int PF = 4;  // chunks of dy, q, k, v in flight per lane (measured: 3 and 6 are 2-8% slower)
+    // Chunks of dy, q, k, v in flight per lane.  A fourth makes long walks at full width slower, not faster: the columns of a
+    // row drift apart (2 / 3 / 4 / 5 / 6, 128 taps, us: 1 x 65536 x 4096 968 / 729 / 744 / 759 / 809, 1 x 8192 x 4096 137 / 104 /
+    // 101 / 101 / 108, 3 x 5000 x 2048 131 / 99 / 100 / 95 / 99; 60 taps 1 x 8192 x 4096 122 / 96 / 113 / 113 / 117).
+    constexpr int PF = 3;
     MrBwdArgs a;
     a.dy = static_cast<const uint16_t*>(p.dy);
     a.q = static_cast<const uint16_t*>(p.q);
@@ -385,12 +481,16 @@ hy_status launch_nw(const BwdPtrs& p, const BwdShape& s, void* ws, hipStream_t s
     a.lh = s.lh;
     a.group = s.group;
     a.ncb = (int32_t)(s.D / (16 * NW));
-    a.rows = (int32_t)mr_bwd_rows(s);
-    a.tiles_per_seq = (int32_t)((s.L + a.rows - 1) / a.rows);
-    *nsets = s.B * a.tiles_per_seq;
+    const Tiling t = tiling(s);
+    a.chunks = (int32_t)t.chunks;
+    a.tiles_per_seq = (int32_t)t.tiles_per_seq;
+    a.across = t.across;
+    a.items = (int32_t)s.B;
+    *nsets = t.ntiles;
     const int64_t nb = *nsets * a.ncb;
     if (nb > 0x7fffffffLL) return HY_ERR_UNSUPPORTED;
-    if (s.sharded()) return launch_kernel((mr_bwd_kernel<NKB, NW, PF, true>), dim3((uint32_t)nb), dim3(NW * 64), st, a);
+    if (s.sharded() || s.D >= 1 << 24)  // (the shard form has wide row offsets)
+        return launch_kernel((mr_bwd_kernel<NKB, NW, PF, true>), dim3((uint32_t)nb), dim3(NW * 64), st, a);
     return launch_kernel((mr_bwd_kernel<NKB, NW, PF, false>), dim3((uint32_t)nb), dim3(NW * 64), st, a);
 }
 
@@ -422,9 +522,7 @@ int64_t mr_bwd_rows(const BwdShape& s) {
 }
 
 int64_t mr_bwd_workspace_bytes(const BwdShape& s) {
-    const int64_t rows = mr_bwd_rows(s);
-    const int64_t tiles = (s.L + rows - 1) / rows;
-    return s.B * tiles * (s.D / 16) * s.lh * (int64_t)sizeof(float);
+    return tiling(s).ntiles * (s.D / 16) * s.lh * (int64_t)sizeof(float);
 }
 
 // dq, dk, dv and dh in one pass.  `ws` holds the partial filter gradients.
