@@ -207,7 +207,7 @@ hy_status gated_fwd(bool mr_first, const void* q, const void* k, const void* v, 
     }
     if (rc == HY_ERR_UNSUPPORTED) rc = launch_cp4(p, s, st);
     if (rc == HY_ERR_UNSUPPORTED) rc = launch_cp_mfma(p, s, st);
-    if (rc == HY_ERR_UNSUPPORTED) rc = launch_general(p, s, st);
+    if (rc == HY_ERR_UNSUPPORTED) rc = launch_direct(&p, 1, s, st);
     return rc;
 }
 
@@ -343,7 +343,7 @@ hy_status hyena_chain_fwd(const void* q, const void* k, const void* v, const flo
     ConvPtrs m{ws, ws + bytes, ws + 2 * bytes, h, y};
     ConvShape ms{B, L, D, lh, group, static_cast<hy_dtype>(dtype), true};
     rc = launch_mr_mfma(m, ms, st);
-    if (rc == HY_ERR_UNSUPPORTED) rc = launch_general(m, ms, st);
+    if (rc == HY_ERR_UNSUPPORTED) rc = launch_direct(&m, 1, ms, st);
     return rc;
 }
 

@@ -478,20 +478,4 @@ hy_status launch_fir(const FirProblem* p, int nprob, int64_t B, int64_t L, int64
     return dtype == HY_BF16 ? launch_t<BF16>(a, nprob, B, st) : launch_t<F32>(a, nprob, B, st);
 }
 
-hy_status launch_direct(const ConvPtrs* p, int nprob, const ConvShape& s, hipStream_t st) {
-    FirProblem f[3];
-    for (int i = 0; i < nprob; ++i) {
-        f[i].a = p[i].k;
-        f[i].b = s.gated ? p[i].v : nullptr;
-        f[i].h = p[i].h;
-        f[i].gate = s.gated ? p[i].q : nullptr;
-        f[i].out = p[i].y;
-        f[i].stride_ab = s.stride_kv();
-        f[i].stride_gate = f[i].stride_out = s.stride_qy();
-        f[i].lo = -(int64_t)s.history;
-        f[i].hi = s.L;
-    }
-    return launch_fir(f, nprob, s.B, s.L, s.D, s.lh, s.group, s.dtype, st);
-}
-
 }  // namespace hy

@@ -194,13 +194,12 @@ struct FirProblem {
 // General fp32 FIR: any lh, any group, any width, both dtypes, up to three problems of one shape per launch.
 hy_status launch_fir(const FirProblem* p, int nprob, int64_t B, int64_t L, int64_t D, int32_t lh, int32_t group,
                      hy_dtype dtype, hipStream_t st);
-hy_status launch_direct(const ConvPtrs* p, int nprob, const ConvShape& s, hipStream_t st);
 // The same sums in the same precision on split bf16 products: up to two gated problems of 9 to 129 taps whose filters are
 // shared by 8 adjacent channels or a multiple.  HY_ERR_UNSUPPORTED outside that.
 hy_status launch_split_fir(const FirProblem* p, int nprob, int64_t B, int64_t L, int64_t D, int32_t lh, int32_t group,
                            hy_dtype dtype, hipStream_t st);
-// Gated forward of any shape: split products where they serve it, else the general kernel.
-hy_status launch_general(const ConvPtrs& p, const ConvShape& s, hipStream_t st);
+// Forward of any shape: split products where they serve it, else the general kernel.
+hy_status launch_direct(const ConvPtrs* p, int nprob, const ConvShape& s, hipStream_t st);
 // Block-Toeplitz contraction on bf16 MFMA.  HY_ERR_UNSUPPORTED outside its domain.
 hy_status launch_mr_mfma(const ConvPtrs& p, const ConvShape& s, hipStream_t st);
 // Chunk-parallel block-Toeplitz contraction on bf16 MFMA for filters not shared by 16 channels (any group).

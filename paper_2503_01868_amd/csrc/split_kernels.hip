@@ -442,19 +442,21 @@ hy_status launch_split_fir(const FirProblem* p, int nprob, int64_t B, int64_t L,
     return dtype == HY_BF16 ? launch_t<BF16>(a, nprob, B, two, st) : launch_t<F32>(a, nprob, B, two, st);
 }
 
-hy_status launch_general(const ConvPtrs& p, const ConvShape& s, hipStream_t st) {
-    FirProblem f;
-    f.a = p.k;
-    f.b = p.v;
-    f.h = p.h;
-    f.gate = p.q;
-    f.out = p.y;
-    f.stride_ab = s.stride_kv();
-    f.stride_gate = f.stride_out = s.stride_qy();
-    f.lo = -(int64_t)s.history;
-    f.hi = s.L;
-    const hy_status rc = launch_split_fir(&f, 1, s.B, s.L, s.D, s.lh, s.group, s.dtype, st);
-    return rc == HY_ERR_UNSUPPORTED ? launch_direct(&p, 1, s, st) : rc;
+hy_status launch_direct(const ConvPtrs* p, int nprob, const ConvShape& s, hipStream_t st) {
+    FirProblem f[3];
+    for (int i = 0; i < nprob; ++i) {
+        f[i].a = p[i].k;
+        f[i].b = s.gated ? p[i].v : nullptr;
+        f[i].h = p[i].h;
+        f[i].gate = s.gated ? p[i].q : nullptr;
+        f[i].out = p[i].y;
+        f[i].stride_ab = s.stride_kv();
+        f[i].stride_gate = f[i].stride_out = s.stride_qy();
+        f[i].lo = -(int64_t)s.history;
+        f[i].hi = s.L;
+    }
+    const hy_status rc = launch_split_fir(f, nprob, s.B, s.L, s.D, s.lh, s.group, s.dtype, st);
+    return rc == HY_ERR_UNSUPPORTED ? launch_fir(f, nprob, s.B, s.L, s.D, s.lh, s.group, s.dtype, st) : rc;
 }
 
 }  // namespace hy
