@@ -1,12 +1,14 @@
 """Thin ctypes binding of the C ABI declared in ``include/hyena.h``.
 
 Argument marshalling only: every step of the operators runs inside ``libhyena.so``.  PyTorch supplies
-device memory and the HIP stream.  There is no CPU or PyTorch fallback: if the library is missing and
+device memory and the HIP stream.  The calls made most go through the extension ``_fastcall`` where their arguments are
+plain (it returns None where they are not).  There is no CPU or PyTorch fallback: if the library is missing and
 cannot be built, or a call fails, an exception is raised.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 
 import torch
@@ -88,7 +90,36 @@ def lib() -> ctypes.CDLL:
         L.hyena_version.argtypes = []
         L.hyena_version.restype = i32
         _lib = L
+        _load_fast()
     return _lib
+
+
+class _Unmarshalled:
+    """Stands in for the extension until it is loaded and where it cannot be: every call takes the path in this file."""
+
+    @staticmethod
+    def _none(*args):
+        return None
+
+    gated = bwd = chain_fwd = chain_bwd = li = _none
+
+
+_fast = _Unmarshalled
+
+
+def _load_fast() -> None:
+    global _fast
+    try:
+        spec = importlib.util.spec_from_file_location(__package__ + "._fastcall", _build.FAST)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        module.init(tuple(ctypes.cast(getattr(_lib, name), ctypes.c_void_p).value for name in (
+            "hyena_se_fwd", "hyena_mr_fwd", "hyena_se_bwd", "hyena_mr_bwd", "hyena_bwd_workspace_bytes", "hyena_chain_fwd",
+            "hyena_chain_workspace_bytes", "hyena_chain_bwd", "hyena_chain_bwd_workspace_bytes", "hyena_li_fwd",
+            "hyena_li_workspace_bytes")), _current_raw_stream)
+    except (ImportError, OSError, AttributeError):  # built for another torch or Python
+        return
+    _fast = module
 
 
 def status_string(code: int) -> str:
@@ -300,11 +331,19 @@ def plan_featurize3(q, k, v, hq, hk, hv, group: int = 1, out=None, stream=None) 
 
 def hyena_se_fwd(q, k, v, h, group: int = 1, out=None, stream=None) -> torch.Tensor:
     """y = q * (h conv (k * v)), short filters; see ``hyena_se_fwd`` in hyena.h."""
+    if out is None and stream is None:
+        y = _fast.gated(0, q, k, v, h, group)
+        if y is not None:
+            return y
     return _gated("hyena_se_fwd", q, k, v, h, group, out, stream)
 
 
 def hyena_mr_fwd(q, k, v, h, group: int = 16, out=None, stream=None) -> torch.Tensor:
     """y = q * (h conv (k * v)), medium grouped filters; see ``hyena_mr_fwd`` in hyena.h."""
+    if out is None and stream is None:
+        y = _fast.gated(1, q, k, v, h, group)
+        if y is not None:
+            return y
     return _gated("hyena_mr_fwd", q, k, v, h, group, out, stream)
 
 
@@ -375,6 +414,10 @@ def _chain_args(q, k, v, hq, hk, hv, h, group, feat_group, out, workspace, strea
 def hyena_chain_fwd(q, k, v, hq, hk, hv, h, group: int = 16, feat_group: int = 1, out=None, workspace=None,
                     stream=None) -> torch.Tensor:
     """Featurize q, k, v and apply the gated medium convolution; see ``hyena_chain_fwd`` in hyena.h."""
+    if out is None and workspace is None and stream is None:
+        y = _fast.chain_fwd(q, k, v, hq, hk, hv, h, group, feat_group)
+        if y is not None:
+            return y
     args, _, y = _chain_args(q, k, v, hq, hk, hv, h, group, feat_group, out, workspace, stream)
     with _on(q):
         rc = lib().hyena_chain_fwd(*args)
@@ -519,11 +562,19 @@ def _bwd(entry: str, dy, q, k, v, h, group, workspace, stream):
 
 def hyena_se_bwd(dy, q, k, v, h, group: int = 1, workspace=None, stream=None):
     """(dq, dk, dv, dh) of ``hyena_se_fwd``; see ``hyena_se_bwd`` in hyena.h."""
+    if workspace is None and stream is None:
+        grads = _fast.bwd(0, dy, q, k, v, h, group)
+        if grads is not None:
+            return grads
     return _bwd("hyena_se_bwd", dy, q, k, v, h, group, workspace, stream)
 
 
 def hyena_mr_bwd(dy, q, k, v, h, group: int = 16, workspace=None, stream=None):
     """(dq, dk, dv, dh) of ``hyena_mr_fwd``; see ``hyena_mr_bwd`` in hyena.h."""
+    if workspace is None and stream is None:
+        grads = _fast.bwd(1, dy, q, k, v, h, group)
+        if grads is not None:
+            return grads
     return _bwd("hyena_mr_bwd", dy, q, k, v, h, group, workspace, stream)
 
 
@@ -595,6 +646,10 @@ def plan_chain_bwd(dy, q, k, v, hq, hk, hv, h, group: int = 16, feat_group: int 
 
 def hyena_chain_bwd(dy, q, k, v, hq, hk, hv, h, group: int = 16, feat_group: int = 1, workspace=None, stream=None):
     """(dq, dk, dv, dhq, dhk, dhv, dh) of ``hyena_chain_fwd``; see ``hyena_chain_bwd`` in hyena.h."""
+    if workspace is None and stream is None:
+        grads = _fast.chain_bwd(dy, q, k, v, hq, hk, hv, h, group, feat_group)
+        if grads is not None:
+            return grads
     with _on(dy):
         return plan_chain_bwd(dy, q, k, v, hq, hk, hv, h, group, feat_group, None, workspace, stream)()
 
@@ -627,6 +682,10 @@ def plan_li(q, k, v, R, lam, group: int = 16, out=None, workspace=None, stream=N
 
 def hyena_li_fwd(q, k, v, R, lam, group: int = 16, out=None, workspace=None, stream=None) -> torch.Tensor:
     """y = q * (h conv (k * v)) with h[g, j] = sum_n R[g, n] lam[g, n]^j; see ``hyena_li_fwd`` in hyena.h."""
+    if out is None and workspace is None and stream is None:
+        y = _fast.li(q, k, v, R, lam, group)
+        if y is not None:
+            return y
     with _on(q):
         return plan_li(q, k, v, R, lam, group, out, workspace, stream)()
 
