@@ -446,6 +446,9 @@ __global__ __launch_bounds__(kKinds * kNW * 64, kKinds) void chain_bwd_kernel(Ch
         for (int j = lane; j < a.lh; j += 64) out[j] = dhw[j];
     } else {
         // ================= data movement (rows 2 rp, 2 rp + 1 of a chunk, channels 4 lp .. 4 lp + 3) and featurizers
+        // Ahead of the multipliers on its SIMD, which wait for its rows at every barrier (priority 0 / 1 / 2 / 3, 128 taps, us: 1 x
+        // 8192 x 4096 145 / 135 / 135 / 136, 4 x 32768 x 4096 2028 / 1899 / 1899 / 1897, 2 x 500 x 1024 28 / 27 / 28 / 28).
+        __builtin_amdgcn_s_setprio(1);
         const int mt = tid - 2 * kNW * 64;
         const int lp = mt % 16, rp = mt / 16;
         const uint32_t row_bytes = (uint32_t)D * 2;
