@@ -47,6 +47,7 @@ struct FirArgs {
     int32_t ncb;             // channel blocks
     int32_t steps;           // tiles a workgroup walks
     int32_t walks_per_seq;
+    uint32_t together;  // neighbouring channel blocks on one XCD: the workgroups of the launch (0: apart)
 };
 
 __device__ __forceinline__ bool not_finite(float x) { return !(__builtin_fabsf(x) <= 3.402823466e+38f); }
@@ -86,7 +87,7 @@ __global__ __launch_bounds__(kThreads, per_cu(kSeg, NT)) void fir_kernel(FirArgs
 
     const FirProblem pr = a.p[blockIdx.y];
     const int tid = threadIdx.x, lane = tid % kWave, w = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const uint32_t lb = blockIdx.x;
+    const uint32_t lb = a.together ? xcd_contiguous(blockIdx.x, a.together) : blockIdx.x;
     const uint32_t walk = lb / (uint32_t)a.ncb;
     const int64_t c0 = (int64_t)(lb % (uint32_t)a.ncb) * kChan;
     const int64_t b = walk / (uint32_t)a.walks_per_seq;
@@ -389,7 +390,13 @@ hy_status launch_nt(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
     if (steps > 0x7fffffffLL || B > 0x7fffffffLL || B * walks > 0x7fffffffLL / a.ncb) return HY_ERR_UNSUPPORTED;
     a.steps = (int32_t)steps;
     a.walks_per_seq = (int32_t)walks;
-    return launch_kernel((fir_kernel<T, VEC, kSeg, NT, kOne>), dim3((uint32_t)(B * walks * a.ncb), (uint32_t)nprob),
+    // Rows of 16-byte pieces that are no whole lines: a row piece shares its first and last line with its neighbours', which one
+    // L2 then holds for all (us, apart / together: 3 x 5003 x 1000 bf16, 16 taps 39 / 33, 128 taps 74 / 68, 1 x 4000 x 1000 fp32
+    // 18.8 / 16.1 and 32 / 28; rows of whole lines run better spread out, and so do few workgroups, 1 x 700 x 1000, 352 of them,
+    // 11.4 / 11.6, and two problems side by side, gradients 2 x 2000 x 1000 120.6 / 122.7).
+    const int64_t nblocks = B * walks * a.ncb;
+    a.together = VEC > 1 && a.D * T::kBytes % 128 != 0 && nprob == 1 && nblocks >= 416 ? (uint32_t)nblocks : 0;
+    return launch_kernel((fir_kernel<T, VEC, kSeg, NT, kOne>), dim3((uint32_t)nblocks, (uint32_t)nprob),
                          dim3(kThreads), st, a);
 }
 
