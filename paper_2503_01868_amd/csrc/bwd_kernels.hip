@@ -389,7 +389,7 @@ struct DhArgs {
 constexpr int kDhThreads = 512;
 constexpr int kDhT = 64;     // steps staged at a time
 constexpr int kDhRing = 192;  // rows of u: the staged steps and 128 before them
-constexpr int kDhLags = 128;  // lags per workgroup
+constexpr int kDhLags = 128;  // lags per workgroup at most
 
 // the partial sums of batch item b, in dk's memory
 template <typename T>
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(kDhThreads, 1) void dh_tile_kernel(DhArgs a) {
     const int64_t ti = tile % (uint32_t)a.tiles_per_seq;
     const int64_t ts = ti * a.rows, te = ts + a.rows < a.L ? ts + a.rows : a.L;
     const int64_t D = a.D, L = a.L;
-    const int64_t l0 = (int64_t)blockIdx.y * kDhLags;   // first lag of this workgroup
+    const int64_t l0 = (int64_t)blockIdx.y * (16 * kLagWaves);  // first lag of this workgroup
     const int lagw = w % kLagWaves, part = w / kLagWaves;
     const int64_t j0 = l0 + 16 * lagw;                  // first lag of this wave
     const bool busy = part < kSplit && j0 < a.lh;
@@ -471,12 +471,14 @@ __global__ __launch_bounds__(kDhThreads, 1) void dh_tile_kernel(DhArgs a) {
         }
     };
 
-    // steps ts - l0 - 128 .. ts - l0 - 1 of u to ring rows 64 .. 191; staging n then writes rows 64 (n % 3) on
-    load_u(ts - l0 - 128, kh[0], vh[0]);
+    // steps ts - l0 - 128 .. ts - l0 - 1 of u (up to 64 lags: 64 of them) to ring rows 64 .. 191; staging n then writes rows
+    // 64 (n % 3) on
+    constexpr bool kFar = kLagWaves > 4;
+    if constexpr (kFar) load_u(ts - l0 - 128, kh[0], vh[0]);
     load_u(ts - l0 - 64, kh[1], vh[1]);
     load_u(ts - l0, kr, vr);
     load_g(ts);
-    write_prod(us + kDhT * kC, kh[0], vh[0]);
+    if constexpr (kFar) write_prod(us + kDhT * kC, kh[0], vh[0]);
     write_prod(us + 2 * kDhT * kC, kh[1], vh[1]);
 
     double acc[16];
@@ -674,12 +676,19 @@ hy_status launch_dh_tile(const BwdPtrs& p, const BwdShape& s, hipStream_t st) {
     a.ncb = (int32_t)ncb;
     a.rows = (int32_t)rows;
     a.tiles_per_seq = (int32_t)tiles;
-    const dim3 grid((uint32_t)(s.B * tiles * ncb), (uint32_t)nlag), block(kDhThreads);
+    // A workgroup takes as many blocks of 16 lags as the filter has, or half and half of that where the launch leaves compute
+    // units without one: its waves then share the steps of a staging (forward and gradients, fp32, whole blocks / shared, us:
+    // 5 x 338 x 256, 128 taps 46 / 33, 2 x 1123 x 256 45 / 39, 1 x 1218 x 1000, one filter per channel 95 / 70; 2 x 2048 x 1024,
+    // which fills the chip, 86 either way).
+    int lagw = s.lh <= 16 ? 1 : s.lh <= 32 ? 2 : s.lh <= 64 ? 4 : 8;
+    auto lag_blocks = [&](int w) { return (s.lh + 16 * w - 1) / (16 * w); };
+    while (lagw > 2 && s.B * tiles * ncb * lag_blocks(lagw / 2) <= 256) lagw /= 2;
+    const dim3 grid((uint32_t)(s.B * tiles * ncb), (uint32_t)lag_blocks(lagw)), block(kDhThreads);
     auto go = [&](auto gated_c) {
         constexpr bool G = decltype(gated_c)::value;
-        if (s.lh <= 16) return launch_kernel((dh_tile_kernel<T, VEC, 1, G>), grid, block, st, a);
-        if (s.lh <= 32) return launch_kernel((dh_tile_kernel<T, VEC, 2, G>), grid, block, st, a);
-        if (s.lh <= 64) return launch_kernel((dh_tile_kernel<T, VEC, 4, G>), grid, block, st, a);
+        if (lagw == 1) return launch_kernel((dh_tile_kernel<T, VEC, 1, G>), grid, block, st, a);
+        if (lagw == 2) return launch_kernel((dh_tile_kernel<T, VEC, 2, G>), grid, block, st, a);
+        if (lagw == 4) return launch_kernel((dh_tile_kernel<T, VEC, 4, G>), grid, block, st, a);
         return launch_kernel((dh_tile_kernel<T, VEC, 8, G>), grid, block, st, a);
     };
     const hy_status rc = s.gated ? go(std::true_type{}) : go(std::false_type{});
