@@ -301,14 +301,20 @@ __device__ __forceinline__ void reduce_item(const ReduceItem& it, double* red) {
     }
 }
 
+// kRedParts: the lanes per output of every item; 0: each has its own
+template <int kRedParts>
 __global__ __launch_bounds__(kBlock) void dh_reduce_kernel(ReduceArgs a) {
     __shared__ double red[kBlock];
     const ReduceItem it = a.p[blockIdx.y];
-    switch (it.parts) {
-        case 1: return reduce_item<1>(it, red);
-        case 32: return reduce_item<32>(it, red);
-        case 256: return reduce_item<256>(it, red);
-        default: return reduce_item<4>(it, red);
+    if constexpr (kRedParts > 0) {
+        reduce_item<kRedParts>(it, red);
+    } else {
+        switch (it.parts) {
+            case 1: return reduce_item<1>(it, red);
+            case 32: return reduce_item<32>(it, red);
+            case 256: return reduce_item<256>(it, red);
+            default: return reduce_item<4>(it, red);
+        }
     }
 }
 
@@ -734,6 +740,7 @@ constexpr int stencil_vec() { return T::kBytes == 2 ? 2 : 1; }
 hy_status launch_reduce(const DhReduce* items, int n, hipStream_t st) {
     ReduceArgs r{};
     int64_t nb = 0;
+    int common = -1;
     for (int i = 0; i < n; ++i) {
         const DhReduce& x = items[i];
         const int64_t nout = (x.rows / x.group) * x.lh, terms = x.nsets * x.group;
@@ -741,10 +748,18 @@ hy_status launch_reduce(const DhReduce* items, int n, hipStream_t st) {
         r.p[i] = ReduceItem{x.partial, x.dh, x.nsets, x.rows, x.lh, x.group, parts};
         const int64_t per = kBlock / parts, blocks = (nout + per - 1) / per;
         nb = blocks > nb ? blocks : nb;
+        common = i == 0 || common == parts ? parts : 0;
     }
     if (nb == 0) return HY_OK;
     if (nb > 0x7fffffffLL) return HY_ERR_UNSUPPORTED;
-    return launch_kernel(dh_reduce_kernel, dim3((uint32_t)nb, (uint32_t)n), dim3(kBlock), st, r);
+    const dim3 grid((uint32_t)nb, (uint32_t)n), block(kBlock);
+    switch (common) {
+        case 1: return launch_kernel(dh_reduce_kernel<1>, grid, block, st, r);
+        case 4: return launch_kernel(dh_reduce_kernel<4>, grid, block, st, r);
+        case 32: return launch_kernel(dh_reduce_kernel<32>, grid, block, st, r);
+        case 256: return launch_kernel(dh_reduce_kernel<256>, grid, block, st, r);
+        default: return launch_kernel(dh_reduce_kernel<0>, grid, block, st, r);
+    }
 }
 
 template <typename T, int LH>
