@@ -216,9 +216,10 @@ __device__ __forceinline__ uint32_t xcd_contiguous(uint32_t i, uint32_t n) {
     return x * q + (x < r ? x : r) + i / 8;
 }
 
-// Note on workgroup order: workgroups are dealt to the 8 XCDs round-robin by launch index.  Every kernel
-// here keeps the plain launch order with the fastest-varying tile index along a row, so that all XCDs
+// Note on workgroup order: workgroups are dealt to the 8 XCDs round-robin by launch index.  The kernels
+// here keep the plain launch order with the fastest-varying tile index along a row, so that all XCDs
 // sweep one compact address window together; giving each XCD its own contiguous range of tiles was
-// measured slower on MI355X for all of them (copy, stencil, MR).
+// measured slower on MI355X for them (copy, stencil, MR).  The general FIR kernels do give XCDs their own ranges
+// where rows are no whole cache lines and neighbouring row pieces share some.
 
 }  // namespace hy
