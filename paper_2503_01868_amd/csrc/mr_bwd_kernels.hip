@@ -58,9 +58,10 @@ struct MrBwdArgs {
 };
 
 constexpr int kChunk = 32;
+constexpr int64_t kWideRows = 1 << 23;  // channels from which on a row's 2 D bytes take more than the 24 bits of __umul24
 
-// kShard: the call is one rank's share of a sequence (halo rows next to the tensors, batch strides); the plain
-// call's instantiation carries none of that arithmetic.
+// kShard: the call is one rank's share of a sequence (halo rows next to the tensors, batch strides), or its rows are of
+// kWideRows channels and more; the plain call's instantiation carries none of that arithmetic.
 template <int NKB, int NW, int PF, bool kShard>
 __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
     constexpr int PPR = 2 * NW;              // 16-byte pieces per staged row
@@ -152,7 +153,7 @@ __global__ __launch_bounds__(NW * 64, 1) void mr_bwd_kernel(MrBwdArgs a) {
     // one cache line per wave
     const int64_t idle_off = kShard ? (L - t_end) * D + cblock0
                                     : item0 * L * D + (L - 1 - (t_start < L ? t_start : L - 1)) * D + cblock0;
-    // plain calls (D < 2^24): a uniform offset and 32 bits per lane
+    // plain calls (D < kWideRows): a uniform offset and 32 bits per lane
     const uint32_t lane_off = kShard ? 0u : 2u * ((uint32_t)(31 - lr) * (uint32_t)D + (uint32_t)ld_off);
     auto bytes_at = [](const uint16_t* p, int64_t base, uint32_t off) { return reinterpret_cast<const char*>(p) + base + off; };
     auto two_rows = [&](const uint16_t* p1, const uint16_t* p2, const At& x, bool used, Words<4>& r1, Words<4>& r2) {
@@ -446,7 +447,7 @@ Tiling tiling(const BwdShape& s) {
     const int64_t ncb = s.D / (16 * kBwdWaves), rows = mr_bwd_rows(s);
     Tiling t{rows / kChunk, (s.L + rows - 1) / rows, 0, false};
     t.ntiles = s.B * t.tiles_per_seq;
-    if (s.sharded() || s.D >= 1 << 24 || s.B < 2 || tuning().mr_rows > 0) return t;
+    if (s.sharded() || s.D >= kWideRows || s.B < 2 || tuning().mr_rows > 0) return t;
     const int64_t lag = (s.lh - 1 + 31) / 32, total = s.B * ((s.L + kChunk - 1) / kChunk + lag) - lag;
     if (total + lag > 0x7fffffffLL) return t;
     const int64_t want = ncb < 256 ? 256 / ncb : 1, chunks = (total + want - 1) / want, n = (total + chunks - 1) / chunks;
@@ -489,7 +490,7 @@ hy_status launch_nw(const BwdPtrs& p, const BwdShape& s, void* ws, hipStream_t s
     *nsets = t.ntiles;
     const int64_t nb = *nsets * a.ncb;
     if (nb > 0x7fffffffLL) return HY_ERR_UNSUPPORTED;
-    if (s.sharded() || s.D >= 1 << 24)  // (the shard form has wide row offsets)
+    if (s.sharded() || s.D >= kWideRows)  // (the shard form has wide row offsets)
         return launch_kernel((mr_bwd_kernel<NKB, NW, PF, true>), dim3((uint32_t)nb), dim3(NW * 64), st, a);
     return launch_kernel((mr_bwd_kernel<NKB, NW, PF, false>), dim3((uint32_t)nb), dim3(NW * 64), st, a);
 }

@@ -47,7 +47,7 @@ struct Fiber {
     std::vector<char> stack;
     dim3 tid;
     Wait wait = Wait::none;
-    uint64_t in[2];  // operands of the operation across lanes that the fiber waits in
+    uint64_t in[4];  // operands of the operation across lanes that the fiber waits in
 };
 
 inline std::vector<Fiber> fibers;
@@ -68,7 +68,7 @@ inline Fiber* wave() { return self - lane(); }
 // every lane's operand; the caller must not pause again before it has read the others'
 template <typename T>
 void exchange(T v, int slot = 0) {
-    static_assert(sizeof(T) <= 8, "one word");
+    static_assert(sizeof(T) <= 16, "two words");
     memcpy(&self->in[slot], &v, sizeof(T));
 }
 template <typename T>
@@ -108,6 +108,37 @@ V mfma_4x4x1(float a, float b, V c) {
     return across([&] {
         for (int i = 0; i < 4; ++i) c[i] = __builtin_fmaf(operand<float>((lane() & ~3) + i), b, c[i]);
         return c;
+    });
+}
+// 16 x 16 outputs: lane = 16 * lq + li holds row (column) li of A (B), terms E lq .. E lq + E - 1, and rows 4 lq .. 4 lq + 3 of
+// column li of the outputs.  The terms and the accumulator round once.
+template <int E, typename A, typename V>
+V mfma_16x16(A a, A b, V c) {
+    struct Row { uint16_t x[E]; };
+    exchange(a);
+    exchange(b, 2);
+    return across([&] {
+        auto value = [](uint16_t x) { return __builtin_bit_cast(float, (uint32_t)x << 16); };
+        for (int r = 0; r < 4; ++r) {
+            double s = c[r];
+            for (int q = 0; q < 4; ++q) {
+                const Row x = operand<Row>(16 * q + 4 * (lane() / 16) + r), y = operand<Row>(16 * q + lane() % 16, 2);
+                for (int e = 0; e < E; ++e) s += (double)value(x.x[e]) * (double)value(y.x[e]);
+            }
+            c[r] = (float)s;
+        }
+        return c;
+    });
+}
+// 16 lanes address 4 values each, lane i columns 4 (i % 4) on of row i / 4; lane i gets column i of the four rows
+template <typename V>
+V read_transposed(const void* p) {
+    exchange(p);
+    return across([&] {
+        V v;
+        const int l = lane() % 16, base = lane() - l;
+        for (int e = 0; e < 4; ++e) v[e] = operand<const short*>(base + 4 * e + l / 4)[l % 4];
+        return v;
     });
 }
 
@@ -172,12 +203,18 @@ inline hipError_t launch(dim3 grid, dim3 block, std::function<void()> call) {
 
 #define threadIdx (emu::self->tid)
 #define blockIdx (emu::block_idx)
+#define gridDim (emu::grid_dim)
 #define __syncthreads() emu::pause(emu::Wait::block)
 #define __shfl(v, from) emu::shfl(v, from)
 #define __builtin_amdgcn_readfirstlane(v) emu::readfirstlane(v)
 #define __builtin_amdgcn_readlane(v, from) emu::shfl(v, from)
 #define __builtin_amdgcn_ballot_w64(b) emu::ballot(b)
 #define __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, x, y, z) emu::mfma_4x4x1(a, b, c)
+#define __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, x, y, z) emu::mfma_16x16<8>(a, b, c)
+#define __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, x, y, z) emu::mfma_16x16<4>(a, b, c)
+#define __builtin_amdgcn_ds_read_tr16_b64_v4i16(p) emu::read_transposed<s16x4_t>((const void*)(p))
+#define __builtin_amdgcn_wave_barrier() emu::pause(emu::Wait::lanes)
 #define __builtin_amdgcn_sched_barrier(x) ((void)0)
+#define __umul24(a, b) (((uint32_t)(a) & 0xffffffu) * ((uint32_t)(b) & 0xffffffu))
 // the launch of `kernel` with `args`, the names they have in hy_launch.hpp
 #define hipLaunchKernel(fn, grid, block, ptrs, shared, st) ((void)(ptrs), emu::launch(grid, block, [&] { kernel(args...); }))

@@ -267,6 +267,25 @@ def test_chunk_parallel_backward_reach_of_non_finite_values(lh):
         assert all(torch.isnan(o[1, reach, c]).all() for o in outs) and torch.isnan(got[3][c]).all(), where
 
 
+@pytest.mark.parametrize("lh,L", [(9, 33), (128, 45)])
+def test_grouped_backward_of_rows_beyond_24_bits(lh, L):
+    """A row of 2^24 bytes and more and a last chunk that is not whole: wide row offsets, by the first and last channels."""
+    D, group, n = 2 ** 23 + 64, 16, 64
+    say("mr bwd wide rows lh=%d L=%d" % (lh, L))
+    g = torch.Generator(device="cuda").manual_seed(9800 + lh)
+    dy, q, k, v = (torch.randn((1, L, D), generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(4))
+    h = torch.randn((D // group, lh), generator=g, device="cuda") * lh ** -0.5
+    outs = binding.hyena_mr_bwd(dy, q, k, v, h, group)
+    for c0 in (0, D - n):
+        c = slice(c0, c0 + n)
+        a = [x[..., c].cpu().contiguous() for x in (dy, q, k, v)]
+        rows = slice(c0 // group, (c0 + n) // group)
+        ref = oracle.gated_conv_bwd(*a, np.ascontiguousarray(h[rows].cpu().numpy()), group=group)
+        for name, got, want, tol in zip(("dq", "dk", "dv", "dh"), outs, ref, (TOL["bf16"],) * 3 + (DH_TOL_MFMA,)):
+            err = oracle.rel_err(host(got[rows] if name == "dh" else got[..., c]), want)
+            assert err <= tol, (name, c0, err)
+
+
 @pytest.mark.parametrize("lh,L", [(9, 70), (66, 130)])
 def test_chunk_parallel_backward_of_rows_beyond_24_bits(lh, L):
     """A row of 2^24 bytes and more (2^23 channels and a block): the same kernel with wide row offsets, by the last channels."""
