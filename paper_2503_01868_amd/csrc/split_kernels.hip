@@ -3,12 +3,13 @@
 //
 //     out[t] = gate[t] * sum_j h[j] x[t -+ j],  x = a*b
 //
-// Every factor is split into bf16 pieces that add up to it exactly (head, then what rounding left, twice): a tap and an
-// fp32 x are three pieces, the product x of two bf16 values has 16 bits and is two.  A product of two pieces is exact in
-// fp32, so the sum of the piece products of weight 2^-16 and up (6 of 9 for fp32, 5 of 6 for bf16; the others are below
-// 2^-26 of their product) carries the rounding of its additions only, and of those the matrix instruction makes one per 32
-// terms and output where a chain of FMAs makes one per term.  At 16 times the rate of the fp32 products that is 2.7 to
-// 3.2 times their rate.
+// Every factor is split into bf16 pieces that add up to it: head, then what rounding left times 2^8, twice, so that a piece
+// is as large as its factor may be and keeps its bits down to the smallest normal numbers.  A tap and an fp32 x are three
+// pieces, the product x of two bf16 values has 16 bits and is two.  A product of two pieces is exact in fp32.  The sums of the
+// piece products of one weight (1, 2^-8, 2^-16; 6 of 9 for fp32, 5 of 6 for bf16) are kept apart and joined at the end; the
+// products left out are two of 2^-25 of theirs at most (bf16: one) and one far below.  What else rounds is the additions, and of
+// those the matrix instruction makes one per 32 terms and output where a chain of FMAs makes one per term.  At 16 times the rate
+// of the fp32 products that is 2.7 to 3.2 times their rate.
 //
 // A workgroup owns 64 channels and walks a tile of the sequence in chunks of 64 steps (towards the past for the transposed
 // sum, which is then causal) like mr_kernels.hip: rows of a and b are loaded two chunks ahead, x goes as bf16 planes
@@ -78,7 +79,8 @@ __global__ __launch_bounds__(kThreads, 2) void split_fir_kernel(SplitArgs a) {
     using Raw = typename PV::Raw;
     __shared__ uint4 planes[kBuf][P * kPlane / 16];
     __shared__ __attribute__((aligned(16))) char zst[2][kChunk * kZRow];
-    __shared__ float hs[kWaves][kTapPad + kTaps];
+    // the pieces of a wave's filter: word kTapPad + j holds those of taps j (low half) and j - 1, zero outside the filter
+    __shared__ uint32_t hs[kWaves][3][kTapPad + kTaps + 1];
 
     uint32_t order = blockIdx.y * gridDim.x + blockIdx.x;
     if (a.together) order = xcd_contiguous(order, gridDim.x * gridDim.y);
@@ -151,25 +153,41 @@ __global__ __launch_bounds__(kThreads, 2) void split_fir_kernel(SplitArgs a) {
     {
         int64_t c0 = cblock + (kGroup == 16 ? 16 * (w >> 1) : 8 * w);
         c0 = c0 < D ? c0 : D - 1;  // past the last channel: any filter
-        stage_filter<kTaps>(hs[w], pr.h + (uint32_t)c0 / (uint32_t)a.group * (int64_t)lh, lh, lane);
-        __syncthreads();
-        const float* p = hs[w] + kTapPad + (kGroup == 16 ? 16 * (w & 1) : 16) + li - 8 * lq;
+        const float* hp = pr.h + (uint32_t)c0 / (uint32_t)a.group * (int64_t)lh;
+        constexpr int kEach = (kTapPad + kTaps + kWave - 1) / kWave;
+        float f[kEach];
 #pragma unroll
-        for (int m = 0; m < NKB; ++m) {
-            Words<4> x[3];
+        for (int i = 0; i < kEach; ++i) {
+            const int j = i * kWave + lane - kTapPad;
+            f[i] = hp[j >= 0 && j < lh ? j : 0];
+        }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float h0 = p[kBlock * m - 2 * e], h1 = p[kBlock * m - 2 * e - 1];
+        for (int i = 0; i < kEach; ++i) {
+            const int word = i * kWave + lane, j = word - kTapPad;
+            float x = j >= 0 && j < lh ? f[i] : 0.0f;
 #pragma unroll
-                for (int s = 0; s < 3; ++s) {
-                    x[s].w[e] = pack_bf16x2(h0, h1);
-                    h0 -= bf16_lo(x[s].w[e]);
-                    h1 -= bf16_hi(x[s].w[e]);
+            for (int s = 0; s < 3; ++s) {
+                const uint32_t piece = pack_bf16x2(x, 0.0f);
+                x = (x - bf16_lo(piece)) * 256.0f;
+                uint16_t* half = reinterpret_cast<uint16_t*>(&hs[w][s][word]);
+                if (word < kTapPad + kTaps) {
+                    half[0] = (uint16_t)piece;
+                    half[3] = (uint16_t)piece;
                 }
             }
-#pragma unroll
-            for (int s = 0; s < 3; ++s) tz[m][s] = __builtin_bit_cast(bf16x8_t, x[s]);
         }
+        __syncthreads();
+        // (no lane reads word 0, whose high half is not written)
+        const int p = kTapPad + (kGroup == 16 ? 16 * (w & 1) : 16) + li - 8 * lq;
+#pragma unroll
+        for (int m = 0; m < NKB; ++m)
+#pragma unroll
+            for (int s = 0; s < 3; ++s) {
+                Words<4> x;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x.w[e] = hs[w][s][p + kBlock * m - 2 * e];
+                tz[m][s] = __builtin_bit_cast(bf16x8_t, x);
+            }
     }
 
     // ---- window: source block m, piece s
@@ -273,12 +291,13 @@ __global__ __launch_bounds__(kThreads, 2) void split_fir_kernel(SplitArgs a) {
         }
     };
 
-    // x of chunk c, from a register stage, into its planes; the stage is refilled with the chunk kAhead later
-    auto stage = [&](int c, int buf, Raw (&xr)[NP], Raw (&yr)[NP]) __attribute__((always_inline)) {
+    // x of chunk c, from a register stage, into its planes; the stage is refilled with the chunk kAhead later.  Only chunks of
+    // the warm-up can hold steps without data (t_data <= 0).
+    auto stage = [&](int c, int buf, Raw (&xr)[NP], Raw (&yr)[NP], auto warming) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
             const int row = i * RPP + lr;
-            const bool data = t_start + c * kChunk + row >= t_data;
+            const bool data = !decltype(warming)::value || t_start + c * kChunk + row >= t_data;
             float x[VEC], y[VEC];
             PV::unpack(xr[i], x);
             PV::unpack(yr[i], y);
@@ -293,8 +312,8 @@ __global__ __launch_bounds__(kThreads, 2) void split_fir_kernel(SplitArgs a) {
 #pragma unroll
                 for (int e = 0; e < VEC / 2; ++e) {
                     wd.w[e] = pack_bf16x2(x[2 * e], x[2 * e + 1]);
-                    x[2 * e] -= bf16_lo(wd.w[e]);
-                    x[2 * e + 1] -= bf16_hi(wd.w[e]);
+                    x[2 * e] = (x[2 * e] - bf16_lo(wd.w[e])) * 256.0f;
+                    x[2 * e + 1] = (x[2 * e + 1] - bf16_hi(wd.w[e])) * 256.0f;
                 }
                 store_words<VEC / 2>(dst + s * kPlane, wd);
             }
@@ -319,7 +338,7 @@ __global__ __launch_bounds__(kThreads, 2) void split_fir_kernel(SplitArgs a) {
             win[0][s] = __builtin_bit_cast(bf16x8_t, x);
         }
     };
-    // the sums of block `sub` of chunk c: heads apart from the rest, whose own roundings then do not count
+    // the sums of block `sub` of chunk c, each weight apart: the roundings of all but the heads' then do not count
     auto products = [&](int c, int sub) __attribute__((always_inline)) {
         f32x4_t hi = {0.0f, 0.0f, 0.0f, 0.0f}, lo[2] = {hi, hi};
 #pragma unroll
@@ -328,27 +347,24 @@ __global__ __launch_bounds__(kThreads, 2) void split_fir_kernel(SplitArgs a) {
             for (int s = P - 1; s >= 0; --s)
 #pragma unroll
                 for (int r = 2 - s; r >= 0; --r) {
-                    f32x4_t& acc = s + r == 0 ? hi : lo[r & 1];
+                    f32x4_t& acc = s + r == 0 ? hi : lo[s + r - 1];
                     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(win[m][s], tz[m][r], acc, 0, 0, 0);
                 }
-        float4 z;
-        z.x = hi[0] + (lo[0][0] + lo[1][0]);
-        z.y = hi[1] + (lo[0][1] + lo[1][1]);
-        z.z = hi[2] + (lo[0][2] + lo[1][2]);
-        z.w = hi[3] + (lo[0][3] + lo[1][3]);
+        auto joined = [&](int i) { return __builtin_fmaf(__builtin_fmaf(lo[1][i], 0x1p-8f, lo[0][i]), 0x1p-8f, hi[i]); };
+        const float4 z = make_float4(joined(0), joined(1), joined(2), joined(3));
         *reinterpret_cast<float4*>(zst[c & 1] + sub * kBlock * kZRow + zw) = z;
     };
     auto next = [&](int buf) __attribute__((always_inline)) { return buf == kBuf - 1 ? 0 : buf + 1; };
 
     int buf = 0;
-    stage(-warm, 0, ar[0], br[0]);
+    stage(-warm, 0, ar[0], br[0], std::true_type{});
 #pragma unroll
     for (int g = 0; g < kWarm; ++g) {
         if (warm > 0) {
             __syncthreads();  // this chunk's rows
             advance(buf, 0);
             advance(buf, 1);
-            stage(g - kWarm + 1, next(buf), ar[(g + 1) % 2], br[(g + 1) % 2]);
+            stage(g - kWarm + 1, next(buf), ar[(g + 1) % 2], br[(g + 1) % 2], std::true_type{});
             buf = next(buf);
         }
     }
@@ -361,7 +377,7 @@ __global__ __launch_bounds__(kThreads, 2) void split_fir_kernel(SplitArgs a) {
                 advance(buf, 0);
                 if (c > 0) finish(c - 1, gr[g ^ 1], gr2[g ^ 1]);
                 load_gate(c + 1, gr[g ^ 1], gr2[g ^ 1]);
-                stage(c + 1, next(buf), ar[(g + 1 + kOdd) % 2], br[(g + 1 + kOdd) % 2]);
+                stage(c + 1, next(buf), ar[(g + 1 + kOdd) % 2], br[(g + 1 + kOdd) % 2], std::false_type{});
                 products(c, 0);
                 advance(buf, 1);
                 products(c, 1);

@@ -6,7 +6,8 @@
 
 #include "mr_bwd_kernels.hip"
 
-static uint16_t to_bf16(float x) {  // round to nearest even, finite values
+// Round to nearest even, finite values.  (Not optimised: the compiler knows the idiom and would call its own conversion.)
+__attribute__((optnone)) static uint16_t to_bf16(float x) {
     const uint32_t u = __builtin_bit_cast(uint32_t, x);
     return (uint16_t)((u + 0x7fff + ((u >> 16) & 1)) >> 16);
 }

@@ -35,6 +35,28 @@ def test_split_products(shape, dtype):
         assert oracle.rel_err(host(got), want) <= (TOL["f32"] if name == "dh" else tol), name
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("group", [8, 16])
+@pytest.mark.parametrize("size,tap", [(1e-18, 1.0), (1e-9, 1e-17), (1.0, 1e-35)])
+def test_small_magnitudes(size, tap, group, dtype):
+    """k * v, or taps, of 1e-36 and sums that are normal numbers: the same relative error as at 1."""
+    say("split products, k and v of %g, taps of %g, groups of %d, %s" % (size, tap, group, dtype))
+    q, k, v, h = draw(9900, 1, 300, 48, 128, group, dtype, kind="mr")
+    dy = synth.normal_tensor(np.random.Generator(np.random.PCG64(9901)), (1, 300, 48), dtype)
+    k, v, h = k * size, v * size, (h * np.float32(tap)).astype(np.float32)
+    # gradients: the transposed sum over dy * q, times k or v (the forward's dq: times dy)
+    dy, q = (dy, q) if tap < 1 else (dy * size, q * size)
+    back = 1.0 if tap < 1 else 1 / size  # gates that bring the results back to sums' sizes
+    tol = 1e-6 if dtype == "f32" else 2.0 ** -8
+    one = torch.ones_like(q)
+    y = host(binding.hyena_mr_fwd(dev(one), dev(k), dev(v), dev(h), group))
+    assert oracle.rel_err(y, oracle.gated_conv(one, k, v, h, group=group)) <= tol
+    kk, vv = k * back, v * back
+    _, dk, dv, _ = (host(x) for x in binding.hyena_mr_bwd(dev(dy), dev(q), dev(kk), dev(vv), dev(h), group))
+    _, rk, rv, _ = oracle.gated_conv_bwd(dy, q, kk, vv, h, group=group)
+    assert oracle.rel_err(dk, rk) <= tol and oracle.rel_err(dv, rv) <= tol
+
+
 @pytest.mark.parametrize("L,at", [(300, 0), (300, 63), (900, 640)])
 def test_values_that_are_not_finite(L, at):
     B, D, lh, group = 1, 24, 128, 8

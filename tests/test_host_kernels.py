@@ -31,3 +31,8 @@ def test_fir_kernel_walks(tmp_path):
 def test_grouped_backward(tmp_path):
     """Gradients of batches and of rows beyond 24 bits, with nothing read or written outside the tensors."""
     run("mr_bwd_emu", "MR backward emulation", tmp_path, "-O1")
+
+
+def test_split_products(tmp_path):
+    """The general FIR on split bf16 products: fp32 precision at every magnitude, whichever wave runs ahead."""
+    run("split_emu", "split emulation", tmp_path, "-O1")
