@@ -405,7 +405,8 @@ hy_status launch_as(SplitArgs& a, int nprob, int64_t B, hipStream_t st) {
     }
     const int64_t rows = (chunks + tiles - 1) / tiles * kChunk;
     tiles = (a.L + rows - 1) / rows;
-    if (B > 0x7fffffffLL || B * tiles > 0x7fffffffLL / a.ncb) return HY_ERR_UNSUPPORTED;
+    // (HIP takes fewer than 2^32 threads: the general kernel's workgroups are half the size)
+    if (B > 0x7fffffffLL || B * tiles > 0xffffffffLL / kThreads / a.ncb) return HY_ERR_UNSUPPORTED;
     a.rows = (int32_t)rows;
     a.tiles_per_seq = (int32_t)tiles;
     return launch_kernel((split_fir_kernel<T, kGroup, NKB, kTwo>), dim3((uint32_t)(B * tiles * a.ncb), (uint32_t)nprob),

@@ -34,7 +34,7 @@ inline double2 make_double2(double x, double y) { return {x, y}; }
 inline float __uint_as_float(uint32_t u) { return __builtin_bit_cast(float, u); }
 inline uint32_t __float_as_uint(float f) { return __builtin_bit_cast(uint32_t, f); }
 typedef void* hipStream_t;
-enum hipError_t { hipSuccess = 0 };
+enum hipError_t { hipSuccess = 0, hipErrorInvalidConfiguration = 9 };
 
 namespace emu {
 
@@ -188,6 +188,7 @@ inline void run_block() {
 }
 
 inline hipError_t launch(dim3 grid, dim3 block, std::function<void()> call) {
+    if ((uint64_t)grid.x * block.x > 0xffffffffu) return hipErrorInvalidConfiguration;
     block_dim = block;
     grid_dim = grid;
     body = call;

@@ -13,7 +13,11 @@ __attribute__((optnone)) static uint16_t to_bf16(float x) {
 extern "C" __bf16 __truncsfbf2(float x) { return __builtin_bit_cast(__bf16, to_bf16(x)); }  // the compiler's conversion
 
 namespace hy {
-hy_status launch_fir(const FirProblem*, int, int64_t, int64_t, int64_t, int32_t, int32_t, hy_dtype, hipStream_t) { return HY_ERR_LAUNCH; }
+static bool g_general;  // a call came to the general kernel
+hy_status launch_fir(const FirProblem*, int, int64_t, int64_t, int64_t, int32_t, int32_t, hy_dtype, hipStream_t) {
+    g_general = true;
+    return HY_OK;
+}
 }  // namespace hy
 
 using namespace hy;
@@ -123,6 +127,22 @@ int check(const Case& k) {
     return bad;
 }
 
+// The kernel that the dispatch takes for a forward call.
+int check_route(int64_t B, int64_t L, int64_t D, int lh, int group, bool bf16, bool general) {
+    ConvShape s;
+    s.B = B; s.L = L; s.D = D; s.lh = lh; s.group = group; s.gated = true; s.dtype = bf16 ? HY_BF16 : HY_F32;
+    float x = 0;
+    const ConvPtrs p{&x, &x, &x, &x, &x};
+    emu::wanted = [](dim3) { return false; };
+    g_general = false;
+    const hy_status rc = launch_direct(&p, 1, s, nullptr);
+    emu::wanted = [](dim3) { return true; };
+    const bool bad = rc != HY_OK || g_general != general;
+    printf("B=%lld L=%lld D=%lld lh=%d group=%d %s: status %d, %s kernel%s\n", (long long)B, (long long)L, (long long)D, lh, group,
+           bf16 ? "bf16" : "f32", (int)rc, g_general ? "general" : "this", bad ? " <-" : "");
+    return bad;
+}
+
 }  // namespace
 
 int main() {
@@ -148,6 +168,11 @@ int main() {
             bad += check({130, 16 + 2 * group, 40, group, bf16, false, 1.0f, 1e-35f});
             bad += check({130, 16 + 2 * group, 9, group, bf16, true, 1e-9f, 1e-17f});
         }
+    bad += check_route(1, 128, 8, 9, 8, false, false);
+    // as many workgroups as HIP takes threads for (fewer than 2^32), and more, which the general kernel's smaller ones may fit
+    bad += check_route((1 << 23) - 1, 64, 8, 9, 8, false, false);
+    bad += check_route(1 << 23, 64, 8, 9, 8, false, true);
+    bad += check_route(10000000, 64, 8, 128, 8, true, true);
     printf("split emulation: %d problem(s)\n", bad);
     return bad != 0;
 }
