@@ -54,7 +54,8 @@ constexpr int kZRow = kChan * 4 + 16;   // a row of sums
 struct SplitArgs {
     FirProblem p[2];
     int64_t L, D;
-    int32_t lh, group;
+    int32_t lh, group;  // lh: the taps that can meet data
+    int32_t row_taps;   // taps per filter in memory
     int32_t rows, tiles_per_seq, ncb;
     int32_t together;  // neighbouring channel blocks on one XCD
 };
@@ -153,7 +154,7 @@ __global__ __launch_bounds__(kThreads, 2) void split_fir_kernel(SplitArgs a) {
     {
         int64_t c0 = cblock + (kGroup == 16 ? 16 * (w >> 1) : 8 * w);
         c0 = c0 < D ? c0 : D - 1;  // past the last channel: any filter
-        const float* hp = pr.h + (uint32_t)c0 / (uint32_t)a.group * (int64_t)lh;
+        const float* hp = pr.h + (uint32_t)c0 / (uint32_t)a.group * (int64_t)a.row_taps;
         constexpr int kEach = (kTapPad + kTaps + kWave - 1) / kWave;
         float f[kEach];
 #pragma unroll
@@ -223,7 +224,7 @@ __global__ __launch_bounds__(kThreads, 2) void split_fir_kernel(SplitArgs a) {
     // chunk c's sums where this lane reads them, term by term from global memory, in ascending source order (causal) or tap
     // order; the channels of a piece share their filter
     auto exact_sums = [&](int c) __attribute__((always_inline)) {
-        const float* hp = pr.h + (uint32_t)col / (uint32_t)a.group * (int64_t)lh;
+        const float* hp = pr.h + (uint32_t)col / (uint32_t)a.group * (int64_t)a.row_taps;
 #pragma unroll 1
         for (int row = lr; row < kChunk; row += RPP) {
             const int tau = t_start + c * kChunk + row;
@@ -435,10 +436,33 @@ hy_status launch_t(SplitArgs& a, int nprob, int64_t B, bool two, hipStream_t st)
 
 hy_status launch_split_fir(const FirProblem* p, int nprob, int64_t B, int64_t L, int64_t D, int32_t lh, int32_t group,
                            hy_dtype dtype, hipStream_t st) {
-    // (gradients of up to 32 taps, general kernel / this one, whole call: 3 x 300 x 1000 bf16 22.3 / 24.3 us, 9 taps, 25.0 /
-    // 25.2, 32 taps, 2 x 2000 x 1000 the same; 33 taps 28.7 / 27.6, 62 / 54)
-    if (nprob == 2 && lh <= 32) return HY_ERR_UNSUPPORTED;
+    const int32_t row_taps = lh;
+    // taps beyond the first row with data (causal) or the last (transposed) meet none
+    int64_t reach = 1;
+    for (int i = 0; i < nprob; ++i) {
+        const int64_t r = p[i].rev ? p[i].hi : L - p[i].lo;
+        if (r > reach) reach = r;
+    }
+    if (lh > reach) lh = (int32_t)reach;
     if (nprob < 1 || nprob > 2 || group % 8 != 0 || lh < 9 || lh > 129 || L > 0x3fff0000LL || D > 0x7fff0000LL) return HY_ERR_UNSUPPORTED;
+    // A workgroup has a compute unit to itself and works in chunks of 64 steps, so where sequences come in several rounds of
+    // workgroups the short ones pay for padding and for starts that nothing hides, which the general kernel's smaller workgroups
+    // hide among themselves; and up to 32 taps its segments of 16 and 32 are about as fast as blocks of 32 source steps.  Columns of
+    // 64 channels; us, general kernel / this one:
+    //   more than 32 taps: 128 columns, 128 taps, bf16 33 steps 7.8 / 6.3, 80 11.8 / 7.0; 512 x 33 x 1000 fp32 74 / 81,
+    //     1600 x 80 x 1000, 40 taps fp32 53 / 53, bf16 49 / 40, 128 taps fp32 83 / 56, 1344 x 97 x 1000, 40 taps fp32 51 / 46;
+    //     17 x 300 x 1000, 40 and 128 taps, this one's share of the time 0.61 and 0.52, fp32 0.68 and 0.50;
+    //   up to 32: 3 x 5003 x 1000 bf16, 9 taps 36.2 / 31.3, 16 36.1 / 30.7, 32 39.2 / 30.7, fp32 55 / 49.3, 54.8 / 49.2, 56.8 / 49.4;
+    //     this one's share at 128 columns, 9, 16, 17 and 32 taps, bf16, 8 x 400 0.95, 0.93, 0.88, 0.88, 8 x 1300 0.88, 0.88, 0.81, 0.80;
+    //     192 columns 12 x 450 1.04, 1.02, 0.93, 0.91, 12 x 1200 1.14, 1.14, 1.05, 1.03, 12 x 1600 0.99, 0.99, 0.91, 0.92; 272 columns
+    //     17 x 300 1.16, 1.15, 1.03, 1.03, fp32 1.18, 1.17, 1.10, 1.11, 17 x 1700 0.89, 0.88, 0.89, 0.89, fp32 0.87, 0.89, 0.93, 0.92;
+    //     1024 columns 64 x 128 0.88 to 0.90, 64 x 160 1.32, 1.16 (9 and 24 taps), 4096 columns and more of 4 to 80 steps 1.3 to 3;
+    //   gradients of up to 32 taps: 3 x 300 x 1000 bf16 22.3 / 24.3, 9 taps, 25.0 / 25.2, 32 taps, 2 x 2000 x 1000 the same (33
+    //     taps 28.7 / 27.6, 62 / 54).
+    const int64_t ncb = (D + kChan - 1) / kChan, columns = B * ncb * nprob;
+    const bool served = lh > 32 ? columns <= 256 || L > (dtype == HY_BF16 || lh > 64 ? 64 : 96)
+                                : nprob == 1 && (L >= 1536 || columns <= (lh > 16 ? 256 : 128));
+    if (!served) return HY_ERR_UNSUPPORTED;
     SplitArgs a;
     bool two = false;
     for (int i = 0; i < 2; ++i) {
@@ -449,8 +473,8 @@ hy_status launch_split_fir(const FirProblem* p, int nprob, int64_t B, int64_t L,
     a.L = L;
     a.D = D;
     a.lh = lh;
+    a.row_taps = row_taps;
     a.group = group;
-    const int64_t ncb = (D + kChan - 1) / kChan;
     a.ncb = (int32_t)ncb;
     // rows that are no whole lines: a piece shares its first and last line with its neighbours', so those go to one L2 (3 x
     // 5003 x 1000 bf16: 216 -> 141 MB, 40.4 -> 37.9 us, fp32 59.1 -> 50.8; rows of whole lines run better spread out, general

@@ -170,9 +170,26 @@ int main() {
         }
     bad += check_route(1, 128, 8, 9, 8, false, false);
     // as many workgroups as HIP takes threads for (fewer than 2^32), and more, which the general kernel's smaller ones may fit
-    bad += check_route((1 << 23) - 1, 64, 8, 9, 8, false, false);
-    bad += check_route(1 << 23, 64, 8, 9, 8, false, true);
-    bad += check_route(10000000, 64, 8, 128, 8, true, true);
+    bad += check_route((1 << 23) - 1, 65, 8, 129, 8, false, false);
+    bad += check_route(1 << 23, 65, 8, 129, 8, false, true);
+    bad += check_route(10000000, 100, 8, 128, 8, true, true);
+    // short sequences in several rounds of workgroups, by taps that meet data; one round
+    for (bool bf16 : {false, true}) {
+        bad += check_route(4096, 4, 1000, 128, 8, bf16, true);
+        bad += check_route(1, 8, 64, 128, 8, bf16, true);
+        bad += check_route(1, 9, 64, 128, 8, bf16, false);
+        bad += check_route(512, 33, 1000, 128, 8, bf16, true);
+        bad += check_route(17, 64, 1000, 129, 8, bf16, true);
+        bad += check_route(16, 64, 1000, 129, 8, bf16, false);
+        bad += check_route(17, 65, 1000, 129, 8, bf16, false);
+        bad += check_route(17, 96, 1000, 64, 8, bf16, !bf16);
+        bad += check_route(17, 97, 1000, 33, 8, bf16, false);
+        bad += check_route(17, 1535, 1000, 32, 8, bf16, true);
+        bad += check_route(17, 1536, 1000, 9, 8, bf16, false);
+        bad += check_route(16, 300, 1000, 17, 8, bf16, false);
+        bad += check_route(9, 300, 1000, 16, 8, bf16, true);
+        bad += check_route(8, 300, 1000, 16, 8, bf16, false);
+    }
     printf("split emulation: %d problem(s)\n", bad);
     return bad != 0;
 }
