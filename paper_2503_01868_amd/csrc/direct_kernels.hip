@@ -390,12 +390,22 @@ hy_status launch_nt(FirArgs& a, int nprob, int64_t B, hipStream_t st) {
     if (steps > 0x7fffffffLL || B > 0x7fffffffLL || B * walks > 0x7fffffffLL / a.ncb) return HY_ERR_UNSUPPORTED;
     a.steps = (int32_t)steps;
     a.walks_per_seq = (int32_t)walks;
-    // Rows of 16-byte pieces that are no whole lines: a row piece shares its first and last line with its neighbours', which one
-    // L2 then holds for all (us, apart / together: 3 x 5003 x 1000 bf16, 16 taps 39 / 33, 128 taps 74 / 68, 1 x 4000 x 1000 fp32
-    // 18.8 / 16.1 and 32 / 28; rows of whole lines run better spread out, and so do few workgroups, 1 x 700 x 1000, 352 of them,
-    // 11.4 / 11.6, and two problems side by side, gradients 2 x 2000 x 1000 120.6 / 122.7).
-    const int64_t nblocks = B * walks * a.ncb;
-    a.together = VEC > 1 && a.D * T::kBytes % 128 != 0 && nprob == 1 && nblocks >= 416 ? (uint32_t)nblocks : 0;
+    // Rows that are no whole lines: a row piece shares its first and last line with its neighbours', which one L2 then holds for
+    // all.  Us, apart / together: 2 x 1500 x 1000, 9 taps bf16 12.5 / 10.4, fp32 16.1 / 13.8, x 1001 15.9 / 14.5 and 17.7 / 16.3;
+    // 1 x 3000 x 1000, 64 taps bf16 17.6 / 15.8, fp32 20.4 / 18.4.  Not
+    // - where every workgroup has a compute unit to itself anyway (128 taps fp32 1 x 300 x 1000, 160 of them, 11.3 / 11.9, 1 x 600 x
+    //   1000, 304 of them, 14.5 / 13.9);
+    // - for rows of whole lines, which run better spread out (2 x 2048 x 1024 fp32, forward and gradients 109 / 118), and two problems
+    //   side by side (gradients 2 x 2000 x 1000 120.6 / 122.7);
+    // - for wide fp32 rows of short sequences (64 x 128 x 4088, 9 taps 121 / 137, 40 x 100 x 4088 68 / 70, 100 x 40 x 6000 94 / 98;
+    //   64 x 128 x 3000 94 / 95, 20 x 200 x 3000 58 / 53, x 6000 95 / 92, 5 x 1000 x 4088 84 / 75, bf16 20 x 200 x 8184 85 / 75);
+    // - for several segments of wide rows (1 x 4000 x 4088, 250 taps fp32 172 / 193), or where XCDs would have unequal shares: the
+    //   first tiles of a sequence leave segments out (2 x 700 x 1000, 300 taps fp32 47 / 50.5, 1 x 9000 x 1000, 1000 taps 344 / 356;
+    //   1 x 4000 x 1000, 250 taps 51 / 46, 8 x 300 x 1000, 250 taps 41.5 / 35.6).
+    const int64_t nblocks = B * walks * a.ncb, row = a.D * T::kBytes;
+    const bool even = kOne ? T::kBytes == 2 || row <= 12288 || a.L >= 192
+                           : row <= 4096 && (B >= 8 || 16 * (int64_t)a.lh <= a.L);
+    a.together = row % 128 != 0 && nprob == 1 && nblocks > 256 && even ? (uint32_t)nblocks : 0;
     return launch_kernel((fir_kernel<T, VEC, kSeg, NT, kOne>), dim3((uint32_t)nblocks, (uint32_t)nprob),
                          dim3(kThreads), st, a);
 }

@@ -68,7 +68,8 @@ int check(int64_t L, int64_t D, int lh, int group, bool bf16, bool rev, bool des
         }
     if (infinite != kFinite) a.set(rev ? t1 - 1 - infinite : t0 + infinite, c0 + 5, INFINITY);
     p.a = a.p; p.b = b.p; p.h = h; p.gate = gate.p; p.out = out.p;
-    emu::wanted = [&](dim3 i) { return i.x == ncb + (ncb - 1); };
+    const uint32_t n = emu::grid_dim.x, block = (uint32_t)(ncb + (ncb - 1));  // (in whichever order the launch has them)
+    emu::wanted = [&](dim3 i) { return i.x == block || xcd_contiguous(i.x, n) == block; };
     emu::wave_order = [&](int i, int n) { return descending ? n - 1 - i : i; };
     if (launch() != HY_OK) return printf("launch\n"), 1;
     int64_t wrong = 0;
@@ -109,8 +110,18 @@ int check_rows(int64_t B, int64_t L, int64_t D, int lh, int rows) {
 }  // namespace
 
 int main() {
+    int lost = 0;  // every tile once, whatever their number
+    for (uint32_t n = 1; n < 700; ++n) {
+        std::vector<int> seen(n, 0);
+        for (uint32_t i = 0; i < n; ++i) {
+            const uint32_t x = xcd_contiguous(i, n);
+            if (x < n) ++seen[x];
+        }
+        for (uint32_t i = 0; i < n; ++i) lost += seen[i] != 1;
+    }
+    if (lost) printf("order of workgroups: %d tiles not once\n", lost);
     const int64_t L = 128 * 3 * 64 - 50;  // three tiles of 128 rows or more of 32 to a walk
-    int bad = 0;
+    int bad = lost != 0;
     for (int lh : {12, 20, 40, 65, 128})  // one segment of 16, 32, 64, 128 taps
         for (int i = 0; i < 4; ++i) {
             const int64_t D = i / 2 ? 509 : 512;  // rows of single elements, of 16-byte pieces

@@ -178,7 +178,8 @@ def us_per_call(call):
 
 def test_odd_widths_keep_up():
     """Rows of single elements (an odd width) against rows of 16-byte pieces, 9 taps: 1.7 (fp32) and 2.1 (bf16) times as
-    long with 16 rows of a workgroup's 64 channels in flight, in tiles of 128; 1.2 and 1.3 times with 32, in tiles of 32."""
+    long with 16 rows of a workgroup's 64 channels in flight, in tiles of 128; 1.2 and 1.4 times with 32, in tiles of 32 and
+    either's channel blocks together on an XCD (1.3 and 1.6 where only the even width's are)."""
 
     def us(D, dtype):
         x = [torch.randn((2, 1500, D), device="cuda:0").to(dtype) for _ in range(3)]
