@@ -391,19 +391,26 @@ __global__ __launch_bounds__(kThreads, 2) void split_fir_kernel(SplitArgs a) {
     else finish(nchunks - 1, gr[0], gr2[0]);
 }
 
-template <typename T, int kGroup, int NKB, bool kTwo>
-hy_status launch_as(SplitArgs& a, int nprob, int64_t B, hipStream_t st) {
-    // as many tiles per sequence as make the fewest chunks in a row, a tile's start and its warm-up priced as chunks
-    const int64_t columns = B * a.ncb * nprob, chunks = (a.L + kChunk - 1) / kChunk;
-    constexpr int64_t resident = 256, kStart = NKB > 3 ? 3 : 2;
-    auto cost = [&](int64_t n) { return (columns * n + resident - 1) / resident * ((chunks + n - 1) / n + kStart); };
+// As many tiles per sequence as make the fewest chunks in a row, a tile's start and its warm-up (by the source blocks of a
+// window) priced as chunks; `cost`: those chunks.
+int64_t tiles_per_sequence(int64_t columns, int64_t chunks, int nkb, int64_t* cost) {
+    constexpr int64_t resident = 256;
+    const int64_t start = nkb > 3 ? 3 : 2, least = (columns + resident - 1) / resident;
+    auto chunks_in_a_row = [&](int64_t n) { return (columns * n + resident - 1) / resident * ((chunks + n - 1) / n + start); };
     int64_t tiles = 1;
-    const int64_t least = (columns + resident - 1) / resident;
     for (int64_t rounds = least; rounds < least + 4; ++rounds) {
         int64_t n = rounds * resident / columns;
         n = n < chunks ? n : chunks;
-        if (n > 0 && cost(n) < cost(tiles)) tiles = n;
+        if (n > 0 && chunks_in_a_row(n) < chunks_in_a_row(tiles)) tiles = n;
     }
+    *cost = chunks_in_a_row(tiles);
+    return tiles;
+}
+
+template <typename T, int kGroup, int NKB, bool kTwo>
+hy_status launch_as(SplitArgs& a, int nprob, int64_t B, hipStream_t st) {
+    const int64_t chunks = (a.L + kChunk - 1) / kChunk;
+    int64_t cost, tiles = tiles_per_sequence(B * a.ncb * nprob, chunks, NKB, &cost);
     const int64_t rows = (chunks + tiles - 1) / tiles * kChunk;
     tiles = (a.L + rows - 1) / rows;
     // (HIP takes fewer than 2^32 threads: the general kernel's workgroups are half the size)
@@ -447,21 +454,31 @@ hy_status launch_split_fir(const FirProblem* p, int nprob, int64_t B, int64_t L,
     if (nprob < 1 || nprob > 2 || group % 8 != 0 || lh < 9 || lh > 129 || L > 0x3fff0000LL || D > 0x7fff0000LL) return HY_ERR_UNSUPPORTED;
     // A workgroup has a compute unit to itself and works in chunks of 64 steps, so where sequences come in several rounds of
     // workgroups the short ones pay for padding and for starts that nothing hides, which the general kernel's smaller workgroups
-    // hide among themselves; and up to 32 taps its segments of 16 and 32 are about as fast as blocks of 32 source steps.  Columns of
-    // 64 channels; us, general kernel / this one:
-    //   more than 32 taps: 128 columns, 128 taps, bf16 33 steps 7.8 / 6.3, 80 11.8 / 7.0; 512 x 33 x 1000 fp32 74 / 81,
-    //     1600 x 80 x 1000, 40 taps fp32 53 / 53, bf16 49 / 40, 128 taps fp32 83 / 56, 1344 x 97 x 1000, 40 taps fp32 51 / 46;
-    //     17 x 300 x 1000, 40 and 128 taps, this one's share of the time 0.61 and 0.52, fp32 0.68 and 0.50;
-    //   up to 32: 3 x 5003 x 1000 bf16, 9 taps 36.2 / 31.3, 16 36.1 / 30.7, 32 39.2 / 30.7, fp32 55 / 49.3, 54.8 / 49.2, 56.8 / 49.4;
-    //     this one's share at 128 columns, 9, 16, 17 and 32 taps, bf16, 8 x 400 0.95, 0.93, 0.88, 0.88, 8 x 1300 0.88, 0.88, 0.81, 0.80;
-    //     192 columns 12 x 450 1.04, 1.02, 0.93, 0.91, 12 x 1200 1.14, 1.14, 1.05, 1.03, 12 x 1600 0.99, 0.99, 0.91, 0.92; 272 columns
-    //     17 x 300 1.16, 1.15, 1.03, 1.03, fp32 1.18, 1.17, 1.10, 1.11, 17 x 1700 0.89, 0.88, 0.89, 0.89, fp32 0.87, 0.89, 0.93, 0.92;
-    //     1024 columns 64 x 128 0.88 to 0.90, 64 x 160 1.32, 1.16 (9 and 24 taps), 4096 columns and more of 4 to 80 steps 1.3 to 3;
-    //   gradients of up to 32 taps: 3 x 300 x 1000 bf16 22.3 / 24.3, 9 taps, 25.0 / 25.2, 32 taps, 2 x 2000 x 1000 the same (33
-    //     taps 28.7 / 27.6, 62 / 54).
+    // hide among themselves; and up to 32 taps its segments of 16 and 32 are about as fast as blocks of 32 source steps.  This
+    // kernel's share of the general one's time, by columns of 64 channels:
+    // - more than 32 taps: 128 columns, 128 taps, bf16 33 steps 0.80, 80 0.59, fp32 0.82, 0.57; 1344 and more, 40 taps 33 steps 0.93,
+    //   fp32 1.10, 64 1.03, 1.11, 80 0.81, 0.99, 97 0.83, 0.90; 128 taps 80 steps 0.58, 0.67; 17 x 300 x 1000, 40 and 128 taps 0.61,
+    //   0.52, fp32 0.68, 0.50;
+    // - up to 32 taps, 9 and 32: 3 x 5003 x 1000 bf16 0.87, 0.78 (31 us), fp32 0.90, 0.87 (49 us); 128 columns 8 x 400 x 1000 0.95, 0.88,
+    //   8 x 1300 0.88, 0.80; 256 columns 16 x 300 0.80, 0.71, fp32 0.87, 0.81; 1024 and more of 4 to 80 steps 1.3 to 3, 64 x 128 x 4088
+    //   0.89, 0.90, fp32 1.13, 1.15 (1600 x 97 x 1000 bf16 0.97, 0.97), 64 x 160 x 1000 1.32, 1.16;
+    //   longer ones by the share of the chip's time that the tiles fill (`filled`): 17 x 300 x 1000, 36%, 1.16, 1.03, fp32 1.18, 1.11,
+    //   40 x 257, 48%, 1.07, 0.96, 24 x 400, 52%, 1.04, 0.94, fp32 1.06, 1.02, 17 x 300 x 4088, 57%, 1.04, 0.87, fp32 0.99, 0.88,
+    //   17 x 300 x 6008, 59%, 0.91, 0.89, fp32 0.86, 0.87, 5 x 1000 x 6008, 80%, 0.90, 0.82, fp32 0.84, 0.82; 17 x 1700 x 1000 0.89, 0.89,
+    //   fp32 0.87, 0.92; and where tiles come in a round or two, which hide no starts, 9 x 1100 x 1000, 60%, 1.09, 0.97, 12 x 1200, 67%,
+    //   1.10, 1.01, fp32 1.00, 0.96, 16 x 600, 78%, 0.95, 0.85, fp32 1.10, 1.07;
+    // - gradients of up to 32 taps: 3 x 300 x 1000 bf16 22.3 / 24.3 us, 9 taps, 25.0 / 25.2, 32 taps, 2 x 2000 x 1000 the same (33
+    //   taps 28.7 / 27.6, 62 / 54).
     const int64_t ncb = (D + kChan - 1) / kChan, columns = B * ncb * nprob;
-    const bool served = lh > 32 ? columns <= 256 || L > (dtype == HY_BF16 || lh > 64 ? 64 : 96)
-                                : nprob == 1 && (L >= 1536 || columns <= (lh > 16 ? 256 : 128));
+    bool served = lh > 32 ? columns <= 256 || L > (dtype == HY_BF16 || lh > 64 ? 64 : 96)
+                          : nprob == 1 && (L >= 1536 || columns <= (lh > 16 || L <= 320 ? 256 : 128));
+    if (lh <= 32 && nprob == 1 && dtype == HY_BF16 && L > 96 && L <= 128) served = true;  // (the general kernel's longest tiles)
+    if (lh <= 32 && nprob == 1 && !served && L > 256) {
+        int64_t cost;
+        tiles_per_sequence(columns, (L + kChunk - 1) / kChunk, 2, &cost);
+        const int64_t filled = 100 * (columns * L) / (cost * 256 * kChunk);
+        served = filled >= (columns <= 256 ? 70 : lh > 16 ? 50 : 59);
+    }
     if (!served) return HY_ERR_UNSUPPORTED;
     SplitArgs a;
     bool two = false;

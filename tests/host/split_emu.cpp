@@ -184,11 +184,22 @@ int main() {
         bad += check_route(17, 65, 1000, 129, 8, bf16, false);
         bad += check_route(17, 96, 1000, 64, 8, bf16, !bf16);
         bad += check_route(17, 97, 1000, 33, 8, bf16, false);
-        bad += check_route(17, 1535, 1000, 32, 8, bf16, true);
-        bad += check_route(17, 1536, 1000, 9, 8, bf16, false);
-        bad += check_route(16, 300, 1000, 17, 8, bf16, false);
-        bad += check_route(9, 300, 1000, 16, 8, bf16, true);
-        bad += check_route(8, 300, 1000, 16, 8, bf16, false);
+        // (up to 32 taps: few columns, long sequences, tiles that fill 78%, 67%, 64%, 52%, 36% of the chip's
+        // time)
+        bad += check_route(16, 320, 1000, 9, 8, bf16, false);
+        bad += check_route(9, 400, 1000, 16, 8, bf16, true);
+        bad += check_route(9, 400, 1000, 17, 8, bf16, false);
+        bad += check_route(8, 400, 1000, 16, 8, bf16, false);
+        bad += check_route(17, 256, 1000, 32, 8, bf16, true);
+        bad += check_route(16, 600, 1000, 9, 8, bf16, false);
+        bad += check_route(12, 1200, 1000, 9, 8, bf16, true);
+        bad += check_route(17, 1535, 1000, 9, 8, bf16, false);
+        bad += check_route(24, 400, 1000, 16, 8, bf16, true);
+        bad += check_route(24, 400, 1000, 32, 8, bf16, false);
+        bad += check_route(17, 300, 1000, 32, 8, bf16, true);
+        bad += check_route(64, 128, 1000, 9, 8, bf16, !bf16);
+        bad += check_route(64, 96, 1000, 9, 8, bf16, true);
+        bad += check_route(12, 1536, 1000, 9, 8, bf16, false);
     }
     printf("split emulation: %d problem(s)\n", bad);
     return bad != 0;
