@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes
 import importlib.util
 import os
+import warnings
 
 import torch
 
@@ -109,15 +110,19 @@ _fast = _Unmarshalled
 
 def _load_fast() -> None:
     global _fast
+    path = _build.ensure_fastcall()
+    if path is None:
+        return
     try:
-        spec = importlib.util.spec_from_file_location(__package__ + "._fastcall", _build.FAST)
+        spec = importlib.util.spec_from_file_location(__package__ + "._fastcall", path)
         module = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(module)
         module.init(tuple(ctypes.cast(getattr(_lib, name), ctypes.c_void_p).value for name in (
             "hyena_se_fwd", "hyena_mr_fwd", "hyena_se_bwd", "hyena_mr_bwd", "hyena_bwd_workspace_bytes", "hyena_chain_fwd",
             "hyena_chain_workspace_bytes", "hyena_chain_bwd", "hyena_chain_bwd_workspace_bytes", "hyena_li_fwd",
             "hyena_li_workspace_bytes")), _current_raw_stream)
-    except (ImportError, OSError, AttributeError):  # built for another torch or Python
+    except (ImportError, OSError, AttributeError) as e:
+        warnings.warn("native marshalling not loaded, calls are marshalled through ctypes: %s" % e, RuntimeWarning)
         return
     _fast = module
 
