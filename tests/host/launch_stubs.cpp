@@ -46,8 +46,7 @@ bool chain_bwd_supported(const ChainShape& s) {
 }
 int64_t chain_bwd_workspace_bytes(const ChainShape& s) { return s.B * (s.D / 16 * s.lh + 3 * s.D * s.lf) * 4; }
 hy_status launch_chain_bwd(const ChainBwdPtrs&, const ChainShape&, void*, hipStream_t) { return HY_OK; }
-hy_status launch_dh_reduce3(const float* const (&)[3], float* const (&)[3], int64_t, int64_t, int32_t, int32_t, hipStream_t) { return HY_OK; }
-hy_status launch_dh_reduce(const float*, float*, int64_t, int64_t, int32_t, int32_t, hipStream_t) { return HY_OK; }
+hy_status launch_dh_reduce(const DhReduce*, int, hipStream_t) { return HY_OK; }
 hy_status launch_stream_gate(const void*, const void*, const void*, void*, int64_t, int64_t, int64_t, int32_t, int64_t,
                              int32_t, int32_t, hipStream_t) { return HY_OK; }
 hy_status launch_bwd_zero_dh(float*, int64_t, int32_t, int32_t, hipStream_t) { return HY_OK; }

@@ -93,6 +93,8 @@ def tile_walk(B, L, D, lh, dtype, problems):
     padded = 4 * 128 * -(-L // 128) > 5 * 32 * -(-L // 32)
     short_tiles = L > 128 if lh <= 32 else single and dtype == "bf16"
     rows = 128 if units * -(-L // 128) >= 256 and not padded and not short_tiles else 32
+    if dtype == "bf16" and not single and lh > 32:
+        rows = 32 if -(-units * -(-L // 32) // 256) == -(-units * -(-L // 64) // 256) else 64
     tiles, resident = -(-L // rows), 1024 if lh <= 32 and rows == 32 else 512
 
     def cost(w):
@@ -107,14 +109,15 @@ def tile_walk(B, L, D, lh, dtype, problems):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("D,group", [(1000, 8), (1001, 1)], ids=["pieces", "elements"])
+@pytest.mark.parametrize("D,group", [(1000, 8), (1000, 4), (1001, 1)], ids=["split", "pieces", "elements"])
 @pytest.mark.parametrize("lh", [12, 20, 40, 65, 100, 128])
 def test_walks_of_several_tiles(lh, D, group, dtype):
-    """Walks of three tiles or more, whose halo stays in LDS: forward and gradients, on the first and the last channels."""
+    """Walks of three tiles or more, whose halo stays in LDS: forward and gradients, on the first and the last channels.
+    (Filters that 8 channels share go to the split products, but for the gradients of up to 32 taps.)"""
     B, L = 3, 5003
     for problems in (1, 2):
         rows, steps = tile_walk(B, L, D, lh, dtype, problems)
-        assert steps >= 3 and rows == (32 if lh <= 32 or (dtype == "bf16" and D % 8) else 128)
+        assert steps >= 3 and rows == (32 if lh <= 32 or (dtype == "bf16" and D % 8) else 64 if dtype == "bf16" else 128)
     say("hyena_mr_fwd / bwd %d x %d x %d lh=%d group=%d %s" % (B, L, D, lh, group, dtype))
     q, k, v, h = draw(9500 + lh, B, L, D, lh, group, dtype, kind="mr")
     dy = synth.normal_tensor(np.random.Generator(np.random.PCG64(9501)), (B, L, D), dtype)
@@ -207,22 +210,34 @@ def test_taps_beyond_the_sequence_cost_nothing():
     assert torch.equal(*dx)
 
 
+@pytest.mark.parametrize("group", [4, 8], ids=["general", "split"])
 @pytest.mark.parametrize("lh", [33, 64, 65, 128])
 @pytest.mark.parametrize("B,L,D", [(1, 63, 72), (2, 64, 8), (1, 65, 136), (3, 129, 200), (2, 4097, 1000), (5, 6464, 264)],
                          ids=lambda x: str(x))
-def test_tiles_of_64_rows(B, L, D, lh):
+def test_tiles_of_64_rows(B, L, D, lh, group):
     """bf16 rows of whole pieces go in 64-row tiles from 33 to 128 taps: a step less than a tile, one more, walks that end
-    inside a tile and with one, channel blocks cut off by the width."""
-    say("64-row tiles %d x %d x %d lh=%d" % (B, L, D, lh))
-    q, k, v, h = draw(9600 + L + lh, B, L, D, lh, 8, "bf16", kind="mr")
+    inside a tile and with one, channel blocks cut off by the width; the split products' chunks of 64 at the same sizes."""
+    say("64-row tiles %d x %d x %d lh=%d group=%d" % (B, L, D, lh, group))
+    q, k, v, h = draw(9600 + L + lh, B, L, D, lh, group, "bf16", kind="mr")
     dy = synth.normal_tensor(np.random.Generator(np.random.PCG64(9601)), (B, L, D), "bf16")
-    y = host(binding.hyena_mr_fwd(dev(q), dev(k), dev(v), dev(h), 8))
-    grads = [host(x) for x in binding.hyena_mr_bwd(dev(dy), dev(q), dev(k), dev(v), dev(h), 8)]
+    y = host(binding.hyena_mr_fwd(dev(q), dev(k), dev(v), dev(h), group))
+    grads = [host(x) for x in binding.hyena_mr_bwd(dev(dy), dev(q), dev(k), dev(v), dev(h), group)]
     c = slice(0, D) if D <= 264 and L < 1000 else slice(D - 24, D)  # (the last channel block where the oracle is slow)
-    g = slice(c.start // 8, c.stop // 8)
+    g = slice(c.start // group, c.stop // group)
     a = [x[..., c].contiguous() for x in (dy, q, k, v)]
     hc = np.ascontiguousarray(h[g])
-    assert oracle.rel_err(y[..., c], oracle.gated_conv(*a[1:], hc, group=8)) <= TOL["bf16"]
-    for name, got, want in zip(("dq", "dk", "dv", "dh"), grads, oracle.gated_conv_bwd(*a, hc, group=8)):
+    assert oracle.rel_err(y[..., c], oracle.gated_conv(*a[1:], hc, group=group)) <= TOL["bf16"]
+    for name, got, want in zip(("dq", "dk", "dv", "dh"), grads, oracle.gated_conv_bwd(*a, hc, group=group)):
         got = got[g] if name == "dh" else got[..., c]
         assert oracle.rel_err(got, want) <= (TOL["f32"] if name == "dh" else TOL["bf16"]), name
+
+
+# B, L, D, lh, group: more than 256 workgroups, rows that are no whole lines: one segment, several on whole and part sequences
+# per XCD; of pieces and of single elements; a number of workgroups that 8 does not divide
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [(2, 1500, 1000, 9, 1), (1, 2100, 1001, 40, 7), (5, 330, 520, 128, 4), (8, 300, 200, 250, 2),
+                                  (9, 290, 203, 140, 1), (1, 2400, 504, 150, 4), (3, 200, 4090, 12, 1)],
+                         ids=lambda c: "B%dL%dD%dlh%dg%d" % c)
+def test_workgroups_together_on_an_xcd(case, dtype):
+    B, L, D, lh, group = case
+    check_gated("hyena_mr_fwd", 9700 + D, B, L, D, lh, group, dtype, kind="mr")

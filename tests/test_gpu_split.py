@@ -57,29 +57,50 @@ def test_small_magnitudes(size, tap, group, dtype):
     assert oracle.rel_err(dk, rk) <= tol and oracle.rel_err(dv, rv) <= tol
 
 
-@pytest.mark.parametrize("L,at", [(300, 0), (300, 63), (900, 640)])
-def test_values_that_are_not_finite(L, at):
-    B, D, lh, group = 1, 24, 128, 8
-    say("split products, not finite, L=%d at=%d" % (L, at))
-    q, k, v, h = draw(9800 + at, B, L, D, lh, group, "f32", kind="mr")
-    dy = torch.from_numpy(np.random.Generator(np.random.PCG64(2)).standard_normal((B, L, D), dtype=np.float32))
-    k[0, at, 3] = float("inf")
-    k[0, at, 12], v[0, at, 12] = 3.4e38, 1.0  # finite; its bf16 head is not
+# B, L, D, lh, group, step of the infinite sample: the first step, the last one of a chunk, the first of a chunk, of a tile and
+# before it; two to five source blocks; blocks of channels cut off by the width
+NON_FINITE = [(1, 300, 24, 128, 8, 0), (1, 300, 24, 128, 8, 63), (1, 900, 24, 128, 8, 640), (1, 130, 88, 33, 8, 64), (1, 400, 48, 128, 16, 63),
+              (1, 300, 80, 65, 16, 128), (2, 200, 48, 97, 16, 191), (3, 5003, 1000, 128, 8, 2048), (3, 5003, 1000, 40, 8, 1023),
+              (2, 2048, 1008, 129, 16, 1024)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", NON_FINITE, ids=lambda c: "B%dL%dD%dlh%dg%dat%d" % c)
+def test_values_that_are_not_finite(case, dtype):
+    B, L, D, lh, group, at = case
+    say("split products, not finite, %s %s" % (case, dtype))
+    q, k, v, h = draw(9800 + at, B, L, D, lh, group, dtype, kind="mr")
+    dy = synth.normal_tensor(np.random.Generator(np.random.PCG64(2)), (B, L, D), dtype)
+    b, mid, last = B - 1, D // 2 // group * group, D - group  # the channels looked at: the first filter's, a middle and the last one's
+    k[b, at, 3] = float("inf")
+    # finite; its bf16 head is not (bf16: only the product's head, 2^127 * 181^2 / 128^2)
+    k[b, at, mid + 4], v[b, at, mid + 4] = (3.4e38, 1.0) if dtype == "f32" else (181 / 128 * 2.0 ** 64, 181 / 128 * 2.0 ** 63)
     h = h.copy()
-    h[1] *= np.float32(1e-2)
-    h[2, 40] = np.nan
-    bad = np.zeros((L, D), dtype=bool)
-    bad[at:at + lh, 3] = True
-    bad[40:, 16:] = True
-    y = host(binding.hyena_mr_fwd(dev(q), dev(k), dev(v), dev(h), group))
-    assert np.array_equal(~np.isfinite(y[0]), bad)
+    h[mid // group] *= np.float32(1e-2)
+    tap = min(40, lh - 1)
+    h[last // group, tap] = np.nan
+    c = np.r_[0:group, mid:mid + group, last:D]
+    first, middle, final = slice(0, group), slice(group, 2 * group), slice(2 * group, 3 * group)
+    bad = np.zeros((B, L, 3 * group), dtype=bool)
+    bad[b, at:at + lh, 3] = True
+    bad[:, tap:, final] = True
+    y = host(binding.hyena_mr_fwd(dev(q), dev(k), dev(v), dev(h), group))[..., c]
+    assert np.array_equal(~np.isfinite(y), bad)
+    rows = [0, mid // group, last // group]
+    part = [x[..., c].contiguous() for x in (dy, q, k, v)]
     with np.errstate(all="ignore"):
-        ref = oracle.gated_conv(q, k, v, h, group=group)
-    assert oracle.rel_err(y[0][:, 8:16], ref[0][:, 8:16]) <= 1e-6
-    dq, dk, dv, _ = (host(x) for x in binding.hyena_mr_bwd(dev(dy), dev(q), dev(k), dev(v), dev(h), group))
-    assert np.array_equal(~np.isfinite(dq[0]), bad)
-    bad_k = np.zeros((L, D), dtype=bool)
-    bad_k[:L - 40, 16:] = True
-    assert np.array_equal(~np.isfinite(dk[0]), bad_k)
-    bad_k[at, 3] = True  # dv = du * k
-    assert np.array_equal(~np.isfinite(dv[0]), bad_k)
+        ref = oracle.gated_conv(*part[1:], np.ascontiguousarray(h[rows]), group=group)
+    tol = 1e-6 if dtype == "f32" else 2.0 ** -8
+    assert oracle.rel_err(y[..., middle], ref[..., middle]) <= tol
+    assert oracle.rel_err(np.where(bad, 0.0, y)[..., first], np.where(bad, 0.0, ref)[..., first]) <= tol
+    dq, dk, dv, _ = (host(x)[..., c] for x in binding.hyena_mr_bwd(dev(dy), dev(q), dev(k), dev(v), dev(h), group)[:3] + (q,))
+    assert np.array_equal(~np.isfinite(dq), bad)
+    bad_k = np.zeros((B, L, 3 * group), dtype=bool)
+    bad_k[:, :L - tap, final] = True
+    dk_ok = np.isfinite(dk) | bad_k
+    dk_ok[b, at, group + 4] = True  # (du * v overflows in bf16)
+    assert dk_ok.all() and not np.isfinite(dk[bad_k]).any()
+    bad_k[b, at, 3] = True  # dv = du * k
+    dv_ok = np.isfinite(dv) | bad_k
+    dv_ok[b, at, group + 4] = True
+    assert dv_ok.all() and not np.isfinite(dv[bad_k]).any()
