@@ -220,6 +220,6 @@ __device__ __forceinline__ uint32_t xcd_contiguous(uint32_t i, uint32_t n) {
 // here keep the plain launch order with the fastest-varying tile index along a row, so that all XCDs
 // sweep one compact address window together; giving each XCD its own contiguous range of tiles was
 // measured slower on MI355X for them (copy, stencil, MR).  The general FIR kernels do give XCDs their own ranges
-// where rows are no whole cache lines and neighbouring row pieces share some.
+// where rows are no whole cache lines and neighbouring row pieces share some (the rules stand where they are launched).
 
 }  // namespace hy

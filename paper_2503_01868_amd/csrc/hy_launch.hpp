@@ -195,7 +195,7 @@ struct FirProblem {
 hy_status launch_fir(const FirProblem* p, int nprob, int64_t B, int64_t L, int64_t D, int32_t lh, int32_t group,
                      hy_dtype dtype, hipStream_t st);
 // The same sums in the same precision on split bf16 products: up to two gated problems of 9 to 129 taps whose filters are
-// shared by 8 adjacent channels or a multiple.  HY_ERR_UNSUPPORTED outside that.
+// shared by 8 adjacent channels or a multiple, of sizes at which it is no slower.  HY_ERR_UNSUPPORTED outside that.
 hy_status launch_split_fir(const FirProblem* p, int nprob, int64_t B, int64_t L, int64_t D, int32_t lh, int32_t group,
                            hy_dtype dtype, hipStream_t st);
 // Forward of any shape: split products where they serve it, else the general kernel.

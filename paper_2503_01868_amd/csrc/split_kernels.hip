@@ -17,8 +17,8 @@
 // steps, the sums go back through LDS to be gated and stored as row pieces.  A product is 16 rows x 32 source steps x 16
 // output steps, and a wave makes one of the two that 16 channels x 32 steps take per source block, so that operands and
 // window of a wave fit 256 registers and two waves per SIMD overlap products with conversions (one wave with both, 32-step
-// chunks, the SIMD to itself: 47 us where this takes 38, 3 x 5003 x 1000 bf16, 128 taps; four chunks ahead instead of two
-// gained that form nothing):
+// chunks, the SIMD to itself: 47 us where this took 38, 3 x 5003 x 1000 bf16, 128 taps, inputs changing from call to call; four
+// chunks ahead instead of two gained that form nothing):
 //   kGroup = 16: rows are 16 channels; the two waves of a slice have a 16-step half of every 32 steps each;
 //   kGroup = 8:  rows are the 8 channels of a filter x the two halves; a source block begins 16 steps before its half.
 //
@@ -27,10 +27,10 @@
 // order, without the terms the definition does not have.  (A value that is not finite, or rounds to infinity as a head,
 // makes every sum not finite that it is multiplied into, by zero or not.)
 //
-// Bound: long sequences the row pieces (fp32 256 bytes of every row, 1 x 8192 x 4096 106 us = 5.0 TB/s; bf16 128 bytes),
+// Bound: long sequences the row pieces (fp32 256 bytes of every row, 1 x 8192 x 4096 108 us = 5.0 TB/s; bf16 128 bytes),
 // short ones the start of a tile (operands, two chunks of warm-up).  General kernel / this one, 128 taps, us: 3 x 5003 x 1000
-// bf16, groups of 8 70 / 32 (33 taps 51 / 27), fp32 95 / 51; 2 x 2048 x 1024 fp32, groups of 16 27 / 17; 1 x 8192 x 4096 fp32
-// 169 / 106; 1 x 300 x 512 fp32 10.3 / 7.9.  Error against 64 bits of 2 x 2048 x 1024 fp32, forward and gradients: 2.6e-7 / 6e-8.
+// bf16, groups of 8 70 / 31 (33 taps 51 / 27), fp32 95 / 51; 2 x 2048 x 1024 fp32, groups of 16 27 / 17; 1 x 8192 x 4096 fp32
+// 169 / 108; 1 x 300 x 512 fp32 10.3 / 7.9.  Error against 64 bits of 2 x 2048 x 1024 fp32, forward and gradients: 2.6e-7 / 6e-8.
 #include <type_traits>
 
 #include "hy_common.hpp"

@@ -11,8 +11,8 @@ from gpu_util import dev, draw, say
 
 pytestmark = pytest.mark.gpu
 
-# B, L, D, lh: batches whose tiles run on from one item into the next (the first six; a tile that begins between two items, in an
-# item's last step, items of a few tiles and of many); others that do not divide 256 workgroups; items of one chunk of 32
+# B, L, D, lh: batches whose tiles run on from one item into the next (the first six; tiles that begin between two items,
+# in an item's last chunk, in its middle); others that do not divide 256 workgroups; items of one chunk of 32
 # steps, of a chunk and a step, of a chunk less a step, shorter than the filter, of many tiles; filters of 2 to 5 source blocks
 CASES = [(3, 250, 8192, 128), (5, 70, 4096, 33), (3, 129, 8192, 129), (257, 40, 64, 30), (3, 5000, 2048, 128), (5, 1000, 4096, 70),
          (3, 1000, 2048, 128), (5, 33, 1536, 129), (7, 31, 192, 40), (2, 32, 64, 65), (6, 65, 768, 97),
