@@ -194,7 +194,7 @@ struct FirProblem {
 // General fp32 FIR: any lh, any group, any width, both dtypes, up to three problems of one shape per launch.
 hy_status launch_fir(const FirProblem* p, int nprob, int64_t B, int64_t L, int64_t D, int32_t lh, int32_t group,
                      hy_dtype dtype, hipStream_t st);
-// The same sums in the same precision on split bf16 products: up to two gated problems of 9 to 129 taps whose filters are
+// The same sums in the same precision on split bf16 products: up to two gated problems of 9 to 129 taps that meet data whose filters are
 // shared by 8 adjacent channels or a multiple, of sizes at which it is no slower.  HY_ERR_UNSUPPORTED outside that.
 hy_status launch_split_fir(const FirProblem* p, int nprob, int64_t B, int64_t L, int64_t D, int32_t lh, int32_t group,
                            hy_dtype dtype, hipStream_t st);

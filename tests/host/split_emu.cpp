@@ -72,6 +72,7 @@ int check(const Case& k) {
             gate.set(t, c, draw());
             gate2.set(t, c, draw());
         }
+    if (k.lh > k.L) h[k.lh - 1] = NAN;  // (meets no data)
     const int64_t bad_c = k.D - 3, huge_c = k.D / 2;
     if (k.infinite >= 0) a.set(k.infinite, bad_c, INFINITY);
     if (k.huge >= 0) {
@@ -168,6 +169,10 @@ int main() {
             bad += check({130, 16 + 2 * group, 40, group, bf16, false, 1.0f, 1e-35f});
             bad += check({130, 16 + 2 * group, 9, group, bf16, true, 1e-9f, 1e-17f});
         }
+    // filters longer than their sequence
+    bad += check({100, 72, 400, 8, false, false});
+    bad += check({40, 80, 150, 16, true, true});
+    bad += check({9, 72, 33, 8, false, true});
     bad += check_route(1, 128, 8, 9, 8, false, false);
     // as many workgroups as HIP takes threads for (fewer than 2^32), and more, which the general kernel's smaller ones may fit
     bad += check_route((1 << 23) - 1, 65, 8, 129, 8, false, false);
